@@ -238,6 +238,8 @@ typedef struct {
 int dsvt_pool_packed_size(const dsvt_pool_cfg* cfg, size_t* bytes);
 int dsvt_pool_pack(const dsvt_pool_cfg* cfg, void* packed, size_t bytes, void* stream);
 
+/* Scratch for dsvt_attn_pool.  (On large frames with mask_empty = 1 this is more than the size reported for
+ * mask_empty = 0, which such a call also takes; regions of a single voxel then share the general path.) */
 int dsvt_attn_pool_workspace_size(const dsvt_pool_cfg* cfg, int32_t n_voxels, size_t* bytes);
 
 /* Every non-empty region (b, x/l, y/w, z/h) becomes one output voxel, in ascending key
@@ -257,8 +259,9 @@ int dsvt_attn_pool(const dsvt_pool_cfg* cfg, const int32_t* coords, const void* 
  * results and errors as dsvt_attn_pool, without `ws`: the scratch (occupancy bitmap, its prefix, the
  * dense slot table) is an array of DSVT_POOL_STATIC_SCRATCH_BYTES built into the library, one copy per
  * GPU, held from the moment the library is loaded until the process ends.  The call allocates and
- * frees nothing.  DSVT_ENOSPC when dsvt_attn_pool_workspace_size(cfg, n_voxels) exceeds that size
- * (8 MiB: e.g. 300,000 voxels in regions of 4 cells on a 468 x 468 x 32 grid).  Every call on a GPU uses
+ * frees nothing.  DSVT_ENOSPC when bitmap, prefix and slot table (8 bytes per 32 pooled cells, 4 l*w*h per
+ * voxel) exceed that size (8 MiB: e.g. 300,000 voxels in regions of 4 cells on a 468 x 468 x 32 grid; the
+ * larger scratch dsvt_attn_pool_workspace_size asks for on big frames with mask_empty = 1 is optional).  Every call on a GPU uses
  * that GPU's one array: calls on different streams of one GPU must not overlap (they would race on
  * it); what the array held before does not matter (each call clears what it reads).  The first call
  * on a device looks the array's address up (no allocation; make it outside graph capture). */

@@ -22,10 +22,14 @@ constexpr int kRowsPad = kRowsMax + 16;          // per-row arrays are read 4 at
 constexpr int kMaxItems = 128;                  // attention items: (set, query tile, group of heads); see item_groups()
 // Sets per workgroup when no tile list is given.
 __host__ __device__ constexpr int fixed_sets(int tau) { return tau <= kRowsMax / 2 ? 2 : 1; }
-// A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each; a larger one
-// (its logits take more registers) into one item per head.  At most one set of a tile is that large,
-// so a tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
-__host__ __device__ constexpr int item_groups(int kts, int heads) { return kts <= 3 ? 2 : heads; }
+// A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each; a larger one (its logits and
+// positional terms take more registers) into items of two heads: the table rows of a (query, key) pair and their
+// indices are fetched and computed once for both.  Per layer of the 20,000-voxel frame of 30 x 30 windows (C = 128, sets
+// of up to 90): one head per item 46 us, two 38 us, four 40 us (spills).  C = 192 with repeats counted as keys
+// keeps one head per item (two spill there).  At most one set of a tile is that large, so a tile has at most
+// 8 * 6 + 2 * (3 + 11) = 76 items.
+__host__ __device__ constexpr int big_heads(int C, bool dup) { return C == 192 && dup ? 1 : 2; }
+__host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
 constexpr int kHalfTiles = kRowTiles / 2;        // the LayerNorm-phase work items cover half of the row tiles
 constexpr int kLayerWaves = 12;                  // three per SIMD: one workgroup per CU (LDS), the other wavefronts hide one's waits
 
@@ -226,18 +230,18 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, T* Qs, const T* Ks,
 }
 
 // An item of a set with kts key tiles: up to three key tiles half of the heads per item, beyond that (BIG kernels
-// only) one head.
+// only) big_heads().
 template <typename T, int C, int HEADS, int HID, bool BIG, bool DUP>
 __device__ __forceinline__ void attn_any(const LayerDev& p, T* Qs, const T* Ks, const T* Vt, const int32_t* row_lin,
                                          const float* row_mult, int r0, int nu, int qt, int hh, int kts, int rows_ready) {
-  constexpr int HG2 = HEADS / 2;
+  constexpr int HG2 = HEADS / 2, HGB = big_heads(C, DUP);
   if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   else if (!BIG || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   else if constexpr (BIG) {
-    if (kts == 4) attn_item<T, C, HEADS, HID, 4, 1, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-    else if (kts == 5) attn_item<T, C, HEADS, HID, 5, 1, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-    else attn_item<T, C, HEADS, HID, 6, 1, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+    if (kts == 4) attn_item<T, C, HEADS, HID, 4, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+    else if (kts == 5) attn_item<T, C, HEADS, HID, 5, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+    else attn_item<T, C, HEADS, HID, 6, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   }
 }
 
@@ -292,7 +296,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       const int ls = lane - 2 - kMaxSets;        // the lanes holding the sets' sizes also list the sets' attention items
       if (ls >= 0 && ls < kMaxSets) set_nu[ls] = nu_s;
       const int kts = (ls >= 0 && ls < hdr_ns) ? (nu_s + 15) >> 4 : 0;
-      const int ngr = item_groups(kts, HEADS);
+      const int ngr = item_groups(kts, HEADS, big_heads(C, DUP));
       int incl = ngr * kts;                      // items: (set, query tile, group of heads)
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
@@ -337,7 +341,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         set_r0[s] = r; r += (set_nu[s] + 3) & ~3;
         const int kts = (set_nu[s] + 15) >> 4;
         for (int qt = 0; qt < kts; ++qt)
-          for (int hh = 0; hh < item_groups(kts, HEADS); ++hh)
+          for (int hh = 0; hh < item_groups(kts, HEADS, big_heads(C, DUP)); ++hh)
             if (n < kMaxItems) items[n++] = s | (qt << 8) | (hh << 12) | (kts << 16);
       }
       set_r0[ns] = r;

@@ -847,7 +847,7 @@ def test_dsvt_v_four_stages(xy, n):
 def test_large_sets(C, heads, hidden, win, tau, n):
     """Sets of more than 48 voxels (the nuScenes variant uses tau = 90 with 30 x 30 windows, appendix "3D
     Perception on nuScenes"; the ablation on set size goes up to 60): a set then spans four to six key
-    tiles and is attended one head per work item."""
+    tiles and is attended two heads per work item."""
     grid = (360, 360, 1) if win[0] == 30 else (96, 96, 1)
     shift = (win[0] // 2, win[1] // 2, 0)
     coords = np.concatenate([np.zeros((n, 1), np.int64), synth.frame_radial(400 + tau, grid, n)], 1).astype(np.int32)
