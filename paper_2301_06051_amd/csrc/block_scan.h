@@ -7,7 +7,8 @@
 // over all chunks in turn took three per chunk).  `in` and `out` must be 16-byte aligned and must
 // not overlap; n_dev, if given, holds the element count on the device and is clamped to n_max;
 // *total gets the sum, and out[n] too when TAIL is set (an offsets array of n + 1 entries).
-// Launch with block_scan_grid(n_max) workgroups of 1,024 threads.
+// Launch with block_scan_grid(n_max) workgroups of 1,024 threads; a grid of (.., 2) scans a second array of the same
+// length, `pitch` elements behind the first in `in` and in `out`, with its sum in *total2.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -21,7 +22,9 @@ inline unsigned block_scan_grid(int64_t n_max) { return n_max <= kScanChunk ? 1u
 
 template <bool POPC, bool TAIL = false>
 __global__ void __launch_bounds__(1024) k_block_scan(const uint32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n_max,
-                                                     const int32_t* __restrict__ n_dev, int32_t* __restrict__ total) {
+                                                     const int32_t* __restrict__ n_dev, int32_t* __restrict__ total,
+                                                     int64_t pitch = 0, int32_t* __restrict__ total2 = nullptr) {
+  if (blockIdx.y != 0) { in += pitch; out += pitch; total = total2; }
   __shared__ int32_t wave_tot[16], wave_pre[16];
   const int32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int64_t n = n_max;

@@ -10,6 +10,9 @@
 // several passes.  Max-pool over the occupied slots gives the query row (Eq. 6); K/V of the occupied
 // slots and Q of the pooled rows are MFMA projections; the P-key softmax per head is plain ALU
 // work; output projection, residual and LayerNorm follow the layer kernels (Eq. 7).
+// With masked holes (mask_empty = 1) a region of one voxel needs no attention: its softmax has one key, whose weight
+// is exactly 1, and its maximum is the voxel itself, so its row is LN(x + (x Wv^T + bv) Wo^T + bo).  kp_single takes
+// these regions (nine in ten of a LiDAR voxel frame's), kp_attention the others.
 #include "common.h"
 #include "block_scan.h"
 #include "mma.h"
@@ -42,18 +45,25 @@ __device__ __forceinline__ bool pool_key(const PoolGeom& g, int4 c, uint32_t* ke
   return true;
 }
 
+// One bit per non-empty region; `multi`, if given, gets the regions of two or more voxels.
 __global__ void kp_mark(PoolGeom g, const int4* __restrict__ coords, int32_t n, uint32_t* __restrict__ bitmap,
-                        int32_t* __restrict__ status) {
+                        uint32_t* __restrict__ multi, int32_t* __restrict__ status) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   uint32_t key; int32_t slot;
   if (!pool_key(g, coords[i], &key, &slot)) { atomicOr(status, DSVT_ST_COORD_RANGE); return; }
-  atomicOr(&bitmap[key >> 5], 1u << (key & 31u));
+  const uint32_t bit = 1u << (key & 31u);
+  if (multi == nullptr) atomicOr(&bitmap[key >> 5], bit);
+  else if (atomicOr(&bitmap[key >> 5], bit) & bit) atomicOr(&multi[key >> 5], bit);      // not the region's first voxel
 }
 
+// With `multi`: regions of several voxels get slot rows of their own (and their output row in multi_reg), the others
+// an entry (voxel, output row) in `single`, both in ascending key order.
 __global__ void kp_emit(PoolGeom g, const int4* __restrict__ coords, int32_t n, const uint32_t* __restrict__ bitmap,
                         const int32_t* __restrict__ word_prefix, int32_t* __restrict__ pool_inds,
-                        int32_t* __restrict__ out_coords) {
+                        int32_t* __restrict__ out_coords, const uint32_t* __restrict__ multi,
+                        const int32_t* __restrict__ multi_prefix, int32_t* __restrict__ multi_reg,
+                        int2* __restrict__ single) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const int4 c = coords[i];
@@ -61,7 +71,14 @@ __global__ void kp_emit(PoolGeom g, const int4* __restrict__ coords, int32_t n, 
   if (!pool_key(g, c, &key, &slot)) return;
   const uint32_t word = key >> 5, bit = key & 31u;
   const int32_t m = word_prefix[word] + __popc(bitmap[word] & ((1u << bit) - 1u));   // m < number of regions <= n
-  pool_inds[(int64_t)m * g.P + slot] = i;
+  if (multi == nullptr) {
+    pool_inds[(int64_t)m * g.P + slot] = i;
+  } else {
+    const uint32_t mw = multi[word];
+    const int32_t mi = multi_prefix[word] + __popc(mw & ((1u << bit) - 1u));         // regions of several voxels before this one
+    if ((mw >> bit) & 1u) { pool_inds[(int64_t)mi * g.P + slot] = i; multi_reg[mi] = m; }   // mi < n / 2
+    else single[m - mi] = make_int2(i, m);
+  }
   // every member of a region writes the same pooled coordinates
   reinterpret_cast<int4*>(out_coords)[m] = make_int4(c.x, c.y / g.pool[0], c.z / g.pool[1], c.w / g.pool[2]);
 }
@@ -70,7 +87,7 @@ struct PoolDev {
   const void *w_kv, *w_q, *w_o;                   // packed: [2C, C] (K rows then V rows), [C, C], [C, C]
   const float *b_kv, *b_q, *b_o, *ln_g, *ln_b;    // b_kv: [2C] in scratch (b_k then b_v)
   float ln_eps;
-  int32_t P, mask_empty;
+  int32_t P, mask_empty, regs;
 };
 
 // D consecutive elements of an LDS row as floats (16-byte reads when the head width allows).
@@ -105,7 +122,8 @@ template <typename T, int C> struct PoolLds {
   static constexpr size_t off_svox = off_misc, off_scum = off_svox + kSlots * 4, off_rcum = off_scum + kSlots * 2,
                           off_pass = off_rcum + (kRegs + 1) * 4, off_rvox = off_pass + (kMaxPool + 2) * 4,
                           off_bias = (off_rvox + kRowsMax * 4 + 15) / 16 * 16, off_wcnt = off_bias + 2 * C * sizeof(T);
-  static constexpr size_t total = off_wcnt + 16 * 4;
+  static constexpr size_t off_orow = off_wcnt + 16 * 4;                           // output row of every region
+  static constexpr size_t total = off_orow + kRegs * 4;
   static_assert(kStat <= kTile && total <= 160 * 1024 && off_bias % 16 == 0, "pooling tile does not fit the LDS");
 };
 
@@ -113,10 +131,11 @@ template <typename T, int C> struct PoolLds {
 // slot table of the next group is requested during the softmax of the current one, and its occupancy scan and the
 // request for its rows come before the current group's output projection and LayerNorm, so that the two memory
 // round trips of a group (slots, then rows) are behind arithmetic of its predecessor.  One workgroup fits a CU.
+// A group has p.regs regions.  reg_row: output row of region m, or nullptr where that is m.
 template <typename T, int C, int HEADS, int NT_KV, int NT_C>
 __global__ void __launch_bounds__(kWaves * 64)
 kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __restrict__ n_out_ptr,
-             const T* __restrict__ x, T* __restrict__ out) {
+             const int32_t* __restrict__ reg_row, const T* __restrict__ x, T* __restrict__ out) {
   typedef PoolLds<T, C> L;
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int LDX = L::LDX, D = C / HEADS, NW = kWaves, NTHREADS = NW * 64;
@@ -138,9 +157,10 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
   T* Vb = Kb + C;
   int32_t* wcnt = reinterpret_cast<int32_t*>(smem + L::off_wcnt);
   const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
-  const int P = p.P;
+  int32_t* out_row = reinterpret_cast<int32_t*>(smem + L::off_orow);
+  const int P = p.P, regs = p.regs;                // regs <= kRegs
   const int n_out = __builtin_amdgcn_readfirstlane(*n_out_ptr);
-  const int n_groups = (n_out + kRegs - 1) / kRegs;
+  const int n_groups = (n_out + regs - 1) / regs;
   if ((int)blockIdx.x >= n_groups) return;
   const int W = kRowsMax + 1 - P;                  // a pass takes the regions whose first occupied slot number lies in one
                                                    // run of W: together at most W - 1 + P = 96 rows
@@ -158,7 +178,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
 
   for (int c = tid0; c < 2 * C; c += NTHREADS) Kb[c] = (T)p.b_kv[c];
   auto slot_of = [&](int grp, int tid) {                              // this thread's slot of a group: its voxel or -1
-    const int m0 = grp * kRegs, mr = (n_out - m0) < kRegs ? (n_out - m0) : kRegs;
+    const int m0 = grp * regs, mr = (n_out - m0) < regs ? (n_out - m0) : regs;
     return tid < mr * P ? pool_inds[(size_t)m0 * P + tid] : -1;
   };
   int v_slot = slot_of((int)blockIdx.x, tid0);
@@ -169,8 +189,8 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
     // once, in front of the loop, and keeps -- spills -- them all)
     const int tid = opaque_tid(), lane = tid & 63, g = lane >> 4;
     const bool have = grp < n_groups, have_prev = grp != (int)blockIdx.x;     // (uniform)
-    const int m0 = grp * kRegs;
-    const int mr = have ? ((n_out - m0) < kRegs ? (n_out - m0) : kRegs) : 0;
+    const int m0 = grp * regs;
+    const int mr = have ? ((n_out - m0) < regs ? (n_out - m0) : regs) : 0;
     int n_pass = 0, RT0 = 0;
     uint4 val[G];
 #pragma unroll
@@ -211,6 +231,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
     }
     if (have_prev) {
       // ---- the group before: out = LN(P + O Wo^T + bo), its rows to memory
+      if (reg_row != nullptr && tid < mr_prev) out_row[tid] = reg_row[m0_prev + tid];    // (published by the LayerNorm's barriers)
       f32x4 bo4[NT_C], ga[NT_C], be[NT_C];
 #pragma unroll
       for (int nt = 0; nt < NT_C; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
@@ -234,7 +255,8 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
       lds_barrier();
       for (int idx = tid; idx < mr_prev * CH; idx += NTHREADS) {
         const int r = idx / CH, c = idx - r * CH;
-        reinterpret_cast<uint4*>(out + (size_t)(m0_prev + r) * C)[c] =
+        const int row = reg_row != nullptr ? out_row[r] : m0_prev + r;
+        reinterpret_cast<uint4*>(out + (size_t)row * C)[c] =
             *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Ps) + (size_t)r * LDX * sizeof(T) + c * 16);
       }
       lds_barrier();                               // (the pooled rows and the statistics are free from here)
@@ -373,11 +395,135 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
   }
 }
 
+// Regions of one voxel, masked holes: out = LN(x + (x Wv^T + bv) Wo^T + bo), a row per voxel -- what kp_attention computes
+// for them, where e^0 / e^0 = 1 weighs the one value row.  No query, no key, no softmax, no slot table: two C x C
+// products on the voxels' own rows.  Four wavefronts, each with 16 NT output features of both matrices, whose weight
+// fragments stay in its registers while the workgroup walks over groups of kSingleRows list entries (a workgroup per
+// group would read 147 KB of weights for 48 rows of 384 bytes); the next group's rows are on their way during
+// the current one's products.  Two workgroups share a compute unit, so that one's barriers and stores are behind the
+// other's products.  Bound by the rows' way in and out (75 MB for the 97,000 such regions of the 120,000-voxel frame);
+// with it the whole call takes 80 us there, 129 with every region in kp_attention.
+constexpr int kSingleRows = 48, kSingleWaves = 4, kSingleGrid = 512;
+template <typename T, int C> struct SingleLds {
+  static constexpr int LDX = C + lds_pad<T>();
+  static constexpr size_t kTile = (size_t)kSingleRows * LDX * sizeof(T);
+  static constexpr size_t off_x = 0, off_v = kTile, off_stat = 2 * kTile, off_vec = off_stat + (size_t)2 * kStatGroupsMax * kRowsMax * 4,
+                          off_ent = off_vec + (size_t)4 * C * 4, total = off_ent + (size_t)2 * kSingleRows * 8;
+  static_assert(total <= 64 * 1024 && kTile % 16 == 0, "kp_single tile");
+};
+template <typename T, int C>
+__global__ void __launch_bounds__(kSingleWaves * 64, 2)
+kp_single(PoolDev p, const int2* __restrict__ list, const int32_t* __restrict__ n_out, const int32_t* __restrict__ n_multi,
+          const T* __restrict__ x, T* __restrict__ out) {
+  typedef SingleLds<T, C> L;
+  typedef typename Mma<T>::Vec4 Vec4;
+  constexpr int LDX = L::LDX, NT = C / (16 * kSingleWaves), NKF = C / Mma<T>::KC, NTHREADS = kSingleWaves * 64, RT = kSingleRows / 16;
+  constexpr int CH = C * (int)sizeof(T) / 16, G = (kSingleRows * CH + NTHREADS - 1) / NTHREADS;
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* Xs = reinterpret_cast<T*>(smem + L::off_x);       // the rows, finally the output
+  T* Vs = reinterpret_cast<T*>(smem + L::off_v);
+  float* stat = reinterpret_cast<float*>(smem + L::off_stat);
+  float* vec = reinterpret_cast<float*>(smem + L::off_vec);      // b_v, b_o, gamma, beta
+  int2* ent = reinterpret_cast<int2*>(smem + L::off_ent);        // two groups' entries
+  const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+  const int n = __builtin_amdgcn_readfirstlane(*n_out - *n_multi);
+  const int n_groups = (n + kSingleRows - 1) / kSingleRows;
+  if ((int)blockIdx.x >= n_groups) return;
+  const int o_own = wave * 16 * NT;
+  auto entry_of = [&](int grp, int tid) {
+    const int64_t e = (int64_t)grp * kSingleRows + tid;
+    return (tid < kSingleRows && e < n) ? list[e] : make_int2(-1, 0);
+  };
+  auto request = [&](uint4 (&val)[G], const int2* en, int tid) {           // pieces of the group's rows, zero past its last entry
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
+      const int v = r < kSingleRows ? en[r].x : -1;
+      val[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (v >= 0) val[k] = reinterpret_cast<const uint4*>(x + (size_t)v * C)[c];
+    }
+  };
+  const int2 first = entry_of((int)blockIdx.x, tid0);
+  for (int c = tid0; c < C; c += NTHREADS) {
+    vec[c] = p.b_kv[C + c]; vec[C + c] = p.b_o[c]; vec[2 * C + c] = p.ln_g[c]; vec[3 * C + c] = p.ln_b[c];
+  }
+  if (tid0 < kSingleRows) ent[tid0] = first;
+  lds_barrier();
+  uint4 val[G];
+  request(val, ent, tid0);
+  int2 next = entry_of((int)(blockIdx.x + gridDim.x), tid0);
+  AFull<T, NT, NKF> av, ao;
+  load_a<T, NT, NKF>(av, reinterpret_cast<const T*>(p.w_kv), C / 16 + wave * NT);
+  load_a<T, NT, NKF>(ao, reinterpret_cast<const T*>(p.w_o), wave * NT);
+  int buf = 0;
+  for (int grp = (int)blockIdx.x; grp < n_groups; grp += (int)gridDim.x, buf ^= kSingleRows) {
+    const int tid = opaque_tid(), lane = tid & 63, m = lane & 15, g = lane >> 4;    // (anew in every trip, see kp_attention)
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
+      if (r < kSingleRows) *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16) = val[k];
+    }
+    if (tid < kSingleRows) ent[(buf ^ kSingleRows) + tid] = next;
+    lds_barrier();
+    request(val, ent + (buf ^ kSingleRows), tid);
+    next = entry_of(grp + 2 * (int)gridDim.x, tid);
+    f32x4 b4[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + o_own + 16 * nt + 4 * g);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      BRow<T, NKF> b;
+      load_b<T, NKF>(b, Xs, LDX, r);
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
+      mma_row<T, NT, NKF>(acc, av, b);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<Vec4*>(Vs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(acc[nt]);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + C + o_own + 16 * nt + 4 * g);
+    f32x4 keep[NT][RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      BRow<T, NKF> b;
+      load_b<T, NKF>(b, Vs, LDX, r);
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
+      mma_row<T, NT, NKF>(acc, ao, b);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g);
+        keep[nt][r] = acc[nt] + f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
+      }
+    }
+    f32x4 ga[NT], be[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      ga[nt] = *reinterpret_cast<const f32x4*>(vec + 2 * C + o_own + 16 * nt + 4 * g);
+      be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
+    }
+    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, ga, be, p.ln_eps, Xs, LDX);
+    lds_barrier();
+    const int rows = n - grp * kSingleRows < kSingleRows ? n - grp * kSingleRows : kSingleRows;
+    for (int idx = tid; idx < rows * CH; idx += NTHREADS) {
+      const int r = idx / CH, c = idx - r * CH;
+      reinterpret_cast<uint4*>(out + (size_t)ent[buf + r].y * C)[c] =
+          *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16);
+    }
+    lds_barrier();                                   // (the rows and this group's entries are free from here)
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 struct PoolPlan {
   PoolGeom g;
   int64_t n_words;
   size_t off_bitmap, off_prefix, off_inds, total;
+  // the layout of a call that takes regions of one voxel apart (two bitmaps and two prefixes, back to back)
+  size_t words_pitch, off_bitmap2, off_prefix2, off_inds2, off_single, off_reg, off_count, total2;
 };
 
 bool aligned16(const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15u) == 0; }
@@ -400,7 +546,28 @@ int make_plan(const dsvt_pool_cfg* cfg, int32_t n_voxels, PoolPlan* pl) {
   pl->off_prefix = o; o = dsvt_align_up(o + (size_t)pl->n_words * 4, 256);
   pl->off_inds = o;   o = dsvt_align_up(o + (size_t)n_voxels * P * 4, 256);
   pl->total = o;
+  pl->words_pitch = dsvt_align_up((size_t)pl->n_words, 64);
+  o = 0;
+  auto take = [&](size_t bytes) { const size_t at = o; o = dsvt_align_up(o + bytes, 256); return at; };
+  pl->off_bitmap2 = take(pl->words_pitch * 8);
+  pl->off_prefix2 = take(pl->words_pitch * 8);
+  pl->off_inds2 = take((size_t)(n_voxels / 2) * P * 4);        // a region here has at least two voxels
+  pl->off_single = take((size_t)n_voxels * 8);
+  pl->off_reg = take((size_t)(n_voxels / 2) * 4);
+  pl->off_count = take(4);
+  pl->total2 = o;
   return DSVT_OK;
+}
+// Whether a call takes regions of one voxel apart: holes masked (with keys of their own the softmax has two entries), and
+// more than two groups of regions per workgroup, were they kept together.  Below that a launch and a shorter walk
+// cost more than the arithmetic they save.  Kept together -> apart, 1 x 1 x 4 regions of 192 channels: 3,000 voxels 27 ->
+// 34 us, 24,000 40.0 -> 41.2, 32,000 51.9 -> 44.8, 120,000 129 -> 80; 2 x 2 x 2 regions: 24,000 38.4 -> 44.2, 32,000 56.6 ->
+// 47.2, 150,000 160 -> 128; 64 and 128 channels cross at the same place.
+bool pool_apart(const dsvt_pool_cfg& c, int32_t n_voxels) { return c.mask_empty == 1 && n_voxels > 2 * kRegs * kPoolGrid; }
+// Scratch a call asks for: room for the layout it would use.  A call with room for the first layout only keeps every
+// region together.
+size_t pool_scratch(const dsvt_pool_cfg& c, const PoolPlan& pl, int32_t n_voxels) {
+  return pool_apart(c, n_voxels) && pl.total2 > pl.total ? pl.total2 : pl.total;
 }
 
 int check_pool(const dsvt_pool_cfg& c, bool need_packed) {
@@ -439,8 +606,16 @@ template <typename T> void pack_matrix(const void* src, void* dst, int out, int 
   k_pack<T><<<(unsigned)dsvt_ceil_div(slots, 256), 256, 0, st>>>(reinterpret_cast<const T*>(src), reinterpret_cast<T*>(dst), out, k);
 }
 
+struct PoolLists {                                  // what the grouping leaves for the attention
+  const int32_t* inds;                              // slot table
+  const int2* single; const int32_t *multi_reg, *n_multi;      // null: every region is in the slot table
+};
+// Regions of a group when those of one voxel are apart: the others have 2.2 voxels on average on LiDAR frames, so that
+// 40 of them fill the 96-row tile once (88 rows) where 48 need a second, nearly empty pass.
+constexpr int kRegsMulti = 40;
+
 template <typename T, int C, int HEADS, int NT_KV, int NT_C>
-int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const int32_t* pool_inds, const int32_t* n_out,
+int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const PoolLists& ls, const int32_t* n_out,
                           const void* x, void* out, int32_t n_voxels, hipStream_t st) {
   auto kern = kp_attention<T, C, HEADS, NT_KV, NT_C>;
   constexpr size_t lds = PoolLds<T, C>::total;
@@ -452,12 +627,18 @@ int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const int3
   d.w_kv = pk + pp.off_kv; d.w_q = pk + pp.off_q; d.w_o = pk + pp.off_o;
   d.b_kv = reinterpret_cast<const float*>(pk + pp.off_bkv);
   d.b_q = c.b_q; d.b_o = c.b_o; d.ln_g = c.ln_g; d.ln_b = c.ln_b; d.ln_eps = c.ln_eps;
-  d.P = pl.g.P; d.mask_empty = c.mask_empty;
+  d.P = pl.g.P; d.mask_empty = c.mask_empty; d.regs = ls.single != nullptr ? kRegsMulti : kRegs;
   dsvt_prof_scope ps(DSVT_K_POOL_ATTN, st);
   // one workgroup per compute unit (the LDS tile fills it), each walking over every grid-th group of regions
-  const int64_t groups = dsvt_ceil_div(n_voxels, kRegs);
-  kern<<<(unsigned)(groups < kPoolGrid ? groups : kPoolGrid), kWaves * 64, lds, st>>>(d, pool_inds, n_out, reinterpret_cast<const T*>(x),
-                                                                                    reinterpret_cast<T*>(out));
+  const int64_t groups = ls.single != nullptr ? dsvt_ceil_div(n_voxels / 2, kRegsMulti) : dsvt_ceil_div(n_voxels, kRegs);
+  if (groups > 0)
+    kern<<<(unsigned)(groups < kPoolGrid ? groups : kPoolGrid), kWaves * 64, lds, st>>>(
+        d, ls.inds, ls.single != nullptr ? ls.n_multi : n_out, ls.multi_reg, reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out));
+  if (ls.single != nullptr) {
+    const int64_t sg = dsvt_ceil_div(n_voxels, kSingleRows);
+    kp_single<T, C><<<(unsigned)(sg < kSingleGrid ? sg : kSingleGrid), kSingleWaves * 64, SingleLds<T, C>::total, st>>>(
+        d, ls.single, n_out, ls.n_multi, reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out));
+  }
   return DSVT_OK;
 }
 
@@ -501,38 +682,48 @@ extern "C" int dsvt_attn_pool_workspace_size(const dsvt_pool_cfg* cfg, int32_t n
   PoolPlan pl;
   int rc = make_plan(cfg, n_voxels, &pl);
   if (rc != DSVT_OK) return rc;
-  *bytes = pl.total;
+  *bytes = pool_scratch(*cfg, pl, n_voxels);
   return DSVT_OK;
 }
 
 namespace {
 
-// The whole call on scratch memory `ws` of at least pl.total bytes (checked by the callers).
+// The whole call on scratch memory `ws` of at least pl.total bytes (checked by the callers); see pool_apart.
 int run_attn_pool(const dsvt_pool_cfg* cfg, const PoolPlan& pl, const int32_t* coords, const void* x, int32_t n_voxels,
-                  int32_t* out_coords, void* out, int32_t* n_out, void* ws, int32_t* status, hipStream_t st) {
+                  int32_t* out_coords, void* out, int32_t* n_out, void* ws, size_t ws_bytes, int32_t* status, hipStream_t st) {
   char* base = reinterpret_cast<char*>(ws);
-  uint32_t* bitmap = reinterpret_cast<uint32_t*>(base + pl.off_bitmap);
-  int32_t* prefix = reinterpret_cast<int32_t*>(base + pl.off_prefix);
-  int32_t* inds = reinterpret_cast<int32_t*>(base + pl.off_inds);
+  const bool split = pool_apart(*cfg, n_voxels) && ws_bytes >= pl.total2;
+  uint32_t* bitmap = reinterpret_cast<uint32_t*>(base + (split ? pl.off_bitmap2 : pl.off_bitmap));
+  int32_t* prefix = reinterpret_cast<int32_t*>(base + (split ? pl.off_prefix2 : pl.off_prefix));
+  int32_t* inds = reinterpret_cast<int32_t*>(base + (split ? pl.off_inds2 : pl.off_inds));
+  uint32_t* multi = split ? bitmap + pl.words_pitch : nullptr;
+  int32_t* multi_prefix = split ? prefix + pl.words_pitch : nullptr;
+  int2* single = split ? reinterpret_cast<int2*>(base + pl.off_single) : nullptr;
+  int32_t* multi_reg = split ? reinterpret_cast<int32_t*>(base + pl.off_reg) : nullptr;
+  int32_t* n_multi = split ? reinterpret_cast<int32_t*>(base + pl.off_count) : nullptr;
   const int tb = 256;
   {
     dsvt_prof_scope ps(DSVT_K_POOL_GROUP, st);
-    const int64_t n_inds = (int64_t)n_voxels * pl.g.P;
-    const int64_t n_clear = pl.n_words > n_inds ? pl.n_words : n_inds;
-    kp_clear<<<(unsigned)dsvt_ceil_div(n_clear, tb), tb, 0, st>>>(bitmap, pl.n_words, inds, n_inds);
+    const int64_t n_inds = (int64_t)(split ? n_voxels / 2 : n_voxels) * pl.g.P;
+    const int64_t n_words = split ? 2 * (int64_t)pl.words_pitch : pl.n_words;
+    const int64_t n_clear = n_words > n_inds ? n_words : n_inds;
+    kp_clear<<<(unsigned)dsvt_ceil_div(n_clear, tb), tb, 0, st>>>(bitmap, n_words, inds, n_inds);
     kp_mark<<<(unsigned)dsvt_ceil_div(n_voxels, tb), tb, 0, st>>>(pl.g, reinterpret_cast<const int4*>(coords), n_voxels,
-                                                                  bitmap, status);
-    k_block_scan<true><<<block_scan_grid(pl.n_words), 1024, 0, st>>>(bitmap, prefix, pl.n_words, nullptr, n_out);
+                                                                  bitmap, multi, status);
+    k_block_scan<true><<<dim3(block_scan_grid(pl.n_words), split ? 2 : 1), 1024, 0, st>>>(
+        bitmap, prefix, pl.n_words, nullptr, n_out, (int64_t)pl.words_pitch, n_multi);
     kp_emit<<<(unsigned)dsvt_ceil_div(n_voxels, tb), tb, 0, st>>>(pl.g, reinterpret_cast<const int4*>(coords), n_voxels,
-                                                                  bitmap, prefix, inds, out_coords);
+                                                                  bitmap, prefix, inds, out_coords, multi, multi_prefix,
+                                                                  multi_reg, single);
   }
+  const PoolLists ls = {inds, single, multi_reg, n_multi};
   int rc;
   if (cfg->dtype == DSVT_BF16) {
-    if (cfg->C == 192) rc = launch_pool_attention<bf16_t, 192, 8, 3, 3>(*cfg, pl, inds, n_out, x, out, n_voxels, st);
-    else if (cfg->C == 128) rc = launch_pool_attention<bf16_t, 128, 8, 2, 2>(*cfg, pl, inds, n_out, x, out, n_voxels, st);
-    else rc = launch_pool_attention<bf16_t, 64, 4, 1, 1>(*cfg, pl, inds, n_out, x, out, n_voxels, st);
+    if (cfg->C == 192) rc = launch_pool_attention<bf16_t, 192, 8, 3, 3>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
+    else if (cfg->C == 128) rc = launch_pool_attention<bf16_t, 128, 8, 2, 2>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
+    else rc = launch_pool_attention<bf16_t, 64, 4, 1, 1>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
   } else {
-    rc = launch_pool_attention<float, 64, 4, 1, 1>(*cfg, pl, inds, n_out, x, out, n_voxels, st);
+    rc = launch_pool_attention<float, 64, 4, 1, 1>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
   }
   if (rc != DSVT_OK) return rc;
   DSVT_HIP_TRY(hipGetLastError());
@@ -582,7 +773,7 @@ extern "C" int dsvt_attn_pool(const dsvt_pool_cfg* cfg, const int32_t* coords, c
   if (rc != DSVT_OK) return rc;
   if (!ws) return DSVT_EINVAL;
   if (ws_bytes < pl.total) return DSVT_ENOSPC;
-  return run_attn_pool(cfg, pl, coords, x, n_voxels, out_coords, out, n_out, ws, status, (hipStream_t)stream);
+  return run_attn_pool(cfg, pl, coords, x, n_voxels, out_coords, out, n_out, ws, ws_bytes, status, (hipStream_t)stream);
 }
 
 extern "C" int dsvt_attn_pool_static(const dsvt_pool_cfg* cfg, const int32_t* coords, const void* x, int32_t n_voxels,
@@ -594,5 +785,5 @@ extern "C" int dsvt_attn_pool_static(const dsvt_pool_cfg* cfg, const int32_t* co
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != DSVT_OK) return rc;
-  return run_attn_pool(cfg, pl, coords, x, n_voxels, out_coords, out, n_out, ws, status, (hipStream_t)stream);
+  return run_attn_pool(cfg, pl, coords, x, n_voxels, out_coords, out, n_out, ws, kStaticScratchBytes, status, (hipStream_t)stream);
 }
