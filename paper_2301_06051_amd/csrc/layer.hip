@@ -368,7 +368,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   DSVT_PHASE(1);                                 // rows known
   const int R = __builtin_amdgcn_readfirstlane(set_r0[ns]);
   const int RT = (R + 15) >> 4;
-  const int RTK = ((RT + 1) >> 1) << 1;          // the LayerNorm phases run on an even number of row tiles
+  const int RTH = (RT + 1) >> 1;                 // the LayerNorm phases: row tiles of the first half
 
   // ---- 2. gather (Eq. 4): rows of x -> Xs, 16 bytes per thread, dead rows zero.  The loads are
   // unconditional (clamped addresses).  The Q/K/V weights are requested after the barrier that
@@ -384,7 +384,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     for (int k = 0; k < G; ++k) {
       const int idx = tid + k * NTHREADS;
       const int r = idx / CH, c = idx - r * CH;
-      const int v = r < RTK * 16 ? row_vox[r] : -1;
+      const int v = r < RT * 16 ? row_vox[r] : -1;
       live[k] = v >= 0;
       gv[k] = reinterpret_cast<const uint4*>(x + (size_t)(v >= 0 ? v : 0) * C)[c];
     }
@@ -392,7 +392,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     for (int k = 0; k < G; ++k) {
       const int idx = tid + k * NTHREADS;
       const int r = idx / CH, c = idx - r * CH;
-      if (idx < RTK * 16 * CH)
+      if (idx < RT * 16 * CH)
         *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16) =
             live[k] ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
     }
@@ -425,13 +425,15 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       }
     }, 2 * C / (16 * NT_QKV));
   }
-  GemmPhase<T, NT_O, C, C, NW, 2> oproj(reinterpret_cast<const T*>(p.w_o), wave);
-  oproj.prefetch();                              // in flight during the attention phase
-  // LayerNorm phases (small weight matrices): every wavefront owns C / 4 features of one half of
+  // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one half of
   // the row tiles; the Q/K/V and first MLP projections (bandwidth-heavy) give a wavefront all rows
-  // of its output tiles instead, so that each of their weight fragments is loaded only once
+  // of its output tiles instead, so that each of their weight fragments is loaded only once.  An odd number of row
+  // tiles gives the second half one less; in a tile of a single one the second half has no rows and requests no
+  // weights (220 KB of the 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
   const int og_own = wave % SG;
-  const int rt_own = (wave / SG) * (RTK >> 1), HC = wave < 2 * SG ? RTK >> 1 : 0;   // HC = 0: a wavefront without an item
+  const int rt_own = wave < SG ? 0 : RTH, HC = wave < SG ? RTH : (wave < 2 * SG ? RT - RTH : 0);   // HC = 0: a wavefront without an item
+  GemmPhase<T, NT_O, C, C, NW, 2> oproj(reinterpret_cast<const T*>(p.w_o), wave);
+  if (HC > 0) oproj.prefetch();                  // in flight during the attention phase
   const int o_own = og_own * 16 * NT_O;
   lds_barrier();
   DSVT_REFRESH_LANE();
@@ -516,7 +518,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       }
     });
     GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
-    ffn2.prefetch();
+    if (HC > 0) ffn2.prefetch();
     const int o_own2 = og_own * 16 * NT_2;
     f32x4 b24[NT_2];
 #pragma unroll

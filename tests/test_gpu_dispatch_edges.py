@@ -64,3 +64,22 @@ def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
         assert torch.all(out[len(ref_c):] == 0)
         outs.append(out)
     assert rel_err(outs[0], outs[1].double().cpu().numpy()) < TOL[dtype]
+
+
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("rows", [1, 16, 17, 33, 49, 65, 81, 96])
+def test_layer_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype, rows):
+    """One tile with every number of 16-row tiles: the LayerNorm phases split them unevenly over two halves, and in a
+    tile of one the second half has nothing."""
+    grid, win, tau = (12, 12, 1), (12, 12, 1), 96
+    cell = np.random.Generator(np.random.Philox(31)).permutation(144)[:rows]
+    coords = np.stack([0 * cell, cell // 12, cell % 12, 0 * cell], 1).astype(np.int32)
+    x = synth.make_features(32, rows, C, dtype)
+    ws = [synth.make_layer_weights(33 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
+    print(f"[case] one tile of {rows} rows C={C} {dtype}", flush=True)
+    oms = [orc.partition(coords, grid, win, (0, 0, 0), tau, a) for a in (0, 1)]
+    cd = dev_coords(coords)
+    gms = [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
+    out = dsvt.dsvt_block([dsvt.LayerWeights(w) for w in ws], gms, cd, dev_feats(x, dtype))
+    torch.cuda.synchronize()
+    assert rel_err(out, orc.block(ws, oms, coords, x)) < TOL[dtype]
