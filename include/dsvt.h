@@ -305,6 +305,8 @@ typedef struct {
   int32_t relu;
 } dsvt_vfe_cfg;
 
+/* Scratch for dsvt_vfe.  (On grids of up to 8 M cells room for a counter per cell is part of it where that is more
+ * than the call needs at least; dsvt_vfe also takes the smaller scratch and then counts the points voxel by voxel.) */
 int dsvt_vfe_workspace_size(const dsvt_vfe_cfg* cfg, int32_t n_points, int32_t max_voxels, size_t* bytes);
 
 /* points      [device] float [n_points, f_in]

@@ -2,10 +2,11 @@
 // through a voxel feature encoding module; the paper cites earlier pillar encoders for it).  Built here: an
 // optional per-point linear map followed by the channel-wise maximum over each voxel's points.
 //
-// Voxels are found without a sort: an occupancy map over the grid's cells, in key order (a byte per cell while
-// the points mark it, then packed to bits), and a pop-count scan number the non-empty cells in ascending key; a
-// counting sort by voxel (one returning atomic per point) then copies each voxel's points into one run of rows,
-// and wavefronts with equal shares of those rows take the maxima from LDS.  The order of a voxel's points in its
+// Voxels are found without a sort: the points are counted in a map over the grid's cells, in key order, and a scan
+// over its words of 32 cells numbers the non-empty ones in ascending key and gives every voxel a run of rows; the value
+// a point's atomic returned is its place there (a counting sort), and wavefronts with equal shares of the rows take
+// the maxima from LDS.  (Grids too large for a counter per cell: the map holds a byte per cell, and the points are
+// counted by voxel once the voxels are numbered.  See count_by_cell.)  The order of a voxel's points in its
 // run varies from call to call, the maximum does not.  Pure bandwidth: points are read twice and copied once,
 // the feature rows written once.
 #include "common.h"
@@ -87,20 +88,75 @@ __global__ void kv_count(const uint32_t* __restrict__ keys, int32_t n, const uin
   point_pos[i] = pos;
 }
 
+// Points counted by cell instead (see count_by_cell): a counter per cell takes the marks, and the value a point's atomic
+// returns is its place among the voxel's points, so that neither kv_count nor a scan of the voxels' counts is needed.
+__global__ void kv_mark_count(VfeGeom g, const float* __restrict__ points, const int32_t* __restrict__ point_batch, int32_t n,
+                              uint32_t* __restrict__ cell_cnt, uint32_t* __restrict__ keys, int32_t* __restrict__ point_pos) {
+  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t key = point_key(g, points + (int64_t)i * g.f_in, point_batch ? point_batch[i] : 0, nullptr);
+  keys[i] = key;
+  if (key != kOutside) point_pos[i] = (int32_t)atomicAdd(&cell_cnt[key], 1u);
+}
+
+// A thread per cell, 32 cells a bitmap word: the word, how many of its cells are occupied and how many points they hold,
+// and in the place of each cell's counter the points of the word's cells before it.
+__global__ void kv_pack_count(uint32_t* __restrict__ cell_cnt, int64_t n_words, uint32_t* __restrict__ bitmap,
+                              uint32_t* __restrict__ word_vox, uint32_t* __restrict__ word_rows) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;      // (whole wavefronts: n_words is a multiple of 64)
+  if (i >= n_words * 32) return;
+  const int32_t lane = threadIdx.x & 63;
+  const uint32_t c = cell_cnt[i];
+  const uint64_t occ = __ballot(c != 0u);
+  uint32_t incl = c;
+#pragma unroll
+  for (int32_t d = 1; d < 32; d <<= 1) {
+    const uint32_t up = __shfl_up(incl, d, 32);
+    if ((lane & 31) >= d) incl += up;
+  }
+  cell_cnt[i] = incl - c;
+  if ((lane & 31) == 31) {
+    const uint32_t word = (uint32_t)(occ >> (lane & 32));
+    bitmap[i >> 5] = word;
+    word_vox[i >> 5] = (uint32_t)__popc(word);
+    word_rows[i >> 5] = incl;
+  }
+}
+
+// Where kv_place finds a point's voxel and run: by voxel (kv_count's arrays), or by cell.
+struct PlaceSrc {
+  const int32_t *point_vox, *offs;                                    // by voxel
+  const uint32_t *keys, *bitmap, *cell_before;                        // by cell
+  const int32_t *vox_prefix, *row_prefix;
+  int32_t max_voxels;
+  int32_t *n_rows, *status;
+};
+
 // Counting sort, second half: every point's row copied to its voxel's run, so that the reduction reads
 // consecutive (zero-padded) rows; run_info[j] = (voxel of row j, first row of its run, first row of the next run).
 // The first point of a voxel also writes the voxel's coordinates.
-template <int PITCH4>
+template <int PITCH4, bool BY_CELL>
 __global__ void kv_place(VfeGeom g, const float* __restrict__ points, const int32_t* __restrict__ point_batch,
-                         const int32_t* __restrict__ point_vox, const int32_t* __restrict__ point_pos,
-                         const int32_t* __restrict__ offs, int32_t n, float4* __restrict__ sorted,
+                         PlaceSrc s, const int32_t* __restrict__ point_pos, int32_t n, float4* __restrict__ sorted,
                          int4* __restrict__ run_info, int32_t* __restrict__ coords) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int32_t v = point_vox[i];
-  if (v < 0) return;
+  int32_t v, start, end;
+  if constexpr (BY_CELL) {
+    const uint32_t key = s.keys[i];
+    if (key == kOutside) return;
+    const uint32_t word = key >> 5, bit = key & 31u;
+    v = s.vox_prefix[word] + __popc(s.bitmap[word] & ((1u << bit) - 1u));
+    if (v >= s.max_voxels) { atomicOr(s.status, DSVT_ST_VOXEL_OVERFLOW); return; }
+    start = s.row_prefix[word] + (int32_t)s.cell_before[key];
+    end = bit == 31u ? s.row_prefix[word + 1] : s.row_prefix[word] + (int32_t)s.cell_before[key + 1];
+  } else {
+    v = s.point_vox[i];
+    if (v < 0) return;
+    start = s.offs[v];
+    end = s.offs[v + 1];
+  }
   const int32_t pos = point_pos[i], f_in = g.f_in;
-  const int32_t start = offs[v], end = offs[v + 1];
   const int32_t j = start + pos;                             // j < end <= n
   const float* src = points + (int64_t)i * f_in;
   float f[4 * PITCH4];                                       // rows padded with zeros to whole 16-byte pieces
@@ -114,6 +170,7 @@ __global__ void kv_place(VfeGeom g, const float* __restrict__ points, const int3
     int4 cell = make_int4(0, 0, 0, 0);
     point_key(g, src, point_batch ? point_batch[i] : 0, &cell);
     reinterpret_cast<int4*>(coords)[v] = cell;
+    if (BY_CELL && v == s.max_voxels - 1) *s.n_rows = end;   // the rows of the voxels that are kept (nobody reads it here)
   }
 }
 
@@ -235,6 +292,9 @@ struct VfePlan {
   VfeGeom g;
   int64_t n_words;
   size_t off_cells, off_bitmap, off_prefix, off_count, off_offs, off_keys, off_vox, off_pos, off_info, off_nrows, off_sorted, total;
+  // the layout of a call that counts points by cell; row prefixes lie words_pitch behind the voxel prefixes, likewise the counts
+  int64_t cells, words_pitch;
+  size_t off_cnt2, off_bitmap2, off_words2, off_prefix2, off_keys2, off_pos2, off_info2, off_nrows2, off_sorted2, total2;
 };
 
 int make_plan(const dsvt_vfe_cfg* cfg, int32_t n_points, int32_t max_voxels, VfePlan* pl) {
@@ -269,8 +329,31 @@ int make_plan(const dsvt_vfe_cfg* cfg, int32_t n_points, int32_t max_voxels, Vfe
   pl->off_nrows = take(4);
   pl->off_sorted = take((size_t)n_points * ((cfg->f_in + 3) / 4) * 16);
   pl->total = off;
+  pl->cells = cells;
+  pl->words_pitch = pl->n_words + 64;                            // room for the entry behind the last word's
+  off = 0;
+  pl->off_cnt2 = take((size_t)pl->n_words * 32 * 4);
+  pl->off_bitmap2 = take((size_t)pl->n_words * 4);
+  pl->off_words2 = take((size_t)pl->words_pitch * 8);
+  pl->off_prefix2 = take((size_t)pl->words_pitch * 8);
+  pl->off_keys2 = take((size_t)n_points * 4);
+  pl->off_pos2 = take((size_t)n_points * 4);
+  pl->off_info2 = take((size_t)n_points * 16);
+  pl->off_nrows2 = take(4);
+  pl->off_sorted2 = take((size_t)n_points * ((cfg->f_in + 3) / 4) * 16);
+  pl->total2 = off;
   return DSVT_OK;
 }
+
+// Whether a call counts its points by cell: six launches in a row where counting by voxel takes eight, for 4 bytes a cell
+// cleared, added up and scanned instead of one.  Bound by the launches and the latency inside them, not by these bytes.  By
+// voxel -> by cell, 468 x 468 cells, C = 192: 20,000 points 32.5 -> 27.5 us, 60,000 39 -> 33.6, 180,000 57.8 -> 51.4,
+// 400,000 104 -> 99; 180,000 points on grids of 4, 8, 16, 32 layers 63.5 -> 58.4, 67.3 -> 63.5, 74.0 -> 72.3, 84.8 -> 83.1.
+// The gain is gone at about the limit: 8 M cells, 32 MB of counters.
+constexpr int64_t kByCellMax = 1ll << 23;
+bool count_by_cell(const VfePlan& pl, size_t ws_bytes) { return pl.cells <= kByCellMax && pl.total2 <= ws_bytes; }
+// Scratch a call asks for: room for the layout it would use.  One with room for the first layout only counts by voxel.
+size_t vfe_scratch(const VfePlan& pl) { return pl.cells <= kByCellMax && pl.total2 > pl.total ? pl.total2 : pl.total; }
 
 }  // namespace
 
@@ -279,7 +362,7 @@ extern "C" int dsvt_vfe_workspace_size(const dsvt_vfe_cfg* cfg, int32_t n_points
   VfePlan pl;
   const int rc = make_plan(cfg, n_points, max_voxels, &pl);
   if (rc != DSVT_OK) return rc;
-  *bytes = pl.total;
+  *bytes = vfe_scratch(pl);
   return DSVT_OK;
 }
 
@@ -295,43 +378,64 @@ extern "C" int dsvt_vfe(const dsvt_vfe_cfg* cfg, const float* points, const int3
   if (ws_bytes < pl.total) return DSVT_ENOSPC;
   hipStream_t st = (hipStream_t)stream;
   char* base = reinterpret_cast<char*>(ws);
-  uint8_t* cells = reinterpret_cast<uint8_t*>(base + pl.off_cells);
-  uint32_t* bitmap = reinterpret_cast<uint32_t*>(base + pl.off_bitmap);
-  int32_t* prefix = reinterpret_cast<int32_t*>(base + pl.off_prefix);
-  int32_t* count = reinterpret_cast<int32_t*>(base + pl.off_count);
-  int32_t* offs = reinterpret_cast<int32_t*>(base + pl.off_offs);
-  uint32_t* keys = reinterpret_cast<uint32_t*>(base + pl.off_keys);
-  int32_t* vox = reinterpret_cast<int32_t*>(base + pl.off_vox);
-  int32_t* pos = reinterpret_cast<int32_t*>(base + pl.off_pos);
-  float* sorted = reinterpret_cast<float*>(base + pl.off_sorted);
-  int4* run_info = reinterpret_cast<int4*>(base + pl.off_info);
-  int32_t* n_rows = reinterpret_cast<int32_t*>(base + pl.off_nrows);
+  const bool by_cell = count_by_cell(pl, ws_bytes);
+  uint32_t* bitmap = reinterpret_cast<uint32_t*>(base + (by_cell ? pl.off_bitmap2 : pl.off_bitmap));
+  uint32_t* keys = reinterpret_cast<uint32_t*>(base + (by_cell ? pl.off_keys2 : pl.off_keys));
+  int32_t* pos = reinterpret_cast<int32_t*>(base + (by_cell ? pl.off_pos2 : pl.off_pos));
+  float4* sorted4 = reinterpret_cast<float4*>(base + (by_cell ? pl.off_sorted2 : pl.off_sorted));
+  int4* run_info = reinterpret_cast<int4*>(base + (by_cell ? pl.off_info2 : pl.off_info));
+  int32_t* n_rows = reinterpret_cast<int32_t*>(base + (by_cell ? pl.off_nrows2 : pl.off_nrows));
   const int tb = 256;
   const unsigned pb = (unsigned)dsvt_ceil_div(n_points, tb);
   {
     dsvt_prof_scope ps(DSVT_K_VFE_GROUP, st);
-    const int64_t n_count = (int64_t)max_voxels + 1, n16 = pl.n_words * 2;
-    const int64_t n_clear = n16 > n_count ? n16 : n_count;
-    kv_clear<<<(unsigned)dsvt_ceil_div(n_clear, tb), tb, 0, st>>>(reinterpret_cast<uint4*>(cells), n16, count, n_count);
-    kv_mark<<<pb, tb, 0, st>>>(pl.g, points, point_batch, n_points, cells, keys);
-    kv_pack<<<(unsigned)dsvt_ceil_div(pl.n_words, tb), tb, 0, st>>>(reinterpret_cast<const uint4*>(cells), pl.n_words, bitmap);
-    k_block_scan<true><<<block_scan_grid(pl.n_words), 1024, 0, st>>>(bitmap, prefix, pl.n_words, nullptr, n_voxels);
-    kv_count<<<pb, tb, 0, st>>>(keys, n_points, bitmap, prefix, max_voxels, count, vox, pos, status);
-    k_block_scan<false, true><<<block_scan_grid(max_voxels), 1024, 0, st>>>(reinterpret_cast<const uint32_t*>(count), offs, max_voxels, n_voxels, n_rows);
-    float4* sorted4 = reinterpret_cast<float4*>(sorted);
-    switch ((cfg->f_in + 3) / 4) {
-      case 1: kv_place<1><<<pb, tb, 0, st>>>(pl.g, points, point_batch, vox, pos, offs, n_points, sorted4, run_info, coords); break;
-      case 2: kv_place<2><<<pb, tb, 0, st>>>(pl.g, points, point_batch, vox, pos, offs, n_points, sorted4, run_info, coords); break;
-      case 3: kv_place<3><<<pb, tb, 0, st>>>(pl.g, points, point_batch, vox, pos, offs, n_points, sorted4, run_info, coords); break;
-      default: kv_place<4><<<pb, tb, 0, st>>>(pl.g, points, point_batch, vox, pos, offs, n_points, sorted4, run_info, coords); break;
+    PlaceSrc src = {};
+    if (by_cell) {
+      uint32_t* cnt = reinterpret_cast<uint32_t*>(base + pl.off_cnt2);
+      uint32_t* words = reinterpret_cast<uint32_t*>(base + pl.off_words2);
+      int32_t* prefix = reinterpret_cast<int32_t*>(base + pl.off_prefix2);
+      const int64_t n16 = pl.n_words * 8;
+      kv_clear<<<(unsigned)dsvt_ceil_div(n16, tb), tb, 0, st>>>(reinterpret_cast<uint4*>(cnt), n16, nullptr, 0);
+      kv_mark_count<<<pb, tb, 0, st>>>(pl.g, points, point_batch, n_points, cnt, keys, pos);
+      kv_pack_count<<<(unsigned)dsvt_ceil_div(pl.n_words * 32, tb), tb, 0, st>>>(cnt, pl.n_words, bitmap, words, words + pl.words_pitch);
+      k_block_scan<false, true><<<dim3(block_scan_grid(pl.n_words), 2), 1024, 0, st>>>(words, prefix, pl.n_words, nullptr, n_voxels,
+                                                                                     pl.words_pitch, n_rows);
+      src.keys = keys; src.bitmap = bitmap; src.cell_before = cnt;
+      src.vox_prefix = prefix; src.row_prefix = prefix + pl.words_pitch;
+      src.max_voxels = max_voxels; src.n_rows = n_rows; src.status = status;
+    } else {
+      uint8_t* cells = reinterpret_cast<uint8_t*>(base + pl.off_cells);
+      int32_t* prefix = reinterpret_cast<int32_t*>(base + pl.off_prefix);
+      int32_t* count = reinterpret_cast<int32_t*>(base + pl.off_count);
+      int32_t* offs = reinterpret_cast<int32_t*>(base + pl.off_offs);
+      int32_t* vox = reinterpret_cast<int32_t*>(base + pl.off_vox);
+      const int64_t n_count = (int64_t)max_voxels + 1, n16 = pl.n_words * 2;
+      const int64_t n_clear = n16 > n_count ? n16 : n_count;
+      kv_clear<<<(unsigned)dsvt_ceil_div(n_clear, tb), tb, 0, st>>>(reinterpret_cast<uint4*>(cells), n16, count, n_count);
+      kv_mark<<<pb, tb, 0, st>>>(pl.g, points, point_batch, n_points, cells, keys);
+      kv_pack<<<(unsigned)dsvt_ceil_div(pl.n_words, tb), tb, 0, st>>>(reinterpret_cast<const uint4*>(cells), pl.n_words, bitmap);
+      k_block_scan<true><<<block_scan_grid(pl.n_words), 1024, 0, st>>>(bitmap, prefix, pl.n_words, nullptr, n_voxels);
+      kv_count<<<pb, tb, 0, st>>>(keys, n_points, bitmap, prefix, max_voxels, count, vox, pos, status);
+      k_block_scan<false, true><<<block_scan_grid(max_voxels), 1024, 0, st>>>(reinterpret_cast<const uint32_t*>(count), offs, max_voxels, n_voxels, n_rows);
+      src.point_vox = vox; src.offs = offs;
     }
+#define DSVT_VFE_PLACE(P4)                                                                                                        \
+    if (by_cell) kv_place<P4, true><<<pb, tb, 0, st>>>(pl.g, points, point_batch, src, pos, n_points, sorted4, run_info, coords);    \
+    else kv_place<P4, false><<<pb, tb, 0, st>>>(pl.g, points, point_batch, src, pos, n_points, sorted4, run_info, coords);           \
+    break
+    switch ((cfg->f_in + 3) / 4) {
+      case 1: DSVT_VFE_PLACE(1);
+      case 2: DSVT_VFE_PLACE(2);
+      case 3: DSVT_VFE_PLACE(3);
+      default: DSVT_VFE_PLACE(4);
+    }
+#undef DSVT_VFE_PLACE
   }
   {
     dsvt_prof_scope ps(DSVT_K_VFE_REDUCE, st);
     const unsigned rb = (unsigned)dsvt_ceil_div(n_points, kQuota * kRedWaves);
     const int cpl = (cfg->C + 63) / 64;                                        // channels per lane: 1, 2, 3, 4 or 8
     const int fin = cfg->f_in <= 6 ? (cfg->f_in < 4 ? 4 : cfg->f_in) : cfg->f_in <= 8 ? 8 : cfg->f_in <= 12 ? 12 : 16;
-    const float4* sorted4 = reinterpret_cast<const float4*>(sorted);
 #define DSVT_VFE_LAUNCH(FIN, CPL)                                                                                  \
     kv_reduce<FIN, CPL><<<rb, 64 * kRedWaves, 0, st>>>(sorted4, run_info, n_rows, n_voxels, max_voxels, n_points, cfg->f_in,    \
                                            cfg->w, cfg->b, cfg->relu, cfg->C, cfg->dtype == DSVT_BF16, x)

@@ -83,3 +83,48 @@ def test_layer_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype, rows):
     out = dsvt.dsvt_block([dsvt.LayerWeights(w) for w in ws], gms, cd, dev_feats(x, dtype))
     torch.cuda.synchronize()
     assert rel_err(out, orc.block(ws, oms, coords, x)) < TOL[dtype]
+
+
+def _vfe_plain_scratch(cells, n_points, max_voxels, f_in):
+    """Scratch of a call that counts its points by voxel: byte map, bitmap and its prefix, counts and their prefix, three
+    words and a run descriptor per point, the row count, the sorted rows."""
+    words = -(-(-(-cells // 32)) // 64) * 64
+    parts = [32 * words, 4 * words, 4 * words, 4 * (max_voxels + 1), 4 * (max_voxels + 1)] + [4 * n_points] * 3
+    return sum(-(-p // 256) * 256 for p in parts + [16 * n_points, 4, n_points * -(-f_in // 4) * 16])
+
+
+@pytest.mark.parametrize("grid,batch,n_points,f_in,cap", [
+    ((64, 32, 1), 1, 5000, 5, None),            # 64 words exactly: the last cell's run ends behind the last word
+    ((64, 32, 1), 1, 5000, 5, 700), ((33, 31, 3), 2, 4000, 3, 1000), ((33, 31, 3), 2, 700, 16, 1),
+    ((1, 1, 1), 1, 257, 4, None), ((512, 512, 2), 1, 3000, 6, None),      # one cell; 16,384 words: one scan chunk
+    ((520, 512, 2), 1, 3000, 12, 2500), ((256, 256, 128), 1, 2000, 5, None), ((256, 256, 129), 1, 2000, 5, None)])   # 8 M cells, more
+def test_vfe_counting_by_cell_and_by_voxel(grid, batch, n_points, f_in, cap):
+    """Both ways of counting, chosen by the scratch: voxels, their order, the maxima and the overflow report are the
+    oracle's bit for bit; every corner of the grid is occupied, and points lie outside it."""
+    lo, size = (-4.0, -2.0, -1.0), (0.5, 0.25, 0.125)
+    rng = np.random.Generator(np.random.Philox(41))
+    ext = np.array(grid, np.float64) * size
+    pts = rng.random((n_points, f_in)).astype(np.float32)
+    pts[:, :3] = lo + ext * (1.1 * rng.random((n_points, 3)) - 0.05)
+    for k in range(8):
+        pts[k, :3] = [l + s * (0.5 if not k >> a & 1 else g - 0.5) for a, (l, s, g) in enumerate(zip(lo, size, grid))]
+    pts[8, 0] = np.nan
+    pb = rng.integers(0, batch, n_points).astype(np.int32)
+    pb[:8] = batch - 1
+    rc, rx = orc.voxel_max_vfe(pts, pb, lo, size, grid, batch)
+    cap = cap or len(rc)
+    kept = min(cap, len(rc))
+    print(f"[case] vfe by cell / by voxel grid={grid} batch={batch} points={n_points} cap={cap} of {len(rc)}", flush=True)
+    vfe = dsvt.Vfe(grid, batch, lo, size, f_in, f_in, "f32", n_points, cap)
+    cells, plain = batch * grid[0] * grid[1] * grid[2], _vfe_plain_scratch(batch * grid[0] * grid[1] * grid[2], n_points, cap, f_in)
+    own = vfe.ws.numel()
+    assert own >= plain and (cells <= 1 << 23 or own == plain)
+    for nbytes in (own, plain, own + 64 * cells):
+        vfe.ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda")
+        vfe.x.fill_(-7.0), vfe.coords.fill_(-7), vfe.status.zero_()
+        dsvt.dsvt_vfe(vfe, torch.as_tensor(pts).cuda(), torch.as_tensor(pb).cuda())
+        torch.cuda.synchronize()
+        assert int(vfe.n_voxels.item()) == len(rc)
+        assert int(vfe.status.item()) == (dsvt.binding.ST_VOXEL_OVERFLOW if cap < len(rc) else 0)
+        assert np.array_equal(vfe.coords[:kept].cpu().numpy(), rc[:kept])
+        assert np.array_equal(vfe.x[:kept].double().cpu().numpy(), rx[:kept])
