@@ -661,7 +661,7 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
 template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2>
 int launch_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,
                  hipStream_t st) {
-  // four instantiations per shape: sets of more than 48 voxels (tau > 48) take one head per attention item, and
+  // four instantiations per shape: sets of more than 48 voxels (tau > 48) take big_heads() heads per attention item, and
   // repeated slots that count as keys (dup_mode 1) multiply the exponentials by the slots' counts
   const bool big = mp.tau > 48, dup = w.dup_mode != 0;
   if (big && dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, true, true>(w, mp, coords, x, out, full, st);
