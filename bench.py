@@ -595,7 +595,7 @@ def vfe_workload(args):
     per_launch_us, per_step_ms = per_kernel(step, 2, min(args.steps, 50))
     nbytes = P * f_in * 4 + N * (C * 2 + 16)               # points read once, rows and coordinates written once
     us = per_launch_us["vfe_group"] + per_launch_us["vfe_reduce"]
-    roofline = {"bound": "hbm", "kernel": "vfe_group (7 launches) + vfe_reduce", "achieved": round(nbytes / (us * 1e-6) / 1e9, 1),
+    roofline = {"bound": "hbm", "kernel": "vfe_group + vfe_reduce", "achieved": round(nbytes / (us * 1e-6) / 1e9, 1),
                 "peak": 8000.0, "unit": "GB/s", "frac": round(nbytes / (us * 1e-6) / 8e12, 5), "traffic": None,
                 "avg_launch_us": round(us, 2), "bytes_per_launch": nbytes}
     return {
