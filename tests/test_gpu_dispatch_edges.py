@@ -128,3 +128,27 @@ def test_vfe_counting_by_cell_and_by_voxel(grid, batch, n_points, f_in, cap):
         assert int(vfe.status.item()) == (dsvt.binding.ST_VOXEL_OVERFLOW if cap < len(rc) else 0)
         assert np.array_equal(vfe.coords[:kept].cpu().numpy(), rc[:kept])
         assert np.array_equal(vfe.x[:kept].double().cpu().numpy(), rx[:kept])
+
+
+@pytest.mark.parametrize("C,f_in,dt", [(1, 5, "f32"), (100, 3, "f32"), (64, 7, "f32"), (192, 5, "bf16"), (260, 4, "f32")])
+@pytest.mark.parametrize("bias", [False, True])
+def test_vfe_runs_at_the_staging_edges(C, f_in, dt, bias):
+    """Voxels whose points end at, before and behind a wavefront's rows, its first load and its staged rows; channels that
+    do not fill the lanes, rows that do not fill the kernel's row length, no bias."""
+    counts = (1, 15, 16, 17, 47, 63, 64, 65, 1, 1, 127, 128, 129, 143, 144, 300, 1, 2, 16, 16)
+    rng = np.random.Generator(np.random.Philox(51))
+    cell = np.repeat(np.arange(len(counts)), counts)[rng.permutation(sum(counts))]
+    pts = rng.random((len(cell), f_in)).astype(np.float32)
+    pts[:, 0] = cell + 0.5 * pts[:, 0] + 0.25
+    pb = np.zeros(len(cell), np.int32)
+    grid, lo, size = (len(counts), 1, 1), (0.0, 0.0, 0.0), (1.0, 1.0, 1.0)
+    w, b = synth.make_vfe_weights(52, C, f_in)
+    print(f"[case] vfe runs C={C} f_in={f_in} {dt} bias={bias}", flush=True)
+    rc, rx = orc.voxel_max_vfe(pts, pb, lo, size, grid, 1, w, b if bias else np.zeros_like(b), False)
+    vfe = dsvt.Vfe(grid, 1, lo, size, f_in, C, dt, len(pts), len(pts), torch.as_tensor(w).cuda(),
+                   torch.as_tensor(b).cuda() if bias else None, False)
+    dsvt.dsvt_vfe(vfe, torch.as_tensor(pts).cuda(), None)
+    torch.cuda.synchronize()
+    n = int(vfe.n_voxels.item())
+    assert n == len(rc) and np.array_equal(vfe.coords[:n].cpu().numpy(), rc)
+    assert rel_err(vfe.x[:n], rx) <= (1e-5 if dt == "f32" else 4e-3)        # f_in fused products; one rounding to bf16
