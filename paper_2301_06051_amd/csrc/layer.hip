@@ -22,13 +22,16 @@ constexpr int kRowsPad = kRowsMax + 16;          // per-row arrays are read 4 at
 constexpr int kMaxItems = 128;                  // attention items: (set, query tile, group of heads); see item_groups()
 // Sets per workgroup when no tile list is given.
 __host__ __device__ constexpr int fixed_sets(int tau) { return tau <= kRowsMax / 2 ? 2 : 1; }
+// The sets a kernel is instantiated for: of up to three key tiles (48 voxels), or of up to six (96), these last also in
+// a form of fewer registers.
+enum SetSize { kSets48, kSets96, kSets96Slim };
 // A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each; a larger one (its logits and
 // positional terms take more registers) into items of two heads: the table rows of a (query, key) pair and their
 // indices are fetched and computed once for both.  Per layer of the 20,000-voxel frame of 30 x 30 windows (C = 128, sets
 // of up to 90): one head per item 46 us, two 38 us, four 40 us (spills).  C = 192 with repeats counted as keys
-// keeps one head per item (two spill there).  At most one set of a tile is that large, so a tile has at most
-// 8 * 6 + 2 * (3 + 11) = 76 items.
-__host__ __device__ constexpr int big_heads(int C, bool dup) { return C == 192 && dup ? 1 : 2; }
+// keeps one head per item (two spill there), and so does kSets96Slim.  At most one set of a tile is that large, so a
+// tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
+__host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
 constexpr int kHalfTiles = kRowTiles / 2;        // the LayerNorm-phase work items cover half of the row tiles
 constexpr int kLayerWaves = 12;                  // three per SIMD: one workgroup per CU (LDS), the other wavefronts hide one's waits
@@ -229,25 +232,24 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, T* Qs, const T* Ks,
   }
 }
 
-// An item of a set with kts key tiles: up to three key tiles half of the heads per item, beyond that (BIG kernels
-// only) big_heads().
-template <typename T, int C, int HEADS, int HID, bool BIG, bool DUP>
+// An item of a set with kts key tiles: up to three key tiles half of the heads per item, beyond that big_heads().
+template <typename T, int C, int HEADS, int HID, SetSize SETS, bool DUP>
 __device__ __forceinline__ void attn_any(const LayerDev& p, T* Qs, const T* Ks, const T* Vt, const int32_t* row_lin,
                                          const float* row_mult, int r0, int nu, int qt, int hh, int kts, int rows_ready) {
-  constexpr int HG2 = HEADS / 2, HGB = big_heads(C, DUP);
+  constexpr int HG2 = HEADS / 2, HGB = big_heads(C, DUP, SETS);
   if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-  else if (!BIG || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-  else if constexpr (BIG) {
+  else if (SETS == kSets48 || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+  else if constexpr (SETS != kSets48) {
     if (kts == 4) attn_item<T, C, HEADS, HID, 4, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
     else if (kts == 5) attn_item<T, C, HEADS, HID, 5, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
     else attn_item<T, C, HEADS, HID, 6, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
   }
 }
 
-// BIG: the instantiation for tau > 48 (sets of four to six key tiles); the common one does not carry that code.
-template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, bool BIG, bool DUP>
-__global__ void __launch_bounds__(kLayerWaves * 64)
+// SETS: the instantiations for sets of four to six key tiles; the common one does not carry that code.
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
+__global__ void __launch_bounds__(kLayerWaves * 64, SETS == kSets96Slim ? 6 : 3)   // (wavefronts per SIMD: two workgroups, one)
 k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* out, int full_layer) {
   // out may be x: a tile's rows are read, then written, by this workgroup only
   typedef LayerLds<T, C, HEADS, HID> L;
@@ -291,12 +293,12 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       hdr_rows = hdr_rows < 0 ? 0 : (hdr_rows > kRowsMax ? kRowsMax : hdr_rows);
       if (lane == 0) { set_nu[kMaxSets] = hdr_ns; set_r0[hdr_ns] = hdr_rows; }
       if (lane >= 2 && lane < 2 + kMaxSets && lane - 2 < hdr_ns) set_r0[lane - 2] = word < 0 ? 0 : (word > kRowsMax - 4 ? kRowsMax - 4 : word);
-      constexpr int kNuMax = BIG ? kTauMax : 48;
+      constexpr int kNuMax = SETS == kSets48 ? 48 : kTauMax;
       const int nu_s = word < 1 ? 1 : (word > kNuMax ? kNuMax : word);
       const int ls = lane - 2 - kMaxSets;        // the lanes holding the sets' sizes also list the sets' attention items
       if (ls >= 0 && ls < kMaxSets) set_nu[ls] = nu_s;
       const int kts = (ls >= 0 && ls < hdr_ns) ? (nu_s + 15) >> 4 : 0;
-      const int ngr = item_groups(kts, HEADS, big_heads(C, DUP));
+      const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS));
       int incl = ngr * kts;                      // items: (set, query tile, group of heads)
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
@@ -341,7 +343,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         set_r0[s] = r; r += (set_nu[s] + 3) & ~3;
         const int kts = (set_nu[s] + 15) >> 4;
         for (int qt = 0; qt < kts; ++qt)
-          for (int hh = 0; hh < item_groups(kts, HEADS, big_heads(C, DUP)); ++hh)
+          for (int hh = 0; hh < item_groups(kts, HEADS, big_heads(C, DUP, SETS)); ++hh)
             if (n < kMaxItems) items[n++] = s | (qt << 8) | (hh << 12) | (kts << 16);
       }
       set_r0[ns] = r;
@@ -446,7 +448,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       const int d = __builtin_amdgcn_readfirstlane(items[it]);
       const int s = d & 255, qt = (d >> 8) & 15, hh = (d >> 12) & 15, kts = d >> 16;
       const int r0 = __builtin_amdgcn_readfirstlane(set_r0[s]), nu = __builtin_amdgcn_readfirstlane(set_nu[s]);
-      attn_any<T, C, HEADS, HID, BIG, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, kts, RT * 16);
+      attn_any<T, C, HEADS, HID, SETS, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, kts, RT * 16);
     }
   }
   f32x4 bo4[NT_O];
@@ -641,10 +643,10 @@ int check_maps(const dsvt_maps& mp) {
   return DSVT_OK;
 }
 
-template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, bool BIG, bool DUP>
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
 int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,
                    hipStream_t st) {
-  auto kern = k_layer<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, BIG, DUP>;
+  auto kern = k_layer<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP>;
   constexpr size_t lds = LayerLds<T, C, HEADS, HID>::total;
   static std::atomic<uint64_t> lds_allowed{0};
   if (int rc = dsvt_allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed)) return rc;
@@ -658,16 +660,37 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
   return DSVT_OK;
 }
 
+// Whether sets of 49 voxels and more take kSets96Slim, where a tile leaves room in the LDS for a second workgroup on the
+// compute unit (C = 64 in bf16): it also leaves room in the registers (69 of them, 80 with repeats as keys; kSets96: 108 and
+// 132), which pays once there are more tiles than compute units -- about max(48, 5 / 6 tau) voxels a tile -- and up to 72
+// voxels a set; beyond, fetching the table rows once for two heads is worth more.  Two layers, 30 x 30 windows, kSets96 -> slim:
+// sets of up to 50 voxels 12,000 voxels 24.0 -> 25.6 us, 14,000 35.9 -> 29.9, 40,000 70.6 -> 50.9; of up to 64 12,000 24.3 ->
+// 29.1, 14,000 36.1 -> 31.7, 30,000 57.5 -> 47.9; of up to 72 14,000 26.9 -> 34.1, 16,000 37.5 -> 36.2, 40,000 65.7 -> 63.6; of
+// up to 80 20,000 41.5 -> 43.2.
+bool slim_sets(const dsvt_maps& mp) {
+  const int per_tile = 5 * mp.tau / 6 > 48 ? 5 * mp.tau / 6 : 48;
+  return mp.tau <= 72 && mp.n_voxels > 256 * per_tile;
+}
+
 template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2>
 int launch_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,
                  hipStream_t st) {
-  // four instantiations per shape: sets of more than 48 voxels (tau > 48) take big_heads() heads per attention item, and
-  // repeated slots that count as keys (dup_mode 1) multiply the exponentials by the slots' counts
-  const bool big = mp.tau > 48, dup = w.dup_mode != 0;
-  if (big && dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, true, true>(w, mp, coords, x, out, full, st);
-  if (big) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, true, false>(w, mp, coords, x, out, full, st);
-  if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, false, true>(w, mp, coords, x, out, full, st);
-  return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, false, false>(w, mp, coords, x, out, full, st);
+  // instantiations per range of set sizes and reading of repeated slots: as keys (dup_mode 1) they multiply the
+  // exponentials by the slots' counts
+  constexpr bool kSlim = 2 * LayerLds<T, C, HEADS, HID>::total <= 160 * 1024;
+  const bool dup = w.dup_mode != 0;
+  if (mp.tau <= 48) {
+    if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, true>(w, mp, coords, x, out, full, st);
+    return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, false>(w, mp, coords, x, out, full, st);
+  }
+  if constexpr (kSlim) {
+    if (slim_sets(mp)) {
+      if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets96Slim, true>(w, mp, coords, x, out, full, st);
+      return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets96Slim, false>(w, mp, coords, x, out, full, st);
+    }
+  }
+  if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets96, true>(w, mp, coords, x, out, full, st);
+  return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets96, false>(w, mp, coords, x, out, full, st);
 }
 
 int run_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,

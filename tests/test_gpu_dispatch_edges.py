@@ -11,7 +11,7 @@ dsvt = pytest.importorskip("paper_2301_06051_amd")
 from gpu_util import TOL, dev_coords, dev_feats, gpu_maps, rel_err  # noqa: E402
 
 
-@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
 @pytest.mark.parametrize("dup_mode", [0, 1])
 def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
     """Sets of four to six key tiles (full windows of 64, 65, 80, 81 and 96 voxels): items of one or two heads."""
@@ -30,6 +30,35 @@ def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
     y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0), cd, dev_feats(x, dtype))
     torch.cuda.synchronize()
     assert rel_err(y, orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype]
+
+
+@pytest.mark.parametrize("tau,n,dup_mode", [(50, 12288, 0), (50, 12289, 0), (50, 12289, 1), (64, 13568, 1), (64, 13569, 0), (64, 13569, 1),
+                                            (72, 15361, 0), (72, 15361, 1), (73, 15617, 0)])
+def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
+    """C = 64 in bf16: the frame sizes and set sizes between which the kernel of fewer registers is taken, and full
+    windows of 49 to 72 voxels in it (without a tile list too, where a set may have 64)."""
+    grid, win, C = (480, 480, 1), (24, 24, 1), 64
+    rng = np.random.Generator(np.random.Philox(15))
+    cnt, left = [], n
+    while left > 0:                                          # windows of one set (up to tau) and of two
+        cnt.append(min(left, (48, 49, 50, 51, 60, 64, 65, 72, 73, 20)[len(cnt) % 10]))
+        left -= cnt[-1]
+    rows = []
+    for w, k in enumerate(cnt):
+        cell = rng.permutation(576)[:k]
+        rows.append(np.stack([0 * cell, 24 * (w // 20) + cell // 24, 24 * (w % 20) + cell % 24, 0 * cell], 1))
+    coords = np.concatenate(rows).astype(np.int32)
+    x = synth.make_features(16, n, C, "bf16")
+    w = synth.make_layer_weights(17, C, 4, 128, win, "bf16")
+    print(f"[case] slim kernel tau={tau} n={n} dup={dup_mode}", flush=True)
+    om = orc.partition(coords, grid, win, (0, 0, 0), tau, 0)
+    ref = orc.set_attention(w, om, coords, x, dup_mode)
+    cd = dev_coords(coords)
+    for tiles in (True, False) if tau <= 64 else (True,):
+        maps = gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0, tiles=tiles)
+        y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), maps, cd, dev_feats(x, "bf16"))
+        torch.cuda.synchronize()
+        assert rel_err(y, ref) < TOL["bf16"]
 
 
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
