@@ -305,8 +305,9 @@ typedef struct {
   int32_t relu;
 } dsvt_vfe_cfg;
 
-/* Scratch for dsvt_vfe.  (On grids of up to 8 M cells room for a counter per cell is part of it where that is more
- * than the call needs at least; dsvt_vfe also takes the smaller scratch and then counts the points voxel by voxel.) */
+/* Scratch for dsvt_vfe; never less for more points.  (Room for a counter per cell is part of it where the call prefers to
+ * count its points by cell -- small grids, and up to 8 M cells for many points.  dsvt_vfe needs less at least, and counts
+ * by voxel in scratch without that room.) */
 int dsvt_vfe_workspace_size(const dsvt_vfe_cfg* cfg, int32_t n_points, int32_t max_voxels, size_t* bytes);
 
 /* points      [device] float [n_points, f_in]

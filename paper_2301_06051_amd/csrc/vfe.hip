@@ -5,8 +5,8 @@
 // Voxels are found without a sort: the points are counted in a map over the grid's cells, in key order, and a scan
 // over its words of 32 cells numbers the non-empty ones in ascending key and gives every voxel a run of rows; the value
 // a point's atomic returned is its place there (a counting sort), and wavefronts with equal shares of the rows take
-// the maxima from LDS.  (Grids too large for a counter per cell: the map holds a byte per cell, and the points are
-// counted by voxel once the voxels are numbered.  See count_by_cell.)  The order of a voxel's points in its
+// the maxima from LDS.  (Grids large for their points: the map holds a byte per cell, and the points are counted by voxel once
+// the voxels are numbered.  See prefer_by_cell.)  The order of a voxel's points in its
 // run varies from call to call, the maximum does not.  Pure bandwidth: points are read twice and copied once,
 // the feature rows written once.
 #include "common.h"
@@ -88,7 +88,7 @@ __global__ void kv_count(const uint32_t* __restrict__ keys, int32_t n, const uin
   point_pos[i] = pos;
 }
 
-// Points counted by cell instead (see count_by_cell): a counter per cell takes the marks, and the value a point's atomic
+// Points counted by cell instead (see prefer_by_cell): a counter per cell takes the marks, and the value a point's atomic
 // returns is its place among the voxel's points, so that neither kv_count nor a scan of the voxels' counts is needed.
 __global__ void kv_mark_count(VfeGeom g, const float* __restrict__ points, const int32_t* __restrict__ point_batch, int32_t n,
                               uint32_t* __restrict__ cell_cnt, uint32_t* __restrict__ keys, int32_t* __restrict__ point_pos) {
@@ -100,7 +100,8 @@ __global__ void kv_mark_count(VfeGeom g, const float* __restrict__ points, const
 }
 
 // A thread per cell, 32 cells a bitmap word: the word, how many of its cells are occupied and how many points they hold,
-// and in the place of each cell's counter the points of the word's cells before it.
+// and in the place of each cell's counter -- where the word has an occupied one, no other is looked at again -- the points
+// of the word's cells before it.
 __global__ void kv_pack_count(uint32_t* __restrict__ cell_cnt, int64_t n_words, uint32_t* __restrict__ bitmap,
                               uint32_t* __restrict__ word_vox, uint32_t* __restrict__ word_rows) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;      // (whole wavefronts: n_words is a multiple of 64)
@@ -114,9 +115,9 @@ __global__ void kv_pack_count(uint32_t* __restrict__ cell_cnt, int64_t n_words, 
     const uint32_t up = __shfl_up(incl, d, 32);
     if ((lane & 31) >= d) incl += up;
   }
-  cell_cnt[i] = incl - c;
+  const uint32_t word = (uint32_t)(occ >> (lane & 32));
+  if (word != 0u) cell_cnt[i] = incl - c;
   if ((lane & 31) == 31) {
-    const uint32_t word = (uint32_t)(occ >> (lane & 32));
     bitmap[i >> 5] = word;
     word_vox[i >> 5] = (uint32_t)__popc(word);
     word_rows[i >> 5] = incl;
@@ -364,14 +365,21 @@ int make_plan(const dsvt_vfe_cfg* cfg, int32_t n_points, int32_t max_voxels, Vfe
 }
 
 // Whether a call counts its points by cell: six launches in a row where counting by voxel takes eight, for 4 bytes a cell
-// cleared, added up and scanned instead of one.  Bound by the launches and the latency inside them, not by these bytes.  By
-// voxel -> by cell, 468 x 468 cells, C = 192: 20,000 points 32.5 -> 27.5 us, 60,000 39 -> 33.6, 180,000 57.8 -> 51.4,
-// 400,000 104 -> 99; 180,000 points on grids of 4, 8, 16, 32 layers 63.5 -> 58.4, 67.3 -> 63.5, 74.0 -> 72.3, 84.8 -> 83.1.
-// The gain is gone at about the limit: 8 M cells, 32 MB of counters.
-constexpr int64_t kByCellMax = 1ll << 23;
-bool count_by_cell(const VfePlan& pl, size_t ws_bytes) { return pl.cells <= kByCellMax && pl.total2 <= ws_bytes; }
-// Scratch a call asks for: room for the layout it would use.  One with room for the first layout only counts by voxel.
-size_t vfe_scratch(const VfePlan& pl) { return pl.cells <= kByCellMax && pl.total2 > pl.total ? pl.total2 : pl.total; }
+// cleared, added up and scanned instead of one -- worth it on small grids whatever the points, on larger ones for many points
+// only.  By voxel -> by cell, us, 468 x 468 cells a layer, C = 192, 5,000 / 20,000 / 60,000 / 130,000 points: 1 layer 28 -> 24,
+// 30 -> 25, 37 -> 31, 42 -> 41; 6 layers (1.3 M cells) 31 -> 30, 34 -> 32, 42 -> 39, 56 -> 50; 8 layers 32 -> 32, 35.5 -> 34.6, 45 ->
+// 43, 58 -> 54; 12 layers 34 -> 37, 38 -> 40, 47.7 -> 47.4, 61 -> 58; 24 layers 42 -> 51, 46 -> 52, 55 -> 57, 69 -> 67; 32 layers
+// (7.0 M) 45 -> 55, 50 -> 55, 60 -> 60, 74 -> 71 (400,000 points: 123 -> 118).  At 16 layers the larger frames go either way with
+// where the buffers lie (180,000 points 73 -> 70 or 78).  kByCellMax bounds the counters' 32 MB.
+constexpr int64_t kByCellMax = 1ll << 23, kByCellAny = 1500000, kByCellPoints = 80000;
+bool prefer_by_cell(const VfePlan& pl, int32_t n_points) {
+  return pl.cells <= kByCellMax && (n_points >= kByCellPoints || pl.cells <= kByCellAny + 20 * (int64_t)n_points);
+}
+// A call without the scratch for it counts by voxel.  (What fewer points take is never more than what more points take, so
+// scratch for the largest frame serves the others.)
+bool count_by_cell(const VfePlan& pl, int32_t n_points, size_t ws_bytes) { return prefer_by_cell(pl, n_points) && pl.total2 <= ws_bytes; }
+// Scratch a call asks for: room for the layout it would use, and at least for counting by voxel.
+size_t vfe_scratch(const VfePlan& pl, int32_t n_points) { return prefer_by_cell(pl, n_points) && pl.total2 > pl.total ? pl.total2 : pl.total; }
 
 }  // namespace
 
@@ -380,7 +388,7 @@ extern "C" int dsvt_vfe_workspace_size(const dsvt_vfe_cfg* cfg, int32_t n_points
   VfePlan pl;
   const int rc = make_plan(cfg, n_points, max_voxels, &pl);
   if (rc != DSVT_OK) return rc;
-  *bytes = vfe_scratch(pl);
+  *bytes = vfe_scratch(pl, n_points);
   return DSVT_OK;
 }
 
@@ -396,7 +404,7 @@ extern "C" int dsvt_vfe(const dsvt_vfe_cfg* cfg, const float* points, const int3
   if (ws_bytes < pl.total) return DSVT_ENOSPC;
   hipStream_t st = (hipStream_t)stream;
   char* base = reinterpret_cast<char*>(ws);
-  const bool by_cell = count_by_cell(pl, ws_bytes);
+  const bool by_cell = count_by_cell(pl, n_points, ws_bytes);
   uint32_t* bitmap = reinterpret_cast<uint32_t*>(base + (by_cell ? pl.off_bitmap2 : pl.off_bitmap));
   uint32_t* keys = reinterpret_cast<uint32_t*>(base + (by_cell ? pl.off_keys2 : pl.off_keys));
   int32_t* pos = reinterpret_cast<int32_t*>(base + (by_cell ? pl.off_pos2 : pl.off_pos));

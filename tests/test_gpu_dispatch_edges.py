@@ -122,14 +122,22 @@ def _vfe_plain_scratch(cells, n_points, max_voxels, f_in):
     return sum(-(-p // 256) * 256 for p in parts + [16 * n_points, 4, n_points * -(-f_in // 4) * 16])
 
 
-@pytest.mark.parametrize("grid,batch,n_points,f_in,cap", [
-    ((64, 32, 1), 1, 5000, 5, None),            # 64 words exactly: the last cell's run ends behind the last word
-    ((64, 32, 1), 1, 5000, 5, 700), ((33, 31, 3), 2, 4000, 3, 1000), ((33, 31, 3), 2, 700, 16, 1),
-    ((1, 1, 1), 1, 257, 4, None), ((512, 512, 2), 1, 3000, 6, None),      # one cell; 16,384 words: one scan chunk
-    ((520, 512, 2), 1, 3000, 12, 2500), ((256, 256, 128), 1, 2000, 5, None), ((256, 256, 129), 1, 2000, 5, None)])   # 8 M cells, more
-def test_vfe_counting_by_cell_and_by_voxel(grid, batch, n_points, f_in, cap):
-    """Both ways of counting, chosen by the scratch: voxels, their order, the maxima and the overflow report are the
-    oracle's bit for bit; every corner of the grid is occupied, and points lie outside it."""
+@pytest.mark.parametrize("grid,batch,n_points,f_in,cap,ways", [
+    # both ways, the scratch choosing: 64 words exactly (the last cell's run ends behind the last word), a part of the voxels
+    ((64, 64, 1), 1, 1500, 5, 500, 2), ((64, 64, 4), 1, 3000, 5, None, 2), ((64, 64, 4), 1, 3000, 5, 700, 2),
+    ((61, 59, 3), 2, 2500, 3, 1000, 2), ((33, 31, 3), 2, 700, 16, 1, 2), ((512, 512, 2), 1, 3000, 6, None, 2),  # 16,384 words: one scan chunk
+    ((520, 512, 2), 1, 3000, 12, 2000, 2),
+    # by cell only: its layout is the smaller one
+    ((64, 32, 1), 1, 5000, 5, None, 1), ((64, 32, 1), 1, 5000, 5, 700, 1), ((33, 31, 3), 2, 4000, 3, 1000, 1),
+    ((1, 1, 1), 1, 257, 4, None, 2),
+    # around the lines between them: 1.5 M cells + 20 a point, 80,000 points, 8 M cells
+    ((1000, 1520, 1), 1, 1000, 5, None, 2), ((1000, 1521, 1), 1, 1000, 5, None, 0), ((1000, 1521, 1), 1, 1000, 5, 500, 0),
+    ((256, 256, 128), 1, 80000, 4, None, 2), ((256, 256, 128), 1, 79999, 4, 40000, 0), ((256, 256, 129), 1, 80000, 4, 50000, 0),
+    ((256, 256, 128), 1, 2000, 5, None, 0), ((256, 256, 129), 1, 2000, 5, None, 0)])
+def test_vfe_counting_by_cell_and_by_voxel(grid, batch, n_points, f_in, cap, ways):
+    """Both ways of counting: voxels, their order, the maxima and the overflow report are the oracle's bit for bit; every
+    corner of the grid is occupied, and points lie outside it.  ways: 2 = the call prefers to count by cell and counts
+    by voxel in the smaller scratch, 1 = it has no need of more than that scratch, 0 = it prefers to count by voxel."""
     lo, size = (-4.0, -2.0, -1.0), (0.5, 0.25, 0.125)
     rng = np.random.Generator(np.random.Philox(41))
     ext = np.array(grid, np.float64) * size
@@ -141,13 +149,14 @@ def test_vfe_counting_by_cell_and_by_voxel(grid, batch, n_points, f_in, cap):
     pb = rng.integers(0, batch, n_points).astype(np.int32)
     pb[:8] = batch - 1
     rc, rx = orc.voxel_max_vfe(pts, pb, lo, size, grid, batch)
+    assert cap is None or cap < len(rc)
     cap = cap or len(rc)
     kept = min(cap, len(rc))
     print(f"[case] vfe by cell / by voxel grid={grid} batch={batch} points={n_points} cap={cap} of {len(rc)}", flush=True)
     vfe = dsvt.Vfe(grid, batch, lo, size, f_in, f_in, "f32", n_points, cap)
     cells, plain = batch * grid[0] * grid[1] * grid[2], _vfe_plain_scratch(batch * grid[0] * grid[1] * grid[2], n_points, cap, f_in)
     own = vfe.ws.numel()
-    assert own >= plain and (cells <= 1 << 23 or own == plain)
+    assert own > plain if ways == 2 else own == plain
     for nbytes in (own, plain, own + 64 * cells):
         vfe.ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda")
         vfe.x.fill_(-7.0), vfe.coords.fill_(-7), vfe.status.zero_()

@@ -105,3 +105,24 @@ def test_committed_traffic_file_matches_the_committed_kernel_sources():
     for w in ("frame", "skewed", "voxel"):
         nbytes, where = bench.layer_traffic(w)
         assert nbytes is not None and nbytes > 0, (w, where)
+
+
+def test_vfe_scratch_follows_the_way_of_counting():
+    """A call whose few points do not pay for a counter per cell does not ask for the counters (grids of 1.5 M cells and 20
+    more a point; 80,000 points; 8 M cells), and more points never ask for less."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    from paper_2301_06051_amd import binding as b
+
+    def size(grid, n, batch=1):
+        cfg = b.VfeCfg(b.I32x3(*grid), batch, b.F32x3(-1.0, -1.0, -1.0), b.F32x3(0.5, 0.5, 0.5), 5, 5, b.DSVT_F32, None, None, 0)
+        return b.dsvt_vfe_workspace_size(cfg, n, n)
+
+    for grid, below, at in (((468, 468, 32), 79999, 80000), ((1500, 1000, 2), 74999, 75000), ((256, 256, 128), 79999, 80000)):
+        counters = 4 * grid[0] * grid[1] * grid[2]
+        assert size(grid, below) < counters <= size(grid, at)
+        sizes = [size(grid, n) for n in (1, 500, 20000, below, at, at + 1, 400000)]
+        assert sizes == sorted(sizes)
+    assert size((468, 468, 8), 12500) < 4 * 468 * 468 * 8 <= size((468, 468, 8), 12610)
+    assert size((256, 256, 129), 100000) < 4 * 256 * 256 * 129 and size((468, 468, 32), 100000, 2) < 4 * 2 * 468 * 468 * 32
+    assert size((468, 468, 6), 1) >= 4 * 468 * 468 * 6
