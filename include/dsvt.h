@@ -238,8 +238,9 @@ typedef struct {
 int dsvt_pool_packed_size(const dsvt_pool_cfg* cfg, size_t* bytes);
 int dsvt_pool_pack(const dsvt_pool_cfg* cfg, void* packed, size_t bytes, void* stream);
 
-/* Scratch for dsvt_attn_pool.  (On large frames with mask_empty = 1 this is more than the size reported for
- * mask_empty = 0, which such a call also takes; regions of a single voxel then share the general path.) */
+/* Scratch for dsvt_attn_pool.  (On large frames with mask_empty = 1 this can be more than the size reported for
+ * mask_empty = 0, which such a call also takes: regions of a single voxel have a path of their own there, taken
+ * whenever the scratch holds its lists -- in regions of eight cells they need no more than the general path's.) */
 int dsvt_attn_pool_workspace_size(const dsvt_pool_cfg* cfg, int32_t n_voxels, size_t* bytes);
 
 /* Every non-empty region (b, x/l, y/w, z/h) becomes one output voxel, in ascending key

@@ -11,8 +11,9 @@
 // slots and Q of the pooled rows are MFMA projections; the P-key softmax per head is plain ALU
 // work; output projection, residual and LayerNorm follow the layer kernels (Eq. 7).
 // With masked holes (mask_empty = 1) a region of one voxel needs no attention: its softmax has one key, whose weight
-// is exactly 1, and its maximum is the voxel itself, so its row is LN(x + (x Wv^T + bv) Wo^T + bo).  kp_single takes
-// these regions (nine in ten of a LiDAR voxel frame's), kp_attention the others.
+// is exactly 1, and its maximum is the voxel itself, so its row is LN(x + (x Wv^T + bv) Wo^T + bo).  On large frames
+// single_regions takes these regions (nine in ten of a LiDAR voxel frame's) apart from the others; what their logits
+// would have been -- infinities among them, which make a row of NaN where the groups compute them -- does not matter there.
 #include "common.h"
 #include "block_scan.h"
 #include "mma.h"
@@ -53,31 +54,86 @@ __global__ void kp_mark(PoolGeom g, const int4* __restrict__ coords, int32_t n, 
   uint32_t key; int32_t slot;
   if (!pool_key(g, coords[i], &key, &slot)) { atomicOr(status, DSVT_ST_COORD_RANGE); return; }
   const uint32_t bit = 1u << (key & 31u);
-  if (multi == nullptr) atomicOr(&bitmap[key >> 5], bit);
-  else if (atomicOr(&bitmap[key >> 5], bit) & bit) atomicOr(&multi[key >> 5], bit);      // not the region's first voxel
+  if (multi == nullptr) { atomicOr(&bitmap[key >> 5], bit); return; }
+  if (atomicOr(&bitmap[key >> 5], bit) & bit) atomicOr(&multi[key >> 5], bit);           // not the region's first voxel
+}
+
+// What the grouping leaves for the attention of a call whose scratch holds regions of one voxel apart from the others.
+struct PoolLists {
+  int2* single;                                     // (voxel, output row) of every region of one voxel; null: plain layout
+  int32_t *multi_reg, *n_multi;                     // output rows of the regions of several voxels, their number
+  int32_t* plan;                                    // regions of the slot table, regions per group, regions of one voxel apart
+};
+
+// Whether such a call keeps its regions together all the same: where few are of one voxel, in share and in number, their
+// rows fill the groups of the others for less than a second kind of work costs, and the slot table, sized for regions of
+// two voxels and more, holds them.  Apart -> together, C = 192, 25,000 / 60,000 / 120,000 voxels: 1 x 1 x 4 regions of one
+// to four (a quarter of one) 45.4 -> 38.0, 69 -> 62, 114 -> 106 us; 2 x 2 x 2 of 2.8 (a third of one) 47 -> 39, 78 -> 72, 111 ->
+// 117; 300,000 (38,000 of one) 222 -> 240.
+constexpr int kFewSingle = 20000;
+__device__ __forceinline__ bool pool_together(int n_out, int n_multi, int n_voxels) {
+  const int n_single = n_out - n_multi;
+  return n_single <= kFewSingle && 5 * (int64_t)n_single <= 2 * (int64_t)n_out && 2 * (int64_t)n_out <= n_voxels;
+}
+
+// Regions per group of such a call: n_single regions of one voxel and n_multi of `rows` voxels in all, walked over by kPoolGrid
+// workgroups.  A group is a trip of its workgroup (about 7 us, loads and barriers in a row) and one pass over 96 rows or
+// more (5.5 us each and half a microsecond per 16 rows): a pass ends with the region that starts at row W or behind.  Every
+// lane prices one count -- its passes from the mean size and, in a ramp, from the spread of the sizes (that of the several
+// taken as half of what sizes of 2 to P can have at their mean), its trips between the longest walk and the mean one --
+// and the cheapest is taken, the smallest of equals.  (A fixed count fits one density: 40 took a second trip for a few of the
+// 10,800 regions of 2.1 voxels in a 120,000-voxel frame, 1 x 1 x 4, which 43 take in one: kp_attention's part 29.3 -> 23.6 us;
+// and a second trip for 10,700 regions of three, which 48 take in one of two passes: a 32,000-voxel call 58 -> 39.)
+__device__ __forceinline__ int regions_per_group(int n_single, int n_multi, int rows, int P) {
+  const int r = (threadIdx.x & 63) + 1, n_reg = n_single + n_multi, W = kRowsMax + 1 - P;
+  const float all = (float)(n_reg > 0 ? n_reg : 1), f1 = (float)n_single / all, top = (float)(P < 2 ? 2 : P);
+  const float several = fminf(fmaxf((float)rows / (float)(n_multi > 0 ? n_multi : 1), 2.f), top);
+  const float mean = f1 + (1.f - f1) * several;
+  const float var = (1.f - f1) * (f1 * (several - 1.f) * (several - 1.f) + 0.45f * (several - 2.f) * (top - several));
+  const float ramp = 4.f * (__builtin_amdgcn_sqrtf(var * (float)r) + 0.5f);
+  float passes = 1.f;
+#pragma unroll
+  for (int k = 1; k <= kSlots / (kRowsMax + 1 - kMaxPool); ++k)
+    passes += fminf(fmaxf(0.5f + ((float)(r - 1) * mean - (float)(k * W)) / ramp, 0.f), 1.f);
+  const int groups = (n_reg + r - 1) / r;
+  const float share = (float)groups / (float)kPoolGrid, trips = fmaxf(0.5f * (share + ceilf(share)), 1.f);
+  const float cost = trips * (7.f + 5.5f * passes + 0.03f * (float)r * mean);        // (> 0: ordered like its bits)
+  unsigned best = r <= kRegs ? (__float_as_uint(cost) & ~63u) | (unsigned)r : ~0u;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { const unsigned t = __shfl_xor(best, o, 64); best = t < best ? t : best; }
+  return (int)(best & 63u);
 }
 
 // With `multi`: regions of several voxels get slot rows of their own (and their output row in multi_reg), the others
-// an entry (voxel, output row) in `single`, both in ascending key order.
+// an entry (voxel, output row) in `single`, both in ascending key order -- unless pool_together says otherwise.
 __global__ void kp_emit(PoolGeom g, const int4* __restrict__ coords, int32_t n, const uint32_t* __restrict__ bitmap,
                         const int32_t* __restrict__ word_prefix, int32_t* __restrict__ pool_inds,
                         int32_t* __restrict__ out_coords, const uint32_t* __restrict__ multi,
-                        const int32_t* __restrict__ multi_prefix, int32_t* __restrict__ multi_reg,
-                        int2* __restrict__ single) {
+                        const int32_t* __restrict__ multi_prefix, PoolLists ls, const int32_t* __restrict__ n_out) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  bool apart = false;
+  if (multi != nullptr) {
+    const int all = *n_out, several = *ls.n_multi, single = all - several;
+    apart = !pool_together(all, several, n);
+    if (i < 64) {                                   // (a whole wavefront.  Cells outside the grid and repeated ones count as
+                                                    // voxels here: another group size, the same results)
+      const int regs = regions_per_group(apart ? 0 : single, several, n - single, g.P);
+      if (i == 0) { ls.plan[0] = apart ? several : all; ls.plan[1] = regs; ls.plan[2] = apart ? single : 0; }
+    }
+  }
   if (i >= n) return;
   const int4 c = coords[i];
   uint32_t key; int32_t slot;
   if (!pool_key(g, c, &key, &slot)) return;
   const uint32_t word = key >> 5, bit = key & 31u;
   const int32_t m = word_prefix[word] + __popc(bitmap[word] & ((1u << bit) - 1u));   // m < number of regions <= n
-  if (multi == nullptr) {
+  if (!apart) {
     pool_inds[(int64_t)m * g.P + slot] = i;
   } else {
     const uint32_t mw = multi[word];
     const int32_t mi = multi_prefix[word] + __popc(mw & ((1u << bit) - 1u));         // regions of several voxels before this one
-    if ((mw >> bit) & 1u) { pool_inds[(int64_t)mi * g.P + slot] = i; multi_reg[mi] = m; }   // mi < n / 2
-    else single[m - mi] = make_int2(i, m);
+    if ((mw >> bit) & 1u) { pool_inds[(int64_t)mi * g.P + slot] = i; ls.multi_reg[mi] = m; }   // mi < n / 2
+    else ls.single[m - mi] = make_int2(i, m);
   }
   // every member of a region writes the same pooled coordinates
   reinterpret_cast<int4*>(out_coords)[m] = make_int4(c.x, c.y / g.pool[0], c.z / g.pool[1], c.w / g.pool[2]);
@@ -87,7 +143,7 @@ struct PoolDev {
   const void *w_kv, *w_q, *w_o;                   // packed: [2C, C] (K rows then V rows), [C, C], [C, C]
   const float *b_kv, *b_q, *b_o, *ln_g, *ln_b;    // b_kv: [2C] in scratch (b_k then b_v)
   float ln_eps;
-  int32_t P, mask_empty, regs;
+  int32_t P, mask_empty;
 };
 
 // D consecutive elements of an LDS row as floats (16-byte reads when the head width allows).
@@ -127,15 +183,137 @@ template <typename T, int C> struct PoolLds {
   static_assert(kStat <= kTile && total <= 160 * 1024 && off_bias % 16 == 0, "pooling tile does not fit the LDS");
 };
 
+// Regions of one voxel, masked holes: out = LN(x + (x Wv^T + bv) Wo^T + bo), a row per voxel -- what the groups' attention
+// computes for them, where e^0 / e^0 = 1 weighs the one value row.  No query, no key, no softmax, no slot table: two C x C
+// products on the voxels' own rows.  Two teams of four wavefronts, each with 16 NT output features of both matrices, whose
+// weight fragments stay in its registers while the team walks over groups of kSingleRows list entries (weights per
+// group would be 147 KB for 48 rows of 384 bytes); the next group's rows are on their way during the current one's products.
+// The last part of kp_attention rather than a launch of its own, which takes 3 us of a call also where it is empty.  Bound by
+// the weights' and the rows' way in, one after the other, on small frames (25,000 voxels, 12 us) and by the rows' way in and
+// out on large ones (97,000 of the 120,000-voxel frame: 26 us for 75 MB).
+constexpr int kSingleRows = 48, kSingleWaves = 4, kTeams = kWaves / kSingleWaves;
+template <typename T, int C> struct SingleLds {
+  static constexpr int LDX = C + lds_pad<T>();
+  static constexpr size_t kTile = (size_t)kSingleRows * LDX * sizeof(T);
+  static constexpr size_t off_x = 0, off_v = kTile, off_stat = 2 * kTile, off_vec = off_stat + (size_t)2 * kStatGroupsMax * kRowsMax * 4,
+                          off_ent = off_vec + (size_t)4 * C * 4, total = off_ent + (size_t)2 * kSingleRows * 8;
+  static_assert(kTeams * total <= 160 * 1024 && total % 16 == 0 && kTile % 16 == 0, "tiles of the regions of one voxel");
+};
+template <typename T, int C>
+__device__ __forceinline__ void single_regions(PoolDev p, const int2* __restrict__ list, int n, const T* __restrict__ x,
+                                               T* __restrict__ out, unsigned char* smem_all) {
+  typedef SingleLds<T, C> L;
+  typedef typename Mma<T>::Vec4 Vec4;
+  constexpr int LDX = L::LDX, NT = C / (16 * kSingleWaves), NKF = C / Mma<T>::KC, NTHREADS = kSingleWaves * 64, RT = kSingleRows / 16;
+  constexpr int CH = C * (int)sizeof(T) / 16, G = (kSingleRows * CH + NTHREADS - 1) / NTHREADS;
+  const int wave8 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wave = wave8 % kSingleWaves, team = wave8 / kSingleWaves;
+  const int tid0 = opaque_tid() % NTHREADS, grp0 = (int)blockIdx.x * kTeams + team, step = (int)gridDim.x * kTeams;
+  unsigned char* smem = smem_all + team * L::total;
+  T* Xs = reinterpret_cast<T*>(smem + L::off_x);       // the rows, finally the output
+  T* Vs = reinterpret_cast<T*>(smem + L::off_v);
+  float* stat = reinterpret_cast<float*>(smem + L::off_stat);
+  float* vec = reinterpret_cast<float*>(smem + L::off_vec);      // b_v, b_o, gamma, beta
+  int2* ent = reinterpret_cast<int2*>(smem + L::off_ent);        // two groups' entries
+  const int n_groups = (n + kSingleRows - 1) / kSingleRows;
+  if ((int)blockIdx.x * kTeams >= n_groups) return;       // (uniform; a team without a group walks along with empty ones)
+  const int o_own = wave * 16 * NT;
+  auto entry_of = [&](int grp, int tid) {
+    const int64_t e = (int64_t)grp * kSingleRows + tid;
+    return (tid < kSingleRows && e < n) ? list[e] : make_int2(-1, 0);
+  };
+  auto request = [&](uint4 (&val)[G], const int2* en, int tid) {           // pieces of the group's rows, zero past its last entry
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
+      const int v = r < kSingleRows ? en[r].x : -1;
+      val[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (v >= 0) val[k] = reinterpret_cast<const uint4*>(x + (size_t)v * C)[c];
+    }
+  };
+  const int2 first = entry_of(grp0, tid0);
+  for (int c = tid0; c < C; c += NTHREADS) {
+    vec[c] = p.b_kv[C + c]; vec[C + c] = p.b_o[c]; vec[2 * C + c] = p.ln_g[c]; vec[3 * C + c] = p.ln_b[c];
+  }
+  if (tid0 < kSingleRows) ent[tid0] = first;
+  lds_barrier();
+  uint4 val[G];
+  request(val, ent, tid0);
+  int2 next = entry_of(grp0 + step, tid0);
+  AFull<T, NT, NKF> av, ao;
+  load_a<T, NT, NKF>(av, reinterpret_cast<const T*>(p.w_kv), C / 16 + wave * NT);
+  load_a<T, NT, NKF>(ao, reinterpret_cast<const T*>(p.w_o), wave * NT);
+  int buf = 0;
+  for (int grp = grp0; grp - team < n_groups; grp += step, buf ^= kSingleRows) {
+    const int tid = opaque_tid() % NTHREADS, lane = tid & 63, m = lane & 15, g = lane >> 4;    // (anew in every trip, see kp_attention)
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
+      if (r < kSingleRows) *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16) = val[k];
+    }
+    if (tid < kSingleRows) ent[(buf ^ kSingleRows) + tid] = next;
+    lds_barrier();
+    request(val, ent + (buf ^ kSingleRows), tid);
+    next = entry_of(grp + 2 * step, tid);
+    f32x4 b4[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + o_own + 16 * nt + 4 * g);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      BRow<T, NKF> b;
+      load_b<T, NKF>(b, Xs, LDX, r);
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
+      mma_row<T, NT, NKF>(acc, av, b);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<Vec4*>(Vs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(acc[nt]);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + C + o_own + 16 * nt + 4 * g);
+    f32x4 keep[NT][RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      BRow<T, NKF> b;
+      load_b<T, NKF>(b, Vs, LDX, r);
+      f32x4 acc[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
+      mma_row<T, NT, NKF>(acc, ao, b);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g);
+        keep[nt][r] = acc[nt] + f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
+      }
+    }
+    f32x4 ga[NT], be[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      ga[nt] = *reinterpret_cast<const f32x4*>(vec + 2 * C + o_own + 16 * nt + 4 * g);
+      be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
+    }
+    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, ga, be, p.ln_eps, Xs, LDX);
+    lds_barrier();
+    const int rows = n - grp * kSingleRows < kSingleRows ? n - grp * kSingleRows : kSingleRows;
+    for (int idx = tid; idx < rows * CH; idx += NTHREADS) {
+      const int r = idx / CH, c = idx - r * CH;
+      reinterpret_cast<uint4*>(out + (size_t)ent[buf + r].y * C)[c] =
+          *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16);
+    }
+    lds_barrier();                                   // (the rows and this group's entries are free from here)
+  }
+}
+
 // A workgroup walks over groups of kRegs regions (group blockIdx.x, then every gridDim.x-th), software-pipelined: the
-// slot table of the next group is requested during the softmax of the current one, and its occupancy scan and the
-// request for its rows come before the current group's output projection and LayerNorm, so that the two memory
-// round trips of a group (slots, then rows) are behind arithmetic of its predecessor.  One workgroup fits a CU.
-// A group has p.regs regions.  reg_row: output row of region m, or nullptr where that is m.
-template <typename T, int C, int HEADS, int NT_KV, int NT_C>
+// slot table (and the output rows) of the next group are requested during the softmax of the current one, and its
+// occupancy scan and the request for its rows come before the current group's output projection and LayerNorm, so that
+// the two memory round trips of a group (slots, then rows) are behind arithmetic of its predecessor.  One workgroup fits a CU.
+// APART: with the lists of regions of one voxel; the plan that kp_emit left says how many regions are in the slot table
+// (those of several voxels or all, pool_together), how many make a group, and how many follow after the groups.
+template <typename T, int C, int HEADS, int NT_KV, int NT_C, bool APART>
 __global__ void __launch_bounds__(kWaves * 64)
-kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __restrict__ n_out_ptr,
-             const int32_t* __restrict__ reg_row, const T* __restrict__ x, T* __restrict__ out) {
+kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, const int32_t* __restrict__ n_out_ptr, const T* __restrict__ x,
+             T* __restrict__ out) {
   typedef PoolLds<T, C> L;
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int LDX = L::LDX, D = C / HEADS, NW = kWaves, NTHREADS = NW * 64;
@@ -158,12 +336,14 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
   int32_t* wcnt = reinterpret_cast<int32_t*>(smem + L::off_wcnt);
   const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
   int32_t* out_row = reinterpret_cast<int32_t*>(smem + L::off_orow);
-  const int P = p.P, regs = p.regs;                // regs <= kRegs
-  const int n_out = __builtin_amdgcn_readfirstlane(*n_out_ptr);
-  const int n_groups = (n_out + regs - 1) / regs;
-  if ((int)blockIdx.x >= n_groups) return;
-  const int W = kRowsMax + 1 - P;                  // a pass takes the regions whose first occupied slot number lies in one
+  const int P = p.P, W = kRowsMax + 1 - P;         // a pass takes the regions whose first occupied slot number lies in one
                                                    // run of W: together at most W - 1 + P = 96 rows
+  const int32_t* plan = APART ? ls.plan : n_out_ptr;
+  const int n_out = __builtin_amdgcn_readfirstlane(plan[0]);
+  const int regs = APART ? __builtin_amdgcn_readfirstlane(plan[1]) : kRegs;                // regs <= kRegs
+  const int n_single = APART ? __builtin_amdgcn_readfirstlane(plan[2]) : 0;
+  const int32_t* reg_row = n_single > 0 ? ls.multi_reg : nullptr;                        // output row of region m; null: m
+  const int n_groups = (n_out + regs - 1) / regs;
   const float scale = rsqrtf((float)D);
   // (a wavefront's loads return in order: weights are requested after the loads whose results are needed first; the
   // barriers wait for LDS traffic only, so none of them waits for weights or rows still on their way)
@@ -176,14 +356,21 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
   const int o_own = og_own * 16 * NT_C, rt_own = half ? 2 : 0, HC = half ? kRegs / 16 - 2 : 2;
   constexpr int G = (kRowsMax * CH + NTHREADS - 1) / NTHREADS;      // 16-byte pieces of a pass's rows per thread
 
-  for (int c = tid0; c < 2 * C; c += NTHREADS) Kb[c] = (T)p.b_kv[c];
+  if (!APART || (int)blockIdx.x < n_groups)
+    for (int c = tid0; c < 2 * C; c += NTHREADS) Kb[c] = (T)p.b_kv[c];
   auto slot_of = [&](int grp, int tid) {                              // this thread's slot of a group: its voxel or -1
     const int m0 = grp * regs, mr = (n_out - m0) < regs ? (n_out - m0) : regs;
     return tid < mr * P ? pool_inds[(size_t)m0 * P + tid] : -1;
   };
-  int v_slot = slot_of((int)blockIdx.x, tid0);
-  int m0_prev = 0, mr_prev = 0;
+  auto row_of = [&](int grp, int tid) {                               // output row of this thread's region of a group
+    const int m = grp * regs + tid;
+    return reg_row != nullptr && tid < regs && m < n_out ? reg_row[m] : m;
+  };
+  int v_slot = slot_of((int)blockIdx.x, tid0), v_row = row_of((int)blockIdx.x, tid0);
+  int mr_prev = 0, row_prev = 0;
 
+  if (!APART && (int)blockIdx.x >= n_groups) return;
+  if (!APART || (int)blockIdx.x < n_groups)
   for (int grp = (int)blockIdx.x;; grp += (int)gridDim.x) {
     // (the thread index is taken anew in every trip, or the compiler computes every address that depends on it
     // once, in front of the loop, and keeps -- spills -- them all)
@@ -231,7 +418,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
     }
     if (have_prev) {
       // ---- the group before: out = LN(P + O Wo^T + bo), its rows to memory
-      if (reg_row != nullptr && tid < mr_prev) out_row[tid] = reg_row[m0_prev + tid];    // (published by the LayerNorm's barriers)
+      if (tid < mr_prev) out_row[tid] = row_prev;                                       // (published by the LayerNorm's barriers)
       f32x4 bo4[NT_C], ga[NT_C], be[NT_C];
 #pragma unroll
       for (int nt = 0; nt < NT_C; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
@@ -255,14 +442,14 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
       lds_barrier();
       for (int idx = tid; idx < mr_prev * CH; idx += NTHREADS) {
         const int r = idx / CH, c = idx - r * CH;
-        const int row = reg_row != nullptr ? out_row[r] : m0_prev + r;
+        const int row = out_row[r];
         reinterpret_cast<uint4*>(out + (size_t)row * C)[c] =
             *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Ps) + (size_t)r * LDX * sizeof(T) + c * 16);
       }
       lds_barrier();                               // (the pooled rows and the statistics are free from here)
     }
     if (!have) break;
-    m0_prev = m0; mr_prev = mr;
+    mr_prev = mr; row_prev = v_row;
     kv.prefetch();
 #pragma unroll
     for (int k = 0; k < G; ++k) {
@@ -344,7 +531,10 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
           for (int nt = 0; nt < NT_C; ++nt) *reinterpret_cast<Vec4*>(Qs + row * LDX + o0 + 16 * nt + 4 * g) = pack4<T>(acc[nt]);
         }
       });
-      if (ps == n_pass - 1) v_slot = grp + (int)gridDim.x < n_groups ? slot_of(grp + (int)gridDim.x, tid) : -1;   // used after the softmax
+      if (ps == n_pass - 1 && grp + (int)gridDim.x < n_groups) {       // used after the softmax
+        v_slot = slot_of(grp + (int)gridDim.x, tid);
+        v_row = row_of(grp + (int)gridDim.x, tid);
+      }
       lds_barrier();
       // Eq. (7) per (region, head): softmax over the region's slots; O replaces the head's Q entries.  The
       // occupied slots are rows r0 .. r0 + cnt - 1; the P - cnt empty ones all have the bias vectors as key and
@@ -392,129 +582,8 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, const int32_t* __
       }
       lds_barrier();
     }
-  }
-}
-
-// Regions of one voxel, masked holes: out = LN(x + (x Wv^T + bv) Wo^T + bo), a row per voxel -- what kp_attention computes
-// for them, where e^0 / e^0 = 1 weighs the one value row.  No query, no key, no softmax, no slot table: two C x C
-// products on the voxels' own rows.  Four wavefronts, each with 16 NT output features of both matrices, whose weight
-// fragments stay in its registers while the workgroup walks over groups of kSingleRows list entries (a workgroup per
-// group would read 147 KB of weights for 48 rows of 384 bytes); the next group's rows are on their way during
-// the current one's products.  Two workgroups share a compute unit, so that one's barriers and stores are behind the
-// other's products.  Bound by the rows' way in and out (75 MB for the 97,000 such regions of the 120,000-voxel frame);
-// with it the whole call takes 80 us there, 129 with every region in kp_attention.
-constexpr int kSingleRows = 48, kSingleWaves = 4, kSingleGrid = 512;
-template <typename T, int C> struct SingleLds {
-  static constexpr int LDX = C + lds_pad<T>();
-  static constexpr size_t kTile = (size_t)kSingleRows * LDX * sizeof(T);
-  static constexpr size_t off_x = 0, off_v = kTile, off_stat = 2 * kTile, off_vec = off_stat + (size_t)2 * kStatGroupsMax * kRowsMax * 4,
-                          off_ent = off_vec + (size_t)4 * C * 4, total = off_ent + (size_t)2 * kSingleRows * 8;
-  static_assert(total <= 64 * 1024 && kTile % 16 == 0, "kp_single tile");
-};
-template <typename T, int C>
-__global__ void __launch_bounds__(kSingleWaves * 64, 2)
-kp_single(PoolDev p, const int2* __restrict__ list, const int32_t* __restrict__ n_out, const int32_t* __restrict__ n_multi,
-          const T* __restrict__ x, T* __restrict__ out) {
-  typedef SingleLds<T, C> L;
-  typedef typename Mma<T>::Vec4 Vec4;
-  constexpr int LDX = L::LDX, NT = C / (16 * kSingleWaves), NKF = C / Mma<T>::KC, NTHREADS = kSingleWaves * 64, RT = kSingleRows / 16;
-  constexpr int CH = C * (int)sizeof(T) / 16, G = (kSingleRows * CH + NTHREADS - 1) / NTHREADS;
-  extern __shared__ __align__(16) unsigned char smem[];
-  T* Xs = reinterpret_cast<T*>(smem + L::off_x);       // the rows, finally the output
-  T* Vs = reinterpret_cast<T*>(smem + L::off_v);
-  float* stat = reinterpret_cast<float*>(smem + L::off_stat);
-  float* vec = reinterpret_cast<float*>(smem + L::off_vec);      // b_v, b_o, gamma, beta
-  int2* ent = reinterpret_cast<int2*>(smem + L::off_ent);        // two groups' entries
-  const int tid0 = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
-  const int n = __builtin_amdgcn_readfirstlane(*n_out - *n_multi);
-  const int n_groups = (n + kSingleRows - 1) / kSingleRows;
-  if ((int)blockIdx.x >= n_groups) return;
-  const int o_own = wave * 16 * NT;
-  auto entry_of = [&](int grp, int tid) {
-    const int64_t e = (int64_t)grp * kSingleRows + tid;
-    return (tid < kSingleRows && e < n) ? list[e] : make_int2(-1, 0);
-  };
-  auto request = [&](uint4 (&val)[G], const int2* en, int tid) {           // pieces of the group's rows, zero past its last entry
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
-      const int v = r < kSingleRows ? en[r].x : -1;
-      val[k] = make_uint4(0u, 0u, 0u, 0u);
-      if (v >= 0) val[k] = reinterpret_cast<const uint4*>(x + (size_t)v * C)[c];
-    }
-  };
-  const int2 first = entry_of((int)blockIdx.x, tid0);
-  for (int c = tid0; c < C; c += NTHREADS) {
-    vec[c] = p.b_kv[C + c]; vec[C + c] = p.b_o[c]; vec[2 * C + c] = p.ln_g[c]; vec[3 * C + c] = p.ln_b[c];
-  }
-  if (tid0 < kSingleRows) ent[tid0] = first;
-  lds_barrier();
-  uint4 val[G];
-  request(val, ent, tid0);
-  int2 next = entry_of((int)(blockIdx.x + gridDim.x), tid0);
-  AFull<T, NT, NKF> av, ao;
-  load_a<T, NT, NKF>(av, reinterpret_cast<const T*>(p.w_kv), C / 16 + wave * NT);
-  load_a<T, NT, NKF>(ao, reinterpret_cast<const T*>(p.w_o), wave * NT);
-  int buf = 0;
-  for (int grp = (int)blockIdx.x; grp < n_groups; grp += (int)gridDim.x, buf ^= kSingleRows) {
-    const int tid = opaque_tid(), lane = tid & 63, m = lane & 15, g = lane >> 4;    // (anew in every trip, see kp_attention)
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int idx = tid + k * NTHREADS, r = idx / CH, c = idx - r * CH;
-      if (r < kSingleRows) *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16) = val[k];
-    }
-    if (tid < kSingleRows) ent[(buf ^ kSingleRows) + tid] = next;
-    lds_barrier();
-    request(val, ent + (buf ^ kSingleRows), tid);
-    next = entry_of(grp + 2 * (int)gridDim.x, tid);
-    f32x4 b4[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + o_own + 16 * nt + 4 * g);
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      BRow<T, NKF> b;
-      load_b<T, NKF>(b, Xs, LDX, r);
-      f32x4 acc[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
-      mma_row<T, NT, NKF>(acc, av, b);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<Vec4*>(Vs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(acc[nt]);
-    }
-    lds_barrier();
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) b4[nt] = *reinterpret_cast<const f32x4*>(vec + C + o_own + 16 * nt + 4 * g);
-    f32x4 keep[NT][RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      BRow<T, NKF> b;
-      load_b<T, NKF>(b, Vs, LDX, r);
-      f32x4 acc[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[nt] = b4[nt];
-      mma_row<T, NT, NKF>(acc, ao, b);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * r + m) * LDX + o_own + 16 * nt + 4 * g);
-        keep[nt][r] = acc[nt] + f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
-      }
-    }
-    f32x4 ga[NT], be[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      ga[nt] = *reinterpret_cast<const f32x4*>(vec + 2 * C + o_own + 16 * nt + 4 * g);
-      be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
-    }
-    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, ga, be, p.ln_eps, Xs, LDX);
-    lds_barrier();
-    const int rows = n - grp * kSingleRows < kSingleRows ? n - grp * kSingleRows : kSingleRows;
-    for (int idx = tid; idx < rows * CH; idx += NTHREADS) {
-      const int r = idx / CH, c = idx - r * CH;
-      reinterpret_cast<uint4*>(out + (size_t)ent[buf + r].y * C)[c] =
-          *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16);
-    }
-    lds_barrier();                                   // (the rows and this group's entries are free from here)
-  }
+  }  if constexpr (APART)
+    if (n_single > 0) single_regions<T, C>(p, ls.single, n_single, x, out, smem);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -554,18 +623,19 @@ int make_plan(const dsvt_pool_cfg* cfg, int32_t n_voxels, PoolPlan* pl) {
   pl->off_inds2 = take((size_t)(n_voxels / 2) * P * 4);        // a region here has at least two voxels
   pl->off_single = take((size_t)n_voxels * 8);
   pl->off_reg = take((size_t)(n_voxels / 2) * 4);
-  pl->off_count = take(4);
+  pl->off_count = take(16);                                    // regions of several voxels, the plan
   pl->total2 = o;
   return DSVT_OK;
 }
-// Whether a call takes regions of one voxel apart: holes masked (with keys of their own the softmax has two entries), and
-// more than two groups of regions per workgroup, were they kept together.  Below that a launch and a shorter walk
-// cost more than the arithmetic they save.  Kept together -> apart, 1 x 1 x 4 regions of 192 channels: 3,000 voxels 27 ->
-// 34 us, 24,000 40.0 -> 41.2, 32,000 51.9 -> 44.8, 120,000 129 -> 80; 2 x 2 x 2 regions: 24,000 38.4 -> 44.2, 32,000 56.6 ->
-// 47.2, 150,000 160 -> 128; 64 and 128 channels cross at the same place.
+// Whether a call lays its scratch out for regions of one voxel apart: holes masked (with keys of their own the softmax has
+// two entries), and more than two groups of regions per workgroup, were they kept together: below that the arithmetic
+// it saves is hidden behind the walk's latency.  Kept together -> apart, C = 192, LiDAR-like frames of 30,000 / 60,000 / 120,000
+// / 150,000 voxels: 1 x 1 x 4 regions 52 -> 43, 77 -> 53, 131 -> 72, 157 -> 90 us; 2 x 2 x 2 58 -> 42, 85 -> 55, 131 -> 88, 152 ->
+// 110.  What it costs where no region is of one voxel (pool_together) is the second mark per voxel and the second array of
+// the scan: regions of three, 25,000 / 60,000 / 120,000 / 300,000 voxels: 36.4 -> 37.8, 58 -> 61, 102 -> 106, 209 -> 219.
 bool pool_apart(const dsvt_pool_cfg& c, int32_t n_voxels) { return c.mask_empty == 1 && n_voxels > 2 * kRegs * kPoolGrid; }
-// Scratch a call asks for: room for the layout it would use.  A call with room for the first layout only keeps every
-// region together.
+// Scratch a call asks for: room for the layout it would use (and at least for the other).  A call without the scratch for
+// it keeps every region together.
 size_t pool_scratch(const dsvt_pool_cfg& c, const PoolPlan& pl, int32_t n_voxels) {
   return pool_apart(c, n_voxels) && pl.total2 > pl.total ? pl.total2 : pl.total;
 }
@@ -606,19 +676,11 @@ template <typename T> void pack_matrix(const void* src, void* dst, int out, int 
   k_pack<T><<<(unsigned)dsvt_ceil_div(slots, 256), 256, 0, st>>>(reinterpret_cast<const T*>(src), reinterpret_cast<T*>(dst), out, k);
 }
 
-struct PoolLists {                                  // what the grouping leaves for the attention
-  const int32_t* inds;                              // slot table
-  const int2* single; const int32_t *multi_reg, *n_multi;      // null: every region is in the slot table
-};
-// Regions of a group when those of one voxel are apart: the others have 2.2 voxels on average on LiDAR frames, so that
-// 40 of them fill the 96-row tile once (88 rows) where 48 need a second, nearly empty pass.
-constexpr int kRegsMulti = 40;
-
-template <typename T, int C, int HEADS, int NT_KV, int NT_C>
-int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const PoolLists& ls, const int32_t* n_out,
-                          const void* x, void* out, int32_t n_voxels, hipStream_t st) {
-  auto kern = kp_attention<T, C, HEADS, NT_KV, NT_C>;
-  constexpr size_t lds = PoolLds<T, C>::total;
+template <typename T, int C, int HEADS, int NT_KV, int NT_C, bool APART>
+int launch_pool_attention_v(const dsvt_pool_cfg& c, const PoolPlan& pl, const int32_t* pool_inds, const PoolLists& ls, const int32_t* n_out,
+                            const void* x, void* out, int32_t n_voxels, hipStream_t st) {
+  auto kern = kp_attention<T, C, HEADS, NT_KV, NT_C, APART>;
+  constexpr size_t lds_g = PoolLds<T, C>::total, lds_s = APART ? kTeams * SingleLds<T, C>::total : 0, lds = lds_g > lds_s ? lds_g : lds_s;
   static std::atomic<uint64_t> lds_allowed{0};
   if (int rc = dsvt_allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed)) return rc;
   const PoolPacked pp = pool_packed(c);
@@ -627,19 +689,21 @@ int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const Pool
   d.w_kv = pk + pp.off_kv; d.w_q = pk + pp.off_q; d.w_o = pk + pp.off_o;
   d.b_kv = reinterpret_cast<const float*>(pk + pp.off_bkv);
   d.b_q = c.b_q; d.b_o = c.b_o; d.ln_g = c.ln_g; d.ln_b = c.ln_b; d.ln_eps = c.ln_eps;
-  d.P = pl.g.P; d.mask_empty = c.mask_empty; d.regs = ls.single != nullptr ? kRegsMulti : kRegs;
+  d.P = pl.g.P; d.mask_empty = c.mask_empty;
   dsvt_prof_scope ps(DSVT_K_POOL_ATTN, st);
   // one workgroup per compute unit (the LDS tile fills it), each walking over every grid-th group of regions
-  const int64_t groups = ls.single != nullptr ? dsvt_ceil_div(n_voxels / 2, kRegsMulti) : dsvt_ceil_div(n_voxels, kRegs);
-  if (groups > 0)
-    kern<<<(unsigned)(groups < kPoolGrid ? groups : kPoolGrid), kWaves * 64, lds, st>>>(
-        d, ls.inds, ls.single != nullptr ? ls.n_multi : n_out, ls.multi_reg, reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out));
-  if (ls.single != nullptr) {
-    const int64_t sg = dsvt_ceil_div(n_voxels, kSingleRows);
-    kp_single<T, C><<<(unsigned)(sg < kSingleGrid ? sg : kSingleGrid), kSingleWaves * 64, SingleLds<T, C>::total, st>>>(
-        d, ls.single, n_out, ls.n_multi, reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out));
-  }
+  // (with regions of one voxel apart a group may be of one region)
+  const int64_t groups = APART ? n_voxels : dsvt_ceil_div(n_voxels, kRegs);
+  kern<<<(unsigned)(groups < kPoolGrid ? groups : kPoolGrid), kWaves * 64, lds, st>>>(
+      d, pool_inds, ls, n_out, reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out));
   return DSVT_OK;
+}
+
+template <typename T, int C, int HEADS, int NT_KV, int NT_C>
+int launch_pool_attention(const dsvt_pool_cfg& c, const PoolPlan& pl, const int32_t* pool_inds, const PoolLists& ls, const int32_t* n_out,
+                          const void* x, void* out, int32_t n_voxels, hipStream_t st) {
+  if (ls.single != nullptr) return launch_pool_attention_v<T, C, HEADS, NT_KV, NT_C, true>(c, pl, pool_inds, ls, n_out, x, out, n_voxels, st);
+  return launch_pool_attention_v<T, C, HEADS, NT_KV, NT_C, false>(c, pl, pool_inds, ls, n_out, x, out, n_voxels, st);
 }
 
 }  // namespace
@@ -698,9 +762,13 @@ int run_attn_pool(const dsvt_pool_cfg* cfg, const PoolPlan& pl, const int32_t* c
   int32_t* inds = reinterpret_cast<int32_t*>(base + (split ? pl.off_inds2 : pl.off_inds));
   uint32_t* multi = split ? bitmap + pl.words_pitch : nullptr;
   int32_t* multi_prefix = split ? prefix + pl.words_pitch : nullptr;
-  int2* single = split ? reinterpret_cast<int2*>(base + pl.off_single) : nullptr;
-  int32_t* multi_reg = split ? reinterpret_cast<int32_t*>(base + pl.off_reg) : nullptr;
-  int32_t* n_multi = split ? reinterpret_cast<int32_t*>(base + pl.off_count) : nullptr;
+  PoolLists ls = {};
+  if (split) {
+    ls.single = reinterpret_cast<int2*>(base + pl.off_single);
+    ls.multi_reg = reinterpret_cast<int32_t*>(base + pl.off_reg);
+    ls.n_multi = reinterpret_cast<int32_t*>(base + pl.off_count);
+    ls.plan = ls.n_multi + 1;
+  }
   const int tb = 256;
   {
     dsvt_prof_scope ps(DSVT_K_POOL_GROUP, st);
@@ -711,19 +779,18 @@ int run_attn_pool(const dsvt_pool_cfg* cfg, const PoolPlan& pl, const int32_t* c
     kp_mark<<<(unsigned)dsvt_ceil_div(n_voxels, tb), tb, 0, st>>>(pl.g, reinterpret_cast<const int4*>(coords), n_voxels,
                                                                   bitmap, multi, status);
     k_block_scan<true><<<dim3(block_scan_grid(pl.n_words), split ? 2 : 1), 1024, 0, st>>>(
-        bitmap, prefix, pl.n_words, nullptr, n_out, (int64_t)pl.words_pitch, n_multi);
+        bitmap, prefix, pl.n_words, nullptr, n_out, (int64_t)pl.words_pitch, ls.n_multi);
     kp_emit<<<(unsigned)dsvt_ceil_div(n_voxels, tb), tb, 0, st>>>(pl.g, reinterpret_cast<const int4*>(coords), n_voxels,
                                                                   bitmap, prefix, inds, out_coords, multi, multi_prefix,
-                                                                  multi_reg, single);
+                                                                  ls, n_out);
   }
-  const PoolLists ls = {inds, single, multi_reg, n_multi};
   int rc;
   if (cfg->dtype == DSVT_BF16) {
-    if (cfg->C == 192) rc = launch_pool_attention<bf16_t, 192, 8, 3, 3>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
-    else if (cfg->C == 128) rc = launch_pool_attention<bf16_t, 128, 8, 2, 2>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
-    else rc = launch_pool_attention<bf16_t, 64, 4, 1, 1>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
+    if (cfg->C == 192) rc = launch_pool_attention<bf16_t, 192, 8, 3, 3>(*cfg, pl, inds, ls, n_out, x, out, n_voxels, st);
+    else if (cfg->C == 128) rc = launch_pool_attention<bf16_t, 128, 8, 2, 2>(*cfg, pl, inds, ls, n_out, x, out, n_voxels, st);
+    else rc = launch_pool_attention<bf16_t, 64, 4, 1, 1>(*cfg, pl, inds, ls, n_out, x, out, n_voxels, st);
   } else {
-    rc = launch_pool_attention<float, 64, 4, 1, 1>(*cfg, pl, ls, n_out, x, out, n_voxels, st);
+    rc = launch_pool_attention<float, 64, 4, 1, 1>(*cfg, pl, inds, ls, n_out, x, out, n_voxels, st);
   }
   if (rc != DSVT_OK) return rc;
   DSVT_HIP_TRY(hipGetLastError());

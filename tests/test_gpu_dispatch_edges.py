@@ -62,11 +62,11 @@ def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
 
 
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
-@pytest.mark.parametrize("n_multi,n_single", [(0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
+@pytest.mark.parametrize("n_multi,n_single", [(0, 24576), (0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
 def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
     """Frames above and around the size from which regions of one voxel are taken apart: only such regions, none,
     a remainder of either kind; with the scratch the size call names and with the plain layout's, the same result.
-    A call below the size (24,576 voxels) asks for the plain layout only."""
+    A call at that size (24,576 voxels) asks for the plain layout only."""
     grid, pool = (128, 128, 8), (1, 1, 4)
     rng = np.random.Generator(np.random.Philox(21))
     reg = rng.permutation(128 * 128 * 2)[:n_multi + n_single]
@@ -82,7 +82,7 @@ def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
     ref_c, ref = orc.attn_pool(w, coords, x, grid, pool, 1)
     pw, plain = dsvt.PoolWeights(w, grid, pool, 1, 1), dsvt.PoolWeights(w, grid, pool, 1, 0)
     sizes = [dsvt.dsvt_attn_pool_workspace_size(p, n) for p in (pw, plain)]
-    assert sizes[0] >= sizes[1] and (n > 24576 or sizes[0] == sizes[1])
+    assert sizes[0] > sizes[1] if n > 24576 else sizes[0] == sizes[1]
     cd, xd, outs = dev_coords(coords), dev_feats(x, dtype), []
     for size in sizes:
         oc, out, n_out, status = dsvt.dsvt_attn_pool(pw, cd, xd, ws=torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda"))
@@ -93,6 +93,86 @@ def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
         assert torch.all(out[len(ref_c):] == 0)
         outs.append(out)
     assert rel_err(outs[0], outs[1].double().cpu().numpy()) < TOL[dtype]
+
+
+def _pool_frame(rng, grid, pool, batch, sizes, outside, repeats):
+    """A frame of regions of the given numbers of voxels (full regions only where the grid cuts none short), then cells outside
+    the grid and repeats: coords, the features' index of every row, and the rows that count (each cell once)."""
+    full = [g // p for g, p in zip(grid, pool)]
+    P = int(np.prod(pool))
+    reg = rng.permutation(batch * int(np.prod(full)))[:len(sizes)]
+    slot = np.argsort(rng.random((len(sizes), P)), 1)
+    k, j = np.nonzero(np.arange(P)[None, :] < np.asarray(sizes)[:, None])
+    s, r = slot[k, j], reg[k]
+    cells = np.stack([r // int(np.prod(full)), r // (full[1] * full[2]) % full[0] * pool[0] + s // (pool[1] * pool[2]),
+                      r // full[2] % full[1] * pool[1] + s // pool[2] % pool[1], r % full[2] * pool[2] + s % pool[2]], 1)
+    if any(g % p for g, p in zip(grid, pool)):               # the regions cut short: the grid's last cell of every frame
+        cells = np.concatenate([cells, [[b] + [g - 1 for g in grid] for b in range(batch)]])
+    n = len(cells)
+    bad = np.tile(cells[:1], (outside, 1))
+    bad[:, 1:] = rng.integers(0, 2, (outside, 3)) * (np.array(grid) + 1) - 1
+    bad[:, 0] = rng.integers(-1, batch + 1, outside)
+    bad[:, 1] = np.where(bad[:, 1] < 0, bad[:, 1], grid[0])
+    rep = rng.integers(0, n, repeats)
+    feat = np.concatenate([np.arange(n), n + np.arange(outside), rep])
+    order = rng.permutation(n + outside + repeats)
+    return np.concatenate([cells, bad, cells[rep]])[order].astype(np.int32), feat[order], n
+
+
+def _cycle(values, total):
+    out = []
+    while total > 0:
+        out.append(min(values[len(out) % len(values)], total))
+        total -= out[-1]
+    return out
+
+
+@pytest.mark.parametrize("C,heads,dtype,grid,pool,batch,sizes,outside,repeats", [
+    (192, 8, "bf16", (100, 90, 9), (2, 2, 2), 2, _cycle((1, 1, 8, 1, 7, 2, 1, 1, 5), 26000), 0, 0),           # one in two alone, up to eight
+    (64, 4, "f32", (101, 91, 9), (2, 2, 2), 2, _cycle((1, 1, 2, 1, 3, 1), 25000), 300, 400),
+    (64, 4, "bf16", (128, 128, 8), (1, 1, 2), 1, _cycle((1, 2), 25001), 0, 77),
+    (128, 8, "bf16", (200, 130, 1), (1, 1, 1), 1, [1] * 25001, 5, 9),                                       # a repeated cell is a region of two
+    (64, 4, "f32", (128, 128, 8), (2, 2, 1), 1, _cycle((4, 4, 4, 1), 30000), 0, 0),                           # kept together: one in four alone
+    (192, 8, "bf16", (128, 128, 8), (2, 2, 2), 1, _cycle((8, 8, 1), 40000), 100, 0),                          # together, five passes and more
+    (64, 4, "bf16", (128, 128, 8), (1, 1, 4), 1, [1] * 10000 + [3] * 15000, 0, 0),                            # together: two fifths alone
+    (64, 4, "bf16", (128, 128, 8), (1, 1, 4), 1, [1] * 10001 + [3] * 15000, 0, 0),                            # apart: one more
+    (64, 4, "f32", (160, 160, 8), (1, 1, 4), 1, [1] * 20000 + [4] * 31000, 0, 0),                             # together: 20,000 alone
+    (64, 4, "f32", (160, 160, 8), (1, 1, 4), 1, [1] * 20001 + [4] * 31000, 0, 0),                             # apart: one more
+    (64, 4, "bf16", (128, 128, 8), (1, 1, 4), 1, [1] * 5000 + [2] * 10000, 0, 0),                             # apart: under two voxels a region
+    (64, 4, "bf16", (4096, 4096, 2), (1, 1, 2), 1, _cycle((1, 2, 1), 25000), 0, 0),                            # larger layout past the built-in scratch
+    (64, 4, "f32", (128, 128, 8), (1, 1, 4), 1, [], 25000, 0)])                                              # nothing inside the grid
+def test_pool_apart_over_region_forms(C, heads, dtype, grid, pool, batch, sizes, outside, repeats):
+    """The large frames' path over regions of one to eight cells, two frames, grids that cut regions short, cells outside the
+    grid and repeated ones, at the lines between regions kept together and apart; with the smaller scratch and
+    on the built-in one too (where the larger layout fits it and where it does not), the same rows."""
+    rng = np.random.Generator(np.random.Philox(25))
+    coords, feat, n = _pool_frame(rng, grid, pool, batch, sizes, outside, repeats) if sizes else (
+        np.tile(np.array([[0, -1, 0, 0]], np.int32), (outside, 1)), np.arange(outside), 0)
+    x_all = synth.make_features(26, max(n + outside, 1), C, dtype)
+    x, N = x_all[feat], len(coords)
+    w = synth.make_pool_weights(27, C, heads, dtype)
+    print(f"[case] pool forms C={C} {dtype} {pool} batch {batch}, {N} rows, {n} cells", flush=True)
+    assert N > 24576
+    once = np.zeros(N, bool)
+    once[np.unique(feat, return_index=True)[1]] = True
+    once &= feat < n
+    ref_c, ref = orc.attn_pool(w, coords[once], x[once], grid, pool, 1) if n else (np.zeros((0, 4), np.int32), np.zeros((0, C)))
+    pw, plain = dsvt.PoolWeights(w, grid, pool, batch, 1), dsvt.PoolWeights(w, grid, pool, batch, 0)
+    cd, xd = dev_coords(coords), dev_feats(x, dtype)
+    for way in (dsvt.dsvt_attn_pool_workspace_size(pw, N), dsvt.dsvt_attn_pool_workspace_size(plain, N), "static", "static"):
+        out = (torch.full((N, 4), -7, dtype=torch.int32, device="cuda"), torch.zeros_like(xd),
+               torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+        if way == "static":
+            dsvt.dsvt_attn_pool_static(pw, cd, xd, out)
+        else:
+            dsvt.dsvt_attn_pool(pw, cd, xd, out=out, ws=torch.full((way,), 0x5A, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        assert int(out[3].item()) == (dsvt.binding.ST_COORD_RANGE if outside else 0)
+        m = int(out[2].item())
+        assert m == len(ref_c) and np.array_equal(out[0][:m].cpu().numpy(), ref_c)
+        assert torch.all(out[0][m:] == -7) and torch.all(out[1][m:] == 0)
+        if m:
+            assert rel_err(out[1][:m], ref) < TOL[dtype]
 
 
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (64, 4, 128, "f32")])
