@@ -126,3 +126,13 @@ def test_vfe_scratch_follows_the_way_of_counting():
     assert size((468, 468, 8), 12500) < 4 * 468 * 468 * 8 <= size((468, 468, 8), 12610)
     assert size((256, 256, 129), 100000) < 4 * 256 * 256 * 129 and size((468, 468, 32), 100000, 2) < 4 * 2 * 468 * 468 * 32
     assert size((468, 468, 6), 1) >= 4 * 468 * 468 * 6
+
+
+def test_bench_counts_the_pooling_operations_that_are_needed():
+    """Two regions of one voxel, one of three, one of two: with masked holes those of one voxel need two products, else four."""
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    coords = [(0, 0, 0, 0), (0, 0, 0, 4), (0, 0, 0, 5), (0, 0, 0, 7), (1, 0, 0, 4), (0, 1, 0, 1), (0, 1, 0, 2)]
+    assert bench.pool_flops(coords, (1, 1, 4), 10, 0) == 200 * (2 * 7 + 2 * 4)
+    assert bench.pool_flops(coords, (1, 1, 4), 10, 1) == 200 * (2 * 5 + 2 * 2 + 2 * 2)
