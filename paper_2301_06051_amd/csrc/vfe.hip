@@ -7,8 +7,8 @@
 // a point's atomic returned is its place there (a counting sort), and wavefronts with equal shares of the rows take
 // the maxima from LDS.  (Grids large for their points: the map holds a byte per cell, and the points are counted by voxel once
 // the voxels are numbered.  See prefer_by_cell.)  The order of a voxel's points in its
-// run varies from call to call, the maximum does not.  Pure bandwidth: points are read twice and copied once,
-// the feature rows written once.
+// run varies from call to call, the maximum does not.  Bound by the launches and by the latency of the
+// atomics and loads inside them, not by bytes: points are read twice and copied once, the feature rows written once.
 #include "common.h"
 #include "block_scan.h"
 
