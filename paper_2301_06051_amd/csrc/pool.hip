@@ -344,6 +344,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
   const int n_single = APART ? __builtin_amdgcn_readfirstlane(plan[2]) : 0;
   const int32_t* reg_row = n_single > 0 ? ls.multi_reg : nullptr;                        // output row of region m; null: m
   const int n_groups = (n_out + regs - 1) / regs;
+  const bool walks = !APART || (int)blockIdx.x < n_groups;   // (uniform)
   const float scale = rsqrtf((float)D);
   // (a wavefront's loads return in order: weights are requested after the loads whose results are needed first; the
   // barriers wait for LDS traffic only, so none of them waits for weights or rows still on their way)
@@ -356,8 +357,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
   const int o_own = og_own * 16 * NT_C, rt_own = half ? 2 : 0, HC = half ? kRegs / 16 - 2 : 2;
   constexpr int G = (kRowsMax * CH + NTHREADS - 1) / NTHREADS;      // 16-byte pieces of a pass's rows per thread
 
-  if (!APART || (int)blockIdx.x < n_groups)
-    for (int c = tid0; c < 2 * C; c += NTHREADS) Kb[c] = (T)p.b_kv[c];
+  for (int c = walks ? tid0 : 2 * C; c < 2 * C; c += NTHREADS) Kb[c] = (T)p.b_kv[c];
   auto slot_of = [&](int grp, int tid) {                              // this thread's slot of a group: its voxel or -1
     const int m0 = grp * regs, mr = (n_out - m0) < regs ? (n_out - m0) : regs;
     return tid < mr * P ? pool_inds[(size_t)m0 * P + tid] : -1;
@@ -369,9 +369,8 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
   int v_slot = slot_of((int)blockIdx.x, tid0), v_row = row_of((int)blockIdx.x, tid0);
   int mr_prev = 0, row_prev = 0;
 
-  if (!APART && (int)blockIdx.x >= n_groups) return;
-  if (!APART || (int)blockIdx.x < n_groups)
-  for (int grp = (int)blockIdx.x;; grp += (int)gridDim.x) {
+  if (!APART && (int)blockIdx.x >= n_groups) return;     // (here rather than further up: there four registers are spilled)
+  for (int grp = (int)blockIdx.x; walks; grp += (int)gridDim.x) {         // (ends at `if (!have) break`)
     // (the thread index is taken anew in every trip, or the compiler computes every address that depends on it
     // once, in front of the loop, and keeps -- spills -- them all)
     const int tid = opaque_tid(), lane = tid & 63, g = lane >> 4;
@@ -582,7 +581,8 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
       }
       lds_barrier();
     }
-  }  if constexpr (APART)
+  }
+  if constexpr (APART)
     if (n_single > 0) single_regions<T, C>(p, ls.single, n_single, x, out, smem);
 }
 
