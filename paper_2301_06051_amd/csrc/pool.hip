@@ -631,8 +631,8 @@ int make_plan(const dsvt_pool_cfg* cfg, int32_t n_voxels, PoolPlan* pl) {
 // two entries), and more than two groups of regions per workgroup, were they kept together: below that the arithmetic
 // it saves is hidden behind the walk's latency.  Kept together -> apart, C = 192, LiDAR-like frames of 30,000 / 60,000 / 120,000
 // / 150,000 voxels: 1 x 1 x 4 regions 52 -> 43, 77 -> 53, 131 -> 72, 157 -> 90 us; 2 x 2 x 2 58 -> 42, 85 -> 55, 131 -> 88, 152 ->
-// 110.  What it costs where no region is of one voxel (pool_together) is the second mark per voxel and the second array of
-// the scan: regions of three, 25,000 / 60,000 / 120,000 / 300,000 voxels: 36.4 -> 37.8, 58 -> 61, 102 -> 106, 209 -> 219.
+// 110.  What it costs where no region is of one voxel (pool_together) is that marking waits for its atomics and the second array of
+// the scan: regions of three, 25,000 / 60,000 / 120,000 / 300,000 voxels: 36.4 -> 37.8, 58 -> 61, 102 -> 107, 209 -> 222.
 bool pool_apart(const dsvt_pool_cfg& c, int32_t n_voxels) { return c.mask_empty == 1 && n_voxels > 2 * kRegs * kPoolGrid; }
 // Scratch a call asks for: room for the layout it would use (and at least for the other).  A call without the scratch for
 // it keeps every region together.
