@@ -279,6 +279,12 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 #define DSVT_REFRESH_LANE() do { tid = opaque_tid(); lane = tid & 63; m = lane & 15; g = lane >> 4; } while (0)
   GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, false> qkv(reinterpret_cast<const T*>(p.w_qkv), wave);
 
+  // The first two output tiles of every wavefront's Q/K/V weights are requested behind the descriptor, and arrive during
+  // the two dependent trips to memory (descriptor, then the rows it names) in which the compute unit's memory pipeline
+  // would have nothing else to do: it takes a 1 KB fragment every ~19 cycles, 2.7 k cycles for 144 of them, about what
+  // the descriptor needs to come back.  C = 192, pass of the 30,000-pillar frame / of the 120,000-voxel one: none ahead
+  // 378.5 / 732 us, one tile 370.0 / 720, two 368.6 / 712, all three 372.2 / 717 (the rows' requests queue behind them).
+  constexpr int kEarly = NT_QKV < 2 ? NT_QKV : 2;
   DSVT_PHASE(0);
   int ns;
   if (mp.tile_desc != nullptr) {
@@ -286,6 +292,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     const int n_tiles = *mp.n_tiles;
     const int word = tid < 256 ? mp.tile_desc[(size_t)blockIdx.x * 256 + tid] : 0;
     if ((int)blockIdx.x >= n_tiles) return;
+    qkv.template prefetch_first<kEarly>();
     for (int r = kRowsMax + tid; r < kRowsPad; r += NTHREADS) { row_vox[r] = -1; row_lin[r] = 0; row_mult[r] = 0.f; }
     if (wave == 0) {
       int hdr_ns = __shfl(word, 1, 64), hdr_rows = __shfl(word, 0, 64);
@@ -327,6 +334,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     const int s_begin = blockIdx.x * per_wg;
     ns = __builtin_amdgcn_readfirstlane((n_sets - s_begin) < per_wg ? (n_sets - s_begin) : per_wg);
     if (ns <= 0) return;
+    qkv.template prefetch_first<kEarly>();
     const int tau = mp.tau;
     for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox[r] = -1; row_lin[r] = 0; row_mult[r] = 0.f; }
     for (int ls = wave; ls < ns; ls += NW) {
@@ -373,11 +381,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   const int RTH = (RT + 1) >> 1;                 // the LayerNorm phases: row tiles of the first half
 
   // ---- 2. gather (Eq. 4): rows of x -> Xs, 16 bytes per thread, dead rows zero.  The loads are
-  // unconditional (clamped addresses).  The Q/K/V weights are requested after the barrier that
-  // publishes the rows, not here: the compute unit's memory pipeline takes one 1 KB fragment every
-  // ~19 cycles whether it hits the cache or not, a wavefront stands still until its requests are
-  // taken, and 216 fragments in front of the stores to LDS kept every wavefront from the barrier
-  // for 3.4 k cycles (measured: gather 5.7 k -> 1.6 k cycles, the tile 47.4 k -> 45.7 k).
+  // unconditional (clamped addresses).  The rest of the Q/K/V weights is requested after the barrier that publishes the
+  // rows, not here: a wavefront stands still until its requests are taken, and all 216 fragments in front of the stores
+  // to LDS kept every wavefront from the barrier for 3.4 k cycles.
   {
     constexpr int CH = C * (int)sizeof(T) / 16, G = (kRowsMax * CH + NTHREADS - 1) / NTHREADS;
     uint4 gv[G];
@@ -402,7 +408,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   lds_barrier();
   DSVT_REFRESH_LANE();
   DSVT_PHASE(2);                                 // rows in LDS
-  qkv.prefetch(p.b_qkv, 2 * C / (16 * NT_QKV));
+  qkv.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
 
   // ---- 3. Q, K, V = X W^T + b; V stored transposed
   {

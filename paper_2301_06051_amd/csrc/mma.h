@@ -101,17 +101,21 @@ template <typename T, int NT, int NKF> struct AFull { typename Mma<T>::Frag f[NK
 // B-operand fragments of one row tile (16 rows) over the whole K.
 template <typename T, int NKF> struct BRow { typename Mma<T>::Frag f[NKF]; };
 
-// Wp: packed matrix with NKF_ALL = K / KC fragments per tile; tiles tile0 .. tile0 + NT - 1,
-// k-fragments kf0 .. kf0 + NKF - 1.
-template <typename T, int NT, int NKF, int NKF_ALL = NKF>
-__device__ __forceinline__ void load_a(AFull<T, NT, NKF>& a, const T* __restrict__ Wp, int tile0, int kf0 = 0) {
+// Wp: packed matrix with NKF_ALL = K / KC fragments per tile; tiles tile0 + NT0 .. tile0 + NT1 - 1 into their places of
+// tiles tile0 .. tile0 + NT - 1, k-fragments kf0 .. kf0 + NKF - 1.
+template <typename T, int NT, int NKF, int NKF_ALL, int NT0, int NT1>
+__device__ __forceinline__ void load_a_tiles(AFull<T, NT, NKF>& a, const T* __restrict__ Wp, int tile0, int kf0 = 0) {
   typedef typename Mma<T>::Frag Frag;
   const int lane = opaque_tid() & 63;
   const Frag* fp = reinterpret_cast<const Frag*>(Wp) + ((size_t)tile0 * NKF_ALL + kf0) * 64 + lane;
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
+  for (int nt = NT0; nt < NT1; ++nt)
 #pragma unroll
     for (int kf = 0; kf < NKF; ++kf) a.f[kf][nt] = fp[(nt * NKF_ALL + kf) * 64];
+}
+template <typename T, int NT, int NKF, int NKF_ALL = NKF>
+__device__ __forceinline__ void load_a(AFull<T, NT, NKF>& a, const T* __restrict__ Wp, int tile0, int kf0 = 0) {
+  load_a_tiles<T, NT, NKF, NKF_ALL, 0, NT>(a, Wp, tile0, kf0);
 }
 
 // Xs: LDS [rows][ldx]; row tile r, k from k0.
@@ -191,6 +195,18 @@ struct GemmPhase {
     if (N_ITEMS >= NW || wave < N_ITEMS) {
       load_a<T, NT, NKF, NKF_ALL>(a[0], Wp, (wave % N_OG) * NT);
       if (bias != nullptr) { load_bias(bias0, bias, wave % N_OG, swap_og < N_OG); bias0_set = true; }
+    }
+  }
+
+  // prefetch() in two parts: the first N output tiles of the first item, then the others and the bias.
+  template <int N> __device__ __forceinline__ void prefetch_first() {
+    if (N_ITEMS >= NW || wave < N_ITEMS) load_a_tiles<T, NT, NKF, NKF_ALL, 0, N>(a[0], Wp, (wave % N_OG) * NT);
+  }
+  template <int N> __device__ __forceinline__ void prefetch_rest(const float* __restrict__ bias, int swap_og) {
+    if (N_ITEMS >= NW || wave < N_ITEMS) {
+      load_a_tiles<T, NT, NKF, NKF_ALL, N, NT>(a[0], Wp, (wave % N_OG) * NT);
+      load_bias(bias0, bias, wave % N_OG, swap_og < N_OG);
+      bias0_set = true;
     }
   }
 
