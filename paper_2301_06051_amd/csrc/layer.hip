@@ -87,8 +87,8 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t off_h = off_q;         // hidden tile reuses Q and K once attention is done
   static constexpr size_t off_misc = off_v + kVt;
   static constexpr size_t kMisc = (size_t)(3 * kRowsPad + 2 * kMaxSets + 2 + kMaxItems + 1) * 4;
-  // after attention the V^T region holds the GELU table and the LayerNorm statistics
-  static constexpr size_t off_gelu = off_v, off_stat = off_v + 4096, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
+  // after attention the V^T region holds the GELU table, the two LayerNorms' scales and shifts, and the LayerNorm statistics
+  static constexpr size_t off_gelu = off_v, off_aff = off_v + 4096, off_stat = off_aff + (size_t)4 * C * 4, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
   static_assert(off_stat + kStat <= off_misc, "GELU table and LayerNorm statistics must fit in the V^T region");
   static constexpr size_t total = off_misc + kMisc;
   static_assert((size_t)kRowsMax * LDH * sizeof(T) <= 2 * kTile, "hidden tile must fit in Q + K");
@@ -457,19 +457,31 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       attn_any<T, C, HEADS, HID, SETS, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, kts, RT * 16);
     }
   }
+  // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
+  // take its place (published by the barriers of the LayerNorm below).  Read from memory where they are used, the latter
+  // would come back behind the weights requested before them, and the LayerNorm of every wavefront would wait for those.
+  // Pass of the 3,001- / 30,000-pillar frame, of the wide windows, of the 120,000-voxel frame: 159.3 -> 156.4, 368.6 ->
+  // 365.5, 326 -> 319, 712 -> 707 us.
+  constexpr bool kGeluTable = sizeof(T) == 2;
+  static_assert(kGeluKnots * sizeof(float2) <= 4096, "GELU table slot");
+  constexpr int kGeluThreads = kGeluTable ? kGeluKnots / 2 : 0, kVecThreads = kGeluThreads + C;     // 16 bytes per thread: 4 C floats in C loads
+  static_assert(kVecThreads <= NTHREADS, "one load per thread");
+  float4 late = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (full_layer && tid < kVecThreads) {
+    const int i = tid - kGeluThreads, v = i / (C / 4);
+    const float* src = v < 2 ? (v == 0 ? p.ln1_g : p.ln1_b) : (v == 2 ? p.ln2_g : p.ln2_b);
+    late = i < 0 ? reinterpret_cast<const float4*>(p.gelu_tab)[tid] : reinterpret_cast<const float4*>(src)[i - v * (C / 4)];
+  }
   f32x4 bo4[NT_O];
 #pragma unroll
   for (int nt = 0; nt < NT_O; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
   lds_barrier();
   DSVT_REFRESH_LANE();
   DSVT_PHASE(4);                                 // attention done
-  // attention is done with V^T: the GELU table of the MLP takes its place (published by the
-  // barriers of the LayerNorm below)
-  constexpr bool kGeluTable = sizeof(T) == 2;
-  static_assert(kGeluKnots * sizeof(float2) <= 4096, "GELU table slot");
   const float2* gelu_lds = reinterpret_cast<const float2*>(smem + L::off_gelu);
-  if (kGeluTable && full_layer && tid < kGeluKnots / 2)
-    reinterpret_cast<float4*>(smem + L::off_gelu)[tid] = reinterpret_cast<const float4*>(p.gelu_tab)[tid];
+  const float* affine_lds = reinterpret_cast<const float*>(smem + L::off_aff);
+  if (full_layer && tid < kVecThreads)
+    *reinterpret_cast<float4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
 
   // ---- 5. Y = O Wo^T + bo (+ x), then LayerNorm; result (or raw Y) replaces x in Xs
   // The first MLP matrix is requested during this phase, by a third of the wavefronts at a time
@@ -484,12 +496,6 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   else if (HC == 2) oproj.template run_keep<2>(Qs, LDX, rt_own, bo4, keep);
   else if (HC == 3) oproj.template run_keep<3>(Qs, LDX, rt_own, bo4, keep);
   if (pf_turn == 1) ffn1.prefetch();
-  f32x4 g1[NT_O], be1[NT_O];                       // fetched while the MFMAs above drain
-#pragma unroll
-  for (int nt = 0; nt < NT_O; ++nt) {
-    g1[nt] = full_layer ? *reinterpret_cast<const f32x4*>(p.ln1_g + o_own + 16 * nt + 4 * g) : bo4[nt];
-    be1[nt] = full_layer ? *reinterpret_cast<const f32x4*>(p.ln1_b + o_own + 16 * nt + 4 * g) : bo4[nt];
-  }
 #pragma unroll
   for (int nt = 0; nt < NT_O; ++nt) {
     const int o = o_own + 16 * nt + 4 * g;
@@ -507,7 +513,10 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   }
   if (full_layer) {
     if (pf_turn == 2) ffn1.prefetch();
-    layer_norm_tile<T, NT_O, C, kHalfTiles>(keep, o_own, og_own, rt_own, HC, stat, g1, be1, p.ln_eps, Xs, LDX);
+    layer_norm_tile<T, NT_O, C, kHalfTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
+      a = *reinterpret_cast<const f32x4*>(affine_lds + o_own + 16 * nt + 4 * g);
+      b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
+    }, p.ln_eps, Xs, LDX);
     lds_barrier();
     DSVT_REFRESH_LANE();
 
@@ -538,12 +547,6 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     if (HC == 1) ffn2.template run_keep<1>(Hs, LDH, rt_own, b24, keep2);
     else if (HC == 2) ffn2.template run_keep<2>(Hs, LDH, rt_own, b24, keep2);
     else if (HC == 3) ffn2.template run_keep<3>(Hs, LDH, rt_own, b24, keep2);
-    f32x4 g2[NT_2], be2[NT_2];
-#pragma unroll
-    for (int nt = 0; nt < NT_2; ++nt) {
-      g2[nt] = *reinterpret_cast<const f32x4*>(p.ln2_g + o_own2 + 16 * nt + 4 * g);
-      be2[nt] = *reinterpret_cast<const f32x4*>(p.ln2_b + o_own2 + 16 * nt + 4 * g);
-    }
 #pragma unroll
     for (int nt = 0; nt < NT_2; ++nt) {
       const int o = o_own2 + 16 * nt + 4 * g;
@@ -555,7 +558,10 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         }
       }
     }
-    layer_norm_tile<T, NT_2, C, kHalfTiles>(keep2, o_own2, og_own, rt_own, HC, stat, g2, be2, p.ln_eps, Xs, LDX);
+    layer_norm_tile<T, NT_2, C, kHalfTiles>(keep2, o_own2, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
+      a = *reinterpret_cast<const f32x4*>(affine_lds + 2 * C + o_own2 + 16 * nt + 4 * g);
+      b = *reinterpret_cast<const f32x4*>(affine_lds + 3 * C + o_own2 + 16 * nt + 4 * g);
+    }, p.ln_eps, Xs, LDX);
   }
   lds_barrier();
   DSVT_REFRESH_LANE();

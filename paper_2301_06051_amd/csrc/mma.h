@@ -407,10 +407,11 @@ template <> __device__ __forceinline__ float gelu_erf_fast<bf16_t>(float x) {
 // accumulator layout: this wavefront holds features o0 .. o0 + 16*NT - 1 (group og of
 // SG = C / (16*NT)) of rows 16*(rt0 + r) + m, r < cnt (cnt = 0: only the barrier).  Per-group sums of x and x^2 (fp32) are
 // exchanged through LDS; variance = E[x^2] - mean^2.  Every thread of the workgroup must call it.
-template <typename T, int NT, int C, int RH>
+// affine(nt, gamma, beta): this lane's four of each for output tile nt; called behind the exchange's barrier, so that they may
+// come from LDS that was written before it.
+template <typename T, int NT, int C, int RH, typename Affine>
 __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int og, int rt0, int cnt, float* stat,
-                                                const f32x4 (&ga)[NT], const f32x4 (&be)[NT], float eps, T* dst,
-                                                int ldd) {
+                                                Affine affine, float eps, T* dst, int ldd) {
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int SG = C / (16 * NT);
   static_assert(SG * 16 * NT == C && SG <= kStatGroupsMax, "LayerNorm feature groups");
@@ -432,6 +433,9 @@ __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int 
     }
   }
   lds_barrier();
+  f32x4 ga[NT], be[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) affine(nt, ga[nt], be[nt]);
 #pragma unroll
   for (int r = 0; r < RH; ++r) {
     if (r < cnt) {

@@ -292,7 +292,7 @@ __device__ __forceinline__ void single_regions(PoolDev p, const int2* __restrict
       ga[nt] = *reinterpret_cast<const f32x4*>(vec + 2 * C + o_own + 16 * nt + 4 * g);
       be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
     }
-    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, ga, be, p.ln_eps, Xs, LDX);
+    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps, Xs, LDX);
     lds_barrier();
     const int rows = n - grp * kSingleRows < kSingleRows ? n - grp * kSingleRows : kSingleRows;
     for (int idx = tid; idx < rows * CH; idx += NTHREADS) {
@@ -437,7 +437,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
             const Vec4 xr = *reinterpret_cast<const Vec4*>(Ps + (16 * (rt_own + r) + (lane & 15)) * LDX + o_own + 16 * nt + 4 * g);
             keep[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
           }
-      layer_norm_tile<T, NT_C, C, RH>(keep, o_own, og_own, rt_own, HC, stat, ga, be, p.ln_eps, Ps, LDX);
+      layer_norm_tile<T, NT_C, C, RH>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps, Ps, LDX);
       lds_barrier();
       for (int idx = tid; idx < mr_prev * CH; idx += NTHREADS) {
         const int r = idx / CH, c = idx - r * CH;
