@@ -522,7 +522,14 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 
     DSVT_PHASE(5);                               // x1 in LDS
     // ---- 6. MLP: H = gelu(x1 W1^T + b1) over the dead Q/K tiles; x2 = LN(x1 + H W2^T + b2)
-    ffn1.run(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1], bool) {
+    // The first half of the second matrix's weights is requested between the last MFMAs of the first product and the GELU of its
+    // last row tiles: the memory pipeline is idle there and needs 2.7 k cycles for these 144 fragments (C = 192), the GELU of two
+    // row tiles and three wavefronts per SIMD about 2 k.  Passes with the request behind the GELU and with it here (two sessions): 3,001-pillar frame 156.4 / 155.7 us,
+    // 30,000-pillar frame 365.5 / 361.8, wide windows 319 / 316, 120,000-voxel frame 707 / 699.  Slower than this, each in one session
+    // with it: the matrix in three slices, two of them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the
+    // LayerNorms' vectors 0.6-1.4 %; the second bias requested in front of the weights 0.1-0.7 %.
+    GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
+    ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1], bool) {
 #pragma unroll
       for (int nt = 0; nt < NT_1; ++nt) {
         const int o = o0 + 16 * nt + 4 * g;
@@ -533,9 +540,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
           v = f32x4{gelu_erf_fast<T>(v[0]), gelu_erf_fast<T>(v[1]), gelu_erf_fast<T>(v[2]), gelu_erf_fast<T>(v[3])};
         *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o) = pack4<T>(v);
       }
-    });
-    GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
-    if (HC > 0) ffn2.prefetch();
+    }, [&]() { if (HC > 0) ffn2.prefetch(); });
     const int o_own2 = og_own * 16 * NT_2;
     f32x4 b24[NT_2];
 #pragma unroll

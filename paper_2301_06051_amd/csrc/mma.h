@@ -286,6 +286,46 @@ struct GemmPhase {
     }
   }
 
+  // run() of a phase of one item per wavefront, over all row tiles (RT > 0), with before_last_epi() called between the last
+  // MFMAs and the epilogue of the last one or two row tiles: the weights' registers are free there, and what it requests
+  // travels while the epilogue computes.  (One place for the call: at two, the compiler keeps the undefined values of the
+  // one alive on the way to the other and spills.)
+  template <typename Epi, typename Before>
+  __device__ __forceinline__ void run_before(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, Before before_last_epi) {
+    static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1, "one item per wavefront");
+    const int o0 = wave * 16 * NT;
+    f32x4 acc0[NT], acc1[NT];
+    const bool some = N_ITEMS >= NW || wave < N_ITEMS;
+    int r = 0;
+    if (some) {
+      Bias bl;
+      load_bias(bl, bias, wave, false);
+      BRow<T, NKF> b0, b1;
+      load_b<T, NKF>(b0, Xs, ldx, 0);
+      for (; r + 2 < RT; r += 2) {
+        load_b<T, NKF>(b1, Xs, ldx, r + 1);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) { acc0[nt] = bl.v[nt]; acc1[nt] = bl.v[nt]; }
+        mma_row<T, NT, NKF>(acc0, a[0], b0);
+        load_b<T, NKF>(b0, Xs, ldx, r + 2);
+        mma_row<T, NT, NKF>(acc1, a[0], b1);
+        epi(o0, r, acc0, false);
+        epi(o0, r + 1, acc1, false);
+      }
+      const bool two = r + 1 < RT;
+      if (two) load_b<T, NKF>(b1, Xs, ldx, r + 1);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) { acc0[nt] = bl.v[nt]; acc1[nt] = bl.v[nt]; }
+      mma_row<T, NT, NKF>(acc0, a[0], b0);
+      if (two) mma_row<T, NT, NKF>(acc1, a[0], b1);
+    }
+    before_last_epi();
+    if (some) {
+      epi(o0, r, acc0, false);
+      if (r + 1 < RT) epi(o0, r + 1, acc1, false);
+    }
+  }
+
   // One item per wavefront: row tiles rt0 .. rt0 + HC - 1 unrolled, all accumulators returned
   // (the LayerNorm phases need a row's values in registers across a workgroup barrier).  With
   // KSPLIT > 1 the weights pass through the registers one K-slice at a time.

@@ -32,6 +32,26 @@ def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
     assert rel_err(y, orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype]
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+def test_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype):
+    """A block over one window of 1 to 96 voxels: the projections' last trip has one or two row tiles, and with a single
+    row tile half of the wavefronts have no rows in the LayerNorm phases (C = 64: some no output tile of the MLP either)."""
+    grid, win, tau = (12, 12, 1), (12, 12, 1), 96
+    rng = np.random.Generator(np.random.Philox(21))
+    ws = [synth.make_layer_weights(22 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
+    layers = [dsvt.LayerWeights(w) for w in ws]
+    for cnt in (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96):
+        cell = rng.permutation(144)[:cnt]
+        coords = np.stack([0 * cell, cell // 12, cell % 12, 0 * cell], 1).astype(np.int32)
+        x = synth.make_features(24 + cnt, cnt, C, dtype)
+        print(f"[case] one window of {cnt} voxels C={C} {dtype}", flush=True)
+        ref = orc.block(ws, [orc.partition(coords, grid, win, (0, 0, 0), tau, a) for a in (0, 1)], coords, x)
+        cd = dev_coords(coords)
+        y = dsvt.dsvt_block(layers, [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a) for a in (0, 1)], cd, dev_feats(x, dtype))
+        torch.cuda.synchronize()
+        assert rel_err(y, ref) < TOL[dtype], cnt
+
+
 @pytest.mark.parametrize("tau,n,dup_mode", [(50, 12288, 0), (50, 12289, 0), (50, 12289, 1), (64, 13568, 1), (64, 13569, 0), (64, 13569, 1),
                                             (72, 15361, 0), (72, 15361, 1), (73, 15617, 0)])
 def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
