@@ -466,11 +466,15 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   static_assert(kGeluKnots * sizeof(float2) <= 4096, "GELU table slot");
   constexpr int kGeluThreads = kGeluTable ? kGeluKnots / 2 : 0, kVecThreads = kGeluThreads + C;     // 16 bytes per thread: 4 C floats in C loads
   static_assert(kVecThreads <= NTHREADS, "one load per thread");
-  float4 late = make_float4(0.f, 0.f, 0.f, 0.f);
+  // (Neither the thread number nor a first value of `late` may live through the attention: four zeros kept for it were four
+  // registers too many for sets of 49 to 72 voxels of C = 64 with repeats as keys, which spilled eight.)
+  DSVT_REFRESH_LANE();
+  f32x4 late;
+  opaque_def(late);
   if (full_layer && tid < kVecThreads) {
     const int i = tid - kGeluThreads, v = i / (C / 4);
     const float* src = v < 2 ? (v == 0 ? p.ln1_g : p.ln1_b) : (v == 2 ? p.ln2_g : p.ln2_b);
-    late = i < 0 ? reinterpret_cast<const float4*>(p.gelu_tab)[tid] : reinterpret_cast<const float4*>(src)[i - v * (C / 4)];
+    late = i < 0 ? reinterpret_cast<const f32x4*>(p.gelu_tab)[tid] : reinterpret_cast<const f32x4*>(src)[i - v * (C / 4)];
   }
   f32x4 bo4[NT_O];
 #pragma unroll
@@ -481,7 +485,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   const float2* gelu_lds = reinterpret_cast<const float2*>(smem + L::off_gelu);
   const float* affine_lds = reinterpret_cast<const float*>(smem + L::off_aff);
   if (full_layer && tid < kVecThreads)
-    *reinterpret_cast<float4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
+    *reinterpret_cast<f32x4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
 
   // ---- 5. Y = O Wo^T + bo (+ x), then LayerNorm; result (or raw Y) replaces x in Xs
   // The first MLP matrix is requested during this phase, by a third of the wavefronts at a time

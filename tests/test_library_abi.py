@@ -52,6 +52,39 @@ def test_instrumented_library_adds_one_symbol_only():
     assert exported - set(_declared()) == {"dsvt_debug_phase_clocks"}
 
 
+def _kernel_metadata(lib):
+    """Name, spilled vector registers and scratch bytes per lane of every kernel in the library: the metadata notes of the
+    gfx950 code objects in its offload bundles (a table of (offset, size, id length, id) behind a magic text and a count)."""
+    import struct
+    import subprocess
+    import tempfile
+    blob, magic, out, at = open(lib, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", [], 0
+    while (at := blob.find(magic, at)) >= 0:
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", blob, pos - 8)[0]):
+            off, size, n = struct.unpack_from("<QQQ", blob, pos)
+            target, pos = blob[pos + 24:pos + 24 + n], pos + 24 + n
+            if b"gfx950" in target:
+                with tempfile.NamedTemporaryFile() as f:
+                    f.write(blob[at + off:at + off + size])
+                    f.flush()
+                    text = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True, text=True, check=True).stdout
+                for kernel in text.split("  - .agpr_count:")[1:]:
+                    field = lambda name: re.search(rf"\.{name}: +(\S+)", kernel).group(1)
+                    out.append((field("symbol"), int(field("vgpr_spill_count")), int(field("private_segment_fixed_size"))))
+        at = pos
+    return out
+
+
+def test_no_kernel_spills_vector_registers():
+    """Scratch reloads wait for every outstanding load, so one spill undoes the layer kernel's early weight requests."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    kernels = _kernel_metadata(LIB)
+    assert len([k for k in kernels if "k_layer" in k[0]]) == 18 and any("kp_attention" in k[0] for k in kernels)
+    assert [k for k in kernels if k[1] or (k[2] and "k_layer" in k[0])] == []
+
+
 def test_host_only_calls_work_without_a_gpu():
     """dsvt_partition_bound is pure host arithmetic: the set bound and a positive scratch size."""
     if not os.path.exists(LIB):
