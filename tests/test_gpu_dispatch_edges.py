@@ -33,31 +33,31 @@ def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
 
 
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
-def test_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype):
-    """A block over one window of 1 to 96 voxels: the projections' last trip has one or two row tiles, and with a single
-    row tile half of the wavefronts have no rows in the LayerNorm phases (C = 64: some no output tile of the MLP either)."""
-    grid, win, tau = (12, 12, 1), (12, 12, 1), 96
+@pytest.mark.parametrize("tau,dup_mode", [(96, 0), (96, 1), (48, 0), (48, 1)])
+def test_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype, tau, dup_mode):
+    """A block over one window of 1 to 96 voxels, in one set or two: the projections' last trip has one or two row tiles, and with a
+    single row tile half of the wavefronts have no rows in the LayerNorm phases (C = 64: some no output tile of the MLP either).
+    (Two sets of 48: the work list of a frame this small gives each its tile, without one a workgroup takes both.)"""
+    grid, win = (12, 12, 1), (12, 12, 1)
     rng = np.random.Generator(np.random.Philox(21))
     ws = [synth.make_layer_weights(22 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
-    layers = [dsvt.LayerWeights(w) for w in ws]
+    layers = [dsvt.LayerWeights(w, dup_mode) for w in ws]
     for cnt in (1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96):
         cell = rng.permutation(144)[:cnt]
         coords = np.stack([0 * cell, cell // 12, cell % 12, 0 * cell], 1).astype(np.int32)
         x = synth.make_features(24 + cnt, cnt, C, dtype)
-        print(f"[case] one window of {cnt} voxels C={C} {dtype}", flush=True)
-        ref = orc.block(ws, [orc.partition(coords, grid, win, (0, 0, 0), tau, a) for a in (0, 1)], coords, x)
+        print(f"[case] one window of {cnt} voxels C={C} {dtype} tau={tau} dup={dup_mode}", flush=True)
+        oms = [orc.partition(coords, grid, win, (0, 0, 0), tau, a) for a in (0, 1)]
+        ref = orc.block(ws, oms, coords, x, dup_mode)
         cd = dev_coords(coords)
-        y = dsvt.dsvt_block(layers, [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a) for a in (0, 1)], cd, dev_feats(x, dtype))
-        torch.cuda.synchronize()
-        assert rel_err(y, ref) < TOL[dtype], cnt
+        for tiles in (True, False) if tau <= 64 else (True,):
+            y = dsvt.dsvt_block(layers, [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a, tiles=tiles) for a in (0, 1)], cd, dev_feats(x, dtype))
+            torch.cuda.synchronize()
+            assert rel_err(y, ref) < TOL[dtype], (cnt, tiles)
 
 
-@pytest.mark.parametrize("tau,n,dup_mode", [(50, 12288, 0), (50, 12289, 0), (50, 12289, 1), (64, 13568, 1), (64, 13569, 0), (64, 13569, 1),
-                                            (72, 15361, 0), (72, 15361, 1), (73, 15617, 0)])
-def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
-    """C = 64 in bf16: the frame sizes and set sizes between which the kernel of fewer registers is taken, and full
-    windows of 49 to 72 voxels in it (without a tile list too, where a set may have 64)."""
-    grid, win, C = (480, 480, 1), (24, 24, 1), 64
+def _windows_of_one_set_and_two(n):
+    """n voxels in 24 x 24 windows of 20 to 73 on a 480 x 480 grid."""
     rng = np.random.Generator(np.random.Philox(15))
     cnt, left = [], n
     while left > 0:                                          # windows of one set (up to tau) and of two
@@ -67,7 +67,16 @@ def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
     for w, k in enumerate(cnt):
         cell = rng.permutation(576)[:k]
         rows.append(np.stack([0 * cell, 24 * (w // 20) + cell // 24, 24 * (w % 20) + cell % 24, 0 * cell], 1))
-    coords = np.concatenate(rows).astype(np.int32)
+    return np.concatenate(rows).astype(np.int32)
+
+
+@pytest.mark.parametrize("tau,n,dup_mode", [(50, 12288, 0), (50, 12289, 0), (50, 12289, 1), (64, 13568, 1), (64, 13569, 0), (64, 13569, 1),
+                                            (72, 15361, 0), (72, 15361, 1), (73, 15617, 0)])
+def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
+    """C = 64 in bf16: the frame sizes and set sizes between which the kernel of fewer registers is taken, and full
+    windows of 49 to 72 voxels in it (without a tile list too, where a set may have 64)."""
+    grid, win, C = (480, 480, 1), (24, 24, 1), 64
+    coords = _windows_of_one_set_and_two(n)
     x = synth.make_features(16, n, C, "bf16")
     w = synth.make_layer_weights(17, C, 4, 128, win, "bf16")
     print(f"[case] slim kernel tau={tau} n={n} dup={dup_mode}", flush=True)
@@ -79,6 +88,24 @@ def test_large_sets_around_the_slim_kernel(tau, n, dup_mode):
         y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), maps, cd, dev_feats(x, "bf16"))
         torch.cuda.synchronize()
         assert rel_err(y, ref) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("tau,n", [(50, 12288), (50, 12289), (64, 13568), (64, 13569), (72, 15360), (72, 15361), (73, 15617)])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_block_around_the_slim_kernel(tau, n, dup_mode):
+    """The same lines with the whole layer behind the attention: residuals, LayerNorms and MLP, twice."""
+    grid, win, C = (480, 480, 1), (24, 24, 1), 64
+    coords = _windows_of_one_set_and_two(n)
+    x = synth.make_features(18, n, C, "bf16")
+    ws = [synth.make_layer_weights(19 + a, C, 4, 128, win, "bf16") for a in (0, 1)]
+    print(f"[case] block, slim kernel tau={tau} n={n} dup={dup_mode}", flush=True)
+    oms = [orc.partition(coords, grid, win, (0, 0, 0), tau, a) for a in (0, 1)]
+    ref = orc.block(ws, oms, coords, x, dup_mode)
+    layers, cd = [dsvt.LayerWeights(w, dup_mode) for w in ws], dev_coords(coords)
+    for tiles in (True, False) if tau <= 64 else (True,):
+        y = dsvt.dsvt_block(layers, [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a, tiles=tiles) for a in (0, 1)], cd, dev_feats(x, "bf16"))
+        torch.cuda.synchronize()
+        assert rel_err(y, ref) < TOL["bf16"], tiles
 
 
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
