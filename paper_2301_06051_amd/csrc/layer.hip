@@ -279,11 +279,14 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 #define DSVT_REFRESH_LANE() do { tid = opaque_tid(); lane = tid & 63; m = lane & 15; g = lane >> 4; } while (0)
   GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, false> qkv(reinterpret_cast<const T*>(p.w_qkv), wave);
 
-  // The first two output tiles of every wavefront's Q/K/V weights are requested behind the descriptor, and arrive during
-  // the two dependent trips to memory (descriptor, then the rows it names) in which the compute unit's memory pipeline
-  // would have nothing else to do: it takes a 1 KB fragment every ~19 cycles, 2.7 k cycles for 144 of them, about what
-  // the descriptor needs to come back.  C = 192, pass of the 30,000-pillar frame / of the 120,000-voxel one: none ahead
-  // 378.5 / 732 us, one tile 370.0 / 720, two 368.6 / 712, all three 372.2 / 717 (the rows' requests queue behind them).
+  // The first two output tiles of every wavefront's Q/K/V weights (C = 192: of three, C = 128: both, C = 64: the only one)
+  // are requested behind the descriptor, and arrive during the two dependent trips to memory (descriptor, then the rows it
+  // names) in which the compute unit's memory pipeline would have nothing else to do: it takes a 1 KB fragment every ~19
+  // cycles, 2.7 k cycles for the 144 of C = 192, about what the descriptor needs to come back.  C = 192, pass of the
+  // 30,000-pillar frame / of the 120,000-voxel one: none ahead 378.5 / 732 us, one tile 370.0 / 720, two 368.6 / 712, all
+  // three 372.2 / 717 (the rows' requests queue behind them).  C = 128 (96 fragments in all), a block of the 30,000-pillar
+  // frame / of 20,000 voxels in 30 x 30 windows: none 61.2 / 67.3 us, one tile 60.4 / 66.7, both 59.9 / 65.7.  C = 64, a block of
+  // 30,000 pillars: bf16 28.1 us without, 28.2 with, 2,000 pillars 16.1 and 15.9; fp32 78.9 and 78.0.
   constexpr int kEarly = NT_QKV < 2 ? NT_QKV : 2;
   DSVT_PHASE(0);
   int ns;
@@ -381,9 +384,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   const int RTH = (RT + 1) >> 1;                 // the LayerNorm phases: row tiles of the first half
 
   // ---- 2. gather (Eq. 4): rows of x -> Xs, 16 bytes per thread, dead rows zero.  The loads are
-  // unconditional (clamped addresses).  The rest of the Q/K/V weights is requested after the barrier that publishes the
-  // rows, not here: a wavefront stands still until its requests are taken, and all 216 fragments in front of the stores
-  // to LDS kept every wavefront from the barrier for 3.4 k cycles.
+  // unconditional (clamped addresses).  The rest of the Q/K/V weights (C = 192: a third; C <= 128: only the biases are left) is
+  // requested after the barrier that publishes the rows, not here: a wavefront stands still until its requests are taken,
+  // and all 216 fragments of C = 192 in front of the stores to LDS kept every wavefront from the barrier for 3.4 k cycles.
   {
     constexpr int CH = C * (int)sizeof(T) / 16, G = (kRowsMax * CH + NTHREADS - 1) / NTHREADS;
     uint4 gv[G];
@@ -526,12 +529,13 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 
     DSVT_PHASE(5);                               // x1 in LDS
     // ---- 6. MLP: H = gelu(x1 W1^T + b1) over the dead Q/K tiles; x2 = LN(x1 + H W2^T + b2)
-    // The first half of the second matrix's weights is requested between the last MFMAs of the first product and the GELU of its
-    // last row tiles: the memory pipeline is idle there and needs 2.7 k cycles for these 144 fragments (C = 192), the GELU of two
-    // row tiles and three wavefronts per SIMD about 2 k.  Passes with the request behind the GELU and with it here (two sessions): 3,001-pillar frame 156.4 / 155.7 us,
-    // 30,000-pillar frame 365.5 / 361.8, wide windows 319 / 316, 120,000-voxel frame 707 / 699.  Slower than this, each in one session
-    // with it: the matrix in three slices, two of them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the
-    // LayerNorms' vectors 0.6-1.4 %; the second bias requested in front of the weights 0.1-0.7 %.
+    // The second matrix's weights (C = 192: the first half of K, C <= 128: all) are requested between the last MFMAs of the first
+    // product and the GELU of its last row tiles: the memory pipeline is idle there and needs 2.7 k cycles for the 144 fragments of
+    // C = 192, the GELU of two row tiles and three wavefronts per SIMD about 2 k.  Passes with the request behind the GELU and with it
+    // here (two sessions): 3,001-pillar frame 156.4 / 155.7 us, 30,000-pillar frame 365.5 / 361.8, wide windows (C = 128) 319 / 316,
+    // 120,000-voxel frame 707 / 699.  Slower than this at C = 192, each in one session with it: the matrix in three slices, two of
+    // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
+    // bias requested in front of the weights 0.1-0.7 %.
     GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
     ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1], bool) {
 #pragma unroll
@@ -541,7 +545,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         if constexpr (kGeluTable)
           v = f32x4{gelu_from_table(gelu_lds, v[0]), gelu_from_table(gelu_lds, v[1]), gelu_from_table(gelu_lds, v[2]), gelu_from_table(gelu_lds, v[3])};
         else
-          v = f32x4{gelu_erf_fast<T>(v[0]), gelu_erf_fast<T>(v[1]), gelu_erf_fast<T>(v[2]), gelu_erf_fast<T>(v[3])};
+          v = f32x4{gelu_erf_fast(v[0]), gelu_erf_fast(v[1]), gelu_erf_fast(v[2]), gelu_erf_fast(v[3])};
         *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o) = pack4<T>(v);
       }
     }, [&]() { if (HC > 0) ffn2.prefetch(); });
@@ -682,12 +686,13 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
 }
 
 // Whether sets of 49 voxels and more take kSets96Slim, where a tile leaves room in the LDS for a second workgroup on the
-// compute unit (C = 64 in bf16): it also leaves room in the registers (69 of them, 80 with repeats as keys; kSets96: 108 and
-// 132), which pays once there are more tiles than compute units -- about max(48, 5 / 6 tau) voxels a tile -- and up to 72
-// voxels a set; beyond, fetching the table rows once for two heads is worth more.  Two layers, 30 x 30 windows, kSets96 -> slim:
-// sets of up to 50 voxels 12,000 voxels 24.0 -> 25.6 us, 14,000 35.9 -> 29.9, 40,000 70.6 -> 50.9; of up to 64 12,000 24.3 ->
-// 29.1, 14,000 36.1 -> 31.7, 30,000 57.5 -> 47.9; of up to 72 14,000 26.9 -> 34.1, 16,000 37.5 -> 36.2, 40,000 65.7 -> 63.6; of
-// up to 80 20,000 41.5 -> 43.2.
+// compute unit (C = 64 in bf16): it also leaves room in the registers (68 of them, 80 with repeats as keys; kSets96: 106 and
+// 131), which pays once there are more tiles than compute units -- about max(48, 5 / 6 tau) voxels a tile -- and up to 72
+// voxels a set; beyond, fetching the table rows once for two heads is worth as much.  Two layers, 30 x 30 windows, kSets96 -> slim
+// (repeats as keys within 0.9 us of these): sets of up to 50 voxels 12,000 voxels 22.9 -> 26.0 us, 12,800 33.8 -> 27.7, 40,000
+// 68.0 -> 51.3; of up to 64 13,568 24.5 -> 28.6, 14,000 34.4 -> 31.4, 30,000 55.4 -> 48.0; of up to 72 15,000 26.5 -> 32.8,
+// 16,000 36.3 -> 34.7, 20,000 39.3 -> 39.8, 40,000 62.4 -> 60.6; of up to 80 16,000 27.5 -> 34.5, 18,000 37.0 -> 36.5,
+// 20,000 39.6 -> 41.6, 40,000 66.4 -> 63.7.
 bool slim_sets(const dsvt_maps& mp) {
   const int per_tile = 5 * mp.tau / 6 > 48 ? 5 * mp.tau / 6 : 48;
   return mp.tau <= 72 && mp.n_voxels > 256 * per_tile;

@@ -69,15 +69,15 @@ __device__ __forceinline__ int opaque_tid() {
   return t;
 }
 
-// Elements of T that pad every LDS row by 32 bytes.  Rows of K elements (K * sizeof(T) a multiple
-// of 64 bytes) then have a pitch that is an odd multiple of 32 bytes, the one pitch at which the
-// 16-byte fragment loads of a wavefront (16 rows x 4 k-slices) run at the full LDS rate; measured
-// on gfx950: 225 B/clk per CU against 125-150 B/clk for pitches of 16, 48 or 0 mod 64 bytes.
 // Declares v defined, with whatever its registers hold and without an instruction.  For variables that are assigned
 // on some paths only and read on those paths only: in a loop, the compiler otherwise moves the "undefined" definition
 // of the other paths in front of the loop and keeps registers for it through every iteration.
 template <typename V> __device__ __forceinline__ void opaque_def(V& v) { asm volatile("" : "=v"(v)); }
 
+// Elements of T that pad every LDS row by 32 bytes.  Rows of K elements (K * sizeof(T) a multiple
+// of 64 bytes) then have a pitch that is an odd multiple of 32 bytes, the one pitch at which the
+// 16-byte fragment loads of a wavefront (16 rows x 4 k-slices) run at the full LDS rate; measured
+// on gfx950: 225 B/clk per CU against 125-150 B/clk for pitches of 16, 48 or 0 mod 64 bytes.
 template <typename T> constexpr int lds_pad() { return 32 / (int)sizeof(T); }
 
 // Packed weights.  A matrix W [OUT, K] is stored fragment by fragment in the order the MFMA "A"
@@ -85,7 +85,6 @@ template <typename T> constexpr int lds_pad() { return 32 / (int)sizeof(T); }
 // is 1 KB, lane l's 16 bytes at offset 16*l, fragments ordered [tile][kf].  A wavefront's load of
 // one fragment is then one fully coalesced 1 KB read (the [out, in] layout would touch 16 rows
 // of 64 bytes each, which the L1/L2 path serves about 3x slower).
-template <typename T> __host__ __device__ constexpr size_t packed_elems(int out, int k) { return (size_t)out * k; }
 
 // Workgroup barrier for data exchanged through LDS: waits for this wavefront's LDS operations
 // only.  __syncthreads() also drains the outstanding global loads (on this target loads and
@@ -173,7 +172,7 @@ struct GemmPhase {
   const T* Wp;
   int wave;
   struct Bias { f32x4 v[NT]; float s[NT]; };          // both forms of an item's bias, see load_bias()
-  Bias bias0;                                            // first item's bias when prefetch() fetched it
+  Bias bias0;                                            // first item's bias when prefetch_rest() fetched it
   bool bias0_set = false;
 
   __device__ __forceinline__ GemmPhase(const T* wp, int wave_) : Wp(wp), wave(wave_) {}
@@ -189,16 +188,12 @@ struct GemmPhase {
         for (int nt = 0; nt < NT; ++nt) opaque_def(a[k].f[kf][nt]);
   }
 
-  // Request the weights of this wavefront's first item (may be called long before run()), and
-  // with them, if given, the bias run() starts that item from.
-  __device__ __forceinline__ void prefetch(const float* __restrict__ bias = nullptr, int swap_og = N_OG) {
-    if (N_ITEMS >= NW || wave < N_ITEMS) {
-      load_a<T, NT, NKF, NKF_ALL>(a[0], Wp, (wave % N_OG) * NT);
-      if (bias != nullptr) { load_bias(bias0, bias, wave % N_OG, swap_og < N_OG); bias0_set = true; }
-    }
+  // Request the weights of this wavefront's first item (may be called long before run()).
+  __device__ __forceinline__ void prefetch() {
+    if (N_ITEMS >= NW || wave < N_ITEMS) load_a<T, NT, NKF, NKF_ALL>(a[0], Wp, (wave % N_OG) * NT);
   }
 
-  // prefetch() in two parts: the first N output tiles of the first item, then the others and the bias.
+  // prefetch() in two parts: the first N output tiles of the first item, then the others and the bias run() starts it from.
   template <int N> __device__ __forceinline__ void prefetch_first() {
     if (N_ITEMS >= NW || wave < N_ITEMS) load_a_tiles<T, NT, NKF, NKF_ALL, 0, N>(a[0], Wp, (wave % N_OG) * NT);
   }
@@ -356,13 +351,6 @@ struct GemmPhase {
   }
 };
 
-template <int NT, int RT_MAX> __device__ __forceinline__ void zero_acc(f32x4 (&acc)[NT][RT_MAX]) {
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int rt = 0; rt < RT_MAX; ++rt) acc[nt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-}
-
 // Reductions over the four lanes m, m + 16, m + 32, m + 48 (one accumulator column) with the
 // gfx950 lane-swap instructions: permlane16_swap(x, x) returns x's 16-lane rows (0,0,2,2) and
 // (1,1,3,3), permlane32_swap(x, x) its halves (lo,lo) and (hi,hi); no LDS round trip.
@@ -390,36 +378,26 @@ __device__ __forceinline__ float col_max(float v) {
   return raw_max(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-
-// erf-GELU, x * Phi(x) = 0.5 x (1 + erf(x / sqrt 2)), with erf(z) = 1 - 1 / p(z)^(2^n) from
-// Abramowitz & Stegun: 7.1.28 (six coefficients, ^16, |error| <= 3e-7) for fp32 features, 7.1.27
-// (four coefficients, ^4, |error| <= 5e-4, below bf16 resolution) for bf16 features.
-// 0.5 x + 0.5 |x| erf(|x|/sqrt 2) = max(x, 0) - |x| / (2 p^(2^n)); the polynomial is taken in
-// a = |x| directly, q(a) = 2^(1/2^n) p(a / sqrt 2), so that q^(2^n) = 2 p^(2^n).
-template <int POW_LOG2> constexpr double gelu_coef(double c, int deg) {
+// erf-GELU of fp32 features, x * Phi(x) = 0.5 x (1 + erf(x / sqrt 2)), with erf(z) = 1 - 1 / p(z)^16 from
+// Abramowitz & Stegun 7.1.28 (six coefficients, |error| <= 3e-7).
+// 0.5 x + 0.5 |x| erf(|x|/sqrt 2) = max(x, 0) - |x| / (2 p^16); the polynomial is taken in
+// a = |x| directly, q(a) = 2^(1/16) p(a / sqrt 2), so that q^16 = 2 p^16.
+constexpr double gelu_coef(double c, int deg) {
   double r = c;
   for (int i = 0; i < deg; ++i) r *= 0.70710678118654752440;              // (1 / sqrt 2)^deg
-  double root = 2.0;                                                        // 2^(1 / 2^POW_LOG2)
-  for (int i = 0; i < POW_LOG2; ++i) {                                      // Newton square roots, constexpr-friendly
+  double root = 2.0;                                                        // 2^(1 / 16)
+  for (int i = 0; i < 4; ++i) {                                             // Newton square roots, constexpr-friendly
     double y = root > 1.0 ? root : 1.0;
     for (int k = 0; k < 60; ++k) y = 0.5 * (y + root / y);
     root = y;
   }
   return r * root;
 }
-template <typename T> __device__ __forceinline__ float gelu_erf_fast(float x);
-template <> __device__ __forceinline__ float gelu_erf_fast<float>(float x) {
-  constexpr float k0 = (float)gelu_coef<4>(1.0, 0), k1 = (float)gelu_coef<4>(0.0705230784, 1),
-                  k2 = (float)gelu_coef<4>(0.0422820123, 2), k3 = (float)gelu_coef<4>(0.0092705272, 3),
-                  k4 = (float)gelu_coef<4>(0.0001520143, 4), k5 = (float)gelu_coef<4>(0.0002765672, 5),
-                  k6 = (float)gelu_coef<4>(0.0000430638, 6);
+__device__ __forceinline__ float gelu_erf_fast(float x) {
+  constexpr float k0 = (float)gelu_coef(1.0, 0), k1 = (float)gelu_coef(0.0705230784, 1),
+                  k2 = (float)gelu_coef(0.0422820123, 2), k3 = (float)gelu_coef(0.0092705272, 3),
+                  k4 = (float)gelu_coef(0.0001520143, 4), k5 = (float)gelu_coef(0.0002765672, 5),
+                  k6 = (float)gelu_coef(0.0000430638, 6);
   const float a = fabsf(x);
   float q = fmaf(k6, a, k5);
   q = fmaf(q, a, k4);
@@ -430,19 +408,6 @@ template <> __device__ __forceinline__ float gelu_erf_fast<float>(float x) {
   q = q * q; q = q * q; q = q * q; q = q * q;
   return fmaf(-a, __builtin_amdgcn_rcpf(q), fmaxf(x, 0.f));
 }
-template <> __device__ __forceinline__ float gelu_erf_fast<bf16_t>(float x) {
-  constexpr float k0 = (float)gelu_coef<2>(1.0, 0), k1 = (float)gelu_coef<2>(0.278393, 1),
-                  k2 = (float)gelu_coef<2>(0.230389, 2), k3 = (float)gelu_coef<2>(0.000972, 3),
-                  k4 = (float)gelu_coef<2>(0.078108, 4);
-  const float a = fabsf(x);
-  float q = fmaf(k4, a, k3);
-  q = fmaf(q, a, k2);
-  q = fmaf(q, a, k1);
-  q = fmaf(q, a, k0);
-  q = q * q; q = q * q;
-  return fmaf(-a, __builtin_amdgcn_rcpf(q), fmaxf(x, 0.f));
-}
-
 // LayerNorm over the C features of every row, for values spread over the workgroup in
 // accumulator layout: this wavefront holds features o0 .. o0 + 16*NT - 1 (group og of
 // SG = C / (16*NT)) of rows 16*(rt0 + r) + m, r < cnt (cnt = 0: only the barrier).  Per-group sums of x and x^2 (fp32) are
