@@ -16,12 +16,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=f
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
 
 
+# layer.hip: the kernel is one loop over tiles, and constants and addresses computed in front of it would be kept (spilled)
+# through the whole of it
+FILE_FLAGS = {"layer.hip": ["-mllvm", "-disable-machine-licm"]}
+
 PHASE_LIB = os.path.join(OBJ_DIR, "libdsvt_phase.so")    # the layer kernel with its optional phase clocks (csrc/phase_clock.h)
 
 
 def _compile(src, extra=(), suffix=".o"):
     obj = os.path.join(OBJ_DIR, os.path.basename(src) + suffix)
-    r = subprocess.run([HIPCC, *FLAGS, *extra, "-c", src, "-o", obj], capture_output=True, text=True)
+    r = subprocess.run([HIPCC, *FLAGS, *FILE_FLAGS.get(os.path.basename(src), []), *extra, "-c", src, "-o", obj], capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
     if r.returncode != 0:

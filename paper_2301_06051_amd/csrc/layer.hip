@@ -19,7 +19,10 @@ namespace {
 constexpr int kTauMax = 96;                     // a set's distinct voxels must fit one tile
 constexpr int kMaxSets = kRowsMax / 4;           // every set takes at least 4 rows of a tile
 constexpr int kRowsPad = kRowsMax + 16;          // per-row arrays are read 4 at a time up to 15 rows past a set's end
-constexpr int kMaxItems = 128;                  // attention items: (set, query tile, group of heads); see item_groups()
+constexpr int kHdrWords = 64;                   // header of a tile descriptor: rows, sets, the sets' first rows, their distinct voxels
+constexpr int kHdrR0 = 2, kHdrNu = kHdrR0 + kMaxSets;
+constexpr int kSetWords = 32;                   // set table of the attention phase, see set_word()
+static_assert(kMaxSets <= kSetWords && kHdrNu + kSetWords <= kHdrWords, "a word per set");
 // Sets per workgroup when no tile list is given.
 __host__ __device__ constexpr int fixed_sets(int tau) { return tau <= kRowsMax / 2 ? 2 : 1; }
 // The sets a kernel is instantiated for: of up to three key tiles (48 voxels), or of up to six (96), these last also in
@@ -33,7 +36,14 @@ enum SetSize { kSets48, kSets96, kSets96Slim };
 // tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
 __host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
+// The attention phase's items -- (set, query tile, group of heads) -- are numbered set by set.  A set's table word: first row
+// (bits 0-7), distinct voxels (8-15) and the number of its first item (from 16 on); words past the last set hold
+// kNoItem, above every item number.  A wavefront holds the table a word per lane and finds the set of an item by counting
+// the sets that start at or before it.
+constexpr unsigned kNoItem = 0x7fffu << 16;
+__device__ __forceinline__ unsigned set_word(int r0, int nu, int first_item) { return (unsigned)r0 | (unsigned)nu << 8 | (unsigned)first_item << 16; }
 constexpr int kHalfTiles = kRowTiles / 2;        // the LayerNorm-phase work items cover half of the row tiles
+constexpr int kComputeUnits = 256;               // MI355X
 constexpr int kLayerWaves = 12;                  // three per SIMD: one workgroup per CU (LDS), the other wavefronts hide one's waits
 
 // erf-GELU (appendix "Network Architecture": the MLP of a DSVT layer) for bf16 features by linear
@@ -60,6 +70,17 @@ __device__ __forceinline__ float gelu_from_table(const float2* tab, float x) {
   return fmaf(e.x, x, e.y);
 }
 
+// Inclusive sum over the first 32 lanes of a wavefront (data-parallel-primitive shifts inside rows of 16 lanes, then lane 15's into
+// the second row).
+__device__ __forceinline__ int half_wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0x2, 0xF, false);
+  return v;
+}
+
 struct LayerDev {
   const void *w_qkv, *w_o, *w_1, *w_2;       // packed (see mma.h)
   const float *b_qkv, *b_o, *b_1, *b_2, *ln1_g, *ln1_b, *ln2_g, *ln2_b, *rel_bias;
@@ -72,7 +93,7 @@ struct LayerDev {
 
 struct MapsDev {
   const int32_t *set_inds, *n_sets, *n_tiles, *tile_desc;
-  int32_t max_sets, tau, n_voxels;
+  int32_t max_sets, max_tiles, tau, n_voxels;
 };
 
 template <typename T, int C, int HEADS, int HID> struct LayerLds {
@@ -82,11 +103,13 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr int LDV = kRowsMax + 16 / (int)sizeof(T);   // pitch of V^T [feature][row]
   static constexpr int LDH = HID + PAD;          // pitch of the MLP hidden tile
   static constexpr size_t kTile = (size_t)kRowsMax * LDX * sizeof(T);
-  static constexpr size_t off_x = 0, off_q = kTile, off_k = 2 * kTile, off_v = 3 * kTile;
+  // X and Q change places from one tile of a workgroup to the next (K stays between them): the rows of the next tile are
+  // stored over this one's Q, and the MLP's hidden tile covers K and Q whichever side Q is on.
+  static constexpr size_t off_k = kTile, off_v = 3 * kTile;
   static constexpr size_t kVt = (size_t)C * LDV * sizeof(T);
-  static constexpr size_t off_h = off_q;         // hidden tile reuses Q and K once attention is done
   static constexpr size_t off_misc = off_v + kVt;
-  static constexpr size_t kMisc = (size_t)(3 * kRowsPad + 2 * kMaxSets + 2 + kMaxItems + 1) * 4;
+  static constexpr size_t kRowTab = (size_t)(3 * kRowsPad + kHdrWords) * 4;       // rows' voxels, position codes, counts; header
+  static constexpr size_t kMisc = 2 * kRowTab + (size_t)(kSetWords + 1) * 4;      // of this tile and of the next one; set table
   // after attention the V^T region holds the GELU table, the two LayerNorms' scales and shifts, and the LayerNorm statistics
   static constexpr size_t off_gelu = off_v, off_aff = off_v + 4096, off_stat = off_aff + (size_t)4 * C * 4, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
   static_assert(off_stat + kStat <= off_misc, "GELU table and LayerNorm statistics must fit in the V^T region");
@@ -247,11 +270,26 @@ __device__ __forceinline__ void attn_any(const LayerDev& p, T* Qs, const T* Ks, 
   }
 }
 
+// Workgroups that share a compute unit, by LDS and registers: with two, each may use 80 registers a thread.
+template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(SetSize sets) {
+  return sets != kSets96 && 2 * LayerLds<T, C, HEADS, HID>::total <= 160 * 1024 ? 2 : 1;
+}
+
 // SETS: the instantiations for sets of four to six key tiles; the common one does not carry that code.
+//
+// The grid is as many workgroups as fit the GPU at once; each takes every gridDim.x-th tile, back and forth (tiles are listed
+// most rows first).  What bounds it is not one unit but the chain of a tile's phases; a tile's beginning -- descriptor, then the
+// rows it names, then weights -- is 8 k of the 42 k clocks of a 64-row tile, and between two tiles of a workgroup all of it is
+// under way during the tile before: the descriptor is requested behind the attention, the rows behind the first MLP matrix
+// (stored over Q once the second one is through with it; X and Q change places), the Q/K/V weights around the last LayerNorm.
+// The rows of a tile leave from registers, 16 bytes a lane, so no tile waits for a copy through LDS.  One tile a workgroup
+// -> this loop, pass of the 30,000-pillar frame (two tiles a workgroup) 360.0 -> 359.1 us, four frames 1,109 -> 1,078, 30 x 30
+// windows 316.9 -> 290.0, 120,000 voxels 679 -> 653, skewed batch 7,686 -> 7,383; 3,001 pillars (one tile a workgroup)
+// 158.5 -> 160.1, of which the kernel's own time is 16.0 -> 15.9 a layer.
 template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
-__global__ void __launch_bounds__(kLayerWaves * 64, SETS == kSets96Slim ? 6 : 3)   // (wavefronts per SIMD: two workgroups, one)
+__global__ void __launch_bounds__(kLayerWaves * 64, (3 * groups_per_cu<T, C, HEADS, HID>(SETS)))
 k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* out, int full_layer) {
-  // out may be x: a tile's rows are read, then written, by this workgroup only
+  // out may be x: a tile's rows are read, then written, by one workgroup only, and the tiles share no rows
   typedef LayerLds<T, C, HEADS, HID> L;
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int LDX = L::LDX, LDV = L::LDV, LDH = L::LDH;
@@ -259,106 +297,164 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   constexpr int SG = C / (16 * NT_O);              // LayerNorm phases: SG feature groups x 2 halves of the row tiles, one item per wavefront
   static_assert(NT_O == NT_2 && SG * 16 * NT_O == C && 2 * SG <= NW && SG <= kStatGroupsMax, "LayerNorm phases: one item per wavefront");
   extern __shared__ __align__(16) unsigned char smem[];
-  T* Xs = reinterpret_cast<T*>(smem + L::off_x);
-  T* Qs = reinterpret_cast<T*>(smem + L::off_q);
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
-  T* Hs = reinterpret_cast<T*>(smem + L::off_h);
-  int32_t* row_vox = reinterpret_cast<int32_t*>(smem + L::off_misc);
-  int32_t* row_lin = row_vox + kRowsPad;
-  float* row_mult = reinterpret_cast<float*>(row_lin + kRowsPad);
-  int32_t* set_r0 = reinterpret_cast<int32_t*>(row_mult + kRowsPad);   // [kMaxSets + 1]
-  int32_t* set_nu = set_r0 + kMaxSets + 1;                              // [kMaxSets + 1]
-  float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // [2][kStatGroupsMax][kRowsMax], over V^T once attention is done
-  int32_t* items = set_nu + kMaxSets + 1;                               // [kMaxItems + 1]
+  float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // over V^T once attention is done
+  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_misc + 2 * L::kRowTab);   // [kSetWords + 1]: set_word() of every set, number of items
 
   // wave-uniform values are read back through readfirstlane so that the compiler keeps them in
   // scalar registers: branches on them are scalar branches, not exec-mask divergence
   int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #define DSVT_REFRESH_LANE() do { tid = opaque_tid(); lane = tid & 63; m = lane & 15; g = lane >> 4; } while (0)
-  GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, false> qkv(reinterpret_cast<const T*>(p.w_qkv), wave);
-
+  typedef GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, false> QkvPhase;
   // The first two output tiles of every wavefront's Q/K/V weights (C = 192: of three, C = 128: both, C = 64: the only one)
-  // are requested behind the descriptor, and arrive during the two dependent trips to memory (descriptor, then the rows it
+  // of a workgroup's first tile are requested behind the descriptor, and arrive during the two dependent trips to memory (descriptor, then the rows it
   // names) in which the compute unit's memory pipeline would have nothing else to do: it takes a 1 KB fragment every ~19
   // cycles, 2.7 k cycles for the 144 of C = 192, about what the descriptor needs to come back.  C = 192, pass of the
-  // 30,000-pillar frame / of the 120,000-voxel one: none ahead 378.5 / 732 us, one tile 370.0 / 720, two 368.6 / 712, all
+  // 30,000-pillar frame / of the 120,000-voxel one, a tile a workgroup: none ahead 378.5 / 732 us, one tile 370.0 / 720, two 368.6 / 712, all
   // three 372.2 / 717 (the rows' requests queue behind them).  C = 128 (96 fragments in all), a block of the 30,000-pillar
   // frame / of 20,000 voxels in 30 x 30 windows: none 61.2 / 67.3 us, one tile 60.4 / 66.7, both 59.9 / 65.7.  C = 64, a block of
   // 30,000 pillars: bf16 28.1 us without, 28.2 with, 2,000 pillars 16.1 and 15.9; fp32 78.9 and 78.0.
   constexpr int kEarly = NT_QKV < 2 ? NT_QKV : 2;
-  DSVT_PHASE(0);
-  int ns;
-  if (mp.tile_desc != nullptr) {
-    // ---- 1a. rows from the tile descriptor the partition wrote for this workgroup (1 KB, one load)
-    const int n_tiles = *mp.n_tiles;
-    const int word = tid < 256 ? mp.tile_desc[(size_t)blockIdx.x * 256 + tid] : 0;
-    if ((int)blockIdx.x >= n_tiles) return;
-    qkv.template prefetch_first<kEarly>();
-    for (int r = kRowsMax + tid; r < kRowsPad; r += NTHREADS) { row_vox[r] = -1; row_lin[r] = 0; row_mult[r] = 0.f; }
-    if (wave == 0) {
-      int hdr_ns = __shfl(word, 1, 64), hdr_rows = __shfl(word, 0, 64);
-      hdr_ns = hdr_ns < 0 ? 0 : (hdr_ns > kMaxSets ? kMaxSets : hdr_ns);
-      hdr_rows = hdr_rows < 0 ? 0 : (hdr_rows > kRowsMax ? kRowsMax : hdr_rows);
-      if (lane == 0) { set_nu[kMaxSets] = hdr_ns; set_r0[hdr_ns] = hdr_rows; }
-      if (lane >= 2 && lane < 2 + kMaxSets && lane - 2 < hdr_ns) set_r0[lane - 2] = word < 0 ? 0 : (word > kRowsMax - 4 ? kRowsMax - 4 : word);
-      constexpr int kNuMax = SETS == kSets48 ? 48 : kTauMax;
-      const int nu_s = word < 1 ? 1 : (word > kNuMax ? kNuMax : word);
-      const int ls = lane - 2 - kMaxSets;        // the lanes holding the sets' sizes also list the sets' attention items
-      if (ls >= 0 && ls < kMaxSets) set_nu[ls] = nu_s;
-      const int kts = (ls >= 0 && ls < hdr_ns) ? (nu_s + 15) >> 4 : 0;
-      const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS));
-      int incl = ngr * kts;                      // items: (set, query tile, group of heads)
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
-      int n = incl - ngr * kts;
-      for (int qt = 0; qt < kts; ++qt)
-        for (int hh = 0; hh < ngr; ++hh)
-          if (n < kMaxItems) items[n++] = ls | (qt << 8) | (hh << 12) | (kts << 16);
-      if (lane == 63) items[kMaxItems] = incl < kMaxItems ? incl : kMaxItems;   // published by the barrier below
-    } else if (tid < 64 + 2 * kRowsMax) {           // words 64 + 2 r and 65 + 2 r: voxel and (slots << 24 | position code) of row r
-      const int r = (tid - 64) >> 1;
+
+  const bool listed = mp.tile_desc != nullptr;
+  const int per_wg = fixed_sets(mp.tau);         // without a work list a tile is two sets
+  int n_tiles, n_sets = 0;
+  if (listed) {
+    n_tiles = *mp.n_tiles;
+    n_tiles = n_tiles < mp.max_tiles ? n_tiles : mp.max_tiles;
+  } else {
+    n_sets = *mp.n_sets;
+    n_sets = n_sets < mp.max_sets ? n_sets : mp.max_sets;
+    n_tiles = (n_sets + per_wg - 1) / per_wg;
+  }
+  int tile = blockIdx.x, stride = 2 * (int)(gridDim.x - blockIdx.x) - 1;
+  int xo = 0, tab = 0;                           // byte offsets of X (Q: the other side of K) and of this tile's row tables
+  DSVT_PHASE(tile, 0);
+
+  // the row tables of a tile from its descriptor, a word per thread of the first four wavefronts
+  const auto row_vox = [&](int t) { return reinterpret_cast<int32_t*>(smem + L::off_misc + t); };
+  const auto row_lin = [&](int t) { return row_vox(t) + kRowsPad; };
+  const auto row_mult = [&](int t) { return reinterpret_cast<float*>(row_vox(t) + 2 * kRowsPad); };
+  const auto header = [&](int t) { return row_vox(t) + 3 * kRowsPad; };
+  const auto store_desc = [&](int word, int t) {
+    if (tid < kHdrWords) {
+      header(t)[tid] = word;
+    } else if (tid < kHdrWords + 2 * kRowsMax) {     // words 64 + 2 r and 65 + 2 r: voxel and (slots << 24 | position code) of row r
+      const int r = (tid - kHdrWords) >> 1;
       if ((tid & 1) == 0) {
-        row_vox[r] = (word >= 0 && word < mp.n_voxels) ? word : -1;
+        row_vox(t)[r] = (word >= 0 && word < mp.n_voxels) ? word : -1;
       } else {
-        row_lin[r] = word & 0xFFFFFF;
-        row_mult[r] = (float)((unsigned)word >> 24);
+        row_lin(t)[r] = word & 0xFFFFFF;
+        if constexpr (DUP) row_mult(t)[r] = (float)((unsigned)word >> 24);
       }
     }
-    lds_barrier();
-    ns = __builtin_amdgcn_readfirstlane(set_nu[kMaxSets]);
-    if (ns <= 0) return;
+  };
+  // rows and row tiles of a tile (no sets: no rows, and one row tile of zeros)
+  const auto tile_rows = [&](int t) {
+    const int ns = __builtin_amdgcn_readfirstlane(header(t)[1]), R = __builtin_amdgcn_readfirstlane(header(t)[0]);
+    return ns <= 0 || R < 0 ? 0 : (R > kRowsMax ? kRowsMax : R);
+  };
+  const auto row_tiles = [](int R) { return R > 0 ? (R + 15) >> 4 : 1; };
+
+  // gather (Eq. 4): rows of x -> LDS, 16 bytes per thread, dead rows zero.  The loads are unconditional (clamped addresses).
+  // Thread t takes piece t % CH of the rows t / CH, t / CH + GR, ...
+  constexpr int CH = C * (int)sizeof(T) / 16, GR = NTHREADS / CH, G = (kRowsMax + GR - 1) / GR;
+  static_assert(NTHREADS % CH == 0 && kRowsMax % GR == 0, "whole rows per pass");
+  const auto request_rows = [&](uint4 (&gv)[G], bool (&live)[G], int t, int RT) {
+    const int r0 = tid / CH, c = tid - r0 * CH;
+#pragma unroll
+    for (int k = 0; k < G; ++k) {
+      const int v = r0 + k * GR < RT * 16 ? row_vox(t)[r0 + k * GR] : -1;
+      live[k] = v >= 0;
+      gv[k] = reinterpret_cast<const uint4*>(x + (size_t)(v >= 0 ? v : 0) * C)[c];
+    }
+  };
+  const auto store_rows = [&](const uint4 (&gv)[G], const bool (&live)[G], int off, int RT) {
+    const int r0 = tid / CH, c = tid - r0 * CH;
+#pragma unroll
+    for (int k = 0; k < G; ++k)
+      if (r0 + k * GR < RT * 16)
+        *reinterpret_cast<uint4*>(smem + off + (r0 + k * GR) * LDX * (int)sizeof(T) + c * 16) = live[k] ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
+  };
+  // A row of a tile from registers in accumulator layout -> the voxel's row of out.
+  const auto put_out = [&](int t, int R, int row, int o0, const f32x4 (&v)[NT_O]) {
+    const int vox = row < R ? row_vox(t)[row] : -1;
+    if constexpr (NT_O == 2 && sizeof(T) == 2) {
+      // neighbouring 16-lane rows exchange halves, so that a lane holds 8 consecutive features: of tile 0 in the even rows, of
+      // tile 1 in the odd ones
+      union { Vec4 h; unsigned u[2]; } a, b;
+      a.h = pack4<T>(v[0]);
+      b.h = pack4<T>(v[1]);
+      const auto s0 = __builtin_amdgcn_permlane16_swap(a.u[0], b.u[0], false, false), s1 = __builtin_amdgcn_permlane16_swap(a.u[1], b.u[1], false, false);
+      if (vox >= 0) *reinterpret_cast<uint4*>(out + (size_t)vox * C + o0 + 16 * (g & 1) + 8 * (g >> 1)) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < NT_O; ++nt)
+        if (vox >= 0) *reinterpret_cast<Vec4*>(out + (size_t)vox * C + o0 + 16 * nt + 4 * g) = pack4<T>(v[nt]);
+    }
+  };
+
+  // ---- 3. Q, K, V = X W^T + b; V stored transposed
+  const auto project = [&](QkvPhase& qkv, int RT) {
+    const T* Xs = reinterpret_cast<const T*>(smem + xo);
+    T* Qs = reinterpret_cast<T*>(smem + (2 * L::kTile - xo));
+    // the V items run with exchanged MFMA operands: a lane then holds four consecutive rows of one
+    // feature, i.e. 8 contiguous bytes of V^T (a plain store instead of four 2-byte ones)
+    static_assert((C / 16) % NT_QKV == 0, "an item never straddles the Q/K/V boundary");
+    const float q_scale = rsqrtf((float)L::D) * 1.4426950408889634f;
+    const int o0 = wave * 16 * NT_QKV;
+    const auto store = [&](T* dst, int r, const f32x4 (&v)[NT_QKV]) {
+#pragma unroll
+      for (int nt = 0; nt < NT_QKV; ++nt) *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + 4 * g) = pack4<T>(v[nt]);
+    };
+    if (o0 >= 2 * C) {
+      qkv.template run_rows<true>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) {
+#pragma unroll
+        for (int nt = 0; nt < NT_QKV; ++nt)
+          *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * nt + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[nt]);
+      });
+    } else if (o0 >= C) {
+      qkv.template run_rows<false>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) { store(Ks + (o0 - C), r, acc); });
+    } else {
+      qkv.template run_rows<false>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) {
+#pragma unroll
+        for (int nt = 0; nt < NT_QKV; ++nt) acc[nt] *= q_scale;      // logits in units of log2(e)
+        store(Qs + o0, r, acc);
+      });
+    }
+  };
+
+  int word = 0;
+  if (listed && tid < 256) word = mp.tile_desc[(size_t)tile * 256 + tid];
+  if (tile >= n_tiles) return;
+  QkvPhase first(reinterpret_cast<const T*>(p.w_qkv), wave);
+  first.template prefetch_first<kEarly>();
+  for (int r = kRowsMax + tid; r < kRowsPad; r += NTHREADS)
+    for (int t = 0; t <= (int)L::kRowTab; t += (int)L::kRowTab) { row_vox(t)[r] = -1; row_lin(t)[r] = 0; row_mult(t)[r] = 0.f; }
+
+  if (listed) {
+    // ---- 1a. rows from the tile descriptor the partition wrote for this tile (1 KB, one load)
+    store_desc(word, tab);
   } else {
-    // ---- 1b. no work list: two sets per workgroup, rows derived from set_inds and coords
-    int n_sets = *mp.n_sets;
-    n_sets = n_sets < mp.max_sets ? n_sets : mp.max_sets;
-    const int per_wg = fixed_sets(mp.tau);
-    const int s_begin = blockIdx.x * per_wg;
-    ns = __builtin_amdgcn_readfirstlane((n_sets - s_begin) < per_wg ? (n_sets - s_begin) : per_wg);
-    if (ns <= 0) return;
-    qkv.template prefetch_first<kEarly>();
-    const int tau = mp.tau;
-    for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox[r] = -1; row_lin[r] = 0; row_mult[r] = 0.f; }
+    // ---- 1b. no work list: two sets per tile, rows derived from set_inds and coords
+    const int tau = mp.tau, s_begin = tile * per_wg, ns = n_sets - s_begin < per_wg ? n_sets - s_begin : per_wg;
+    int32_t* hdr = header(tab);
+    for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox(tab)[r] = -1; row_lin(tab)[r] = 0; row_mult(tab)[r] = 0.f; }
     for (int ls = wave; ls < ns; ls += NW) {
       const int v = lane < tau ? mp.set_inds[(size_t)(s_begin + ls) * tau + lane] : -2;
       const int prev = __shfl_up(v, 1, 64);
       const bool first = lane < tau && (lane == 0 || v != prev);   // repeats are adjacent
       const unsigned long long mask = __ballot(first);
-      if (lane == 0) set_nu[ls] = __popcll(mask);
+      if (lane == 0) hdr[kHdrNu + ls] = __popcll(mask);
     }
     lds_barrier();
     if (tid == 0) {
-      int r = 0, n = 0;
-      for (int s = 0; s < ns; ++s) {             // each set starts on a multiple of 4 rows
-        set_r0[s] = r; r += (set_nu[s] + 3) & ~3;
-        const int kts = (set_nu[s] + 15) >> 4;
-        for (int qt = 0; qt < kts; ++qt)
-          for (int hh = 0; hh < item_groups(kts, HEADS, big_heads(C, DUP, SETS)); ++hh)
-            if (n < kMaxItems) items[n++] = s | (qt << 8) | (hh << 12) | (kts << 16);
-      }
-      set_r0[ns] = r;
-      items[kMaxItems] = n;
+      int r = 0;
+      for (int s = 0; s < ns; ++s) { hdr[kHdrR0 + s] = r; r += (hdr[kHdrNu + s] + 3) & ~3; }   // each set starts on a multiple of 4 rows
+      hdr[0] = r;
+      hdr[1] = ns;
     }
     lds_barrier();
     for (int ls = wave; ls < ns; ls += NW) {
@@ -367,167 +463,159 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       const bool first = lane < tau && (lane == 0 || v != prev);
       const unsigned long long mask = __ballot(first);
       if (first && v >= 0 && v < mp.n_voxels) {
-        const int r = set_r0[ls] + __popcll(mask & ((1ull << lane) - 1ull));
+        const int r = hdr[kHdrR0 + ls] + __popcll(mask & ((1ull << lane) - 1ull));
         const unsigned long long later = mask >> (lane + 1);
         const int run = later ? (__ffsll((long long)later)) : (tau - lane);   // slots holding this voxel
         const int4 c = coords[v];
-        row_vox[r] = v;
-        row_mult[r] = (float)run;
-        row_lin[r] = (c.y * p.rel_my + c.z) * p.rel_mz + c.w;
+        row_vox(tab)[r] = v;
+        row_mult(tab)[r] = (float)run;
+        row_lin(tab)[r] = (c.y * p.rel_my + c.z) * p.rel_mz + c.w;
       }
     }
-    lds_barrier();
   }
-  DSVT_PHASE(1);                                 // rows known
-  const int R = __builtin_amdgcn_readfirstlane(set_r0[ns]);
-  const int RT = (R + 15) >> 4;
-  const int RTH = (RT + 1) >> 1;                 // the LayerNorm phases: row tiles of the first half
-
-  // ---- 2. gather (Eq. 4): rows of x -> Xs, 16 bytes per thread, dead rows zero.  The loads are
-  // unconditional (clamped addresses).  The rest of the Q/K/V weights (C = 192: a third; C <= 128: only the biases are left) is
-  // requested after the barrier that publishes the rows, not here: a wavefront stands still until its requests are taken,
-  // and all 216 fragments of C = 192 in front of the stores to LDS kept every wavefront from the barrier for 3.4 k cycles.
+  lds_barrier();
+  DSVT_PHASE(tile, 1);                             // rows known
+  // ---- 2. gather
+  int R = tile_rows(tab), RT = row_tiles(R);
   {
-    constexpr int CH = C * (int)sizeof(T) / 16, G = (kRowsMax * CH + NTHREADS - 1) / NTHREADS;
     uint4 gv[G];
     bool live[G];
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int idx = tid + k * NTHREADS;
-      const int r = idx / CH, c = idx - r * CH;
-      const int v = r < RT * 16 ? row_vox[r] : -1;
-      live[k] = v >= 0;
-      gv[k] = reinterpret_cast<const uint4*>(x + (size_t)(v >= 0 ? v : 0) * C)[c];
-    }
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int idx = tid + k * NTHREADS;
-      const int r = idx / CH, c = idx - r * CH;
-      if (idx < RT * 16 * CH)
-        *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16) =
-            live[k] ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
-    }
+    request_rows(gv, live, tab, RT);
+    store_rows(gv, live, xo, RT);
   }
   lds_barrier();
   DSVT_REFRESH_LANE();
-  DSVT_PHASE(2);                                 // rows in LDS
-  qkv.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
+  DSVT_PHASE(tile, 2);                                 // rows in LDS
+  first.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
+  project(first, RT);
 
-  // ---- 3. Q, K, V = X W^T + b; V stored transposed
-  {
-    // the V items run with exchanged MFMA operands: a lane then holds four consecutive rows of one
-    // feature, i.e. 8 contiguous bytes of V^T (a plain store instead of four 2-byte ones)
-    static_assert((C / 16) % NT_QKV == 0, "an item never straddles the Q/K/V boundary");
-    const float q_scale = rsqrtf((float)L::D) * 1.4426950408889634f;
-    qkv.run(Xs, LDX, RT, p.b_qkv, [&](int o0, int r, f32x4 (&acc)[NT_QKV], bool swapped) {
-      if (swapped) {
-#pragma unroll
-        for (int nt = 0; nt < NT_QKV; ++nt)
-          *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * nt + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[nt]);
-      } else {
-        const int row = 16 * r + m;
-#pragma unroll
-        for (int nt = 0; nt < NT_QKV; ++nt) {
-          const int ot = o0 + 16 * nt;
-          const int o = ot + 4 * g;
-          if (ot < C) *reinterpret_cast<Vec4*>(Qs + row * LDX + o) = pack4<T>(acc[nt] * q_scale);   // logits in units of log2(e)
-          else *reinterpret_cast<Vec4*>(Ks + row * LDX + (o - C)) = pack4<T>(acc[nt]);
-        }
-      }
-    }, 2 * C / (16 * NT_QKV));
-  }
-  // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one half of
-  // the row tiles; the Q/K/V and first MLP projections (bandwidth-heavy) give a wavefront all rows
-  // of its output tiles instead, so that each of their weight fragments is loaded only once.  An odd number of row
-  // tiles gives the second half one less; in a tile of a single one the second half has no rows and requests no
-  // weights (220 KB of the 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
-  const int og_own = wave % SG;
-  const int rt_own = wave < SG ? 0 : RTH, HC = wave < SG ? RTH : (wave < 2 * SG ? RT - RTH : 0);   // HC = 0: a wavefront without an item
-  GemmPhase<T, NT_O, C, C, NW, 2> oproj(reinterpret_cast<const T*>(p.w_o), wave);
-  if (HC > 0) oproj.prefetch();                  // in flight during the attention phase
-  const int o_own = og_own * 16 * NT_O;
-  lds_barrier();
-  DSVT_REFRESH_LANE();
+  for (;;) {
+    DSVT_REFRESH_LANE();
+    T* Xs = reinterpret_cast<T*>(smem + xo);
+    T* Qs = reinterpret_cast<T*>(smem + (2 * L::kTile - xo));
+    T* Hs = reinterpret_cast<T*>(smem + (L::kTile - xo / 2));
+    const int next = tile + stride;
+    const bool more = next < n_tiles;
+    const int RTH = (RT + 1) >> 1;               // the LayerNorm phases: row tiles of the first half
 
-  DSVT_PHASE(3);                                 // Q, K, V^T in LDS
-  // ---- 4. attention inside every set; O overwrites Q
-  {
-    const int n_items = __builtin_amdgcn_readfirstlane(items[kMaxItems]);
-    for (int it = wave; it < n_items; it += NW) {
-      const int d = __builtin_amdgcn_readfirstlane(items[it]);
-      const int s = d & 255, qt = (d >> 8) & 15, hh = (d >> 12) & 15, kts = d >> 16;
-      const int r0 = __builtin_amdgcn_readfirstlane(set_r0[s]), nu = __builtin_amdgcn_readfirstlane(set_nu[s]);
-      attn_any<T, C, HEADS, HID, SETS, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, kts, RT * 16);
+    // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one half of
+    // the row tiles; the Q/K/V and first MLP projections (bandwidth-heavy) give a wavefront all rows
+    // of its output tiles instead, so that each of their weight fragments is loaded only once.  An odd number of row
+    // tiles gives the second half one less; in a tile of a single one the second half has no rows and requests no
+    // weights (220 KB of the 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
+    const int og_own = wave % SG;
+    const int rt_own = wave < SG ? 0 : RTH, HC = wave < SG ? RTH : (wave < 2 * SG ? RT - RTH : 0);   // HC = 0: a wavefront without an item
+    GemmPhase<T, NT_O, C, C, NW, 2> oproj(reinterpret_cast<const T*>(p.w_o), wave);
+    oproj.forget();
+    if (HC > 0) oproj.prefetch();                // in flight during the attention phase
+    const int o_own = og_own * 16 * NT_O;
+    // The set table, by the first wavefront: it is through with its part of the projection first (the compute unit issues its
+    // oldest wavefronts first) and would wait for the others.  (In front of the rows' request every wavefront waits for it: 0.6 k
+    // clocks a tile, 4 k with sets of 90 rows and a list of the items instead of this table.)
+    if (wave == 0) {
+      const int32_t* hdr = header(tab);
+      int ns = __builtin_amdgcn_readfirstlane(hdr[1]);
+      ns = ns < 0 ? 0 : (ns > kMaxSets ? kMaxSets : ns);
+      const int sl = lane & (kSetWords - 1), r0 = hdr[kHdrR0 + sl], nu_w = hdr[kHdrNu + sl];
+      constexpr int kNuMax = SETS == kSets48 ? 48 : kTauMax;
+      const int nu = nu_w < 1 ? 1 : (nu_w > kNuMax ? kNuMax : nu_w), kts = (nu + 15) >> 4;
+      const int cnt = lane < ns ? kts * item_groups(kts, HEADS, big_heads(C, DUP, SETS)) : 0;
+      const int incl = half_wave_scan(cnt);
+      if (lane < kSetWords) set_tab[lane] = lane < ns ? set_word(r0 < 0 ? 0 : (r0 > kRowsMax - 4 ? kRowsMax - 4 : r0), nu, incl - cnt) : kNoItem;
+      if (lane == kSetWords - 1) set_tab[kSetWords] = (unsigned)incl;
     }
-  }
-  // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
-  // take its place (published by the barriers of the LayerNorm below).  Read from memory where they are used, the latter
-  // would come back behind the weights requested before them, and the LayerNorm of every wavefront would wait for those.
-  // Pass of the 3,001- / 30,000-pillar frame, of the wide windows, of the 120,000-voxel frame: 159.3 -> 156.4, 368.6 ->
-  // 365.5, 326 -> 319, 712 -> 707 us.
-  constexpr bool kGeluTable = sizeof(T) == 2;
-  static_assert(kGeluKnots * sizeof(float2) <= 4096, "GELU table slot");
-  constexpr int kGeluThreads = kGeluTable ? kGeluKnots / 2 : 0, kVecThreads = kGeluThreads + C;     // 16 bytes per thread: 4 C floats in C loads
-  static_assert(kVecThreads <= NTHREADS, "one load per thread");
-  // (Neither the thread number nor a first value of `late` may live through the attention: four zeros kept for it were four
-  // registers too many for sets of 49 to 72 voxels of C = 64 with repeats as keys, which spilled eight.)
-  DSVT_REFRESH_LANE();
-  f32x4 late;
-  opaque_def(late);
-  if (full_layer && tid < kVecThreads) {
-    const int i = tid - kGeluThreads, v = i / (C / 4);
-    const float* src = v < 2 ? (v == 0 ? p.ln1_g : p.ln1_b) : (v == 2 ? p.ln2_g : p.ln2_b);
-    late = i < 0 ? reinterpret_cast<const f32x4*>(p.gelu_tab)[tid] : reinterpret_cast<const f32x4*>(src)[i - v * (C / 4)];
-  }
-  f32x4 bo4[NT_O];
-#pragma unroll
-  for (int nt = 0; nt < NT_O; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
-  lds_barrier();
-  DSVT_REFRESH_LANE();
-  DSVT_PHASE(4);                                 // attention done
-  const float2* gelu_lds = reinterpret_cast<const float2*>(smem + L::off_gelu);
-  const float* affine_lds = reinterpret_cast<const float*>(smem + L::off_aff);
-  if (full_layer && tid < kVecThreads)
-    *reinterpret_cast<f32x4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
+    lds_barrier();
+    DSVT_REFRESH_LANE();
 
-  // ---- 5. Y = O Wo^T + bo (+ x), then LayerNorm; result (or raw Y) replaces x in Xs
-  // The first MLP matrix is requested during this phase, by a third of the wavefronts at a time
-  // (before the projection, after it, after the residual): a CU takes a 16-byte load per
-  // wavefront every ~16 cycles, a wavefront waits until its requests are taken, and twelve
-  // wavefronts asking at once would all stand still for 3 k cycles.
-  GemmPhase<T, NT_1, C, HID, NW, 1, false> ffn1(reinterpret_cast<const T*>(p.w_1), wave);
-  const int pf_turn = full_layer ? wave / (NW / 3) : -1;
-  if (pf_turn == 0) ffn1.prefetch();
-  f32x4 keep[NT_O][kHalfTiles];
-  if (HC == 1) oproj.template run_keep<1>(Qs, LDX, rt_own, bo4, keep);
-  else if (HC == 2) oproj.template run_keep<2>(Qs, LDX, rt_own, bo4, keep);
-  else if (HC == 3) oproj.template run_keep<3>(Qs, LDX, rt_own, bo4, keep);
-  if (pf_turn == 1) ffn1.prefetch();
-#pragma unroll
-  for (int nt = 0; nt < NT_O; ++nt) {
-    const int o = o_own + 16 * nt + 4 * g;
-#pragma unroll
-    for (int r = 0; r < kHalfTiles; ++r) {
-      if (r < HC) {
-        if (full_layer) {
-          const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * (rt_own + r) + m) * LDX + o);
-          keep[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
-        } else {
-          *reinterpret_cast<Vec4*>(Xs + (16 * (rt_own + r) + m) * LDX + o) = pack4<T>(keep[nt][r]);
-        }
+    DSVT_PHASE(tile, 3);                               // Q, K, V^T in LDS
+    // ---- 4. attention inside every set; O overwrites Q
+    {
+      const unsigned my_set = set_tab[lane & (kSetWords - 1)];
+      const int n_items = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords]);
+      for (int it = wave; it < n_items; it += NW) {
+        // (both halves of the wavefront hold the table; set 0 starts at item 0)
+        const int s = __popcll(__ballot((int)(my_set >> 16) <= it) & 0xffffffffull) - 1;
+        const unsigned sw = (unsigned)__builtin_amdgcn_readlane((int)my_set, s);
+        const int r0 = sw & 255, nu = (sw >> 8) & 255, kts = (nu + 15) >> 4, k = it - (int)(sw >> 16);
+        const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS));      // (a power of two)
+        const int qt = k >> __builtin_ctz(ngr), hh = k & (ngr - 1);
+        attn_any<T, C, HEADS, HID, SETS, DUP>(p, Qs, Ks, Vt, row_lin(tab), row_mult(tab), r0, nu, qt, hh, kts, RT * 16);
       }
     }
-  }
-  if (full_layer) {
+    // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
+    // take its place (published by the barriers of the LayerNorm below).  Read from memory where they are used, the latter
+    // would come back behind the weights requested before them, and the LayerNorm of every wavefront would wait for those.
+    // Pass of the 3,001- / 30,000-pillar frame, of the wide windows, of the 120,000-voxel frame: 159.3 -> 156.4, 368.6 ->
+    // 365.5, 326 -> 319, 712 -> 707 us.
+    constexpr bool kGeluTable = sizeof(T) == 2;
+    static_assert(kGeluKnots * sizeof(float2) <= 4096, "GELU table slot");
+    constexpr int kGeluThreads = kGeluTable ? kGeluKnots / 2 : 0, kVecThreads = kGeluThreads + C;     // 16 bytes per thread: 4 C floats in C loads
+    static_assert(kVecThreads <= NTHREADS, "one load per thread");
+    // (Neither the thread number nor a first value of `late` may live through the attention: four zeros kept for it were four
+    // registers too many for sets of 49 to 72 voxels of C = 64 with repeats as keys, which spilled eight.)
+    DSVT_REFRESH_LANE();
+    f32x4 late;
+    opaque_def(late);
+    if (full_layer && tid < kVecThreads) {
+      const int i = tid - kGeluThreads, v = i / (C / 4);
+      const float* src = v < 2 ? (v == 0 ? p.ln1_g : p.ln1_b) : (v == 2 ? p.ln2_g : p.ln2_b);
+      late = i < 0 ? reinterpret_cast<const f32x4*>(p.gelu_tab)[tid] : reinterpret_cast<const f32x4*>(src)[i - v * (C / 4)];
+    }
+    f32x4 bo4[NT_O];
+#pragma unroll
+    for (int nt = 0; nt < NT_O; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
+    int next_word;
+    opaque_def(next_word);
+    if (more && tid < 256) next_word = mp.tile_desc[(size_t)next * 256 + tid];
+    lds_barrier();
+    DSVT_REFRESH_LANE();
+    DSVT_PHASE(tile, 4);                               // attention done
+    const float2* gelu_lds = reinterpret_cast<const float2*>(smem + L::off_gelu);
+    const float* affine_lds = reinterpret_cast<const float*>(smem + L::off_aff);
+    if (full_layer && tid < kVecThreads)
+      *reinterpret_cast<f32x4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
+
+    // ---- 5. Y = O Wo^T + bo (+ x), then LayerNorm; the result replaces x in Xs (or raw Y goes out)
+    // The first MLP matrix is requested during this phase, by a third of the wavefronts at a time
+    // (before the projection, after it, after the residual): a CU takes a 16-byte load per
+    // wavefront every ~16 cycles, a wavefront waits until its requests are taken, and twelve
+    // wavefronts asking at once would all stand still for 3 k cycles.
+    GemmPhase<T, NT_1, C, HID, NW, 1, false> ffn1(reinterpret_cast<const T*>(p.w_1), wave);
+    const int pf_turn = full_layer ? wave / (NW / 3) : -1;
+    ffn1.forget();
+    if (pf_turn == 0) ffn1.prefetch();
+    f32x4 keep[NT_O][kHalfTiles];
+    QkvPhase qkv(reinterpret_cast<const T*>(p.w_qkv), wave);     // of the next tile
+    if (HC == 1) oproj.template run_keep<1>(Qs, LDX, rt_own, bo4, keep);
+    else if (HC == 2) oproj.template run_keep<2>(Qs, LDX, rt_own, bo4, keep);
+    else if (HC == 3) oproj.template run_keep<3>(Qs, LDX, rt_own, bo4, keep);
+    else undefined(keep);
+    if (pf_turn == 1) ffn1.prefetch();
+    if (!full_layer) {                           // attention and its projection only: raw Y goes out, one tile per workgroup
+#pragma unroll
+      for (int r = 0; r < kHalfTiles; ++r)
+        if (r < HC) {
+          f32x4 y[NT_O];
+#pragma unroll
+          for (int nt = 0; nt < NT_O; ++nt) y[nt] = keep[nt][r];
+          put_out(tab, R, 16 * (rt_own + r) + m, o_own, y);
+        }
+      return;
+    }
+    add_rows<T, NT_O, kHalfTiles>(keep, Xs, LDX, rt_own, HC, o_own);
     if (pf_turn == 2) ffn1.prefetch();
     layer_norm_tile<T, NT_O, C, kHalfTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       a = *reinterpret_cast<const f32x4*>(affine_lds + o_own + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
-    }, p.ln_eps, Xs, LDX);
+    }, p.ln_eps, [&](int row, const f32x4 (&y)[NT_O]) {
+#pragma unroll
+      for (int nt = 0; nt < NT_O; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
+    });
+    if (more) store_desc(next_word, (int)L::kRowTab - tab);
     lds_barrier();
     DSVT_REFRESH_LANE();
 
-    DSVT_PHASE(5);                               // x1 in LDS
+    DSVT_PHASE(tile, 5);                             // x1 in LDS
     // ---- 6. MLP: H = gelu(x1 W1^T + b1) over the dead Q/K tiles; x2 = LN(x1 + H W2^T + b2)
     // The second matrix's weights (C = 192: the first half of K, C <= 128: all) are requested between the last MFMAs of the first
     // product and the GELU of its last row tiles: the memory pipeline is idle there and needs 2.7 k cycles for the 144 fragments of
@@ -537,7 +625,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
     // bias requested in front of the weights 0.1-0.7 %.
     GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
-    ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1], bool) {
+    ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
 #pragma unroll
       for (int nt = 0; nt < NT_1; ++nt) {
         const int o = o0 + 16 * nt + 4 * g;
@@ -548,50 +636,58 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
           v = f32x4{gelu_erf_fast(v[0]), gelu_erf_fast(v[1]), gelu_erf_fast(v[2]), gelu_erf_fast(v[3])};
         *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o) = pack4<T>(v);
       }
-    }, [&]() { if (HC > 0) ffn2.prefetch(); });
+    }, [&]() {
+      ffn2.forget();
+      if (HC > 0) ffn2.prefetch();
+    });
     const int o_own2 = og_own * 16 * NT_2;
     f32x4 b24[NT_2];
 #pragma unroll
     for (int nt = 0; nt < NT_2; ++nt) b24[nt] = *reinterpret_cast<const f32x4*>(p.b_2 + o_own2 + 16 * nt + 4 * g);
+    // The next tile's rows: in flight during the second product, stored over Q when every wavefront is through with it
+    const int next_tab = (int)L::kRowTab - tab, next_RT = more ? row_tiles(tile_rows(next_tab)) : 0;
+    uint4 gv[G];
+    bool live[G];
+#pragma unroll
+    for (int k = 0; k < G; ++k) { opaque_def(gv[k].x); opaque_def(gv[k].y); opaque_def(gv[k].z); opaque_def(gv[k].w); live[k] = false; }
+    if (more) request_rows(gv, live, next_tab, next_RT);
     lds_barrier();
     DSVT_REFRESH_LANE();
-    DSVT_PHASE(6);                               // H in LDS
+    DSVT_PHASE(tile, 6);                             // H in LDS
     f32x4 keep2[NT_2][kHalfTiles];
     if (HC == 1) ffn2.template run_keep<1>(Hs, LDH, rt_own, b24, keep2);
     else if (HC == 2) ffn2.template run_keep<2>(Hs, LDH, rt_own, b24, keep2);
     else if (HC == 3) ffn2.template run_keep<3>(Hs, LDH, rt_own, b24, keep2);
-#pragma unroll
-    for (int nt = 0; nt < NT_2; ++nt) {
-      const int o = o_own2 + 16 * nt + 4 * g;
-#pragma unroll
-      for (int r = 0; r < kHalfTiles; ++r) {
-        if (r < HC) {
-          const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * (rt_own + r) + m) * LDX + o);
-          keep2[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
-        }
-      }
-    }
+    else undefined(keep2);
+    qkv.forget();
+    if (more && pf_turn == 0) qkv.template prefetch_first<kEarly>();
+    add_rows<T, NT_2, kHalfTiles>(keep2, Xs, LDX, rt_own, HC, o_own2);
+    if (more && pf_turn == 1) qkv.template prefetch_first<kEarly>();
     layer_norm_tile<T, NT_2, C, kHalfTiles>(keep2, o_own2, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
+      if (nt == 0) DSVT_PHASE(tile, 7);          // everybody's part of the second product done
+      if (nt == 0 && more) {
+        store_rows(gv, live, 2 * (int)L::kTile - xo, next_RT);
+        if (pf_turn == 2) qkv.template prefetch_first<kEarly>();
+      }
       a = *reinterpret_cast<const f32x4*>(affine_lds + 2 * C + o_own2 + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + 3 * C + o_own2 + 16 * nt + 4 * g);
-    }, p.ln_eps, Xs, LDX);
+    }, p.ln_eps, [&](int row, const f32x4 (&y)[NT_2]) { put_out(tab, R, row, o_own2, y); });
+    DSVT_PHASE(tile, 8);
+    if (!more) return;
+    DSVT_PHASE(next, 0);
+    DSVT_PHASE(next, 1);
+    qkv.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
+    tile = next;
+    stride = 2 * (int)gridDim.x - stride;
+    xo = 2 * (int)L::kTile - xo;
+    tab = (int)L::kRowTab - tab;
+    R = tile_rows(tab);
+    RT = row_tiles(R);
+    lds_barrier();
+    DSVT_REFRESH_LANE();
+    DSVT_PHASE(tile, 2);
+    project(qkv, RT);
   }
-  lds_barrier();
-  DSVT_REFRESH_LANE();
-
-  DSVT_PHASE(7);                                 // x2 in LDS
-  // ---- 7. scatter: rows of Xs -> the voxels' rows of out, 16 bytes per thread
-  {
-    constexpr int CH = C * (int)sizeof(T) / 16;
-    for (int idx = tid; idx < R * CH; idx += NTHREADS) {
-      const int r = idx / CH, c = idx - r * CH;
-      const int v = row_vox[r];
-      if (v >= 0)
-        reinterpret_cast<uint4*>(out + (size_t)v * C)[c] =
-            *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(Xs) + (size_t)r * LDX * sizeof(T) + c * 16);
-    }
-  }
-  DSVT_PHASE(8);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -677,8 +773,10 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
   if (int rc = dsvt_allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed)) return rc;
   MapsDev md;
   md.set_inds = mp.set_inds; md.n_sets = mp.n_sets; md.n_tiles = mp.tiles.n_tiles; md.tile_desc = mp.tiles.tile_desc;
-  md.max_sets = mp.max_sets; md.tau = mp.tau; md.n_voxels = mp.n_voxels;
-  const unsigned grid = mp.tiles.tile_desc ? (unsigned)mp.tiles.max_tiles : (unsigned)dsvt_ceil_div(mp.max_sets, fixed_sets(mp.tau));
+  md.max_sets = mp.max_sets; md.max_tiles = mp.tiles.max_tiles; md.tau = mp.tau; md.n_voxels = mp.n_voxels;
+  const int64_t tiles = mp.tiles.tile_desc ? mp.tiles.max_tiles : dsvt_ceil_div(mp.max_sets, fixed_sets(mp.tau));
+  constexpr int64_t fit = kComputeUnits * groups_per_cu<T, C, HEADS, HID>(SETS);
+  const unsigned grid = (unsigned)(full && mp.tiles.tile_desc && tiles > fit ? fit : tiles);
   dsvt_prof_scope ps(DSVT_K_LAYER, st);
   kern<<<grid, kLayerWaves * 64, lds, st>>>(to_dev(w), md, reinterpret_cast<const int4*>(coords),
                                        reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out), full);

@@ -74,6 +74,13 @@ __device__ __forceinline__ int opaque_tid() {
 // of the other paths in front of the loop and keeps registers for it through every iteration.
 template <typename V> __device__ __forceinline__ void opaque_def(V& v) { asm volatile("" : "=v"(v)); }
 
+template <int A, int B> __device__ __forceinline__ void undefined(f32x4 (&v)[A][B]) {
+#pragma unroll
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int b = 0; b < B; ++b) opaque_def(v[a][b]);
+}
+
 // Elements of T that pad every LDS row by 32 bytes.  Rows of K elements (K * sizeof(T) a multiple
 // of 64 bytes) then have a pitch that is an odd multiple of 32 bytes, the one pitch at which the
 // 16-byte fragment loads of a wavefront (16 rows x 4 k-slices) run at the full LDS rate; measured
@@ -171,9 +178,8 @@ struct GemmPhase {
   AFull<T, NT, NKF> a[(IPW > 1 && DOUBLE_A) ? 2 : 1];   // DOUBLE_A: the next item's weights load during the current item
   const T* Wp;
   int wave;
-  struct Bias { f32x4 v[NT]; float s[NT]; };          // both forms of an item's bias, see load_bias()
-  Bias bias0;                                            // first item's bias when prefetch_rest() fetched it
-  bool bias0_set = false;
+  struct Bias { f32x4 v[NT]; };                         // an item's bias, see load_bias()
+  Bias bias0;                                            // run_rows(): the bias that prefetch_rest() fetched
 
   __device__ __forceinline__ GemmPhase(const T* wp, int wave_) : Wp(wp), wave(wave_) {}
 
@@ -193,41 +199,45 @@ struct GemmPhase {
     if (N_ITEMS >= NW || wave < N_ITEMS) load_a<T, NT, NKF, NKF_ALL>(a[0], Wp, (wave % N_OG) * NT);
   }
 
-  // prefetch() in two parts: the first N output tiles of the first item, then the others and the bias run() starts it from.
+  // prefetch() in two parts: the first N output tiles of the first item, then the others and the bias run_rows() starts it from.
   template <int N> __device__ __forceinline__ void prefetch_first() {
     if (N_ITEMS >= NW || wave < N_ITEMS) load_a_tiles<T, NT, NKF, NKF_ALL, 0, N>(a[0], Wp, (wave % N_OG) * NT);
   }
   template <int N> __device__ __forceinline__ void prefetch_rest(const float* __restrict__ bias, int swap_og) {
     if (N_ITEMS >= NW || wave < N_ITEMS) {
       load_a_tiles<T, NT, NKF, NKF_ALL, N, NT>(a[0], Wp, (wave % N_OG) * NT);
-      load_bias(bias0, bias, wave % N_OG, swap_og < N_OG);
-      bias0_set = true;
+      load_bias(bias0, bias, wave % N_OG, wave % N_OG >= swap_og);
     }
   }
 
-  // Accumulator start values of output group og: feature 16*nt + 4*g + i for element i, or, with
-  // exchanged operands, feature 16*nt + m for all four.  Both forms are loaded (no branch, no
-  // wait at the point of the request) and select() picks one when the item starts.
-  __device__ __forceinline__ void load_bias(Bias& b, const float* __restrict__ bias, int og, bool need_s) const {
+  // Accumulator start values of output group og: feature 16*nt + 4*g + i for element i, or, with exchanged operands ("sw",
+  // wave-uniform), feature 16*nt + m for all four: then element 0 is loaded, and start_bias(), called where the item starts, spreads it.
+  __device__ __forceinline__ void load_bias(Bias& b, const float* __restrict__ bias, int og, bool sw) const {
     const int tl = opaque_tid(), lane16 = tl & 15, g4 = ((tl & 63) >> 4) * 4;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      b.v[nt] = *reinterpret_cast<const f32x4*>(bias + og * 16 * NT + 16 * nt + g4);
-      b.s[nt] = need_s ? bias[og * 16 * NT + 16 * nt + lane16] : 0.f;
+    for (int nt = 0; nt < NT; ++nt) opaque_def(b.v[nt]);
+    if (sw) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) b.v[nt][0] = bias[og * 16 * NT + 16 * nt + lane16];
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) b.v[nt] = *reinterpret_cast<const f32x4*>(bias + og * 16 * NT + 16 * nt + g4);
     }
   }
-  static __device__ __forceinline__ void select_bias(f32x4 (&b4)[NT], const Bias& b, bool sw) {
+  static __device__ __forceinline__ void start_bias(f32x4 (&b4)[NT], const Bias& b, bool sw) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) b4[nt] = sw ? f32x4{b.s[nt], b.s[nt], b.s[nt], b.s[nt]} : b.v[nt];
+    for (int nt = 0; nt < NT; ++nt) b4[nt] = b.v[nt];
+    if (sw) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) b4[nt] = f32x4{b4[nt][0], b4[nt][0], b4[nt][0], b4[nt][0]};
+    }
   }
 
-  // Row tiles in a rolled loop, two per trip.  epi(o0, r, acc, swapped): acc[nt][i] is output
-  // feature o0 + 16*nt + 4*g + i of row 16*r + m, bias included -- or, for the items whose output
-  // group is >= swap_og ("swapped": operands exchanged), feature o0 + 16*nt + m of row
-  // 16*r + 4*g + i.  The bias is fetched before the next item's weights are requested, so waiting
-  // for it never waits for them.
+  // Row tiles in a rolled loop, two per trip.  epi(o0, r, acc): acc[nt][i] is output
+  // feature o0 + 16*nt + 4*g + i of row 16*r + m, bias included.  The bias is fetched before the next item's weights are
+  // requested, so waiting for it never waits for them.
   template <typename Epi>
-  __device__ __forceinline__ void run(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, int swap_og = N_OG) {
+  __device__ __forceinline__ void run(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi) {
     static_assert(KSPLIT == 1, "run() holds the whole K");
     const int h0 = RSPLIT == 1 ? RT : (RT + 1) >> 1;
 #pragma unroll
@@ -236,15 +246,8 @@ struct GemmPhase {
       if (item >= N_ITEMS) break;
       const int og = item % N_OG, half = item / N_OG;
       const int rt0 = half ? h0 : 0, cnt = half ? RT - h0 : h0;
-      const bool sw = og >= swap_og;                 // wave-uniform
-      f32x4 b4[NT];
-      if (it == 0 && bias0_set) {
-        select_bias(b4, bias0, sw);
-      } else {
-        Bias bl;
-        load_bias(bl, bias, og, swap_og < N_OG);
-        select_bias(b4, bl, sw);
-      }
+      Bias bl;
+      load_bias(bl, bias, og, false);
       if (DOUBLE_A && it + 1 < IPW && item + NW < N_ITEMS) load_a<T, NT, NKF>(a[(it + 1) & 1], Wp, ((item + NW) % N_OG) * NT);
       const AFull<T, NT, NKF>& A = a[DOUBLE_A ? (it & 1) : 0];
       if constexpr (DOUBLE_A && RSPLIT == 2) {
@@ -255,9 +258,9 @@ struct GemmPhase {
           load_b<T, NKF>(b0, Xs, ldx, rt0 + r);
           f32x4 acc0[NT];
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) acc0[nt] = b4[nt];
-          if (sw) mma_row_swapped<T, NT, NKF>(acc0, A, b0); else mma_row<T, NT, NKF>(acc0, A, b0);
-          epi(og * 16 * NT, rt0 + r, acc0, sw);
+          for (int nt = 0; nt < NT; ++nt) acc0[nt] = bl.v[nt];
+          mma_row<T, NT, NKF>(acc0, A, b0);
+          epi(og * 16 * NT, rt0 + r, acc0);
         }
       } else {
         BRow<T, NKF> b0, b1;
@@ -267,24 +270,53 @@ struct GemmPhase {
           if (two) load_b<T, NKF>(b1, Xs, ldx, rt0 + r + 1);
           f32x4 acc0[NT], acc1[NT];              // the bias is the accumulators' initial value
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) { acc0[nt] = b4[nt]; acc1[nt] = b4[nt]; }
-          if (sw) mma_row_swapped<T, NT, NKF>(acc0, A, b0); else mma_row<T, NT, NKF>(acc0, A, b0);
+          for (int nt = 0; nt < NT; ++nt) { acc0[nt] = bl.v[nt]; acc1[nt] = bl.v[nt]; }
+          mma_row<T, NT, NKF>(acc0, A, b0);
           if (two) {
             if (r + 2 < cnt) load_b<T, NKF>(b0, Xs, ldx, rt0 + r + 2);
-            if (sw) mma_row_swapped<T, NT, NKF>(acc1, A, b1); else mma_row<T, NT, NKF>(acc1, A, b1);
+            mma_row<T, NT, NKF>(acc1, A, b1);
           }
-          epi(og * 16 * NT, rt0 + r, acc0, sw);
-          if (two) epi(og * 16 * NT, rt0 + r + 1, acc1, sw);
+          epi(og * 16 * NT, rt0 + r, acc0);
+          if (two) epi(og * 16 * NT, rt0 + r + 1, acc1);
         }
       }
       if (!DOUBLE_A && it + 1 < IPW && item + NW < N_ITEMS) load_a<T, NT, NKF>(a[0], Wp, ((item + NW) % N_OG) * NT);
     }
   }
 
-  // run() of a phase of one item per wavefront, over all row tiles (RT > 0), with before_last_epi() called between the last
-  // MFMAs and the epilogue of the last one or two row tiles: the weights' registers are free there, and what it requests
-  // travels while the epilogue computes.  (One place for the call: at two, the compiler keeps the undefined values of the
-  // one alive on the way to the other and spills.)
+  // run() of a phase of one item per wavefront, over all row tiles (RT > 0).  prefetch_rest() has fetched the bias.
+  template <bool SWAPPED> __device__ __forceinline__ void mma_tile(f32x4 (&acc)[NT], const f32x4 (&start)[NT], const BRow<T, NKF>& b) const {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = start[nt];
+    if (SWAPPED) mma_row_swapped<T, NT, NKF>(acc, a[0], b); else mma_row<T, NT, NKF>(acc, a[0], b);
+  }
+  template <bool SWAPPED, typename Epi>
+  __device__ __forceinline__ void run_rows(const T* Xs, int ldx, int RT, Epi epi) {
+    static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1 && N_ITEMS == NW, "one item per wavefront");
+    f32x4 b4[NT];
+    start_bias(b4, bias0, SWAPPED);
+    BRow<T, NKF> b0, b1;
+    load_b<T, NKF>(b0, Xs, ldx, 0);
+    int r = 0;
+    for (; r + 1 < RT; r += 2) {
+      f32x4 acc0[NT], acc1[NT];
+      load_b<T, NKF>(b1, Xs, ldx, r + 1);
+      mma_tile<SWAPPED>(acc0, b4, b0);
+      load_b<T, NKF>(b0, Xs, ldx, r + 2 < RT ? r + 2 : r);
+      mma_tile<SWAPPED>(acc1, b4, b1);
+      epi(r, acc0);
+      epi(r + 1, acc1);
+    }
+    if (r < RT) {
+      f32x4 acc0[NT];
+      mma_tile<SWAPPED>(acc0, b4, b0);
+      epi(r, acc0);
+    }
+  }
+
+  // The same with the bias fetched here and before_last_epi() called between the last MFMAs and the epilogue of the last one
+  // or two row tiles: the weights' registers are free there, and what it requests travels while the epilogue computes.  (One
+  // place for the call: at two, the compiler keeps the undefined values of the one alive on the way to the other and spills.)
   template <typename Epi, typename Before>
   __device__ __forceinline__ void run_before(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, Before before_last_epi) {
     static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1, "one item per wavefront");
@@ -299,25 +331,29 @@ struct GemmPhase {
       load_b<T, NKF>(b0, Xs, ldx, 0);
       for (; r + 2 < RT; r += 2) {
         load_b<T, NKF>(b1, Xs, ldx, r + 1);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) { acc0[nt] = bl.v[nt]; acc1[nt] = bl.v[nt]; }
-        mma_row<T, NT, NKF>(acc0, a[0], b0);
+        mma_tile<false>(acc0, bl.v, b0);
         load_b<T, NKF>(b0, Xs, ldx, r + 2);
-        mma_row<T, NT, NKF>(acc1, a[0], b1);
-        epi(o0, r, acc0, false);
-        epi(o0, r + 1, acc1, false);
+        mma_tile<false>(acc1, bl.v, b1);
+        epi(o0, r, acc0);
+        epi(o0, r + 1, acc1);
       }
-      const bool two = r + 1 < RT;
-      if (two) load_b<T, NKF>(b1, Xs, ldx, r + 1);
+      if (r + 1 < RT) {
+        load_b<T, NKF>(b1, Xs, ldx, r + 1);
+        mma_tile<false>(acc0, bl.v, b0);
+        mma_tile<false>(acc1, bl.v, b1);
+      } else {
+        mma_tile<false>(acc0, bl.v, b0);
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) { acc0[nt] = bl.v[nt]; acc1[nt] = bl.v[nt]; }
-      mma_row<T, NT, NKF>(acc0, a[0], b0);
-      if (two) mma_row<T, NT, NKF>(acc1, a[0], b1);
+        for (int nt = 0; nt < NT; ++nt) opaque_def(acc1[nt]);
+      }
+    } else {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) { opaque_def(acc0[nt]); opaque_def(acc1[nt]); }
     }
     before_last_epi();
     if (some) {
-      epi(o0, r, acc0, false);
-      if (r + 1 < RT) epi(o0, r + 1, acc1, false);
+      epi(o0, r, acc0);
+      if (r + 1 < RT) epi(o0, r + 1, acc1);
     }
   }
 
@@ -327,7 +363,6 @@ struct GemmPhase {
   template <int HC>
   __device__ __forceinline__ void run_keep(const T* Xs, int ldx, int rt0, const f32x4 (&b4)[NT], f32x4 (&acc)[NT][RH]) {
     static_assert(IPW == 1 && HC <= RH, "one item per wavefront");
-    if (wave >= N_ITEMS) return;                       // wavefronts beyond the items only take part in the barriers
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -348,6 +383,10 @@ struct GemmPhase {
         for (int nt = 0; nt < NT; ++nt) acc[nt][r] = t[nt];
       }
     }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = HC; r < RH; ++r) opaque_def(acc[nt][r]);
   }
 };
 
@@ -361,6 +400,16 @@ __device__ __forceinline__ float col_sum(float v) {
   const unsigned w = __float_as_uint(s);
   const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// permlane32_swap(a, b) returns a's halves and b's as (a.lo, b.lo) and (a.hi, b.hi): a's sums over lanes l, l + 32 in the lower half,
+// b's in the upper one; permlane16_swap(a, b) the even and the odd 16-lane rows: (a0, b0, a2, b2) and (a1, b1, a3, b3).
+__device__ __forceinline__ float merge32(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+}
+__device__ __forceinline__ float merge16(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
 }
 // (the maxima are taken by the instruction itself: fmaxf() on values that come out of a lane swap as plain bits
 // is compiled with an extra quieting operation per operand)
@@ -408,33 +457,51 @@ __device__ __forceinline__ float gelu_erf_fast(float x) {
   q = q * q; q = q * q; q = q * q; q = q * q;
   return fmaf(-a, __builtin_amdgcn_rcpf(q), fmaxf(x, 0.f));
 }
+// v += rows of Xs (LDS, pitch ldx), for values in accumulator layout: features o0 .. o0 + 16*NT - 1 of rows 16*(rt0 + r) + m, r < cnt.
+template <typename T, int NT, int RH>
+__device__ __forceinline__ void add_rows(f32x4 (&v)[NT][RH], const T* Xs, int ldx, int rt0, int cnt, int o0) {
+  typedef typename Mma<T>::Vec4 Vec4;
+  const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+    for (int r = 0; r < RH; ++r)
+      if (r < cnt) {
+        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * (rt0 + r) + m) * ldx + o0 + 16 * nt + 4 * g);
+        v[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
+      }
+}
+
+// (One lane-swap reduction serves two sums of two row tiles, and a row's sums lie together, three 16-byte reads at C = 192
+// where twelve 4-byte ones were: pass of 3,001 pillars 164.0 -> 160.3 us, 30,000 383.8 -> 379.1, skewed batch 7,937 -> 7,800.)
 // LayerNorm over the C features of every row, for values spread over the workgroup in
 // accumulator layout: this wavefront holds features o0 .. o0 + 16*NT - 1 (group og of
 // SG = C / (16*NT)) of rows 16*(rt0 + r) + m, r < cnt (cnt = 0: only the barrier).  Per-group sums of x and x^2 (fp32) are
 // exchanged through LDS; variance = E[x^2] - mean^2.  Every thread of the workgroup must call it.
 // affine(nt, gamma, beta): this lane's four of each for output tile nt; called behind the exchange's barrier, so that they may
 // come from LDS that was written before it.
-template <typename T, int NT, int C, int RH, typename Affine>
+// put(row, y): a normalised row's features o0 + 16*nt + 4*g .. + 3, every lane of the wavefront together.
+template <typename T, int NT, int C, int RH, typename Affine, typename Put>
 __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int og, int rt0, int cnt, float* stat,
-                                                Affine affine, float eps, T* dst, int ldd) {
-  typedef typename Mma<T>::Vec4 Vec4;
+                                                Affine affine, float eps, Put put) {
   constexpr int SG = C / (16 * NT);
-  static_assert(SG * 16 * NT == C && SG <= kStatGroupsMax, "LayerNorm feature groups");
+  static_assert(SG * 16 * NT == C && SG <= kStatGroupsMax && SG % 2 == 0, "LayerNorm feature groups");
   const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
-  float* stat1 = stat;
-  float* stat2 = stat + kStatGroupsMax * kRowsMax;
 #pragma unroll
-  for (int r = 0; r < RH; ++r) {
+  for (int r = 0; r < RH; r += 2) {
     if (r < cnt) {
-      float s = 0.f, q = 0.f;
+      float s[2] = {0.f, 0.f}, q[2] = {0.f, 0.f};
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+      for (int k = 0; k < 2; ++k)
+        if (r + k < RH && r + k < cnt) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { s += v[nt][r][i]; q = fmaf(v[nt][r][i], v[nt][r][i], q); }
-      }
-      s = col_sum(s);
-      q = col_sum(q);
-      if (g == 0) { stat1[og * kRowsMax + 16 * (rt0 + r) + m] = s; stat2[og * kRowsMax + 16 * (rt0 + r) + m] = q; }
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s[k] += v[nt][r + k][i]; q[k] = fmaf(v[nt][r + k][i], v[nt][r + k][i], q[k]); }
+        }
+      // the sums over the four lanes of a column, of two row tiles at once: lane group g ends up with quantity g >> 1 of row tile r + (g & 1)
+      const float sum = merge16(merge32(s[0], q[0]), merge32(s[1], q[1]));
+      if ((g & 1) == 0 || (r + 1 < RH && r + 1 < cnt)) stat[((16 * (rt0 + r + (g & 1)) + m) * SG + og) * 2 + (g >> 1)] = sum;
     }
   }
   lds_barrier();
@@ -447,18 +514,19 @@ __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int 
       const int row = 16 * (rt0 + r) + m;
       float s = 0.f, q = 0.f;
 #pragma unroll
-      for (int k = 0; k < SG; ++k) { s += stat1[k * kRowsMax + row]; q += stat2[k * kRowsMax + row]; }
+      for (int k = 0; k < SG / 2; ++k) {
+        const f32x4 t = *reinterpret_cast<const f32x4*>(stat + (row * SG + 2 * k) * 2);
+        s += t[0]; q += t[1]; s += t[2]; q += t[3];
+      }
       const float mean = s * (1.0f / C);
       const float rs = __builtin_amdgcn_rsqf(fmaxf(fmaf(-mean, mean, q * (1.0f / C)), 0.f) + eps);
       const float sh = -mean * rs;
+      f32x4 y[NT];
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int o = o0 + 16 * nt + 4 * g;
-        f32x4 y;
+      for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = fmaf(fmaf(v[nt][r][i], rs, sh), ga[nt][i], be[nt][i]);
-        *reinterpret_cast<Vec4*>(dst + row * ldd + o) = pack4<T>(y);
-      }
+        for (int i = 0; i < 4; ++i) y[nt][i] = fmaf(fmaf(v[nt][r][i], rs, sh), ga[nt][i], be[nt][i]);
+      put(row, y);
     }
   }
 }

@@ -292,7 +292,11 @@ __device__ __forceinline__ void single_regions(PoolDev p, const int2* __restrict
       ga[nt] = *reinterpret_cast<const f32x4*>(vec + 2 * C + o_own + 16 * nt + 4 * g);
       be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
     }
-    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps, Xs, LDX);
+    layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps,
+                                  [&](int row, const f32x4 (&y)[NT]) {
+#pragma unroll
+                                    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
+                                  });
     lds_barrier();
     const int rows = n - grp * kSingleRows < kSingleRows ? n - grp * kSingleRows : kSingleRows;
     for (int idx = tid; idx < rows * CH; idx += NTHREADS) {
@@ -437,7 +441,11 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
             const Vec4 xr = *reinterpret_cast<const Vec4*>(Ps + (16 * (rt_own + r) + (lane & 15)) * LDX + o_own + 16 * nt + 4 * g);
             keep[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
           }
-      layer_norm_tile<T, NT_C, C, RH>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps, Ps, LDX);
+      layer_norm_tile<T, NT_C, C, RH>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps,
+                                  [&](int row, const f32x4 (&y)[NT_C]) {
+#pragma unroll
+                                    for (int nt = 0; nt < NT_C; ++nt) *reinterpret_cast<Vec4*>(Ps + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
+                                  });
       lds_barrier();
       for (int idx = tid; idx < mr_prev * CH; idx += NTHREADS) {
         const int r = idx / CH, c = idx - r * CH;
@@ -511,7 +519,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
         for (int e = 0; e < EPC; ++e) o4[e] = (T)best[e];
         *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Ps) + (size_t)mm * LDX * sizeof(T) + c * 16) = packed;
       }
-      kv.run(Xs, LDX, RT, p.b_kv, [&](int o0, int r, f32x4 (&acc)[NT_KV], bool) {
+      kv.run(Xs, LDX, RT, p.b_kv, [&](int o0, int r, f32x4 (&acc)[NT_KV]) {
         const int row = 16 * r + (lane & 15);
 #pragma unroll
         for (int nt = 0; nt < NT_KV; ++nt) {
@@ -523,7 +531,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
       qp.prefetch();
       lds_barrier();
       // Q of the pooled rows of this pass (the rows of earlier passes hold their results already)
-      qp.run(Ps, LDX, kRegs / 16, p.b_q, [&](int o0, int r, f32x4 (&acc)[NT_C], bool) {
+      qp.run(Ps, LDX, kRegs / 16, p.b_q, [&](int o0, int r, f32x4 (&acc)[NT_C]) {
         const int row = 16 * r + (lane & 15);
         if (row >= ma && row < mb) {
 #pragma unroll

@@ -4,9 +4,9 @@ library (csrc/phase_clock.h; the product library carries none of it).
     python -m paper_2301_06051_amd.phase_clocks --build      # here or on the GPU machine: compiles _build/libdsvt_phase.so
     python -m paper_2301_06051_amd.phase_clocks [--config 2]  # on the GPU: one block on the config's frame, a table
 
-Thread 0 of every workgroup notes the clock at the phase boundaries (all behind workgroup barriers); the table gives
-the mean over the workgroups of the last layer launch, and the same for the tiles of the first and the second half
-of the launch order (tiles are launched longest first)."""
+Thread 0 of every workgroup notes the clock at the phase boundaries of its tiles (all but the last behind workgroup
+barriers); the table gives the mean over the tiles of the last layer launch, and the same for the first and the second
+half of them (tiles are listed longest first; a workgroup's second tile finds its rows and tables fetched)."""
 import argparse
 import ctypes as C
 import os
@@ -16,7 +16,7 @@ from . import build as _build
 
 PHASE_LIB = _build.PHASE_LIB
 PHASES = ["descriptor -> rows known", "gather -> rows in LDS", "Q, K, V projection", "attention", "out projection + LN",
-          "MLP first matrix + GELU", "MLP second matrix + LN", "scatter"]
+          "MLP first matrix + GELU", "MLP second matrix", "LN, rows out, next rows in"]
 
 
 def main():
@@ -59,7 +59,7 @@ def main():
     nt = min(int(pair[0].n_tiles.item()), blocks.value)
     d = np.diff(t[:nt, :9], axis=1)                   # [tile][phase] clocks
     rows = pair[1].tile_desc.view(-1, 256)[:nt, 0].cpu().numpy()
-    print(f"config {args.config}: {len(coords)} voxels, {nt} tiles, {rows.mean():.1f} rows per tile; last layer launch of a block; shader clocks, thread 0 of each workgroup")
+    print(f"config {args.config}: {len(coords)} voxels, {nt} tiles, {rows.mean():.1f} rows per tile; last layer launch of a block; shader clocks, thread 0 of each tile's workgroup")
     print("| phase | all tiles | first half of the launch order | second half |")
     print("|---|---|---|---|")
     h = nt // 2

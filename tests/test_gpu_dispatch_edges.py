@@ -108,6 +108,37 @@ def test_block_around_the_slim_kernel(tau, n, dup_mode):
         assert rel_err(y, ref) < TOL["bf16"], tiles
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("tau,dup_mode", [(96, 0), (72, 1), (36, 0), (36, 1)])
+def test_workgroups_that_take_several_tiles(C, heads, hidden, dtype, tau, dup_mode):
+    """Frames of one tile per workgroup, of one more, of two, of two and one, and so on: a workgroup's next tile is fetched during the one
+    before, its rows over that one's queries.  The windows are five patterns in turn, so five windows' oracle gives every row."""
+    win, sizes = (12, 12, 1), [min(s, 144) for s in (tau, tau - 1, tau // 2 + 1, tau - 3, tau // 2 + 2)]
+    rng = np.random.Generator(np.random.Philox(31))
+    cells = [rng.permutation(144)[:s] for s in sizes]
+    place = lambda w, cell: np.stack([0 * cell, 12 * (w // 50) + cell // 12, 12 * (w % 50) + cell % 12, 0 * cell], 1).astype(np.int32)
+    ws = [synth.make_layer_weights(32 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
+    layers = [dsvt.LayerWeights(w, dup_mode) for w in ws]
+    one = np.concatenate([place(k, c) for k, c in enumerate(cells)])
+    x1 = synth.make_features(34, len(one), C, dtype)
+    ref1 = orc.block(ws, [orc.partition(one, (600, 600, 1), win, (0, 0, 0), tau, a) for a in (0, 1)], one, x1, dup_mode)
+    att1 = orc.set_attention(ws[0], orc.partition(one, (600, 600, 1), win, (0, 0, 0), tau, 0), one, x1, dup_mode)
+    first = np.cumsum([0] + sizes)
+    for n_win in (256, 257, 512, 513, 1025, 1600):
+        coords = np.concatenate([place(w, cells[w % 5]) for w in range(n_win)])
+        rows = np.concatenate([np.arange(first[w % 5], first[w % 5 + 1]) for w in range(n_win)])
+        cd, xd = dev_coords(coords), dev_feats(x1[rows], dtype)
+        maps = [gpu_maps(cd, (600, 600, 1), win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
+        print(f"[case] {n_win} windows, {int(maps[0].n_tiles.item())} tiles, C={C} {dtype} tau={tau} dup={dup_mode}", flush=True)
+        y = dsvt.dsvt_block(layers, maps, cd, xd)
+        z = dsvt.dsvt_set_attention(layers[0], maps[0], cd, xd)
+        torch.cuda.synchronize()
+        assert rel_err(y, ref1[rows]) < TOL[dtype] and rel_err(z, att1[rows]) < TOL[dtype]
+        again = dsvt.dsvt_block(layers, maps, cd, xd, x_out=xd)                  # in place: the same bits
+        torch.cuda.synchronize()
+        assert torch.equal(again, y)
+
+
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
 @pytest.mark.parametrize("n_multi,n_single", [(0, 24576), (0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
 def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
