@@ -81,12 +81,20 @@ __device__ __forceinline__ int half_wave_scan(int v) {
   return v;
 }
 
+// v into [0, hi], one instruction (hi is not below 0, which the compiler does not know).
+__device__ __forceinline__ int clamp_to(int v, int hi) {
+  int r;
+  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "s"(hi));
+  return r;
+}
+
 struct LayerDev {
   const void *w_qkv, *w_o, *w_1, *w_2;       // packed (see mma.h)
   const float *b_qkv, *b_o, *b_1, *b_2, *ln1_g, *ln1_b, *ln2_g, *ln2_b, *rel_bias;
   const float2* gelu_tab;                    // kGeluKnots (slope, intercept) pairs, see k_pack_gelu_table
   float ln_eps;
-  int rel_size, rel_const, rel_my, rel_mz;   // table entries per head; index = lin(q) - lin(k) + rel_const
+  // position table [index][heads], in bytes: index of (q, k) = code(q) - code(k) + rel_const, at most rel_last; rel_none: the row of -inf
+  int rel_const, rel_last, rel_none, rel_my, rel_mz;
   int dup_mode;
 };
 
@@ -109,7 +117,9 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t kVt = (size_t)C * LDV * sizeof(T);
   static constexpr size_t off_misc = off_v + kVt;
   static constexpr size_t kRowTab = (size_t)(3 * kRowsPad + kHdrWords) * 4;       // rows' voxels, position codes, counts; header
-  static constexpr size_t kMisc = 2 * kRowTab + (size_t)(kSetWords + 1) * 4;      // of this tile and of the next one; set table
+  // of this tile and of the next one; 16 zero bytes, a place for results nobody needs (see attn_item), set table
+  static constexpr size_t off_zero = off_misc + 2 * kRowTab, off_spare = off_zero + 16, kSpare = (size_t)C / 2 * sizeof(T) + 16 * sizeof(T);
+  static constexpr size_t off_sets = off_spare + kSpare, kMisc = off_sets + (size_t)(kSetWords + 1) * 4 - off_misc;
   // after attention the V^T region holds the GELU table, the two LayerNorms' scales and shifts, and the LayerNorm statistics
   static constexpr size_t off_gelu = off_v, off_aff = off_v + 4096, off_stat = off_aff + (size_t)4 * C * 4, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
   static_assert(off_stat + kStat <= off_misc, "GELU table and LayerNorm statistics must fit in the V^T region");
@@ -130,36 +140,46 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
 // initial accumulator value, so the logits come out of the matrix cores finished.  The keys past
 // the set's last voxel take the table's extra last row, which holds -inf: no mask arithmetic.
 // DUP: repeated slots count as keys (the exponentials are multiplied by the slots' counts).
+// One basic block: lanes past the head width read their queries from 16 zero bytes, and queries that do not exist are written
+// to a spare place, so that nothing stands between the heads and their instructions mix.  Everything a head adds to an
+// address is a constant, i.e. an offset in the instruction.  (Before, with a branch around every such read and write and the
+// addresses computed head by head: 450 instructions an item of two key tiles and four heads, 370 now.  Pass of the
+// 30,000-pillar frame 359.1 -> 354.2 us, windows of 12 and 24 cells 507.6 -> 502.7, four frames 1,078 -> 1,065, 120,000 voxels 653.1
+// -> 648.6, skewed batch 7,383 -> 7,318; 30 x 30 windows, sets of four to six key tiles, 290.0 -> 290.9.)  Tried: the first item's
+// positional terms requested in front of the output projection's weights, behind which they come back -- 48 more registers across
+// the barrier, spills, and with those weights requested behind the attention instead no gain.
 template <typename T, int C, int HEADS, int HID, int KTC, int HG, bool DUP>
-__device__ __forceinline__ void attn_item(const LayerDev& p, T* Qs, const T* Ks, const T* Vt, const int32_t* row_lin,
+__device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem, int q_off, const int32_t* row_code,
                                           const float* row_mult, int r0, int nu, int qt, int hh, int rows_ready) {
   typedef LayerLds<T, C, HEADS, HID> L;
   typedef Mma<T> M;
   typedef typename M::Frag Frag;
   typedef typename M::Vec4 Vec4;
-  constexpr int D = L::D, LDX = L::LDX, LDV = L::LDV, KC = M::KC, KL = M::KL;
+  constexpr int D = L::D, KC = M::KC, KL = M::KL, ES = (int)sizeof(T);
+  constexpr int PX = L::LDX * ES, PV = L::LDV * ES;                // row pitches in bytes
   constexpr int TPC = KC / 16;                    // key tiles per PV fragment: 2 (bf16) or 1 (fp32)
   constexpr int NCH = (KTC + TPC - 1) / TPC;
   static_assert(HG == 1 || HG == 2 || HG == 4, "heads per item");
+  static_assert(D <= KC, "one fragment per query");
   const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
   const int qi = 16 * qt + m;
   const int qrow = r0 + (qi < nu ? qi : nu - 1);
+  const int h0 = hh * HG * D * ES;                // this item's heads in a row
 
   f32x4 bias[HG][KTC];
-  f32x4 mult[KTC];
   {
-    const int ql = row_lin[qrow] + p.rel_const;
+    const int qc = row_code[qrow] + p.rel_const;
+    const int left = nu - (16 * (KTC - 1) + 4 * g);                // keys of the last tile from this lane's first on
+    const char* tab = reinterpret_cast<const char*>(p.rel_bias) + hh * HG * 4;
 #pragma unroll
     for (int kt = 0; kt < KTC; ++kt) {
-      const int4 kl = *reinterpret_cast<const int4*>(row_lin + r0 + 16 * kt + 4 * g);
+      const int4 kl = *reinterpret_cast<const int4*>(row_code + r0 + 16 * kt + 4 * g);
       const int kls[4] = {kl.x, kl.y, kl.z, kl.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        int idx = ql - kls[i];
-        idx = idx < 0 ? 0 : (idx >= p.rel_size ? p.rel_size - 1 : idx);
-        if (kt == KTC - 1) idx = 16 * kt + 4 * g + i < nu ? idx : p.rel_size;   // only the last key tile is ragged
-        const float* tp = reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.rel_bias) +
-                                                         (unsigned)idx * (unsigned)(HEADS * 4) + (unsigned)(hh * HG * 4));
+        int at = clamp_to(qc - kls[i], p.rel_last);
+        if (kt == KTC - 1) at = i < left ? at : p.rel_none;        // only the last key tile is ragged
+        const float* tp = reinterpret_cast<const float*>(tab + (unsigned)at);
         if constexpr (HG == 4) {
           const f32x4 t = *reinterpret_cast<const f32x4*>(tp);
           bias[0][kt][i] = t[0]; bias[1][kt][i] = t[1]; bias[2][kt][i] = t[2]; bias[3][kt][i] = t[3];
@@ -172,101 +192,104 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, T* Qs, const T* Ks,
       }
     }
   }
-  if constexpr (DUP) {
+  const bool live = g * KL < D;                   // lanes past the head width
+  int q_at = live ? q_off + qrow * PX + h0 + g * KL * ES : (int)L::off_zero;
+  const int q_step = live ? D * ES : 0;
+  int k_at[KTC];
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt) mult[kt] = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * kt + 4 * g);
+  for (int kt = 0; kt < KTC; ++kt) {              // (dead k lanes: finite K times the zero Q)
+    const int ki = 16 * kt + m;
+    k_at[kt] = (int)L::off_k + (r0 + (ki < nu ? ki : nu - 1)) * PX + h0 + (live ? g * KL * ES : 0);
   }
+  // Key columns past the tile's rows hold no V: their P is an exact zero, so any finite column will do, and the set's first
+  // one is read instead.  (Rows past the head width: the tile's row of a lane below it; results thrown away.)
+  constexpr int DT = (D + 15) / 16;
+  int v_at[DT][NCH * TPC];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int c = 0; c < NCH * TPC; ++c) {
+      const int col = r0 + 16 * c + 4 * g, dv = 16 * dt + m;
+      v_at[dt][c] = (int)L::off_v + hh * HG * D * PV + (dv < D ? dv : m) * PV + (col < rows_ready ? col : r0) * ES;
+    }
+  int o_at[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+    o_at[dt] = qi < nu && 16 * dt + 4 * g < D ? q_off + qrow * PX + h0 + (16 * dt + 4 * g) * ES : (int)L::off_spare;
 
 #pragma unroll
   for (int hl = 0; hl < HG; ++hl) {
-    const int h = hh * HG + hl;
     f32x4 S[KTC];                                 // S[kt][i]: key 16*kt + 4*g + i, query 16*qt + m
+    const Frag fq = *reinterpret_cast<const Frag*>(smem + q_at);
+    q_at += q_step;
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt) S[kt] = bias[hl][kt];
-#pragma unroll
-    for (int kc = 0; kc < D; kc += KC) {
-      const int kk = kc + g * KL;
-      const bool live = kk < D;                   // lanes past the head width feed zeros
-      const int kkc = live ? kk : 0;
-      Frag fb = *reinterpret_cast<const Frag*>(Qs + qrow * LDX + h * D + kkc);
-      fb = live ? fb : M::zero();
-#pragma unroll
-      for (int kt = 0; kt < KTC; ++kt) {
-        const int ki = 16 * kt + m;
-        const Frag fa = *reinterpret_cast<const Frag*>(Ks + (r0 + (ki < nu ? ki : nu - 1)) * LDX + h * D + kkc);
-        S[kt] = M::mma(fa, fb, S[kt]);                  // dead k lanes: finite K times the zeroed Q
-      }
-    }
+    for (int kt = 0; kt < KTC; ++kt) S[kt] = M::mma(*reinterpret_cast<const Frag*>(smem + k_at[kt] + hl * D * ES), fq, bias[hl][kt]);
     // S holds the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
+    // (fmaxf and not raw_max: an asm statement that reads a matrix instruction's result would not be given the wait it needs)
     float mx = S[0][0];
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (kt + i > 0) mx = fmaxf(mx, S[kt][i]);
+    for (int k = 1; k < 4 * KTC; ++k) mx = fmaxf(mx, S[k >> 2][k & 3]);
     mx = col_max(mx);                             // (key 0 exists for every query: finite)
     float sum = 0.f;
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt)
+    for (int kt = 0; kt < KTC; ++kt) {
+      f32x4 mult;
+      if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * kt + 4 * g);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float e = __builtin_amdgcn_exp2f(S[kt][i] - mx);       // exp2(-inf) = 0
-        if constexpr (DUP) e *= mult[kt][i];
+        if constexpr (DUP) e *= mult[i];
         S[kt][i] = e;
-        sum += e;
+        sum = kt + i == 0 ? e : sum + e;
       }
+    }
     sum = col_sum(sum);
     const float inv = __builtin_amdgcn_rcpf(sum);
 
-    // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q].  Key columns past the tile's rows hold no V: their P is an
-    // exact zero, so any finite column will do, and the set's first one is read instead.
+    // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q]
+    Frag fp[NCH];
 #pragma unroll
-    for (int dt = 0; dt < (D + 15) / 16; ++dt) {
+    for (int c = 0; c < NCH; ++c) {
+      if constexpr (TPC == 2) {
+        const f32x4 p0 = S[2 * c], p1 = 2 * c + 1 < KTC ? S[2 * c + 1 < KTC ? 2 * c + 1 : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
+        fp[c] = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
+      } else {
+        fp[c] = S[c];
+      }
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
       f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
-      const int dv = 16 * dt + m;
-      const T* vrow = Vt + (h * D + (dv < D ? dv : 0)) * LDV;      // (rows past the head width: results thrown away)
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
-        Frag fa, fb;
+        Frag fv;
         if constexpr (TPC == 2) {
-          const int c0 = r0 + 32 * c + 4 * g, c1 = c0 + 16;
-          const bf16x4 lo = *reinterpret_cast<const bf16x4*>(vrow + (c0 < rows_ready ? c0 : r0));
-          const f32x4 p0 = S[2 * c];
-          if (2 * c + 1 < KTC) {
-            const bf16x4 hi = *reinterpret_cast<const bf16x4*>(vrow + (c1 < rows_ready ? c1 : r0));
-            const f32x4 p1 = S[2 * c + 1 < KTC ? 2 * c + 1 : 0];
-            fa = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            fb = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3],
-                      (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
-          } else {
-            fa = Frag{lo[0], lo[1], lo[2], lo[3], 0, 0, 0, 0};
-            fb = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], 0, 0, 0, 0};
-          }
+          const bf16x4 lo = *reinterpret_cast<const bf16x4*>(smem + v_at[dt][2 * c] + hl * D * PV);
+          bf16x4 hi = {0, 0, 0, 0};
+          if (2 * c + 1 < KTC) hi = *reinterpret_cast<const bf16x4*>(smem + v_at[dt][2 * c + 1] + hl * D * PV);
+          fv = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         } else {
-          const int c0 = r0 + 16 * c + 4 * g;
-          fa = *reinterpret_cast<const Frag*>(vrow + (c0 < rows_ready ? c0 : r0));
-          fb = S[c];
+          fv = *reinterpret_cast<const Frag*>(smem + v_at[dt][c] + hl * D * PV);
         }
-        O = M::mma(fa, fb, O);
+        O = M::mma(fv, fp[c], O);
       }
-      if (qi < nu && 16 * dt + 4 * g < D)
-        *reinterpret_cast<Vec4*>(Qs + (r0 + qi) * LDX + h * D + 16 * dt + 4 * g) = pack4<T>(O * inv);
+      *reinterpret_cast<Vec4*>(smem + o_at[dt] + hl * D * ES) = pack4<T>(O * inv);
     }
   }
 }
 
 // An item of a set with kts key tiles: up to three key tiles half of the heads per item, beyond that big_heads().
 template <typename T, int C, int HEADS, int HID, SetSize SETS, bool DUP>
-__device__ __forceinline__ void attn_any(const LayerDev& p, T* Qs, const T* Ks, const T* Vt, const int32_t* row_lin,
+__device__ __forceinline__ void attn_any(const LayerDev& p, unsigned char* smem, int q_off, const int32_t* row_code,
                                          const float* row_mult, int r0, int nu, int qt, int hh, int kts, int rows_ready) {
   constexpr int HG2 = HEADS / 2, HGB = big_heads(C, DUP, SETS);
-  if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-  else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-  else if (SETS == kSets48 || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+  if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+  else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+  else if (SETS == kSets48 || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
   else if constexpr (SETS != kSets48) {
-    if (kts == 4) attn_item<T, C, HEADS, HID, 4, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-    else if (kts == 5) attn_item<T, C, HEADS, HID, 5, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
-    else attn_item<T, C, HEADS, HID, 6, HGB, DUP>(p, Qs, Ks, Vt, row_lin, row_mult, r0, nu, qt, hh, rows_ready);
+    if (kts == 4) attn_item<T, C, HEADS, HID, 4, HGB, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+    else if (kts == 5) attn_item<T, C, HEADS, HID, 5, HGB, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+    else attn_item<T, C, HEADS, HID, 6, HGB, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
   }
 }
 
@@ -300,7 +323,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
   float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // over V^T once attention is done
-  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_misc + 2 * L::kRowTab);   // [kSetWords + 1]: set_word() of every set, number of items
+  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_sets);   // [kSetWords + 1]: set_word() of every set, number of items
 
   // wave-uniform values are read back through readfirstlane so that the compiler keeps them in
   // scalar registers: branches on them are scalar branches, not exec-mask divergence
@@ -335,7 +358,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 
   // the row tables of a tile from its descriptor, a word per thread of the first four wavefronts
   const auto row_vox = [&](int t) { return reinterpret_cast<int32_t*>(smem + L::off_misc + t); };
-  const auto row_lin = [&](int t) { return row_vox(t) + kRowsPad; };
+  const auto row_code = [&](int t) { return row_vox(t) + kRowsPad; };
   const auto row_mult = [&](int t) { return reinterpret_cast<float*>(row_vox(t) + 2 * kRowsPad); };
   const auto header = [&](int t) { return row_vox(t) + 3 * kRowsPad; };
   const auto store_desc = [&](int word, int t) {
@@ -346,7 +369,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       if ((tid & 1) == 0) {
         row_vox(t)[r] = (word >= 0 && word < mp.n_voxels) ? word : -1;
       } else {
-        row_lin(t)[r] = word & 0xFFFFFF;
+        row_code(t)[r] = (word & 0xFFFFFF) * (HEADS * 4);
         if constexpr (DUP) row_mult(t)[r] = (float)((unsigned)word >> 24);
       }
     }
@@ -431,8 +454,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   if (tile >= n_tiles) return;
   QkvPhase first(reinterpret_cast<const T*>(p.w_qkv), wave);
   first.template prefetch_first<kEarly>();
+  if (tid < 4) reinterpret_cast<unsigned*>(smem + L::off_zero)[tid] = 0u;
   for (int r = kRowsMax + tid; r < kRowsPad; r += NTHREADS)
-    for (int t = 0; t <= (int)L::kRowTab; t += (int)L::kRowTab) { row_vox(t)[r] = -1; row_lin(t)[r] = 0; row_mult(t)[r] = 0.f; }
+    for (int t = 0; t <= (int)L::kRowTab; t += (int)L::kRowTab) { row_vox(t)[r] = -1; row_code(t)[r] = 0; row_mult(t)[r] = 0.f; }
 
   if (listed) {
     // ---- 1a. rows from the tile descriptor the partition wrote for this tile (1 KB, one load)
@@ -441,7 +465,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // ---- 1b. no work list: two sets per tile, rows derived from set_inds and coords
     const int tau = mp.tau, s_begin = tile * per_wg, ns = n_sets - s_begin < per_wg ? n_sets - s_begin : per_wg;
     int32_t* hdr = header(tab);
-    for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox(tab)[r] = -1; row_lin(tab)[r] = 0; row_mult(tab)[r] = 0.f; }
+    for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox(tab)[r] = -1; row_code(tab)[r] = 0; row_mult(tab)[r] = 0.f; }
     for (int ls = wave; ls < ns; ls += NW) {
       const int v = lane < tau ? mp.set_inds[(size_t)(s_begin + ls) * tau + lane] : -2;
       const int prev = __shfl_up(v, 1, 64);
@@ -469,7 +493,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         const int4 c = coords[v];
         row_vox(tab)[r] = v;
         row_mult(tab)[r] = (float)run;
-        row_lin(tab)[r] = (c.y * p.rel_my + c.z) * p.rel_mz + c.w;
+        row_code(tab)[r] = ((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (HEADS * 4);
       }
     }
   }
@@ -539,7 +563,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         const int r0 = sw & 255, nu = (sw >> 8) & 255, kts = (nu + 15) >> 4, k = it - (int)(sw >> 16);
         const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS));      // (a power of two)
         const int qt = k >> __builtin_ctz(ngr), hh = k & (ngr - 1);
-        attn_any<T, C, HEADS, HID, SETS, DUP>(p, Qs, Ks, Vt, row_lin(tab), row_mult(tab), r0, nu, qt, hh, kts, RT * 16);
+        attn_any<T, C, HEADS, HID, SETS, DUP>(p, smem, 2 * (int)L::kTile - xo, row_code(tab), row_mult(tab), r0, nu, qt, hh, kts, RT * 16);
       }
     }
     // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
@@ -730,8 +754,9 @@ LayerDev to_dev(const dsvt_layer_w& w) {
   d.ln_eps = w.ln_eps; d.dup_mode = w.dup_mode;
   const int my = 2 * w.win[1] - 1, mz = 2 * w.win[2] - 1;
   d.rel_my = my; d.rel_mz = mz;
-  d.rel_size = pl.rel_size;
-  d.rel_const = w.rel_bias != nullptr ? ((w.win[0] - 1) * my + (w.win[1] - 1)) * mz + (w.win[2] - 1) : 0;
+  d.rel_last = (pl.rel_size - 1) * w.heads * 4;
+  d.rel_none = pl.rel_size * w.heads * 4;
+  d.rel_const = w.rel_bias != nullptr ? (((w.win[0] - 1) * my + (w.win[1] - 1)) * mz + (w.win[2] - 1)) * w.heads * 4 : 0;
   return d;
 }
 
