@@ -202,10 +202,15 @@ __device__ __forceinline__ void fill_tile_starts(const int32_t* P, uint16_t* jum
   int32_t* piece_first = reinterpret_cast<int32_t*>((reinterpret_cast<uintptr_t>(jump2) + 3) & ~(uintptr_t)3);
   if (tid == 0) n_pieces = 0;
   lds_barrier();
-  constexpr int32_t kB = 8;                                  // sets a thread works on side by side: their LDS reads overlap
-  for (int32_t base = 0; base <= n_sets; base += 1024 * kB) {
+  // (Two sets a thread side by side, and no wavefront without a set goes along: the search is bound by instruction issue on this
+  // one compute unit, and with eight sets a thread and seven halvings it took 6 us whatever the number of sets.  The fills of
+  // k_front, two such searches each: windows of 24 cells 13.4 -> 7.8 us, 30 x 30 windows 13.0 -> 6.7.  Strides of eight jumps by
+  // pointer doubling for the walk below: 1.6 us less with 318 sets, 5 us more with 6,500.)
+  constexpr int32_t kB = 2;
+  static_assert(kTileRows / 4 + 2 <= 32, "five halvings");
+  for (int32_t base = 0; base + (tid & ~63) <= n_sets; base += 1024 * kB) {
     // smallest t in (s, n_sets] with P[t + 1] - P[s] > cap (n_sets = none).  A set has at least 4 rows, so t is at most
-    // s + cap / 4 + 1: five or six halvings, taken in step for the kB sets.  (A set longer than cap gets a tile of its own.)
+    // s + cap / 4 + 1: five halvings, taken in step for the kB sets.  (A set longer than cap gets a tile of its own.)
     int32_t lo[kB], hi[kB], lim[kB];
 #pragma unroll
     for (int32_t k = 0; k < kB; ++k) {
@@ -217,7 +222,7 @@ __device__ __forceinline__ void fill_tile_starts(const int32_t* P, uint16_t* jum
       if (s < n_sets && (s == 0 || (P[s] >> kFillPieceShift) != (P[s - 1] >> kFillPieceShift)))
         piece_first[atomicAdd(&n_pieces, 1)] = s;
     }
-    for (int32_t step = 0; step < 7; ++step) {               // 2^7 > 96 / 4 + 2
+    for (int32_t step = 0; step < 5; ++step) {
       int32_t mid[kB], pv[kB];                               // (no branches: the kB reads of a step go out together)
 #pragma unroll
       for (int32_t k = 0; k < kB; ++k) { mid[k] = (lo[k] + hi[k]) >> 1; pv[k] = P[min(mid[k] + 1, n_sets)]; }
@@ -294,9 +299,9 @@ __device__ __forceinline__ bool fill_tiles(const int32_t* P, uint16_t* jump, uin
     if (threadIdx.x == 0) n_starts = 0;
     fill_tile_starts(P, jump, jump2, mark, n_sets, cap);      // (barriers inside: n_starts is zero for everybody after)
     if (rounds > kTunedRounds) return true;
-    int32_t mine = 0;
-    for (int32_t s = threadIdx.x; s < n_sets; s += 1024) mine += mark[s];
-    if (mine) atomicAdd(&n_starts, mine);
+    int32_t mine = 0;                                        // (counted by wavefronts: 1,024 additions to one LDS word queue up)
+    for (int32_t s = threadIdx.x; s - (int32_t)(threadIdx.x & 63) < n_sets; s += 1024) mine += __popcll(__ballot(s < n_sets && mark[s] != 0));
+    if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&n_starts, mine);
     lds_barrier();
     const int32_t tiles = n_starts;
     lds_barrier();
@@ -994,7 +999,8 @@ __global__ void __launch_bounds__(1024) k_front(Jobs jobs) {
     // that is when (rows before set s - 1) mod rows_per_cut plus the rows of set s - 1 reach rows_per_cut.
     const int32_t prev_rows0 = prev >= 0 ? (prev & 127) : 0;
     const uint32_t d0 = (uint32_t)(P0 - prev_rows0);          // rows before the previous set
-    const int32_t m0 = (int32_t)(d0 % (uint32_t)rows_per_cut);
+    const int32_t m0 = filled ? 0 : (int32_t)(d0 % (uint32_t)rows_per_cut);
+    const float rcp_cut = __frcp_rn((float)rows_per_cut);
     auto for_each_set = [&](auto&& fn) {
       int32_t P = P0, pr = prev_rows0, m = m0;
       walk.restart();
@@ -1003,25 +1009,40 @@ __global__ void __launch_bounds__(1024) k_front(Jobs jobs) {
         if (s == set_cap) p_cap = P;
         if (s >= set_cap) break;
         const bool first = filled ? mark[s] != 0 : (s == 0 || m + pr >= rows_per_cut);
-        m += pr;
-        while (m >= rows_per_cut) m -= rows_per_cut;
+        if (!filled) {                                        // (below 2^8, where (m + 0.5) / cut in float truncates to the quotient)
+          m += pr;
+          m -= rows_per_cut * (int32_t)(((float)m + 0.5f) * rcp_cut);
+        }
         fn(s, P, first);
         pr = set_rows(walk.next());
         P += pr;
       }
     };
-    int32_t F = 0;
-    for_each_set([&](int32_t, int32_t, bool first) { F += first ? 1 : 0; });
+    // (A window's first two tile starts are kept from the walk that counts them; few windows have more, and walk again.  With
+    // the remainders by multiplication, and none where the tiles are filled: 4.4 -> 3.4 us for 1,600 windows of up to four sets,
+    // 6.9 -> 3.6 for 169 of up to ten, where cuts 8 rows apart made a loop of eleven subtractions a set.)
+    int32_t F = 0, s0 = 0, s1 = 0, p0 = 0, p1 = 0;
+    for_each_set([&](int32_t s, int32_t P, bool first) {
+      if (!first) return;
+      if (F == 0) { s0 = s; p0 = P; } else { s1 = s; p1 = P; }
+      ++F;
+    });
     const int32_t f_incl = block_scan1(F, wave_tot[0], carry2);
     if (w < nw) {
       int32_t t = f_incl - F;                                 // tiles started before this window
       wT0[w] = t;
-      for_each_set([&](int32_t s, int32_t P, bool first) {
+      const auto starts = [&](int32_t s, int32_t P, bool first) {
         if (!first) return;
         if (t < tile_lim) { tFirst[t] = s; tRows[t] = P; out.tile_first[t] = s; }
         else if (t == tile_lim) { over_s = s; over_p = P; }        // first set that no tile is left for
         ++t;
-      });
+      };
+      if (F <= 2) {
+        starts(s0, p0, F > 0);
+        starts(s1, p1, F > 1);
+      } else {
+        for_each_set(starts);
+      }
     }
   }
   lds_barrier();
