@@ -36,6 +36,13 @@ enum SetSize { kSets48, kSets96, kSets96Slim };
 // tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
 __host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
+// A tile whose items leave half of the wavefronts without one -- a set or two: sparse frames -- gets items of a quarter of
+// the heads (sets of up to three key tiles; beyond, there are 16 items and more): an item's heads are one dependent chain
+// after the other, 4.4 k of the 35 k clocks of a 24-row tile.  Pass of
+// 3,001 pillars 159.5 -> 157.9 us, one block of 2,000 voxels in fp32 52.1 -> 51.7; the code costs frames of full tiles up to
+// 0.2 %.  (Where more wavefronts have an item, halving them
+// costs the second fetch of the positional terms: 2-3 % of a layer.)
+__device__ __forceinline__ bool split_items(int items, bool large_set, int waves) { return !large_set && 2 * items <= waves; }
 // The attention phase's items -- (set, query tile, group of heads) -- are numbered set by set.  A set's table word: first row
 // (bits 0-7), distinct voxels (8-15) and the number of its first item (from 16 on); words past the last set hold
 // kNoItem, above every item number.  A wavefront holds the table a word per lane and finds the set of an item by counting
@@ -119,7 +126,7 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t kRowTab = (size_t)(3 * kRowsPad + kHdrWords) * 4;       // rows' voxels, position codes, counts; header
   // of this tile and of the next one; 16 zero bytes, a place for results nobody needs (see attn_item), set table
   static constexpr size_t off_zero = off_misc + 2 * kRowTab, off_spare = off_zero + 16, kSpare = (size_t)C / 2 * sizeof(T) + 16 * sizeof(T);
-  static constexpr size_t off_sets = off_spare + kSpare, kMisc = off_sets + (size_t)(kSetWords + 1) * 4 - off_misc;
+  static constexpr size_t off_sets = off_spare + kSpare, kMisc = off_sets + (size_t)(kSetWords + 2) * 4 - off_misc;
   // after attention the V^T region holds the GELU table, the two LayerNorms' scales and shifts, and the LayerNorm statistics
   static constexpr size_t off_gelu = off_v, off_aff = off_v + 4096, off_stat = off_aff + (size_t)4 * C * 4, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
   static_assert(off_stat + kStat <= off_misc, "GELU table and LayerNorm statistics must fit in the V^T region");
@@ -278,12 +285,17 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem
   }
 }
 
-// An item of a set with kts key tiles: up to three key tiles half of the heads per item, beyond that big_heads().
+// An item of a set with kts key tiles: up to three key tiles half of the heads per item (split_items: a quarter), beyond that
+// big_heads().
 template <typename T, int C, int HEADS, int HID, SetSize SETS, bool DUP>
 __device__ __forceinline__ void attn_any(const LayerDev& p, unsigned char* smem, int q_off, const int32_t* row_code,
-                                         const float* row_mult, int r0, int nu, int qt, int hh, int kts, int rows_ready) {
-  constexpr int HG2 = HEADS / 2, HGB = big_heads(C, DUP, SETS);
-  if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+                                         const float* row_mult, int r0, int nu, int qt, int hh, int kts, bool split, int rows_ready) {
+  constexpr int HG2 = HEADS / 2, HG4 = HEADS / 4, HGB = big_heads(C, DUP, SETS);
+  if (split) {
+    if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG4, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+    else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG4, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+    else attn_item<T, C, HEADS, HID, 3, HG4, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
+  } else if (kts == 1) attn_item<T, C, HEADS, HID, 1, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
   else if (kts == 2) attn_item<T, C, HEADS, HID, 2, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
   else if (SETS == kSets48 || kts == 3) attn_item<T, C, HEADS, HID, 3, HG2, DUP>(p, smem, q_off, row_code, row_mult, r0, nu, qt, hh, rows_ready);
   else if constexpr (SETS != kSets48) {
@@ -323,7 +335,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
   float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // over V^T once attention is done
-  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_sets);   // [kSetWords + 1]: set_word() of every set, number of items
+  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_sets);   // [kSetWords + 2]: set_word() of every set, number of items, whether they are split
 
   // wave-uniform values are read back through readfirstlane so that the compiler keeps them in
   // scalar registers: branches on them are scalar branches, not exec-mask divergence
@@ -545,8 +557,10 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       const int nu = nu_w < 1 ? 1 : (nu_w > kNuMax ? kNuMax : nu_w), kts = (nu + 15) >> 4;
       const int cnt = lane < ns ? kts * item_groups(kts, HEADS, big_heads(C, DUP, SETS)) : 0;
       const int incl = half_wave_scan(cnt);
-      if (lane < kSetWords) set_tab[lane] = lane < ns ? set_word(r0 < 0 ? 0 : (r0 > kRowsMax - 4 ? kRowsMax - 4 : r0), nu, incl - cnt) : kNoItem;
-      if (lane == kSetWords - 1) set_tab[kSetWords] = (unsigned)incl;
+      const int split = split_items(__builtin_amdgcn_readlane(incl, kSetWords - 1), __ballot(lane < ns && kts > 3) != 0ull, NW) ? 1 : 0;
+      if (lane < kSetWords)
+        set_tab[lane] = lane < ns ? set_word(r0 < 0 ? 0 : (r0 > kRowsMax - 4 ? kRowsMax - 4 : r0), nu, (incl - cnt) << split) : kNoItem;
+      if (lane == kSetWords - 1) { set_tab[kSetWords] = (unsigned)(incl << split); set_tab[kSetWords + 1] = (unsigned)split; }
     }
     lds_barrier();
     DSVT_REFRESH_LANE();
@@ -555,15 +569,15 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // ---- 4. attention inside every set; O overwrites Q
     {
       const unsigned my_set = set_tab[lane & (kSetWords - 1)];
-      const int n_items = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords]);
+      const int n_items = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords]), split = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords + 1]);
       for (int it = wave; it < n_items; it += NW) {
         // (both halves of the wavefront hold the table; set 0 starts at item 0)
         const int s = __popcll(__ballot((int)(my_set >> 16) <= it) & 0xffffffffull) - 1;
         const unsigned sw = (unsigned)__builtin_amdgcn_readlane((int)my_set, s);
         const int r0 = sw & 255, nu = (sw >> 8) & 255, kts = (nu + 15) >> 4, k = it - (int)(sw >> 16);
-        const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS));      // (a power of two)
+        const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS)) << split;      // (a power of two)
         const int qt = k >> __builtin_ctz(ngr), hh = k & (ngr - 1);
-        attn_any<T, C, HEADS, HID, SETS, DUP>(p, smem, 2 * (int)L::kTile - xo, row_code(tab), row_mult(tab), r0, nu, qt, hh, kts, RT * 16);
+        attn_any<T, C, HEADS, HID, SETS, DUP>(p, smem, 2 * (int)L::kTile - xo, row_code(tab), row_mult(tab), r0, nu, qt, hh, kts, split != 0, RT * 16);
       }
     }
     // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
