@@ -49,7 +49,6 @@ __device__ __forceinline__ bool split_items(int items, bool large_set, int waves
 // the sets that start at or before it.
 constexpr unsigned kNoItem = 0x7fffu << 16;
 __device__ __forceinline__ unsigned set_word(int r0, int nu, int first_item) { return (unsigned)r0 | (unsigned)nu << 8 | (unsigned)first_item << 16; }
-constexpr int kHalfTiles = kRowTiles / 2;        // the LayerNorm-phase work items cover half of the row tiles
 constexpr int kComputeUnits = 256;               // MI355X
 constexpr int kLayerWaves = 12;                  // three per SIMD: one workgroup per CU (LDS), the other wavefronts hide one's waits
 
@@ -341,8 +340,12 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int LDX = L::LDX, LDV = L::LDV, LDH = L::LDH;
   constexpr int NW = kLayerWaves, NTHREADS = NW * 64;
-  constexpr int SG = C / (16 * NT_O);              // LayerNorm phases: SG feature groups x 2 halves of the row tiles, one item per wavefront
-  static_assert(NT_O == NT_2 && SG * 16 * NT_O == C && 2 * SG <= NW && SG <= kStatGroupsMax, "LayerNorm phases: one item per wavefront");
+  // LayerNorm phases: SG feature groups x RS parts of the row tiles (C = 192 six groups and halves, else four and thirds), one
+  // item per wavefront.  (Halves leave a third of the wavefronts of C <= 128 without an item: C = 128, 46,827 pillars
+  // 399.2 -> 384.7 us, 11,491 pillars 155.6 -> 151.1, 30 x 30 windows 282.0 -> 280.8.  The first MLP matrix in the same parts, each
+  // fragment then loaded three times: 395.0, 154.0 and 286.1: it keeps all rows per wavefront.)
+  constexpr int SG = C / (16 * NT_O), RS = NW / SG, kOwnTiles = kRowTiles / RS;
+  static_assert(NT_O == NT_2 && SG * 16 * NT_O == C && RS * SG == NW && RS * kOwnTiles == kRowTiles && SG <= kStatGroupsMax, "LayerNorm phases: one item per wavefront");
   extern __shared__ __align__(16) unsigned char smem[];
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
@@ -544,16 +547,14 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     T* Hs = reinterpret_cast<T*>(smem + (L::kTile - xo / 2));
     const int next = tile + stride;
     const bool more = next < n_tiles;
-    const int RTH = (RT + 1) >> 1;               // the LayerNorm phases: row tiles of the first half
-
-    // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one half of
+    // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one part of
     // the row tiles; the Q/K/V and first MLP projections (bandwidth-heavy) give a wavefront all rows
-    // of its output tiles instead, so that each of their weight fragments is loaded only once.  An odd number of row
-    // tiles gives the second half one less; in a tile of a single one the second half has no rows and requests no
-    // weights (220 KB of the 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
-    const int og_own = wave % SG;
-    const int rt_own = wave < SG ? 0 : RTH, HC = wave < SG ? RTH : (wave < 2 * SG ? RT - RTH : 0);   // HC = 0: a wavefront without an item
-    GemmPhase<T, NT_O, C, C, NW, 2> oproj(reinterpret_cast<const T*>(p.w_o), wave);
+    // of its output tiles instead, so that each of their weight fragments is loaded only once.  The last part may have fewer
+    // row tiles than the others, or none: its wavefronts request no weights (C = 192, a tile of a single row tile: 220 KB of the
+    // 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
+    const int og_own = wave % SG, own_max = (RT + RS - 1) / RS, rt_own = wave / SG * own_max;
+    const int HC = RT - rt_own < 0 ? 0 : (RT - rt_own < own_max ? RT - rt_own : own_max);       // HC = 0: a wavefront without an item
+    GemmPhase<T, NT_O, C, C, NW, RS> oproj(reinterpret_cast<const T*>(p.w_o), wave);
     oproj.forget();
     if (HC > 0) oproj.prefetch();                // in flight during the attention phase
     const int o_own = og_own * 16 * NT_O;
@@ -634,16 +635,16 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     const int pf_turn = full_layer ? wave / (NW / 3) : -1;
     ffn1.forget();
     if (pf_turn == 0) ffn1.prefetch();
-    f32x4 keep[NT_O][kHalfTiles];
+    f32x4 keep[NT_O][kOwnTiles];
     QkvPhase qkv(reinterpret_cast<const T*>(p.w_qkv), wave);     // of the next tile
     if (HC == 1) oproj.template run_keep<1>(Qs, LDX, rt_own, bo4, keep);
     else if (HC == 2) oproj.template run_keep<2>(Qs, LDX, rt_own, bo4, keep);
-    else if (HC == 3) oproj.template run_keep<3>(Qs, LDX, rt_own, bo4, keep);
+    else if (kOwnTiles == 3 && HC == 3) oproj.template run_keep<kOwnTiles>(Qs, LDX, rt_own, bo4, keep);
     else undefined(keep);
     if (pf_turn == 1) ffn1.prefetch();
     if (!full_layer) {                           // attention and its projection only: raw Y goes out, one tile per workgroup
 #pragma unroll
-      for (int r = 0; r < kHalfTiles; ++r)
+      for (int r = 0; r < kOwnTiles; ++r)
         if (r < HC) {
           f32x4 y[NT_O];
 #pragma unroll
@@ -652,9 +653,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         }
       return;
     }
-    add_rows<T, NT_O, kHalfTiles>(keep, Xs, LDX, rt_own, HC, o_own);
+    add_rows<T, NT_O, kOwnTiles>(keep, Xs, LDX, rt_own, HC, o_own);
     if (pf_turn == 2) ffn1.prefetch();
-    layer_norm_tile<T, NT_O, C, kHalfTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
+    layer_norm_tile<T, NT_O, C, kOwnTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       a = *reinterpret_cast<const f32x4*>(affine_lds + o_own + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
     }, p.ln_eps, [&](int row, const f32x4 (&y)[NT_O]) {
@@ -674,7 +675,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // 120,000-voxel frame 707 / 699.  Slower than this at C = 192, each in one session with it: the matrix in three slices, two of
     // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
     // bias requested in front of the weights 0.1-0.7 %.
-    GemmPhase<T, NT_2, HID, C, NW, 2, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
+    GemmPhase<T, NT_2, HID, C, NW, RS, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
     const float gelu0 = gelu_start(smem + L::off_gelu);
     ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
 #pragma unroll
@@ -705,16 +706,16 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     lds_barrier();
     DSVT_REFRESH_LANE();
     DSVT_PHASE(tile, 6);                             // H in LDS
-    f32x4 keep2[NT_2][kHalfTiles];
+    f32x4 keep2[NT_2][kOwnTiles];
     if (HC == 1) ffn2.template run_keep<1>(Hs, LDH, rt_own, b24, keep2);
     else if (HC == 2) ffn2.template run_keep<2>(Hs, LDH, rt_own, b24, keep2);
-    else if (HC == 3) ffn2.template run_keep<3>(Hs, LDH, rt_own, b24, keep2);
+    else if (kOwnTiles == 3 && HC == 3) ffn2.template run_keep<kOwnTiles>(Hs, LDH, rt_own, b24, keep2);
     else undefined(keep2);
     qkv.forget();
     if (more && pf_turn == 0) qkv.template prefetch_first<kEarly>();
-    add_rows<T, NT_2, kHalfTiles>(keep2, Xs, LDX, rt_own, HC, o_own2);
+    add_rows<T, NT_2, kOwnTiles>(keep2, Xs, LDX, rt_own, HC, o_own2);
     if (more && pf_turn == 1) qkv.template prefetch_first<kEarly>();
-    layer_norm_tile<T, NT_2, C, kHalfTiles>(keep2, o_own2, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
+    layer_norm_tile<T, NT_2, C, kOwnTiles>(keep2, o_own2, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       if (nt == 0) DSVT_PHASE(tile, 7);          // everybody's part of the second product done
       if (nt == 0 && more) {
         store_rows(gv, live, 2 * (int)L::kTile - xo, next_RT);

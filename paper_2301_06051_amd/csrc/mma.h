@@ -174,7 +174,7 @@ struct GemmPhase {
   static constexpr int N_ITEMS = RSPLIT * N_OG;
   static constexpr int IPW = (N_ITEMS + NW - 1) / NW;   // items per wavefront (the last round may be partial)
   static constexpr int RH = kRowTiles / RSPLIT;          // row tiles an item can cover
-  static_assert(K % KC == 0 && NOUT % (16 * NT) == 0 && (RSPLIT == 1 || RSPLIT == 2), "phase shape");
+  static_assert(K % KC == 0 && NOUT % (16 * NT) == 0 && kRowTiles % RSPLIT == 0, "phase shape");
   AFull<T, NT, NKF> a[(IPW > 1 && DOUBLE_A) ? 2 : 1];   // DOUBLE_A: the next item's weights load during the current item
   const T* Wp;
   int wave;
