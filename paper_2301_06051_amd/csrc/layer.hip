@@ -368,18 +368,23 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   // 30,000 pillars: bf16 28.1 us without, 28.2 with, 2,000 pillars 16.1 and 15.9; fp32 78.9 and 78.0.
   constexpr int kEarly = NT_QKV < 2 ? NT_QKV : 2;
 
+  // The arguments (four cache lines) in one go, then the number of tiles and the first tile's descriptor together: three waits less in a
+  // row.  Passes: pillar frame 348.8 -> 347.8 us, hybrid windows 490.1 -> 488.2, 4,137 pillars 74.4 -> 73.6.
+  int tile = blockIdx.x;
+  asm("" : "+s"(tile) : "s"(p.w_qkv), "s"(p.gelu_tab), "s"(mp.tile_desc), "s"(mp.n_tiles), "s"(mp.max_tiles), "s"(mp.tau), "s"(x));
   const bool listed = mp.tile_desc != nullptr;
   const int per_wg = fixed_sets(mp.tau);         // without a work list a tile is two sets
-  int n_tiles, n_sets = 0;
+  int n_tiles, n_sets = 0, word = 0;
   if (listed) {
     n_tiles = *mp.n_tiles;
+    if (tid < 256) word = mp.tile_desc[(size_t)tile * 256 + tid];
     n_tiles = n_tiles < mp.max_tiles ? n_tiles : mp.max_tiles;
   } else {
     n_sets = *mp.n_sets;
     n_sets = n_sets < mp.max_sets ? n_sets : mp.max_sets;
     n_tiles = (n_sets + per_wg - 1) / per_wg;
   }
-  int tile = blockIdx.x, stride = 2 * (int)(gridDim.x - blockIdx.x) - 1;
+  int stride = 2 * (int)(gridDim.x - blockIdx.x) - 1;
   int xo = 0, tab = 0;                           // byte offsets of X (Q: the other side of K) and of this tile's row tables
   DSVT_PHASE(tile, 0);
 
@@ -476,8 +481,6 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     }
   };
 
-  int word = 0;
-  if (listed && tid < 256) word = mp.tile_desc[(size_t)tile * 256 + tid];
   if (tile >= n_tiles) return;
   QkvPhase first(reinterpret_cast<const T*>(p.w_qkv), wave);
   first.template prefetch_first<kEarly>();
