@@ -37,8 +37,8 @@ enum SetSize { kSets48, kSets96, kSets96Slim };
 __host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
 // A tile whose items leave half of the wavefronts without one -- a set or two: sparse frames -- gets items of a quarter of
-// the heads (sets of up to three key tiles; beyond, there are 16 items and more): an item's heads are one dependent chain
-// after the other, 4.4 k of the 35 k clocks of a 24-row tile.  Pass of
+// the heads (sets of up to three key tiles; a larger one makes 16 items and more of eight heads, 8 to 12 at C = 64): an item's
+// heads are one dependent chain after the other, 4.4 k of the 35 k clocks of a 24-row tile.  Pass of
 // 3,001 pillars 159.5 -> 157.9 us, one block of 2,000 voxels in fp32 52.1 -> 51.7; the code costs frames of full tiles up to
 // 0.2 %.  (Where more wavefronts have an item, halving them
 // costs the second fetch of the positional terms: 2-3 % of a layer.)
@@ -146,6 +146,17 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static_assert(C % 64 == 0 && D % Mma<T>::KL == 0 && D % 4 == 0, "shape");
   static_assert(total <= 160 * 1024, "LDS of one CU");
 };
+
+// Whether a tile leaves room in the LDS for a second workgroup on the compute unit: C = 64 in bf16.
+template <typename T, int C, int HEADS, int HID> constexpr bool two_groups_fit() { return 2 * LayerLds<T, C, HEADS, HID>::total <= 160 * 1024; }
+
+// Key tiles of the largest set in a tile whose items may be split (split_items).  At C = 64 in bf16 an item of a quarter of the heads is a
+// single head, and it is a workgroup beside it on the compute unit, not idle wavefronts, that fills its waits: sets of three key tiles
+// stay whole there, and so does every set once there are two workgroups to a compute unit (n_tiles > 256).  Two layers, 30 x 30
+// windows, sets of up to 48, all split -> so: 3,000 voxels 18.5 -> 16.9 us, 27,000 40.1 -> 36.2, 45,000 49.9 -> 42.7; 12 x 12 windows,
+// 60,000 49.5 -> 47.2; never split: 300 voxels 13.3 -> 13.6.  The other shapes, never split -> as here: fp32 500 voxels 21.1 -> 20.8,
+// 3,000 29.7 -> 29.1, C = 128 18.8 -> 18.2 and 23.6 -> 23.3, C = 192 25.0 -> 24.4 and 33.2 -> 32.3.
+template <typename T, int C, int HEADS, int HID> constexpr int split_key_tiles() { return two_groups_fit<T, C, HEADS, HID>() ? 2 : 3; }
 
 // Attention of one (set, query tile, group of heads) item (Eq. 5): for each of its heads,
 // logits = Q K^T (+ PE), softmax over the set's distinct voxels, O = P V; O overwrites the Q
@@ -318,7 +329,7 @@ __device__ __forceinline__ void attn_any(const LayerDev& p, unsigned char* smem,
 
 // Workgroups that share a compute unit, by LDS and registers: with two, each may use 80 registers a thread.
 template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(SetSize sets) {
-  return sets != kSets96 && 2 * LayerLds<T, C, HEADS, HID>::total <= 160 * 1024 ? 2 : 1;
+  return sets != kSets96 && two_groups_fit<T, C, HEADS, HID>() ? 2 : 1;
 }
 
 // SETS: the instantiations for sets of four to six key tiles; the common one does not carry that code.
@@ -573,7 +584,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       const int nu = nu_w < 1 ? 1 : (nu_w > kNuMax ? kNuMax : nu_w), kts = (nu + 15) >> 4;
       const int cnt = lane < ns ? kts * item_groups(kts, HEADS, big_heads(C, DUP, SETS)) : 0;
       const int incl = half_wave_scan(cnt);
-      const int split = split_items(__builtin_amdgcn_readlane(incl, kSetWords - 1), __ballot(lane < ns && kts > 3) != 0ull, NW) ? 1 : 0;
+      const bool shared = groups_per_cu<T, C, HEADS, HID>(SETS) > 1 && n_tiles > kComputeUnits;
+      const int split = !shared && split_items(__builtin_amdgcn_readlane(incl, kSetWords - 1),
+                                               __ballot(lane < ns && kts > split_key_tiles<T, C, HEADS, HID>()) != 0ull, NW) ? 1 : 0;
       if (lane < kSetWords)
         set_tab[lane] = lane < ns ? set_word(r0 < 0 ? 0 : (r0 > kRowsMax - 4 ? kRowsMax - 4 : r0), nu, (incl - cnt) << split) : kNoItem;
       if (lane == kSetWords - 1) { set_tab[kSetWords] = (unsigned)(incl << split); set_tab[kSetWords + 1] = (unsigned)split; }
@@ -857,7 +870,7 @@ int launch_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coor
                  hipStream_t st) {
   // instantiations per range of set sizes and reading of repeated slots: as keys (dup_mode 1) they multiply the
   // exponentials by the slots' counts
-  constexpr bool kSlim = 2 * LayerLds<T, C, HEADS, HID>::total <= 160 * 1024;
+  constexpr bool kSlim = two_groups_fit<T, C, HEADS, HID>();
   const bool dup = w.dup_mode != 0;
   if (mp.tau <= 48) {
     if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, true>(w, mp, coords, x, out, full, st);

@@ -139,6 +139,32 @@ def test_workgroups_that_take_several_tiles(C, heads, hidden, dtype, tau, dup_mo
         assert torch.equal(again, y)
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_attention_items_split_and_whole(C, heads, hidden, dtype, dup_mode):
+    """Tiles of few attention items split them (C = 64 bf16: up to 256 tiles, sets of one and two key tiles); a head's result does not
+    depend on it.  Without a work list a tile is two sets: 512 windows are 256 tiles, 514 are 257."""
+    win, sizes = (12, 12, 1), (16, 17, 32, 1, 33, 5, 48, 48, 9, 12)
+    rng = np.random.Generator(np.random.Philox(41))
+    cells = [rng.permutation(144)[:s] for s in sizes]
+    place = lambda w: np.stack([0 * cells[w % 10], 12 * (w // 50) + cells[w % 10] // 12, 12 * (w % 50) + cells[w % 10] % 12, 0 * cells[w % 10]], 1)
+    coords = np.concatenate([place(w) for w in range(514)]).astype(np.int32)
+    first = sum(sizes[w % 10] for w in range(512))
+    w, x = synth.make_layer_weights(42, C, heads, hidden, win, dtype), synth.make_features(43, len(coords), C, dtype)
+    layer = dsvt.LayerWeights(w, dup_mode)
+    out = []
+    for n in (first, len(coords)):
+        cd = dev_coords(coords[:n])
+        maps = gpu_maps(cd, (600, 600, 1), win, (0, 0, 0), 48, 1, 0, tiles=False)
+        print(f"[case] items split and whole C={C} {dtype} dup={dup_mode} {int(maps.n_sets.item())} sets", flush=True)
+        assert int(maps.n_sets.item()) == (512 if n == first else 514)
+        out.append(dsvt.dsvt_set_attention(layer, maps, cd, dev_feats(x[:n], dtype)))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1][:first])
+    om = orc.partition(coords, (600, 600, 1), win, (0, 0, 0), 48, 0)
+    assert rel_err(out[1], orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype]
+
+
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
 @pytest.mark.parametrize("n_multi,n_single", [(0, 24576), (0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
 def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
