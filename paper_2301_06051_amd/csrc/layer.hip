@@ -444,12 +444,12 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       if (r0 + k * GR < RT * 16)
         *reinterpret_cast<uint4*>(smem + off + (r0 + k * GR) * LDX * (int)sizeof(T) + c * 16) = live[k] ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
   };
-  // A row of a tile from registers in accumulator layout -> the voxel's row of out.
+  // A row of a tile from registers in accumulator layout -> the voxel's row of out; bf16 in 16-byte pieces: neighbouring 16-lane
+  // rows exchange halves, so that a lane holds 8 consecutive features.  Two output tiles: of the first one in the even rows, of the
+  // second in the odd ones.
   const auto put_out = [&](int t, int R, int row, int o0, const f32x4 (&v)[NT_O]) {
     const int vox = row < R ? row_vox(t)[row] : -1;
     if constexpr (NT_O == 2 && sizeof(T) == 2) {
-      // neighbouring 16-lane rows exchange halves, so that a lane holds 8 consecutive features: of tile 0 in the even rows, of
-      // tile 1 in the odd ones
       union { Vec4 h; unsigned u[2]; } a, b;
       a.h = pack4<T>(v[0]);
       b.h = pack4<T>(v[1]);
@@ -460,6 +460,19 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       for (int nt = 0; nt < NT_O; ++nt)
         if (vox >= 0) *reinterpret_cast<Vec4*>(out + (size_t)vox * C + o0 + 16 * nt + 4 * g) = pack4<T>(v[nt]);
     }
+  };
+  // One output tile (C = 64): row of one row tile in the even 16-lane rows and, if there is a next one, row + 16 of it in the odd ones.
+  // 8 bytes a lane -> this: two layers of 100,000 voxels in 12 x 12 windows 70.8 -> 69.0 us, of 20,000 in 30 x 30 windows, sets of up to 48,
+  // 27.0 -> 26.3; attention without a work list, 60,000 voxels, 20.7 -> 19.9 (a copy through LDS 20.1, and slower than 8 bytes in small frames).
+  constexpr bool kPairs = NT_O == 1 && sizeof(T) == 2;
+  static_assert(!kPairs || kOwnTiles == 2, "the row tiles of a wavefront are one pair");
+  const auto put_pair = [&](int t, int R, int row, bool two, int o0, Vec4 v0, Vec4 v1) {
+    union { Vec4 h; unsigned u[2]; } a, b;
+    a.h = v0;
+    b.h = v1;
+    const int mine = row + 16 * (g & 1), vox = (two || (g & 1) == 0) && mine < R ? row_vox(t)[mine] : -1;
+    const auto s0 = __builtin_amdgcn_permlane16_swap(a.u[0], b.u[0], false, false), s1 = __builtin_amdgcn_permlane16_swap(a.u[1], b.u[1], false, false);
+    if (vox >= 0) *reinterpret_cast<uint4*>(out + (size_t)vox * C + o0 + 8 * (g >> 1)) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
   };
 
   // ---- 3. Q, K, V = X W^T + b; V stored transposed
@@ -659,14 +672,18 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     else undefined(keep);
     if (pf_turn == 1) ffn1.prefetch();
     if (!full_layer) {                           // attention and its projection only: raw Y goes out, one tile per workgroup
+      if constexpr (kPairs) {
+        if (HC > 0) put_pair(tab, R, 16 * rt_own + m, HC > 1, o_own, pack4<T>(keep[0][0]), pack4<T>(keep[0][kOwnTiles - 1]));
+      } else {
 #pragma unroll
-      for (int r = 0; r < kOwnTiles; ++r)
-        if (r < HC) {
-          f32x4 y[NT_O];
+        for (int r = 0; r < kOwnTiles; ++r)
+          if (r < HC) {
+            f32x4 y[NT_O];
 #pragma unroll
-          for (int nt = 0; nt < NT_O; ++nt) y[nt] = keep[nt][r];
-          put_out(tab, R, 16 * (rt_own + r) + m, o_own, y);
-        }
+            for (int nt = 0; nt < NT_O; ++nt) y[nt] = keep[nt][r];
+            put_out(tab, R, 16 * (rt_own + r) + m, o_own, y);
+          }
+      }
       return;
     }
     add_rows<T, NT_O, kOwnTiles>(keep, Xs, LDX, rt_own, HC, o_own);
@@ -674,7 +691,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     layer_norm_tile<T, NT_O, C, kOwnTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       a = *reinterpret_cast<const f32x4*>(affine_lds + o_own + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
-    }, p.ln_eps, [&](int row, const f32x4 (&y)[NT_O]) {
+    }, p.ln_eps, [&](int, int row, const f32x4 (&y)[NT_O]) {
 #pragma unroll
       for (int nt = 0; nt < NT_O; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
     });
@@ -731,6 +748,8 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     if (more && pf_turn == 0) qkv.template prefetch_first<kEarly>();
     add_rows<T, NT_2, kOwnTiles>(keep2, Xs, LDX, rt_own, HC, o_own2);
     if (more && pf_turn == 1) qkv.template prefetch_first<kEarly>();
+    Vec4 held;                                   // the first of two row tiles' rows (kPairs)
+    opaque_def(held);
     layer_norm_tile<T, NT_2, C, kOwnTiles>(keep2, o_own2, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       if (nt == 0) DSVT_PHASE(tile, 7);          // everybody's part of the second product done
       if (nt == 0 && more) {
@@ -739,7 +758,14 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       }
       a = *reinterpret_cast<const f32x4*>(affine_lds + 2 * C + o_own2 + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + 3 * C + o_own2 + 16 * nt + 4 * g);
-    }, p.ln_eps, [&](int row, const f32x4 (&y)[NT_2]) { put_out(tab, R, row, o_own2, y); });
+    }, p.ln_eps, [&](int r, int row, const f32x4 (&y)[NT_2]) {
+      if constexpr (kPairs) {
+        if (r == 0) held = pack4<T>(y[0]);
+        if (r + 1 == HC) put_pair(tab, R, row - 16 * r, r > 0, o_own2, held, pack4<T>(y[0]));
+      } else {
+        put_out(tab, R, row, o_own2, y);
+      }
+    });
     DSVT_PHASE(tile, 8);
     if (!more) return;
     DSVT_PHASE(next, 0);

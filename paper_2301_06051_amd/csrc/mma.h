@@ -480,7 +480,7 @@ __device__ __forceinline__ void add_rows(f32x4 (&v)[NT][RH], const T* Xs, int ld
 // exchanged through LDS; variance = E[x^2] - mean^2.  Every thread of the workgroup must call it.
 // affine(nt, gamma, beta): this lane's four of each for output tile nt; called behind the exchange's barrier, so that they may
 // come from LDS that was written before it.
-// put(row, y): a normalised row's features o0 + 16*nt + 4*g .. + 3, every lane of the wavefront together.
+// put(r, row, y): a normalised row's features o0 + 16*nt + 4*g .. + 3, row tile by row tile, every lane of the wavefront together.
 template <typename T, int NT, int C, int RH, typename Affine, typename Put>
 __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int og, int rt0, int cnt, float* stat,
                                                 Affine affine, float eps, Put put) {
@@ -526,7 +526,7 @@ __device__ __forceinline__ void layer_norm_tile(f32x4 (&v)[NT][RH], int o0, int 
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) y[nt][i] = fmaf(fmaf(v[nt][r][i], rs, sh), ga[nt][i], be[nt][i]);
-      put(row, y);
+      put(r, row, y);
     }
   }
 }

@@ -293,7 +293,7 @@ __device__ __forceinline__ void single_regions(PoolDev p, const int2* __restrict
       be[nt] = *reinterpret_cast<const f32x4*>(vec + 3 * C + o_own + 16 * nt + 4 * g);
     }
     layer_norm_tile<T, NT, C, RT>(keep, o_own, wave, 0, RT, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps,
-                                  [&](int row, const f32x4 (&y)[NT]) {
+                                  [&](int, int row, const f32x4 (&y)[NT]) {
 #pragma unroll
                                     for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
                                   });
@@ -442,7 +442,7 @@ kp_attention(PoolDev p, const int32_t* __restrict__ pool_inds, PoolLists ls, con
             keep[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
           }
       layer_norm_tile<T, NT_C, C, RH>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) { a = ga[nt]; b = be[nt]; }, p.ln_eps,
-                                  [&](int row, const f32x4 (&y)[NT_C]) {
+                                  [&](int, int row, const f32x4 (&y)[NT_C]) {
 #pragma unroll
                                     for (int nt = 0; nt < NT_C; ++nt) *reinterpret_cast<Vec4*>(Ps + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
                                   });

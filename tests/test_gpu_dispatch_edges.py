@@ -56,6 +56,27 @@ def test_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype, tau, dup_mode):
             assert rel_err(y, ref) < TOL[dtype], (cnt, tiles)
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+def test_attention_alone_of_one_to_six_row_tiles(C, heads, hidden, dtype):
+    """Attention without the rest of a layer over one window of 1 to 96 voxels: its rows leave by row tile (C = 64 bf16: by pairs of them, the
+    last one alone), rows that pad the last row tile not at all."""
+    grid, win, tau = (12, 12, 1), (12, 12, 1), 96
+    rng = np.random.Generator(np.random.Philox(51))
+    w = synth.make_layer_weights(52, C, heads, hidden, win, dtype)
+    layer = dsvt.LayerWeights(w)
+    for cnt in (1, 15, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 81, 95, 96):
+        cell = rng.permutation(144)[:cnt]
+        coords = np.stack([0 * cell, cell // 12, cell % 12, 0 * cell], 1).astype(np.int32)
+        x = synth.make_features(54 + cnt, cnt, C, dtype)
+        print(f"[case] attention alone, one window of {cnt} voxels C={C} {dtype}", flush=True)
+        om = orc.partition(coords, grid, win, (0, 0, 0), tau, 0)
+        cd = dev_coords(coords)
+        both = torch.full((cnt + 16, C), 7.0, dtype=layer.dtype, device="cuda")          # (rows past the last one keep what they held)
+        y = dsvt.dsvt_set_attention(layer, gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0), cd, dev_feats(x, dtype), y=both[:cnt])
+        torch.cuda.synchronize()
+        assert rel_err(y, orc.set_attention(w, om, coords, x)) < TOL[dtype] and bool((both[cnt:] == 7.0).all()), cnt
+
+
 def _windows_of_one_set_and_two(n):
     """n voxels in 24 x 24 windows of 20 to 73 on a 480 x 480 grid."""
     rng = np.random.Generator(np.random.Philox(15))
