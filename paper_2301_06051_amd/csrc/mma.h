@@ -159,11 +159,11 @@ constexpr int kWaves = 8;                        // wavefronts of a pooling work
 constexpr int kStatGroupsMax = 6;                // LayerNorm phases: the C features are split over at most 6 groups of output tiles
 
 // One GEMM phase of a workgroup of NW wavefronts: Out^T[NOUT x rows] = W[NOUT x K] . X^T.
-// A work item is a group of NT output tiles over all row tiles (RSPLIT = 1) or over one half of
-// them (RSPLIT = 2, for workgroups with two wavefronts per SIMD); wavefront w takes items
-// w, w + NW, ...  An item's weight fragments sit in registers for the whole item, the next item's
-// are requested before the current one is consumed, and inside an item the activations of row
-// tile r + 1 are read from LDS while row tile r is in the matrix cores.  Every activation
+// A work item is a group of NT output tiles over all row tiles (RSPLIT = 1) or over one of RSPLIT parts of them; wavefront w
+// takes items w, w + NW, ...  run() knows all row tiles and halves (two wavefronts per SIMD), run_keep() any parts of one item
+// per wavefront, run_rows() and run_before() one item per wavefront over all row tiles.  An item's weight fragments sit in
+// registers for the whole item, run() requests the next item's before the current one is consumed, and the activations of
+// row tile r + 1 are read from LDS while row tile r is in the matrix cores.  Every activation
 // fragment read from LDS feeds NT MFMAs; a weight fragment is loaded by RSPLIT wavefronts.
 template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, bool DOUBLE_A = true, int KSPLIT = 1>
 struct GemmPhase {
@@ -238,7 +238,7 @@ struct GemmPhase {
   // requested, so waiting for it never waits for them.
   template <typename Epi>
   __device__ __forceinline__ void run(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi) {
-    static_assert(KSPLIT == 1, "run() holds the whole K");
+    static_assert(KSPLIT == 1 && (RSPLIT == 1 || RSPLIT == 2), "run() holds the whole K, and an item takes all row tiles or halves");
     const int h0 = RSPLIT == 1 ? RT : (RT + 1) >> 1;
 #pragma unroll
     for (int it = 0; it < IPW; ++it) {

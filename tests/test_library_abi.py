@@ -85,6 +85,25 @@ def test_no_kernel_spills_vector_registers():
     assert [k for k in kernels if k[1] or (k[2] and "k_layer" in k[0])] == []
 
 
+@pytest.mark.parametrize("parts,compiles", [(1, True), (2, True), (3, False), (6, False)])
+def test_projection_over_parts_of_the_row_tiles_that_it_cannot_cover_does_not_compile(tmp_path, parts, compiles):
+    """GemmPhase::run() gives an item all row tiles or a half of them; the phases that take thirds have walks of their own."""
+    import subprocess
+    from paper_2301_06051_amd import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no compiler")
+    src = tmp_path / "phase.hip"
+    src.write_text('#include "mma.h"\n'
+                   "__global__ void k(const float* w, const float* b, float* x) {\n"
+                   f"  GemmPhase<float, 1, 64, 64, 8, {parts}> phase(w, threadIdx.x >> 6);\n"
+                   "  phase.prefetch();\n"
+                   "  phase.run(x, 72, 6, b, [&](int o0, int r, f32x4 (&acc)[1]) { x[o0 + r] = acc[0][0]; });\n"
+                   "}\n")
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-fsyntax-only", str(src)], capture_output=True, text=True)
+    assert (r.returncode == 0) == compiles, r.stderr
+    assert compiles or "all row tiles or halves" in r.stderr
+
+
 def test_host_only_calls_work_without_a_gpu():
     """dsvt_partition_bound is pure host arithmetic: the set bound and a positive scratch size."""
     if not os.path.exists(LIB):
