@@ -99,20 +99,14 @@ __device__ __forceinline__ int half_wave_scan(int v) {
   return v;
 }
 
-// v into [0, hi], one instruction (hi is not below 0, which the compiler does not know).
-__device__ __forceinline__ int clamp_to(int v, int hi) {
-  int r;
-  asm("v_med3_i32 %0, %1, 0, %2" : "=v"(r) : "v"(v), "s"(hi));
-  return r;
-}
-
 struct LayerDev {
   const void *w_qkv, *w_o, *w_1, *w_2;       // packed (see mma.h)
   const float *b_qkv, *b_o, *b_1, *b_2, *ln1_g, *ln1_b, *ln2_g, *ln2_b, *rel_bias;
   const float2* gelu_tab;                    // kGeluKnots (slope, intercept) pairs, see k_pack_gelu_table
   float ln_eps;
-  // position table [index][heads], in bytes: index of (q, k) = code(q) - code(k) + rel_const, at most rel_last; rel_none: the row of -inf
-  int rel_const, rel_last, rel_none, rel_my, rel_mz;
+  // position table [index][heads], in bytes (below 2^32): index of (q, k) = code(q) - code(k) + rel_const, at most rel_last; rel_none: the row of -inf
+  unsigned rel_const, rel_last, rel_none;
+  int rel_my, rel_mz;
   int dup_mode;
 };
 
@@ -197,7 +191,7 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem
 
   f32x4 bias[HG][KTC];
   {
-    const int qc = row_code[qrow] + p.rel_const;
+    const unsigned qc = (unsigned)row_code[qrow] + p.rel_const;
     const int left = nu - (16 * (KTC - 1) + 4 * g);                // keys of the last tile from this lane's first on
     const char* tab = reinterpret_cast<const char*>(p.rel_bias) + hh * HG * 4;
 #pragma unroll
@@ -206,9 +200,9 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem
       const int kls[4] = {kl.x, kl.y, kl.z, kl.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        int at = clamp_to(qc - kls[i], p.rel_last);
+        unsigned at = min(qc - (unsigned)kls[i], p.rel_last);      // (modulo 2^32: right for every index of the table)
         if (kt == KTC - 1) at = i < left ? at : p.rel_none;        // only the last key tile is ragged
-        const float* tp = reinterpret_cast<const float*>(tab + (unsigned)at);
+        const float* tp = reinterpret_cast<const float*>(tab + at);
         if constexpr (HG == 4) {
           const f32x4 t = *reinterpret_cast<const f32x4*>(tp);
           bias[0][kt][i] = t[0]; bias[1][kt][i] = t[1]; bias[2][kt][i] = t[2]; bias[3][kt][i] = t[3];
@@ -547,7 +541,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         const int4 c = coords[v];
         row_vox(tab)[r] = v;
         row_mult(tab)[r] = (float)run;
-        row_code(tab)[r] = ((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (HEADS * 4);
+        row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)(HEADS * 4));
       }
     }
   }
@@ -824,9 +818,10 @@ LayerDev to_dev(const dsvt_layer_w& w) {
   d.ln_eps = w.ln_eps; d.dup_mode = w.dup_mode;
   const int my = 2 * w.win[1] - 1, mz = 2 * w.win[2] - 1;
   d.rel_my = my; d.rel_mz = mz;
-  d.rel_last = (pl.rel_size - 1) * w.heads * 4;
-  d.rel_none = pl.rel_size * w.heads * 4;
-  d.rel_const = w.rel_bias != nullptr ? (((w.win[0] - 1) * my + (w.win[1] - 1)) * mz + (w.win[2] - 1)) * w.heads * 4 : 0;
+  const unsigned row = (unsigned)w.heads * 4u;
+  d.rel_last = (unsigned)(pl.rel_size - 1) * row;
+  d.rel_none = (unsigned)pl.rel_size * row;
+  d.rel_const = w.rel_bias != nullptr ? (unsigned)(((w.win[0] - 1) * my + (w.win[1] - 1)) * mz + (w.win[2] - 1)) * row : 0u;
   return d;
 }
 

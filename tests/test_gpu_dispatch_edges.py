@@ -77,6 +77,29 @@ def test_attention_alone_of_one_to_six_row_tiles(C, heads, hidden, dtype):
         assert rel_err(y, orc.set_attention(w, om, coords, x)) < TOL[dtype] and bool((both[cnt:] == 7.0).all()), cnt
 
 
+def test_position_table_of_more_than_2_gib():
+    """A window whose table of relative positions has byte offsets past 2^31 (811 x 811 x 103 entries of eight heads): pairs of voxels whose
+    coordinate difference lies at the table's start, in its middle, around 2^31 and at its end."""
+    C, heads, win, tau = 128, 8, (406, 406, 52), 32
+    far = [(0, 0, 0), (1, 7, 50), (398, 400, 3), (399, 0, 0), (400, 1, 51), (405, 405, 51), (200, 203, 26), (405, 0, 0), (0, 405, 51), (201, 3, 1)]
+    coords = np.array([(0, *c) for c in far], np.int32)
+    x = synth.make_features(61, len(coords), C, "bf16")
+    w = synth.make_layer_weights(62, C, heads, 256, win, "bf16", rel_bias=False)
+    size = (2 * win[0] - 1) * (2 * win[1] - 1) * (2 * win[2] - 1)
+    at = np.unique(orc.rel_index(coords[:, None, 1:].astype(np.int64), coords[None, :, 1:].astype(np.int64), win))
+    assert at[0] == 0 and at[-1] == size - 1 and 10 < np.count_nonzero(at * heads * 4 >= 2 ** 31) < len(at) // 2
+    values = np.random.Generator(np.random.Philox(63)).standard_normal((heads, len(at))).astype(np.float32)
+    table, table64 = np.zeros((heads, size), np.float32), np.zeros((heads, size))          # (pages nobody writes take no memory)
+    table[:, at], table64[:, at] = values, values
+    print(f"[case] position table of {table.nbytes} bytes", flush=True)
+    om = orc.partition(coords, win, win, (0, 0, 0), tau, 0)
+    cd = dev_coords(coords)
+    layer = dsvt.LayerWeights(dict(w, rel_bias=table))
+    y = dsvt.dsvt_set_attention(layer, gpu_maps(cd, win, win, (0, 0, 0), tau, 1, 0, tiles=False), cd, dev_feats(x, "bf16"))
+    torch.cuda.synchronize()
+    assert rel_err(y, orc.set_attention(dict(w, rel_bias=table64), om, coords, x)) < TOL["bf16"]
+
+
 def _windows_of_one_set_and_two(n):
     """n voxels in 24 x 24 windows of 20 to 73 on a 480 x 480 grid."""
     rng = np.random.Generator(np.random.Philox(15))
