@@ -107,9 +107,7 @@ struct LayerDev {
   // position table [index][heads], in bytes (below 2^32): index of (q, k) = code(q) - code(k) + rel_const, at most rel_last; rel_none: the row of -inf
   unsigned rel_const, rel_last, rel_none;
   int rel_my, rel_mz;
-  int dup_mode;
 };
-
 
 struct MapsDev {
   const int32_t *set_inds, *n_sets, *n_tiles, *tile_desc;
@@ -362,7 +360,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #define DSVT_REFRESH_LANE() do { tid = opaque_tid(); lane = tid & 63; m = lane & 15; g = lane >> 4; } while (0)
-  typedef GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, false> QkvPhase;
+  typedef GemmPhase<T, NT_QKV, C, 3 * C, NW> QkvPhase;
   // The first two output tiles of every wavefront's Q/K/V weights (C = 192: of three, C = 128: both, C = 64: the only one)
   // of a workgroup's first tile are requested behind the descriptor, and arrive during the two dependent trips to memory (descriptor, then the rows it
   // names) in which the compute unit's memory pipeline would have nothing else to do: it takes a 1 KB fragment every ~19
@@ -654,7 +652,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // (before the projection, after it, after the residual): a CU takes a 16-byte load per
     // wavefront every ~16 cycles, a wavefront waits until its requests are taken, and twelve
     // wavefronts asking at once would all stand still for 3 k cycles.
-    GemmPhase<T, NT_1, C, HID, NW, 1, false> ffn1(reinterpret_cast<const T*>(p.w_1), wave);
+    GemmPhase<T, NT_1, C, HID, NW> ffn1(reinterpret_cast<const T*>(p.w_1), wave);
     const int pf_turn = full_layer ? wave / (NW / 3) : -1;
     ffn1.forget();
     if (pf_turn == 0) ffn1.prefetch();
@@ -702,7 +700,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // 120,000-voxel frame 707 / 699.  Slower than this at C = 192, each in one session with it: the matrix in three slices, two of
     // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
     // bias requested in front of the weights 0.1-0.7 %.
-    GemmPhase<T, NT_2, HID, C, NW, RS, true, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
+    GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
     const float gelu0 = gelu_start(smem + L::off_gelu);
     ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
 #pragma unroll
@@ -815,7 +813,7 @@ LayerDev to_dev(const dsvt_layer_w& w) {
   d.ln1_g = w.ln1_g; d.ln1_b = w.ln1_b; d.ln2_g = w.ln2_g; d.ln2_b = w.ln2_b;
   d.rel_bias = reinterpret_cast<const float*>(pk + pl.off[4]);
   d.gelu_tab = reinterpret_cast<const float2*>(pk + pl.off[5]);
-  d.ln_eps = w.ln_eps; d.dup_mode = w.dup_mode;
+  d.ln_eps = w.ln_eps;
   const int my = 2 * w.win[1] - 1, mz = 2 * w.win[2] - 1;
   d.rel_my = my; d.rel_mz = mz;
   const unsigned row = (unsigned)w.heads * 4u;

@@ -29,7 +29,6 @@ template <> struct Mma<bf16_t> {
   static __device__ __forceinline__ f32x4 mma(Frag a, Frag b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ Frag zero() { Frag z = {0, 0, 0, 0, 0, 0, 0, 0}; return z; }
 };
 
 // fp32: four v_mfma_f32_16x16x4_f32 per fragment pair; a lane owns 4 consecutive k and step e of
@@ -47,7 +46,6 @@ template <> struct Mma<float> {
     c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
     return c;
   }
-  static __device__ __forceinline__ Frag zero() { Frag z = {0.f, 0.f, 0.f, 0.f}; return z; }
 };
 
 template <typename T> __device__ __forceinline__ typename Mma<T>::Vec4 pack4(f32x4 v);
@@ -165,7 +163,7 @@ constexpr int kStatGroupsMax = 6;                // LayerNorm phases: the C feat
 // registers for the whole item, run() requests the next item's before the current one is consumed, and the activations of
 // row tile r + 1 are read from LDS while row tile r is in the matrix cores.  Every activation
 // fragment read from LDS feeds NT MFMAs; a weight fragment is loaded by RSPLIT wavefronts.
-template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, bool DOUBLE_A = true, int KSPLIT = 1>
+template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, int KSPLIT = 1>
 struct GemmPhase {
   static constexpr int KC = Mma<T>::KC;
   static constexpr int NKF_ALL = K / KC;
@@ -175,7 +173,7 @@ struct GemmPhase {
   static constexpr int IPW = (N_ITEMS + NW - 1) / NW;   // items per wavefront (the last round may be partial)
   static constexpr int RH = kRowTiles / RSPLIT;          // row tiles an item can cover
   static_assert(K % KC == 0 && NOUT % (16 * NT) == 0 && kRowTiles % RSPLIT == 0, "phase shape");
-  AFull<T, NT, NKF> a[(IPW > 1 && DOUBLE_A) ? 2 : 1];   // DOUBLE_A: the next item's weights load during the current item
+  AFull<T, NT, NKF> a[IPW > 1 ? 2 : 1];                 // two: the next item's weights load during the current item
   const T* Wp;
   int wave;
   struct Bias { f32x4 v[NT]; };                         // an item's bias, see load_bias()
@@ -248,9 +246,9 @@ struct GemmPhase {
       const int rt0 = half ? h0 : 0, cnt = half ? RT - h0 : h0;
       Bias bl;
       load_bias(bl, bias, og, false);
-      if (DOUBLE_A && it + 1 < IPW && item + NW < N_ITEMS) load_a<T, NT, NKF>(a[(it + 1) & 1], Wp, ((item + NW) % N_OG) * NT);
-      const AFull<T, NT, NKF>& A = a[DOUBLE_A ? (it & 1) : 0];
-      if constexpr (DOUBLE_A && RSPLIT == 2) {
+      if (it + 1 < IPW && item + NW < N_ITEMS) load_a<T, NT, NKF>(a[(it + 1) & 1], Wp, ((item + NW) % N_OG) * NT);
+      const AFull<T, NT, NKF>& A = a[it & 1];
+      if constexpr (RSPLIT == 2) {
         // two wavefronts per SIMD: the other one covers the LDS latency, so one row tile at a
         // time keeps the registers for the second weight buffer
         for (int r = 0; r < cnt; ++r) {
@@ -280,7 +278,6 @@ struct GemmPhase {
           if (two) epi(og * 16 * NT, rt0 + r + 1, acc1);
         }
       }
-      if (!DOUBLE_A && it + 1 < IPW && item + NW < N_ITEMS) load_a<T, NT, NKF>(a[0], Wp, ((item + NW) % N_OG) * NT);
     }
   }
 
