@@ -153,27 +153,33 @@ def test_block_around_the_slim_kernel(tau, n, dup_mode):
 
 
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
-@pytest.mark.parametrize("tau,dup_mode", [(96, 0), (72, 1), (36, 0), (36, 1)])
+@pytest.mark.parametrize("tau,dup_mode", [(96, 0), (72, 1), (48, 0), (36, 0), (36, 1)])
 def test_workgroups_that_take_several_tiles(C, heads, hidden, dtype, tau, dup_mode):
-    """Frames of one tile per workgroup, of one more, of two, of two and one, and so on: a workgroup's next tile is fetched during the one
-    before, its rows over that one's queries.  The windows are five patterns in turn, so five windows' oracle gives every row."""
+    """Frames of one tile per workgroup (256 of them, 512 at C = 64 bf16), of one less and one more, of two, of two and one, and so on: a
+    workgroup's next tile is fetched during the one before, its rows over that one's queries.  The windows are five patterns in turn, so five
+    windows' oracle gives every row.  Sets of more than 48 voxels have a tile each; of the smaller ones as many windows are taken as make
+    the tiles that are wanted."""
     win, sizes = (12, 12, 1), [min(s, 144) for s in (tau, tau - 1, tau // 2 + 1, tau - 3, tau // 2 + 2)]
+    windows_tiles = {36: ((311, 255), (380, 256), (555, 257), (1105, 511), (1106, 512), (1600, 647), (3054, 1024), (3057, 1025)),
+                     48: ((255, 255), (333, 256), (334, 257), (664, 511), (665, 512), (1000, 600), (1706, 1024), (2041, 1025), (3061, 1537))}
+    windows_tiles = windows_tiles.get(tau, [(n, n) for n in (255, 256, 257, 511, 512, 513, 1024, 1025, 1537)])
     rng = np.random.Generator(np.random.Philox(31))
     cells = [rng.permutation(144)[:s] for s in sizes]
-    place = lambda w, cell: np.stack([0 * cell, 12 * (w // 50) + cell // 12, 12 * (w % 50) + cell % 12, 0 * cell], 1).astype(np.int32)
+    place = lambda w, cell: np.stack([0 * cell, 12 * (w // 60) + cell // 12, 12 * (w % 60) + cell % 12, 0 * cell], 1).astype(np.int32)
     ws = [synth.make_layer_weights(32 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
     layers = [dsvt.LayerWeights(w, dup_mode) for w in ws]
     one = np.concatenate([place(k, c) for k, c in enumerate(cells)])
     x1 = synth.make_features(34, len(one), C, dtype)
-    ref1 = orc.block(ws, [orc.partition(one, (600, 600, 1), win, (0, 0, 0), tau, a) for a in (0, 1)], one, x1, dup_mode)
-    att1 = orc.set_attention(ws[0], orc.partition(one, (600, 600, 1), win, (0, 0, 0), tau, 0), one, x1, dup_mode)
+    ref1 = orc.block(ws, [orc.partition(one, (720, 720, 1), win, (0, 0, 0), tau, a) for a in (0, 1)], one, x1, dup_mode)
+    att1 = orc.set_attention(ws[0], orc.partition(one, (720, 720, 1), win, (0, 0, 0), tau, 0), one, x1, dup_mode)
     first = np.cumsum([0] + sizes)
-    for n_win in (256, 257, 512, 513, 1025, 1600):
+    for n_win, n_tiles in windows_tiles:
         coords = np.concatenate([place(w, cells[w % 5]) for w in range(n_win)])
         rows = np.concatenate([np.arange(first[w % 5], first[w % 5 + 1]) for w in range(n_win)])
         cd, xd = dev_coords(coords), dev_feats(x1[rows], dtype)
-        maps = [gpu_maps(cd, (600, 600, 1), win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
+        maps = [gpu_maps(cd, (720, 720, 1), win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
         print(f"[case] {n_win} windows, {int(maps[0].n_tiles.item())} tiles, C={C} {dtype} tau={tau} dup={dup_mode}", flush=True)
+        assert [int(m.n_tiles.item()) for m in maps] == [n_tiles, n_tiles]
         y = dsvt.dsvt_block(layers, maps, cd, xd)
         z = dsvt.dsvt_set_attention(layers[0], maps[0], cd, xd)
         torch.cuda.synchronize()
