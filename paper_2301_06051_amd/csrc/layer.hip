@@ -109,10 +109,31 @@ struct LayerDev {
   int rel_my, rel_mz;
 };
 
+struct PositionTable { const float* rel_bias; unsigned rel_const, rel_last, rel_none; };     // what attention takes of LayerDev
+
 struct MapsDev {
   const int32_t *set_inds, *n_sets, *n_tiles, *tile_desc;
   int32_t max_sets, max_tiles, tau, n_voxels;
 };
+
+template <typename T> struct LayerCall {
+  LayerDev layer;
+  MapsDev maps;
+  const int4* coords;
+  const T* x;
+  T* out;                                    // may be x: a tile's rows are read, then written, by one workgroup only, and the tiles share no rows
+  int full_layer;
+};
+// The kernel's one argument where it lies in memory.  Behind an empty asm, so that inside the loop over tiles a pointer is loaded where it is
+// used: the compiler otherwise loads all of them in front of the loop and spills what the scalar registers do not hold into lanes of vector
+// registers, 18 to 30 of them a kernel and two vector instructions each time one is needed.  With -> without: 3,001 pillars 151.1 ->
+// 147.2 us, pillar frame 355.0 -> 351.1, hybrid windows 496.7 -> 488.7, four frames 1,079 -> 1,069, voxel frame 659.8 -> 648.4, skewed batch
+// 7,616 -> 7,508, one block of 2,000 voxels in fp32 48.9 -> 47.9; attention of 4,000 voxels without a work list, C = 64, 10.1 -> 9.7.
+template <typename T> __device__ __forceinline__ const __attribute__((address_space(4))) LayerCall<T>* layer_call() {
+  auto call = (const __attribute__((address_space(4))) LayerCall<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(call));
+  return call;
+}
 
 template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr int D = C / HEADS;
@@ -170,7 +191,7 @@ template <typename T, int C, int HEADS, int HID> constexpr int split_key_tiles()
 // positional terms requested in front of the output projection's weights, behind which they come back -- 48 more registers across
 // the barrier, spills, and with those weights requested behind the attention instead no gain.
 template <typename T, int C, int HEADS, int HID, int KTC, int HG, bool DUP>
-__device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem, int q_off, const int32_t* row_code,
+__device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char* smem, int q_off, const int32_t* row_code,
                                           const float* row_mult, int r0, int nu, int qt, int hh, int rows_ready) {
   typedef LayerLds<T, C, HEADS, HID> L;
   typedef Mma<T> M;
@@ -302,7 +323,7 @@ __device__ __forceinline__ void attn_item(const LayerDev& p, unsigned char* smem
 // An item of a set with kts key tiles: up to three key tiles half of the heads per item (split_items: a quarter), beyond that
 // big_heads().
 template <typename T, int C, int HEADS, int HID, SetSize SETS, bool DUP>
-__device__ __forceinline__ void attn_any(const LayerDev& p, unsigned char* smem, int q_off, const int32_t* row_code,
+__device__ __forceinline__ void attn_any(const PositionTable& p, unsigned char* smem, int q_off, const int32_t* row_code,
                                          const float* row_mult, int r0, int nu, int qt, int hh, int kts, bool split, int rows_ready) {
   constexpr int HG2 = HEADS / 2, HG4 = HEADS / 4, HGB = big_heads(C, DUP, SETS);
   if (split) {
@@ -337,8 +358,9 @@ template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(Set
 // 158.5 -> 160.1, of which the kernel's own time is 16.0 -> 15.9 a layer.
 template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
 __global__ void __launch_bounds__(kLayerWaves * 64, (3 * groups_per_cu<T, C, HEADS, HID>(SETS)))
-k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* out, int full_layer) {
-  // out may be x: a tile's rows are read, then written, by one workgroup only, and the tiles share no rows
+k_layer(LayerCall<T> call) {
+  const LayerDev& p = call.layer;
+  const MapsDev& mp = call.maps;
   typedef LayerLds<T, C, HEADS, HID> L;
   typedef typename Mma<T>::Vec4 Vec4;
   constexpr int LDX = L::LDX, LDV = L::LDV, LDH = L::LDH;
@@ -374,7 +396,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   // The arguments (four cache lines) in one go, then the number of tiles and the first tile's descriptor together: three waits less in a
   // row.  Passes: pillar frame 348.8 -> 347.8 us, hybrid windows 490.1 -> 488.2, 4,137 pillars 74.4 -> 73.6.
   int tile = blockIdx.x;
-  asm("" : "+s"(tile) : "s"(p.w_qkv), "s"(p.gelu_tab), "s"(mp.tile_desc), "s"(mp.n_tiles), "s"(mp.max_tiles), "s"(mp.tau), "s"(x));
+  asm("" : "+s"(tile) : "s"(p.w_qkv), "s"(p.gelu_tab), "s"(mp.tile_desc), "s"(mp.n_tiles), "s"(mp.max_tiles), "s"(mp.tau), "s"(call.x));
   const bool listed = mp.tile_desc != nullptr;
   const int per_wg = fixed_sets(mp.tau);         // without a work list a tile is two sets
   int n_tiles, n_sets = 0, word = 0;
@@ -396,13 +418,13 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   const auto row_code = [&](int t) { return row_vox(t) + kRowsPad; };
   const auto row_mult = [&](int t) { return reinterpret_cast<float*>(row_vox(t) + 2 * kRowsPad); };
   const auto header = [&](int t) { return row_vox(t) + 3 * kRowsPad; };
-  const auto store_desc = [&](int word, int t) {
+  const auto store_desc = [&](int word, int t, int n_voxels) {
     if (tid < kHdrWords) {
       header(t)[tid] = word;
     } else if (tid < kHdrWords + 2 * kRowsMax) {     // words 64 + 2 r and 65 + 2 r: voxel and (slots << 24 | position code) of row r
       const int r = (tid - kHdrWords) >> 1;
       if ((tid & 1) == 0) {
-        row_vox(t)[r] = (word >= 0 && word < mp.n_voxels) ? word : -1;
+        row_vox(t)[r] = (word >= 0 && word < n_voxels) ? word : -1;
       } else {
         row_code(t)[r] = (word & 0xFFFFFF) * (HEADS * 4);
         if constexpr (DUP) row_mult(t)[r] = (float)((unsigned)word >> 24);
@@ -420,26 +442,26 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   // Thread t takes piece t % CH of the rows t / CH, t / CH + GR, ...
   constexpr int CH = C * (int)sizeof(T) / 16, GR = NTHREADS / CH, G = (kRowsMax + GR - 1) / GR;
   static_assert(NTHREADS % CH == 0 && kRowsMax % GR == 0, "whole rows per pass");
-  const auto request_rows = [&](uint4 (&gv)[G], bool (&live)[G], int t, int RT) {
+  const auto request_rows = [&](uint4 (&gv)[G], unsigned& live, int t, int RT, const T* x) {
     const int r0 = tid / CH, c = tid - r0 * CH;
 #pragma unroll
     for (int k = 0; k < G; ++k) {
       const int v = r0 + k * GR < RT * 16 ? row_vox(t)[r0 + k * GR] : -1;
-      live[k] = v >= 0;
+      live |= v >= 0 ? 1u << k : 0u;
       gv[k] = reinterpret_cast<const uint4*>(x + (size_t)(v >= 0 ? v : 0) * C)[c];
     }
   };
-  const auto store_rows = [&](const uint4 (&gv)[G], const bool (&live)[G], int off, int RT) {
+  const auto store_rows = [&](const uint4 (&gv)[G], unsigned live, int off, int RT) {
     const int r0 = tid / CH, c = tid - r0 * CH;
 #pragma unroll
     for (int k = 0; k < G; ++k)
       if (r0 + k * GR < RT * 16)
-        *reinterpret_cast<uint4*>(smem + off + (r0 + k * GR) * LDX * (int)sizeof(T) + c * 16) = live[k] ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
+        *reinterpret_cast<uint4*>(smem + off + (r0 + k * GR) * LDX * (int)sizeof(T) + c * 16) = (live >> k & 1u) != 0u ? gv[k] : make_uint4(0u, 0u, 0u, 0u);
   };
   // A row of a tile from registers in accumulator layout -> the voxel's row of out; bf16 in 16-byte pieces: neighbouring 16-lane
   // rows exchange halves, so that a lane holds 8 consecutive features.  Two output tiles: of the first one in the even rows, of the
   // second in the odd ones.
-  const auto put_out = [&](int t, int R, int row, int o0, const f32x4 (&v)[NT_O]) {
+  const auto put_out = [&](T* out, int t, int R, int row, int o0, const f32x4 (&v)[NT_O]) {
     const int vox = row < R ? row_vox(t)[row] : -1;
     if constexpr (NT_O == 2 && sizeof(T) == 2) {
       union { Vec4 h; unsigned u[2]; } a, b;
@@ -458,7 +480,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   // 27.0 -> 26.3; attention without a work list, 60,000 voxels, 20.7 -> 19.9 (a copy through LDS 20.1, and slower than 8 bytes in small frames).
   constexpr bool kPairs = NT_O == 1 && sizeof(T) == 2;
   static_assert(!kPairs || kOwnTiles == 2, "the row tiles of a wavefront are one pair");
-  const auto put_pair = [&](int t, int R, int row, bool two, int o0, Vec4 v0, Vec4 v1) {
+  const auto put_pair = [&](T* out, int t, int R, int row, bool two, int o0, Vec4 v0, Vec4 v1) {
     union { Vec4 h; unsigned u[2]; } a, b;
     a.h = v0;
     b.h = v1;
@@ -506,7 +528,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 
   if (listed) {
     // ---- 1a. rows from the tile descriptor the partition wrote for this tile (1 KB, one load)
-    store_desc(word, tab);
+    store_desc(word, tab, mp.n_voxels);
   } else {
     // ---- 1b. no work list: two sets per tile, rows derived from set_inds and coords
     const int tau = mp.tau, s_begin = tile * per_wg, ns = n_sets - s_begin < per_wg ? n_sets - s_begin : per_wg;
@@ -536,7 +558,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         const int r = hdr[kHdrR0 + ls] + __popcll(mask & ((1ull << lane) - 1ull));
         const unsigned long long later = mask >> (lane + 1);
         const int run = later ? (__ffsll((long long)later)) : (tau - lane);   // slots holding this voxel
-        const int4 c = coords[v];
+        const int4 c = call.coords[v];
         row_vox(tab)[r] = v;
         row_mult(tab)[r] = (float)run;
         row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)(HEADS * 4));
@@ -549,8 +571,8 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
   int R = tile_rows(tab), RT = row_tiles(R);
   {
     uint4 gv[G];
-    bool live[G];
-    request_rows(gv, live, tab, RT);
+    unsigned live = 0u;
+    request_rows(gv, live, tab, RT, call.x);
     store_rows(gv, live, xo, RT);
   }
   lds_barrier();
@@ -561,6 +583,8 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
 
   for (;;) {
     DSVT_REFRESH_LANE();
+    const auto args = layer_call<T>();
+    const int full_layer = args->full_layer;
     T* Xs = reinterpret_cast<T*>(smem + xo);
     T* Qs = reinterpret_cast<T*>(smem + (2 * L::kTile - xo));
     T* Hs = reinterpret_cast<T*>(smem + (L::kTile - xo / 2));
@@ -573,7 +597,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
     const int og_own = wave % SG, own_max = (RT + RS - 1) / RS, rt_own = wave / SG * own_max;
     const int HC = RT - rt_own < 0 ? 0 : (RT - rt_own < own_max ? RT - rt_own : own_max);       // HC = 0: a wavefront without an item
-    GemmPhase<T, NT_O, C, C, NW, RS> oproj(reinterpret_cast<const T*>(p.w_o), wave);
+    GemmPhase<T, NT_O, C, C, NW, RS> oproj(reinterpret_cast<const T*>(args->layer.w_o), wave);
     oproj.forget();
     if (HC > 0) oproj.prefetch();                // in flight during the attention phase
     const int o_own = og_own * 16 * NT_O;
@@ -602,6 +626,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     DSVT_PHASE(tile, 3);                               // Q, K, V^T in LDS
     // ---- 4. attention inside every set; O overwrites Q
     {
+      const PositionTable table = {args->layer.rel_bias, args->layer.rel_const, args->layer.rel_last, args->layer.rel_none};
       const unsigned my_set = set_tab[lane & (kSetWords - 1)];
       const int n_items = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords]), split = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords + 1]);
       for (int it = wave; it < n_items; it += NW) {
@@ -611,7 +636,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
         const int r0 = sw & 255, nu = (sw >> 8) & 255, kts = (nu + 15) >> 4, k = it - (int)(sw >> 16);
         const int ngr = item_groups(kts, HEADS, big_heads(C, DUP, SETS)) << split;      // (a power of two)
         const int qt = k >> __builtin_ctz(ngr), hh = k & (ngr - 1);
-        attn_any<T, C, HEADS, HID, SETS, DUP>(p, smem, 2 * (int)L::kTile - xo, row_code(tab), row_mult(tab), r0, nu, qt, hh, kts, split != 0, RT * 16);
+        attn_any<T, C, HEADS, HID, SETS, DUP>(table, smem, 2 * (int)L::kTile - xo, row_code(tab), row_mult(tab), r0, nu, qt, hh, kts, split != 0, RT * 16);
       }
     }
     // attention is done with V^T behind the next barrier: the GELU table of the MLP and the LayerNorms' scales and shifts
@@ -630,15 +655,15 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     opaque_def(late);
     if (full_layer && tid < kVecThreads) {
       const int i = tid - kGeluThreads, v = i / (C / 4);
-      const float* src = v < 2 ? (v == 0 ? p.ln1_g : p.ln1_b) : (v == 2 ? p.ln2_g : p.ln2_b);
-      late = i < 0 ? reinterpret_cast<const f32x4*>(p.gelu_tab)[tid] : reinterpret_cast<const f32x4*>(src)[i - v * (C / 4)];
+      const float* src = v < 2 ? (v == 0 ? args->layer.ln1_g : args->layer.ln1_b) : (v == 2 ? args->layer.ln2_g : args->layer.ln2_b);
+      late = i < 0 ? reinterpret_cast<const f32x4*>(args->layer.gelu_tab)[tid] : reinterpret_cast<const f32x4*>(src)[i - v * (C / 4)];
     }
     f32x4 bo4[NT_O];
 #pragma unroll
-    for (int nt = 0; nt < NT_O; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(p.b_o + o_own + 16 * nt + 4 * g);
+    for (int nt = 0; nt < NT_O; ++nt) bo4[nt] = *reinterpret_cast<const f32x4*>(args->layer.b_o + o_own + 16 * nt + 4 * g);
     int next_word;
     opaque_def(next_word);
-    if (more && tid < 256) next_word = mp.tile_desc[(size_t)next * 256 + tid];
+    if (more && tid < 256) next_word = args->maps.tile_desc[(size_t)next * 256 + tid];
     lds_barrier();
     DSVT_REFRESH_LANE();
     DSVT_PHASE(tile, 4);                               // attention done
@@ -652,12 +677,12 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // (before the projection, after it, after the residual): a CU takes a 16-byte load per
     // wavefront every ~16 cycles, a wavefront waits until its requests are taken, and twelve
     // wavefronts asking at once would all stand still for 3 k cycles.
-    GemmPhase<T, NT_1, C, HID, NW> ffn1(reinterpret_cast<const T*>(p.w_1), wave);
+    GemmPhase<T, NT_1, C, HID, NW> ffn1(reinterpret_cast<const T*>(args->layer.w_1), wave);
     const int pf_turn = full_layer ? wave / (NW / 3) : -1;
     ffn1.forget();
     if (pf_turn == 0) ffn1.prefetch();
     f32x4 keep[NT_O][kOwnTiles];
-    QkvPhase qkv(reinterpret_cast<const T*>(p.w_qkv), wave);     // of the next tile
+    QkvPhase qkv(reinterpret_cast<const T*>(args->layer.w_qkv), wave);     // of the next tile
     if (HC == 1) oproj.template run_keep<1>(Qs, LDX, rt_own, bo4, keep);
     else if (HC == 2) oproj.template run_keep<2>(Qs, LDX, rt_own, bo4, keep);
     else if (kOwnTiles == 3 && HC == 3) oproj.template run_keep<kOwnTiles>(Qs, LDX, rt_own, bo4, keep);
@@ -665,7 +690,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     if (pf_turn == 1) ffn1.prefetch();
     if (!full_layer) {                           // attention and its projection only: raw Y goes out, one tile per workgroup
       if constexpr (kPairs) {
-        if (HC > 0) put_pair(tab, R, 16 * rt_own + m, HC > 1, o_own, pack4<T>(keep[0][0]), pack4<T>(keep[0][kOwnTiles - 1]));
+        if (HC > 0) put_pair(args->out, tab, R, 16 * rt_own + m, HC > 1, o_own, pack4<T>(keep[0][0]), pack4<T>(keep[0][kOwnTiles - 1]));
       } else {
 #pragma unroll
         for (int r = 0; r < kOwnTiles; ++r)
@@ -673,7 +698,7 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
             f32x4 y[NT_O];
 #pragma unroll
             for (int nt = 0; nt < NT_O; ++nt) y[nt] = keep[nt][r];
-            put_out(tab, R, 16 * (rt_own + r) + m, o_own, y);
+            put_out(args->out, tab, R, 16 * (rt_own + r) + m, o_own, y);
           }
       }
       return;
@@ -683,11 +708,11 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     layer_norm_tile<T, NT_O, C, kOwnTiles>(keep, o_own, og_own, rt_own, HC, stat, [&](int nt, f32x4& a, f32x4& b) {
       a = *reinterpret_cast<const f32x4*>(affine_lds + o_own + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
-    }, p.ln_eps, [&](int, int row, const f32x4 (&y)[NT_O]) {
+    }, args->layer.ln_eps, [&](int, int row, const f32x4 (&y)[NT_O]) {
 #pragma unroll
       for (int nt = 0; nt < NT_O; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
     });
-    if (more) store_desc(next_word, (int)L::kRowTab - tab);
+    if (more) store_desc(next_word, (int)L::kRowTab - tab, args->maps.n_voxels);
     lds_barrier();
     DSVT_REFRESH_LANE();
 
@@ -700,9 +725,9 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     // 120,000-voxel frame 707 / 699.  Slower than this at C = 192, each in one session with it: the matrix in three slices, two of
     // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
     // bias requested in front of the weights 0.1-0.7 %.
-    GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(p.w_2), wave);
+    GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(args->layer.w_2), wave);
     const float gelu0 = gelu_start(smem + L::off_gelu);
-    ffn1.run_before(Xs, LDX, RT, p.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
+    ffn1.run_before(Xs, LDX, RT, args->layer.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
 #pragma unroll
       for (int nt = 0; nt < NT_1; ++nt) {
         const int o = o0 + 16 * nt + 4 * g;
@@ -720,14 +745,14 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
     const int o_own2 = og_own * 16 * NT_2;
     f32x4 b24[NT_2];
 #pragma unroll
-    for (int nt = 0; nt < NT_2; ++nt) b24[nt] = *reinterpret_cast<const f32x4*>(p.b_2 + o_own2 + 16 * nt + 4 * g);
+    for (int nt = 0; nt < NT_2; ++nt) b24[nt] = *reinterpret_cast<const f32x4*>(args->layer.b_2 + o_own2 + 16 * nt + 4 * g);
     // The next tile's rows: in flight during the second product, stored over Q when every wavefront is through with it
     const int next_tab = (int)L::kRowTab - tab, next_RT = more ? row_tiles(tile_rows(next_tab)) : 0;
     uint4 gv[G];
-    bool live[G];
+    unsigned live = 0u;
 #pragma unroll
-    for (int k = 0; k < G; ++k) { opaque_def(gv[k].x); opaque_def(gv[k].y); opaque_def(gv[k].z); opaque_def(gv[k].w); live[k] = false; }
-    if (more) request_rows(gv, live, next_tab, next_RT);
+    for (int k = 0; k < G; ++k) { opaque_def(gv[k].x); opaque_def(gv[k].y); opaque_def(gv[k].z); opaque_def(gv[k].w); }
+    if (more) request_rows(gv, live, next_tab, next_RT, args->x);
     lds_barrier();
     DSVT_REFRESH_LANE();
     DSVT_PHASE(tile, 6);                             // H in LDS
@@ -750,19 +775,19 @@ k_layer(LayerDev p, MapsDev mp, const int4* __restrict__ coords, const T* x, T* 
       }
       a = *reinterpret_cast<const f32x4*>(affine_lds + 2 * C + o_own2 + 16 * nt + 4 * g);
       b = *reinterpret_cast<const f32x4*>(affine_lds + 3 * C + o_own2 + 16 * nt + 4 * g);
-    }, p.ln_eps, [&](int r, int row, const f32x4 (&y)[NT_2]) {
+    }, args->layer.ln_eps, [&](int r, int row, const f32x4 (&y)[NT_2]) {
       if constexpr (kPairs) {
         if (r == 0) held = pack4<T>(y[0]);
-        if (r + 1 == HC) put_pair(tab, R, row - 16 * r, r > 0, o_own2, held, pack4<T>(y[0]));
+        if (r + 1 == HC) put_pair(args->out, tab, R, row - 16 * r, r > 0, o_own2, held, pack4<T>(y[0]));
       } else {
-        put_out(tab, R, row, o_own2, y);
+        put_out(args->out, tab, R, row, o_own2, y);
       }
     });
     DSVT_PHASE(tile, 8);
     if (!more) return;
     DSVT_PHASE(next, 0);
     DSVT_PHASE(next, 1);
-    qkv.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
+    qkv.template prefetch_rest<kEarly>(args->layer.b_qkv, 2 * C / (16 * NT_QKV));
     tile = next;
     stride = 2 * (int)gridDim.x - stride;
     xo = 2 * (int)L::kTile - xo;
@@ -866,8 +891,8 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
   constexpr int64_t fit = kComputeUnits * groups_per_cu<T, C, HEADS, HID>(SETS);
   const unsigned grid = (unsigned)(full && mp.tiles.tile_desc && tiles > fit ? fit : tiles);
   dsvt_prof_scope ps(DSVT_K_LAYER, st);
-  kern<<<grid, kLayerWaves * 64, lds, st>>>(to_dev(w), md, reinterpret_cast<const int4*>(coords),
-                                       reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out), full);
+  const LayerCall<T> call = {to_dev(w), md, reinterpret_cast<const int4*>(coords), reinterpret_cast<const T*>(x), reinterpret_cast<T*>(out), full};
+  kern<<<grid, kLayerWaves * 64, lds, st>>>(call);
   return DSVT_OK;
 }
 

@@ -53,7 +53,7 @@ def test_instrumented_library_adds_one_symbol_only():
 
 
 def _kernel_metadata(lib):
-    """Name, spilled vector registers and scratch bytes per lane of every kernel in the library: the metadata notes of the
+    """Name, spilled vector registers, scratch bytes per lane and spilled scalar registers of every kernel in the library: the metadata notes of the
     gfx950 code objects in its offload bundles (a table of (offset, size, id length, id) behind a magic text and a count)."""
     import struct
     import subprocess
@@ -71,7 +71,8 @@ def _kernel_metadata(lib):
                     text = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True, text=True, check=True).stdout
                 for kernel in text.split("  - .agpr_count:")[1:]:
                     field = lambda name: re.search(rf"\.{name}: +(\S+)", kernel).group(1)
-                    out.append((field("symbol"), int(field("vgpr_spill_count")), int(field("private_segment_fixed_size"))))
+                    out.append((field("symbol"), int(field("vgpr_spill_count")), int(field("private_segment_fixed_size")),
+                                int(field("sgpr_spill_count"))))
         at = pos
     return out
 
@@ -83,6 +84,14 @@ def test_no_kernel_spills_vector_registers():
     kernels = _kernel_metadata(LIB)
     assert len([k for k in kernels if "k_layer" in k[0]]) == 18 and any("kp_attention" in k[0] for k in kernels)
     assert [k for k in kernels if k[1] or (k[2] and "k_layer" in k[0])] == []
+
+
+def test_layer_kernel_spills_no_scalar_registers():
+    """Every pointer of the arguments kept through the loop over tiles is two lanes of a vector register written and read back: up to 30 a
+    kernel, 2-5 % of a layer."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    assert [k for k in _kernel_metadata(LIB) if "k_layer" in k[0] and k[3]] == []
 
 
 @pytest.mark.parametrize("parts,compiles", [(1, True), (2, True), (3, False), (6, False)])
