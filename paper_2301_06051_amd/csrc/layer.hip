@@ -54,8 +54,9 @@ constexpr int kLayerWaves = 12;                  // three per SIMD: one workgrou
 
 // erf-GELU (appendix "Network Architecture": the MLP of a DSVT layer) for bf16 features by linear
 // interpolation: kGeluKnots intervals of width 1 / kGeluScale over [-4, 4), each with the slope
-// and intercept of the chord through the exact values at its ends; below -4 the result is 0, from
-// 4 on it is x (both within 1.4e-4 of the exact function; the chords are within 3.5e-5).  The
+// and intercept of the chord through the exact values at its ends; below -4 + 1/64 the result is 0, from
+// 4 - 1/64 on it is x - 6.5e-7 (both within 1.35e-4 of the exact function, from which x itself is 1.353e-4 away at the interval's
+// lower end and x - 6.5e-7 is 1.347e-4; the chords are within 3.5e-5).  The
 // table (4 KB) sits in LDS during the MLP: a lookup and one fma replace a dozen ALU instructions.
 constexpr int kGeluKnots = 512;
 constexpr float kGeluScale = 64.f;
@@ -157,7 +158,7 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t total = off_misc + kMisc;
   static_assert((size_t)kRowsMax * LDH * sizeof(T) <= 2 * kTile, "hidden tile must fit in Q + K");
   static_assert(C % 64 == 0 && D % Mma<T>::KL == 0 && D % 4 == 0, "shape");
-  static_assert(total <= 160 * 1024, "LDS of one CU");
+  static_assert(total <= 160 * 1024, "LDS of one CU");            // C = 192: 163,320 bytes, 520 below it
 };
 
 // Whether a tile leaves room in the LDS for a second workgroup on the compute unit: C = 64 in bf16.
@@ -349,7 +350,7 @@ template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(Set
 //
 // The grid is as many workgroups as fit the GPU at once; each takes every gridDim.x-th tile, back and forth (tiles are listed
 // most rows first).  What bounds it is not one unit but the chain of a tile's phases; a tile's beginning -- descriptor, then the
-// rows it names, then weights -- is 8 k of the 42 k clocks of a 64-row tile, and between two tiles of a workgroup all of it is
+// rows it names, then weights -- takes 8 k of the 42 k clocks of a workgroup's only 64-row tile, and between two tiles of a workgroup all of it is
 // under way during the tile before: the descriptor is requested behind the attention, the rows behind the first MLP matrix
 // (stored over Q once the second one is through with it; X and Q change places), the Q/K/V weights around the last LayerNorm.
 // The rows of a tile leave from registers, 16 bytes a lane, so no tile waits for a copy through LDS.  One tile a workgroup
@@ -897,13 +898,15 @@ int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* co
 }
 
 // Whether sets of 49 voxels and more take kSets96Slim, where a tile leaves room in the LDS for a second workgroup on the
-// compute unit (C = 64 in bf16): it also leaves room in the registers (68 of them, 80 with repeats as keys; kSets96: 106 and
-// 131), which pays once there are more tiles than compute units -- about max(48, 5 / 6 tau) voxels a tile -- and up to 72
-// voxels a set; beyond, fetching the table rows once for two heads is worth as much.  Two layers, 30 x 30 windows, kSets96 -> slim
-// (repeats as keys within 0.9 us of these): sets of up to 50 voxels 12,000 voxels 22.9 -> 26.0 us, 12,800 33.8 -> 27.7, 40,000
-// 68.0 -> 51.3; of up to 64 13,568 24.5 -> 28.6, 14,000 34.4 -> 31.4, 30,000 55.4 -> 48.0; of up to 72 15,000 26.5 -> 32.8,
-// 16,000 36.3 -> 34.7, 20,000 39.3 -> 39.8, 40,000 62.4 -> 60.6; of up to 80 16,000 27.5 -> 34.5, 18,000 37.0 -> 36.5,
-// 20,000 39.6 -> 41.6, 40,000 66.4 -> 63.7.
+// compute unit (C = 64 in bf16): it also leaves room in the registers (67 of them, 74 with repeats as keys; kSets96: 96 and
+// 104), which pays once there are more tiles than compute units -- about max(48, 5 / 6 tau) voxels a tile --; with larger sets,
+// fetching the table rows once for two heads is worth as much.  Two layers, kSets96 -> slim (repeats as keys within 0.9 us of
+// these).  30 x 30 windows, sets of up to 50 voxels: 12,000 voxels 20.0 -> 21.9 us, 12,800 29.6 -> 25.6, 20,000 31.8 -> 29.1, 40,000 57.7 -> 46.4; up
+// to 64: 13,568 21.6 -> 24.5, 14,000 29.9 -> 28.3, 20,000 34.4 -> 32.9, 40,000 51.8 -> 52.2; up to 72: 15,000 23.5 -> 28.4, 16,000
+// 31.6 -> 32.9, 20,000 34.9 -> 36.9, 40,000 53.9 -> 56.9; up to 80: 18,000 32.4 -> 34.7, 40,000 57.6 -> 62.5.  24 x 24 windows, up to 60: 25,000
+// 34.5 -> 32.5, 40,000 59.1 -> 46.3; up to 72: 25,000 35.2 -> 36.7, 40,000 52.5 -> 50.2, 60,000 71.7 -> 68.0.  Without a work list, 12 x 12 windows,
+// up to 50 to 64, slim takes a third less throughout.  So the line could lie at 64 where windows are full; and a frame whose tiles, few voxels over the
+// line, still fit the compute units once loses up to a fifth: 18,000 voxels in 24 x 24 windows, up to 60: 23.5 -> 28.2.  (The number of tiles is not known on the host.)
 bool slim_sets(const dsvt_maps& mp) {
   const int per_tile = 5 * mp.tau / 6 > 48 ? 5 * mp.tau / 6 : 48;
   return mp.tau <= 72 && mp.n_voxels > 256 * per_tile;

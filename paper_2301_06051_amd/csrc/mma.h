@@ -470,7 +470,8 @@ __device__ __forceinline__ void add_rows(f32x4 (&v)[NT][RH], const T* Xs, int ld
 }
 
 // (One lane-swap reduction serves two sums of two row tiles, and a row's sums lie together, three 16-byte reads at C = 192
-// where twelve 4-byte ones were: pass of 3,001 pillars 164.0 -> 160.3 us, 30,000 383.8 -> 379.1, skewed batch 7,937 -> 7,800.)
+// where twelve 4-byte ones were.  A reduction per sum and 4-byte reads -> this, one session: pass of 3,001 pillars 149.2 -> 147.1 us,
+// 30,000 376.7 -> 372.0, 120,000 voxels 682.5 -> 676.4, skewed batch 7,682 -> 7,610.)
 // LayerNorm over the C features of every row, for values spread over the workgroup in
 // accumulator layout: this wavefront holds features o0 .. o0 + 16*NT - 1 (group og of
 // SG = C / (16*NT)) of rows 16*(rt0 + r) + m, r < cnt (cnt = 0: only the barrier).  Per-group sums of x and x^2 (fp32) are

@@ -269,9 +269,11 @@ __device__ __forceinline__ void fill_tile_starts(const int32_t* P, uint16_t* jum
 // when it saves a whole round over the compute units, or when the frame takes more than two rounds anyway.  A frame
 // of a few rounds gets the capacity that puts its tile count just under a whole number of rounds (a last round of a
 // few full-size tiles costs as much as a full round); should the count still come out above it, the next number of
-// rounds is tried.  Frames of more than four rounds get the whole 96 rows (measured at seven rounds: fewer, fuller
-// tiles beat a full last round, 167 against 185 us per layer).  Same arguments as fill_tile_starts; every thread returns
-// the same answer.
+// rounds is tried.  Frames of more than four rounds get the whole 96 rows: fewer, fuller tiles beat a full last round.
+// Two layers, C = 192, cut -> filled: 15,000 pillars (two rounds become one) 71.1 -> 49.4 us, 20,000 74.8 -> 57.0, 35,000 (three
+// become two) 116.7 -> 92.6, 40,000 117.3 -> 99.0, 45,000 119.1 -> 118.5, 52,000 149.5 -> 132.2, 64,000 180 -> 164; 22,000 to 30,000 keep
+// the cut.  Five rounds and more, tuned capacity -> 96 rows: 80,000 pillars 197 -> 189, 120,000 voxels 295.4 -> 293.8, 200,000 483 -> 465.
+// Same arguments as fill_tile_starts; every thread returns the same answer.
 constexpr int32_t kTunedRounds = 4;
 __device__ __forceinline__ bool fill_wanted(int32_t total_rows, int32_t n_sets, int32_t rpc_max) {   // fill_tiles' first test
   if (n_sets <= 0 || rpc_max < 4) return false;
@@ -402,8 +404,9 @@ __device__ __forceinline__ int32_t set_rows(int32_t nu) {
 
 // Rows between two tile cuts: at most rpc_max = 100 - pad4(tau), so that a tile never exceeds 96 rows.  A frame
 // whose tiles would not fill the GPU's compute units once gets a smaller cut, i.e. more and shorter tiles on
-// more units (measured: a 3,000-voxel frame 28 -> 22 us per layer, 8,000 voxels 29 -> 26 us).  Larger frames keep
-// rpc_max: 12 k of a 64-row tile's 42 k clocks do not depend on its rows, so more tiles per unit buy nothing there.
+// more units (two layers, C = 192: 1,000 pillars 40.7 -> 25.8 us, 3,000 42.0 -> 31.8, 12,000 47.3 -> 43.2; C = 64 18.4 -> 13.0, 19.0 ->
+// 15.6, 20.6 -> 19.8).  Larger frames keep rpc_max: 11 k of a 64-row tile's 39 k clocks do not depend on its rows, so more tiles
+// per unit buy nothing there.
 __device__ __forceinline__ int32_t tile_cut(int32_t total_rows, int32_t rpc_max) {
   if (rpc_max < 16 || total_rows <= 0 || total_rows > rpc_max * kComputeUnits) return rpc_max;
   int32_t rpc = ((total_rows + kComputeUnits - 1) / kComputeUnits + 3) & ~3;     // at most 256 tiles
