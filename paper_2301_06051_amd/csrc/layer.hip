@@ -532,16 +532,16 @@ k_layer(LayerCall<T> call) {
     store_desc(word, tab, mp.n_voxels);
   } else {
     // ---- 1b. no work list: two sets per tile, rows derived from set_inds and coords
+    // (A set's slots stay in its wavefront's registers.  Read a second time once the rows are numbered -> kept: C = 64 bf16, attention of 300 voxels
+    // 5.44 -> 5.22 us, of 4,000 9.76 -> 9.34; C = 64 bf16, two layers of 20,000 voxels, sets of up to 64, 47.9 -> 46.6.)
     const int tau = mp.tau, s_begin = tile * per_wg, ns = n_sets - s_begin < per_wg ? n_sets - s_begin : per_wg;
     int32_t* hdr = header(tab);
     for (int r = tid; r < kRowsPad; r += NTHREADS) { row_vox(tab)[r] = -1; row_code(tab)[r] = 0; row_mult(tab)[r] = 0.f; }
-    for (int ls = wave; ls < ns; ls += NW) {
-      const int v = lane < tau ? mp.set_inds[(size_t)(s_begin + ls) * tau + lane] : -2;
-      const int prev = __shfl_up(v, 1, 64);
-      const bool first = lane < tau && (lane == 0 || v != prev);   // repeats are adjacent
-      const unsigned long long mask = __ballot(first);
-      if (lane == 0) hdr[kHdrNu + ls] = __popcll(mask);
-    }
+    const int v = wave < ns && lane < tau ? mp.set_inds[(size_t)(s_begin + wave) * tau + lane] : -2;      // (a wavefront has one set at most)
+    const int prev = __shfl_up(v, 1, 64);
+    const bool first = wave < ns && lane < tau && (lane == 0 || v != prev), valid = first && v >= 0 && v < mp.n_voxels;   // repeats are adjacent
+    const unsigned long long mask = __ballot(first);
+    if (wave < ns && lane == 0) hdr[kHdrNu + wave] = __popcll(mask);
     lds_barrier();
     if (tid == 0) {
       int r = 0;
@@ -550,20 +550,14 @@ k_layer(LayerCall<T> call) {
       hdr[1] = ns;
     }
     lds_barrier();
-    for (int ls = wave; ls < ns; ls += NW) {
-      const int v = lane < tau ? mp.set_inds[(size_t)(s_begin + ls) * tau + lane] : -2;
-      const int prev = __shfl_up(v, 1, 64);
-      const bool first = lane < tau && (lane == 0 || v != prev);
-      const unsigned long long mask = __ballot(first);
-      if (first && v >= 0 && v < mp.n_voxels) {
-        const int r = hdr[kHdrR0 + ls] + __popcll(mask & ((1ull << lane) - 1ull));
-        const unsigned long long later = mask >> (lane + 1);
-        const int run = later ? (__ffsll((long long)later)) : (tau - lane);   // slots holding this voxel
-        const int4 c = call.coords[v];
-        row_vox(tab)[r] = v;
-        row_mult(tab)[r] = (float)run;
-        row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)(HEADS * 4));
-      }
+    if (valid) {
+      const int r = hdr[kHdrR0 + wave] + __popcll(mask & ((1ull << lane) - 1ull));
+      const unsigned long long later = mask >> (lane + 1);
+      const int run = later ? (__ffsll((long long)later)) : (tau - lane);   // slots holding this voxel
+      const int4 c = call.coords[v];
+      row_vox(tab)[r] = v;
+      row_mult(tab)[r] = (float)run;
+      row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)(HEADS * 4));
     }
   }
   lds_barrier();
