@@ -63,7 +63,7 @@ constexpr float kGeluScale = 64.f;
 __global__ void k_pack_gelu_table(float2* __restrict__ tab) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= kGeluKnots) return;
-  const double x0 = (i - kGeluKnots / 2 - 0.0625) / (double)kGeluScale, x1 = x0 + 1.0 / kGeluScale;   // (see gelu_from_table)
+  const double x0 = (i - kGeluKnots / 2 - 0.0625) / (double)kGeluScale, x1 = x0 + 1.0 / kGeluScale;   // (see gelu_entry)
   const double g0 = 0.5 * x0 * (1.0 + erf(x0 * 0.70710678118654752440)), g1 = 0.5 * x1 * (1.0 + erf(x1 * 0.70710678118654752440));
   const double sl = (g1 - g0) * kGeluScale;
   float2 e = make_float2((float)sl, (float)(g0 - sl * x0));
@@ -82,11 +82,10 @@ __device__ __forceinline__ float gelu_start(const unsigned char* tab) {        /
   const unsigned at = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)tab;
   return __uint_as_float(0x4B000000u + at + kGeluKnots / 2 * 8);
 }
-__device__ __forceinline__ float gelu_from_table(float start, float x) {
+__device__ __forceinline__ f32x2 gelu_entry(float start, float x) {          // the result is entry.x * x + entry.y
   constexpr float kEnd = kGeluKnots / 2 / kGeluScale;
   const float t = fmaf(__builtin_amdgcn_fmed3f(x, -kEnd, kEnd - 0.125f / kGeluScale), 8.f * kGeluScale, start);
-  const f32x2 e = *(lds_pair)(uintptr_t)(__float_as_uint(t) & 0x3FFF8u);
-  return fmaf(e.x, x, e.y);
+  return *(lds_pair)(uintptr_t)(__float_as_uint(t) & 0x3FFF8u);
 }
 
 // Inclusive sum over the first 32 lanes of a wavefront (data-parallel-primitive shifts inside rows of 16 lanes, then lane 15's into
@@ -499,23 +498,19 @@ k_layer(LayerCall<T> call) {
     static_assert((C / 16) % NT_QKV == 0, "an item never straddles the Q/K/V boundary");
     const float q_scale = rsqrtf((float)L::D) * 1.4426950408889634f;
     const int o0 = wave * 16 * NT_QKV;
-    const auto store = [&](T* dst, int r, const f32x4 (&v)[NT_QKV]) {
-#pragma unroll
-      for (int nt = 0; nt < NT_QKV; ++nt) *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + 4 * g) = pack4<T>(v[nt]);
-    };
+    // (part k of a row tile's epilogue takes output tile k - 1)
+    const auto store = [&](T* dst, int r, int nt, const f32x4& v) { *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + 4 * g) = pack4<T>(v); };
     if (o0 >= 2 * C) {
-      qkv.template run_rows<true>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) {
-#pragma unroll
-        for (int nt = 0; nt < NT_QKV; ++nt)
-          *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * nt + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[nt]);
+      qkv.template run_rows<true>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+        if (k >= 1 && k <= NT_QKV) *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * (k - 1) + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[k - 1]);
       });
     } else if (o0 >= C) {
-      qkv.template run_rows<false>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) { store(Ks + (o0 - C), r, acc); });
+      qkv.template run_rows<false>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+        if (k >= 1 && k <= NT_QKV) store(Ks + (o0 - C), r, k - 1, acc[k - 1]);
+      });
     } else {
-      qkv.template run_rows<false>(Xs, LDX, RT, [&](int r, f32x4 (&acc)[NT_QKV]) {
-#pragma unroll
-        for (int nt = 0; nt < NT_QKV; ++nt) acc[nt] *= q_scale;      // logits in units of log2(e)
-        store(Qs + o0, r, acc);
+      qkv.template run_rows<false>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+        if (k >= 1 && k <= NT_QKV) store(Qs + o0, r, k - 1, acc[k - 1] * q_scale);      // logits in units of log2(e)
       });
     }
   };
@@ -662,7 +657,7 @@ k_layer(LayerCall<T> call) {
     lds_barrier();
     DSVT_REFRESH_LANE();
     DSVT_PHASE(tile, 4);                               // attention done
-    static_assert(L::total < 0x40000 && L::off_gelu % 8 == 0, "gelu_from_table's addresses");
+    static_assert(L::total < 0x40000 && L::off_gelu % 8 == 0, "gelu_entry's addresses");
     const float* affine_lds = reinterpret_cast<const float*>(smem + L::off_aff);
     if (full_layer && tid < kVecThreads)
       *reinterpret_cast<f32x4*>(smem + (tid < kGeluThreads ? L::off_gelu : L::off_aff - kGeluThreads * 16) + tid * 16) = late;
@@ -722,16 +717,19 @@ k_layer(LayerCall<T> call) {
     // bias requested in front of the weights 0.1-0.7 %.
     GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(args->layer.w_2), wave);
     const float gelu0 = gelu_start(smem + L::off_gelu);
-    ffn1.run_before(Xs, LDX, RT, args->layer.b_1, [&](int o0, int r, f32x4 (&acc)[NT_1]) {
+    // Parts of a row tile's epilogue: the table entries of output tile 0, 1, .. requested, then the values of output tile 0, 1, ..
+    f32x2 chord[NT_1][4];
+    ffn1.run_before(Xs, LDX, RT, args->layer.b_1, [&](int k, int o0, int r, f32x4 (&acc)[NT_1]) {
+      if (kGeluTable && k < NT_1) {
 #pragma unroll
-      for (int nt = 0; nt < NT_1; ++nt) {
-        const int o = o0 + 16 * nt + 4 * g;
+        for (int i = 0; i < 4; ++i) chord[k][i] = gelu_entry(gelu0, acc[k][i]);
+      }
+      if (k >= NT_1 && k < 2 * NT_1) {
+        const int nt = k - NT_1;
         f32x4 v = acc[nt];
-        if constexpr (kGeluTable)
-          v = f32x4{gelu_from_table(gelu0, v[0]), gelu_from_table(gelu0, v[1]), gelu_from_table(gelu0, v[2]), gelu_from_table(gelu0, v[3])};
-        else
-          v = f32x4{gelu_erf_fast(v[0]), gelu_erf_fast(v[1]), gelu_erf_fast(v[2]), gelu_erf_fast(v[3])};
-        *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o) = pack4<T>(v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = kGeluTable ? fmaf(chord[nt][i].x, v[i], chord[nt][i].y) : gelu_erf_fast(v[i]);
+        *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o0 + 16 * nt + 4 * g) = pack4<T>(v);
       }
     }, [&]() {
       ffn2.forget();

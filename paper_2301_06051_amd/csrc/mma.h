@@ -154,6 +154,7 @@ __device__ __forceinline__ void mma_row_swapped(f32x4 (&acc)[NT], const AFull<T,
 constexpr int kRowTiles = 6;                     // row tiles of a workgroup tile
 constexpr int kRowsMax = 16 * kRowTiles;         // 96 rows
 constexpr int kWaves = 8;                        // wavefronts of a pooling workgroup, two per SIMD
+constexpr int kKeepRing = 4;                     // see GemmPhase::run_keep() (six fragments spill at C = 192; three and five: no difference)
 constexpr int kStatGroupsMax = 6;                // LayerNorm phases: the C features are split over at most 6 groups of output tiles
 
 // One GEMM phase of a workgroup of NW wavefronts: Out^T[NOUT x rows] = W[NOUT x K] . X^T.
@@ -281,104 +282,107 @@ struct GemmPhase {
     }
   }
 
-  // run() of a phase of one item per wavefront, over all row tiles (RT > 0).  prefetch_rest() has fetched the bias.
-  template <bool SWAPPED> __device__ __forceinline__ void mma_tile(f32x4 (&acc)[NT], const f32x4 (&start)[NT], const BRow<T, NKF>& b) const {
+  // One row tile, k-fragment by k-fragment: its MFMAs, the same fragment of the row tile at `next` (this lane's piece of it)
+  // into the registers just read, then part kf of what the caller has to do meanwhile.  The order is fixed: left to
+  // itself the compiler reads a fragment right in front of its MFMAs to save registers, and every one of them waits for LDS.
+  // Two row tiles a trip, fragments and table entries where the compiler puts them -> this and run_keep() as it is now: clocks of a 64-row
+  // tile of C = 192 38.6 k -> 37.2 k (Q/K/V 6.8 -> 6.3 k, second MLP matrix 5.6 -> 5.1 k, first one 7.25 -> 7.0 k), of an 82-row tile 46.2 -> 44.4 k;
+  // passes of 3,001 pillars 146.0 -> 141.8 us, 30,000 339.5 -> 331.4, four frames 1,067 -> 1,030, 30 x 30 windows 273.7 -> 265.6,
+  // 120,000 voxels 647.7 -> 631.3, skewed batch 7,217 -> 7,158 (in long runs the clock falls as the units get busier: 2.31 -> 2.25 GHz).
+  template <bool SWAPPED, typename Part>
+  __device__ __forceinline__ void row_step(f32x4 (&acc)[NT], const f32x4 (&start)[NT], BRow<T, NKF>& b, const T* next, Part part) const {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = start[nt];
-    if (SWAPPED) mma_row_swapped<T, NT, NKF>(acc, a[0], b); else mma_row<T, NT, NKF>(acc, a[0], b);
+    for (int kf = 0; kf < NKF; ++kf) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const f32x4 c = kf == 0 ? start[nt] : acc[nt];
+        acc[nt] = SWAPPED ? Mma<T>::mma(b.f[kf], a[0].f[kf][nt], c) : Mma<T>::mma(a[0].f[kf][nt], b.f[kf], c);
+      }
+      b.f[kf] = *reinterpret_cast<const typename Mma<T>::Frag*>(next + kf * KC);
+      part(kf);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+  // All row tiles (RT > 0) of one item.  The epilogue of a row tile runs in NKF parts -- epi(part, r, acc) -- beside the next one's
+  // MFMAs; before_last() is called in front of the last one's, where the weights' registers are free.
+  template <bool SWAPPED, typename Epi, typename Before>
+  __device__ __forceinline__ void row_steps(const T* Xs, int ldx, int RT, const f32x4 (&start)[NT], Epi epi, Before before_last) const {
+    const int lane = opaque_tid() & 63;
+    const T* next = Xs + (lane & 15) * ldx + (lane >> 4) * Mma<T>::KL;
+    f32x4 acc0[NT], acc1[NT];
+    BRow<T, NKF> b;
+#pragma unroll
+    for (int kf = 0; kf < NKF; ++kf) b.f[kf] = *reinterpret_cast<const typename Mma<T>::Frag*>(next + kf * KC);
+    const auto advance = [&](int r) { next += r + 1 < RT ? 16 * ldx : 0; };
+    advance(0);
+    row_step<SWAPPED>(acc0, start, b, next, [](int) {});
+    int r = 1;
+    for (; r + 1 < RT; r += 2) {
+      advance(r);
+      row_step<SWAPPED>(acc1, start, b, next, [&](int k) { epi(k, r - 1, acc0); });
+      advance(r + 1);
+      row_step<SWAPPED>(acc0, start, b, next, [&](int k) { epi(k, r, acc1); });
+    }
+    if (r < RT) {
+      row_step<SWAPPED>(acc1, start, b, next, [&](int k) { epi(k, r - 1, acc0); });
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc0[nt] = acc1[nt];
+      ++r;
+    }
+    before_last();
+#pragma unroll
+    for (int k = 0; k < NKF; ++k) epi(k, r - 1, acc0);
+  }
+  // run() of a phase of one item per wavefront, over all row tiles.  prefetch_rest() has fetched the bias.
   template <bool SWAPPED, typename Epi>
-  __device__ __forceinline__ void run_rows(const T* Xs, int ldx, int RT, Epi epi) {
+  __device__ __forceinline__ void run_rows(const T* Xs, int ldx, int RT, Epi epi) const {
     static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1 && N_ITEMS == NW, "one item per wavefront");
     f32x4 b4[NT];
     start_bias(b4, bias0, SWAPPED);
-    BRow<T, NKF> b0, b1;
-    load_b<T, NKF>(b0, Xs, ldx, 0);
-    int r = 0;
-    for (; r + 1 < RT; r += 2) {
-      f32x4 acc0[NT], acc1[NT];
-      load_b<T, NKF>(b1, Xs, ldx, r + 1);
-      mma_tile<SWAPPED>(acc0, b4, b0);
-      load_b<T, NKF>(b0, Xs, ldx, r + 2 < RT ? r + 2 : r);
-      mma_tile<SWAPPED>(acc1, b4, b1);
-      epi(r, acc0);
-      epi(r + 1, acc1);
-    }
-    if (r < RT) {
-      f32x4 acc0[NT];
-      mma_tile<SWAPPED>(acc0, b4, b0);
-      epi(r, acc0);
-    }
+    row_steps<SWAPPED>(Xs, ldx, RT, b4, epi, []() {});
   }
 
-  // The same with the bias fetched here and before_last_epi() called between the last MFMAs and the epilogue of the last one
-  // or two row tiles: the weights' registers are free there, and what it requests travels while the epilogue computes.  (One
-  // place for the call: at two, the compiler keeps the undefined values of the one alive on the way to the other and spills.)
+  // The same with the bias fetched here and before_last_epi() called between the last MFMAs and the last epilogue: what it requests
+  // travels while the epilogue computes.
   template <typename Epi, typename Before>
-  __device__ __forceinline__ void run_before(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, Before before_last_epi) {
+  __device__ __forceinline__ void run_before(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, Before before_last_epi) const {
     static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1, "one item per wavefront");
-    const int o0 = wave * 16 * NT;
-    f32x4 acc0[NT], acc1[NT];
-    const bool some = N_ITEMS >= NW || wave < N_ITEMS;
-    int r = 0;
-    if (some) {
+    if (N_ITEMS >= NW || wave < N_ITEMS) {
       Bias bl;
       load_bias(bl, bias, wave, false);
-      BRow<T, NKF> b0, b1;
-      load_b<T, NKF>(b0, Xs, ldx, 0);
-      for (; r + 2 < RT; r += 2) {
-        load_b<T, NKF>(b1, Xs, ldx, r + 1);
-        mma_tile<false>(acc0, bl.v, b0);
-        load_b<T, NKF>(b0, Xs, ldx, r + 2);
-        mma_tile<false>(acc1, bl.v, b1);
-        epi(o0, r, acc0);
-        epi(o0, r + 1, acc1);
-      }
-      if (r + 1 < RT) {
-        load_b<T, NKF>(b1, Xs, ldx, r + 1);
-        mma_tile<false>(acc0, bl.v, b0);
-        mma_tile<false>(acc1, bl.v, b1);
-      } else {
-        mma_tile<false>(acc0, bl.v, b0);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) opaque_def(acc1[nt]);
-      }
+      row_steps<false>(Xs, ldx, RT, bl.v, [&](int k, int r, f32x4 (&acc)[NT]) { epi(k, wave * 16 * NT, r, acc); }, before_last_epi);
     } else {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) { opaque_def(acc0[nt]); opaque_def(acc1[nt]); }
-    }
-    before_last_epi();
-    if (some) {
-      epi(o0, r, acc0);
-      if (r + 1 < RT) epi(o0, r + 1, acc1);
+      before_last_epi();
     }
   }
 
   // One item per wavefront: row tiles rt0 .. rt0 + HC - 1 unrolled, all accumulators returned
-  // (the LayerNorm phases need a row's values in registers across a workgroup barrier).  With
-  // KSPLIT > 1 the weights pass through the registers one K-slice at a time.
+  // (the LayerNorm phases need a row's values in registers across a workgroup barrier).  k-fragment by k-fragment over all row
+  // tiles, so that with KSPLIT > 1 the next slice of K is requested into a fragment's registers as soon as that is used; the activations
+  // are read kKeepRing fragments ahead.  (In fixed order, see row_step().)
   template <int HC>
   __device__ __forceinline__ void run_keep(const T* Xs, int ldx, int rt0, const f32x4 (&b4)[NT], f32x4 (&acc)[NT][RH]) {
     static_assert(IPW == 1 && HC <= RH, "one item per wavefront");
+    typedef typename Mma<T>::Frag Frag;
+    constexpr int ALL = NKF_ALL * HC, RING = ALL < kKeepRing ? ALL : kKeepRing;       // activation fragments, k by k and row tile by row tile
+    const int lane = opaque_tid() & 63;
+    const T* xp = Xs + (16 * rt0 + (lane & 15)) * ldx + (lane >> 4) * Mma<T>::KL;
+    const Frag* wp = reinterpret_cast<const Frag*>(Wp) + (size_t)((wave % N_OG) * NT) * NKF_ALL * 64 + lane;
+    const auto read = [&](int f) { return *reinterpret_cast<const Frag*>(xp + 16 * (f % HC) * ldx + f / HC * KC); };
+    Frag b[RING];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int f = 0; f < RING; ++f) b[f] = read(f);
 #pragma unroll
-      for (int r = 0; r < HC; ++r) acc[nt][r] = b4[nt];
+    for (int f = 0; f < ALL; ++f) {
+      const int kf = f / HC, r = f % HC;
 #pragma unroll
-    for (int ks = 0; ks < KSPLIT; ++ks) {
-      if (ks > 0) load_a<T, NT, NKF, NKF_ALL>(a[0], Wp, (wave % N_OG) * NT, ks * NKF);
-      BRow<T, NKF> b[2];
-      load_b<T, NKF>(b[0], Xs, ldx, rt0, ks * NKF * KC);
+      for (int nt = 0; nt < NT; ++nt) acc[nt][r] = Mma<T>::mma(a[0].f[kf % NKF][nt], b[f % RING], kf == 0 ? b4[nt] : acc[nt][r]);
+      if (f + RING < ALL) b[f % RING] = read(f + RING);
+      if (r == HC - 1 && kf + NKF < NKF_ALL) {
 #pragma unroll
-      for (int r = 0; r < HC; ++r) {
-        if (r + 1 < HC) load_b<T, NKF>(b[(r + 1) & 1], Xs, ldx, rt0 + r + 1, ks * NKF * KC);
-        f32x4 t[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) t[nt] = acc[nt][r];
-        mma_row<T, NT, NKF>(t, a[0], b[r & 1]);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[nt][r] = t[nt];
+        for (int nt = 0; nt < NT; ++nt) a[0].f[kf % NKF][nt] = wp[(nt * NKF_ALL + kf + NKF) * 64];
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
