@@ -21,6 +21,7 @@ constexpr int kMaxSets = kRowsMax / 4;           // every set takes at least 4 r
 constexpr int kRowsPad = kRowsMax + 16;          // per-row arrays are read 4 at a time up to 15 rows past a set's end
 constexpr int kHdrWords = 64;                   // header of a tile descriptor: rows, sets, the sets' first rows, their distinct voxels
 constexpr int kHdrR0 = 2, kHdrNu = kHdrR0 + kMaxSets;
+constexpr int kRelRow = 16;                      // bytes of a position table's row: four heads
 constexpr int kSetWords = 32;                   // set table of the attention phase, see set_word()
 static_assert(kMaxSets <= kSetWords && kHdrNu + kSetWords <= kHdrWords, "a word per set");
 // Sets per workgroup when no tile list is given.
@@ -78,6 +79,7 @@ __global__ void k_pack_gelu_table(float2* __restrict__ tab) {
 // of the 30,000-pillar frame 365.9 -> 363.6 us, 120,000 voxels 660.5 -> 655.1, skewed batch 7,380 -> 7,334.
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(3))) f32x2* lds_pair;
+typedef const __attribute__((address_space(3))) unsigned char* lds_byte;
 __device__ __forceinline__ float gelu_start(const unsigned char* tab) {        // of every lookup: 2^23 + address of the interval of x = 0
   const unsigned at = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)tab;
   return __uint_as_float(0x4B000000u + at + kGeluKnots / 2 * 8);
@@ -104,7 +106,8 @@ struct LayerDev {
   const float *b_qkv, *b_o, *b_1, *b_2, *ln1_g, *ln1_b, *ln2_g, *ln2_b, *rel_bias;
   const float2* gelu_tab;                    // kGeluKnots (slope, intercept) pairs, see k_pack_gelu_table
   float ln_eps;
-  // position table [index][heads], in bytes (below 2^32): index of (q, k) = code(q) - code(k) + rel_const, at most rel_last; rel_none: the row of -inf
+  // position table [heads / 4][index][4], an index in bytes of a row of four heads (below 2^32): index of (q, k) = code(q) - code(k) + rel_const, at most
+  // rel_last; rel_none: the row of -inf, the last one
   unsigned rel_const, rel_last, rel_none;
   int rel_my, rel_mz;
 };
@@ -171,6 +174,10 @@ template <typename T, int C, int HEADS, int HID> constexpr bool two_groups_fit()
 // 3,000 29.7 -> 29.1, C = 128 18.8 -> 18.2 and 23.6 -> 23.3, C = 192 25.0 -> 24.4 and 33.2 -> 32.3.
 template <typename T, int C, int HEADS, int HID> constexpr int split_key_tiles() { return two_groups_fit<T, C, HEADS, HID>() ? 2 : 3; }
 
+// LDS by its 32-bit address: constants added to it become the instruction's offset.
+template <typename V> __device__ __forceinline__ V lds_read(int at) { return *(const __attribute__((address_space(3))) V*)(uintptr_t)(unsigned)at; }
+template <typename V> __device__ __forceinline__ void lds_write(int at, V v) { *(__attribute__((address_space(3))) V*)(uintptr_t)(unsigned)at = v; }
+
 // Attention of one (set, query tile, group of heads) item (Eq. 5): for each of its heads,
 // logits = Q K^T (+ PE), softmax over the set's distinct voxels, O = P V; O overwrites the Q
 // entries it was computed from.  KTC = key tiles of the set (compile time: no branches inside).
@@ -178,18 +185,25 @@ template <typename T, int C, int HEADS, int HID> constexpr int split_key_tiles()
 // softmax reductions are in-lane plus two cross-lane steps, and P^T is already laid out as the B
 // operand of O^T = V^T P^T.  Q arrives scaled by log2(e) / sqrt(d) (the projection's epilogue does
 // it), and the positional term -- which depends on (query, key) only through the coordinate
-// difference, one table row [index][heads] per pair, fetched once for all heads -- is the MFMA's
-// initial accumulator value, so the logits come out of the matrix cores finished.  The keys past
+// difference -- comes from a table, one row of four heads per pair, fetched once for all heads of the item.  The keys past
 // the set's last voxel take the table's extra last row, which holds -inf: no mask arithmetic.
 // DUP: repeated slots count as keys (the exponentials are multiplied by the slots' counts).
 // One basic block: lanes past the head width read their queries from 16 zero bytes, and queries that do not exist are written
 // to a spare place, so that nothing stands between the heads and their instructions mix.  Everything a head adds to an
-// address is a constant, i.e. an offset in the instruction.  (Before, with a branch around every such read and write and the
-// addresses computed head by head: 450 instructions an item of two key tiles and four heads, 370 now.  Pass of the
-// 30,000-pillar frame 359.1 -> 354.2 us, windows of 12 and 24 cells 507.6 -> 502.7, four frames 1,078 -> 1,065, 120,000 voxels 653.1
-// -> 648.6, skewed batch 7,383 -> 7,318; 30 x 30 windows, sets of four to six key tiles, 290.0 -> 290.9.)  Tried: the first item's
-// positional terms requested in front of the output projection's weights, behind which they come back -- 48 more registers across
-// the barrier, spills, and with those weights requested behind the attention instead no gain.
+// address is a constant, i.e. an offset in the instruction.
+// What bounds it is the issue of vector instructions (an item of two key tiles and four heads: 36 exp and rcp at a quarter of the rate and
+// 250 others, 3 wavefronts a SIMD) and, within a head, one dependent step after the other.  So the heads go through the steps side by side -- all
+// products with the keys, all maxima, .. --, the heads' maxima share the lane swaps (col_reduce()), the terms are added behind the
+// products (as the MFMAs' start values they had to be moved into place, an instruction each too, and to be there first), and in bf16 the
+// sums of the probabilities come from the matrix cores, from a fragment of ones: every lane gets them, from the very bf16 probabilities the
+// numerators have, added in 32 bits.  (Against 64 bits the outputs of whole stacks are nearer than with 32-bit sums of the probabilities before
+// they are rounded: 0.997 to 0.9998 of that distance on 15 frames, C = 128 and 192, five to ten seeds each.)  Head after head, 336 + 36 instructions and 46 waits -> this,
+// attention of a 64-row tile 7.6 -> 6.3 k clocks, of an 82-row tile 10.5 -> 9.0 k; passes of 3,001 pillars 141.9 -> 138.7 us, 30,000 337.6 -> 328.1,
+// windows of 12 and 24 cells 472.8 -> 456.8, 30 x 30 windows 267.7 -> 265.0, 120,000 voxels 619.7 -> 602.7 (32-bit sums: 138.7, 330.5, 458.1, 265.8, 604.1).  Position
+// table rows of all heads -> of four: 30 x 30 windows 264.8 -> 261.2 (a table of 111 KB: the rows that a load touches lie in half as many
+// lines), 12 x 12 windows no difference.
+// Tried: the first item's positional terms requested in front of the output projection's weights, behind which they come back -- 48 more
+// registers across the barrier, spills, and with those weights requested behind the attention instead no gain.
 template <typename T, int C, int HEADS, int HID, int KTC, int HG, bool DUP>
 __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char* smem, int q_off, const int32_t* row_code,
                                           const float* row_mult, int r0, int nu, int qt, int hh, int rows_ready) {
@@ -203,16 +217,20 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   constexpr int NCH = (KTC + TPC - 1) / TPC;
   static_assert(HG == 1 || HG == 2 || HG == 4, "heads per item");
   static_assert(D <= KC, "one fragment per query");
+  constexpr bool kSumByMma = sizeof(T) == 2;
+  constexpr int HS = C == 192 && KTC > 4 ? 1 : HG;                // heads side by side (two heads of six key tiles spill eight registers at C = 192)
   const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
   const int qi = 16 * qt + m;
   const int qrow = r0 + (qi < nu ? qi : nu - 1);
   const int h0 = hh * HG * D * ES;                // this item's heads in a row
 
-  f32x4 bias[HG][KTC];
+  // The keys' positional terms, one table row per (query, key) for all heads of the item
+  typedef float Terms __attribute__((ext_vector_type(HG)));          // (indexed by head)
+  Terms bias[KTC][4];
   {
     const unsigned qc = (unsigned)row_code[qrow] + p.rel_const;
     const int left = nu - (16 * (KTC - 1) + 4 * g);                // keys of the last tile from this lane's first on
-    const char* tab = reinterpret_cast<const char*>(p.rel_bias) + hh * HG * 4;
+    const char* tab = reinterpret_cast<const char*>(p.rel_bias) + (size_t)(hh * HG / 4) * ((size_t)p.rel_none + kRelRow) + hh * HG % 4 * 4;
 #pragma unroll
     for (int kt = 0; kt < KTC; ++kt) {
       const int4 kl = *reinterpret_cast<const int4*>(row_code + r0 + 16 * kt + 4 * g);
@@ -221,28 +239,18 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
       for (int i = 0; i < 4; ++i) {
         unsigned at = min(qc - (unsigned)kls[i], p.rel_last);      // (modulo 2^32: right for every index of the table)
         if (kt == KTC - 1) at = i < left ? at : p.rel_none;        // only the last key tile is ragged
-        const float* tp = reinterpret_cast<const float*>(tab + at);
-        if constexpr (HG == 4) {
-          const f32x4 t = *reinterpret_cast<const f32x4*>(tp);
-          bias[0][kt][i] = t[0]; bias[1][kt][i] = t[1]; bias[2][kt][i] = t[2]; bias[3][kt][i] = t[3];
-        } else if constexpr (HG == 2) {
-          const float2 t = *reinterpret_cast<const float2*>(tp);
-          bias[0][kt][i] = t.x; bias[1][kt][i] = t.y;
-        } else {
-          bias[0][kt][i] = *tp;
-        }
+        bias[kt][i] = *reinterpret_cast<const Terms*>(tab + at);
       }
     }
   }
+  const int lds0 = (int)(uintptr_t)(lds_byte)smem;
   const bool live = g * KL < D;                   // lanes past the head width
-  int q_at = live ? q_off + qrow * PX + h0 + g * KL * ES : (int)L::off_zero;
+  const int q_at = lds0 + (live ? q_off + qrow * PX + h0 + g * KL * ES : (int)L::off_zero);
   const int q_step = live ? D * ES : 0;
   int k_at[KTC];
 #pragma unroll
-  for (int kt = 0; kt < KTC; ++kt) {              // (dead k lanes: finite K times the zero Q)
-    const int ki = 16 * kt + m;
-    k_at[kt] = (int)L::off_k + (r0 + (ki < nu ? ki : nu - 1)) * PX + h0 + (live ? g * KL * ES : 0);
-  }
+  for (int kt = 0; kt < KTC; ++kt)                // (dead k lanes: finite K times the zero Q)
+    k_at[kt] = lds0 + (int)L::off_k + (r0 + min(16 * kt + m, nu - 1)) * PX + h0 + (live ? g * KL * ES : 0);
   // Key columns past the tile's rows hold no V: their P is an exact zero, so any finite column will do, and the set's first
   // one is read instead.  (Rows past the head width: the tile's row of a lane below it; results thrown away.)
   constexpr int DT = (D + 15) / 16;
@@ -252,71 +260,93 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
 #pragma unroll
     for (int c = 0; c < NCH * TPC; ++c) {
       const int col = r0 + 16 * c + 4 * g, dv = 16 * dt + m;
-      v_at[dt][c] = (int)L::off_v + hh * HG * D * PV + (dv < D ? dv : m) * PV + (col < rows_ready ? col : r0) * ES;
+      v_at[dt][c] = lds0 + (int)L::off_v + hh * HG * D * PV + (dv < D ? dv : m) * PV + (col < rows_ready ? col : r0) * ES;
     }
   int o_at[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
-    o_at[dt] = qi < nu && 16 * dt + 4 * g < D ? q_off + qrow * PX + h0 + (16 * dt + 4 * g) * ES : (int)L::off_spare;
+    o_at[dt] = lds0 + (qi < nu && 16 * dt + 4 * g < D ? q_off + qrow * PX + h0 + (16 * dt + 4 * g) * ES : (int)L::off_spare);
 
 #pragma unroll
-  for (int hl = 0; hl < HG; ++hl) {
-    f32x4 S[KTC];                                 // S[kt][i]: key 16*kt + 4*g + i, query 16*qt + m
-    const Frag fq = *reinterpret_cast<const Frag*>(smem + q_at);
-    q_at += q_step;
+  for (int hb = 0; hb < HG; hb += HS) {
+    f32x4 S[HS][KTC];                               // S[hl][kt][i]: key 16*kt + 4*g + i, query 16*qt + m
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt) S[kt] = M::mma(*reinterpret_cast<const Frag*>(smem + k_at[kt] + hl * D * ES), fq, bias[hl][kt]);
-    // S holds the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
-    // (fmaxf and not raw_max: an asm statement that reads a matrix instruction's result would not be given the wait it needs)
-    float mx = S[0][0];
+    for (int hl = 0; hl < HS; ++hl) {
+      const Frag fq = lds_read<Frag>(q_at + (hb + hl) * q_step);
 #pragma unroll
-    for (int k = 1; k < 4 * KTC; ++k) mx = fmaxf(mx, S[k >> 2][k & 3]);
-    mx = col_max(mx);                             // (key 0 exists for every query: finite)
-    float sum = 0.f;
+      for (int kt = 0; kt < KTC; ++kt) S[hl][kt] = M::mma(lds_read<Frag>(k_at[kt] + (hb + hl) * D * ES), fq, f32x4{0.f, 0.f, 0.f, 0.f});
+    }
+    // S + terms: the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
+    float mx[HS];
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt) {
-      f32x4 mult;
-      if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * kt + 4 * g);
+    for (int hl = 0; hl < HS; ++hl) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float e = __builtin_amdgcn_exp2f(S[kt][i] - mx);       // exp2(-inf) = 0
-        if constexpr (DUP) e *= mult[i];
-        S[kt][i] = e;
-        sum = kt + i == 0 ? e : sum + e;
+      for (int k = 0; k < 4 * KTC; ++k) {
+        float& x = reinterpret_cast<float(&)[4]>(S[hl][k >> 2])[k & 3];
+        x += bias[k >> 2][k & 3][hb + hl];
+        mx[hl] = k == 0 ? x : fmaxf(mx[hl], x);
       }
     }
-    sum = col_sum(sum);
-    const float inv = __builtin_amdgcn_rcpf(sum);
-
-    // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q]
-    Frag fp[NCH];
+    col_reduce(mx, [](float a, float b) { return raw_max(a, b); }, [](float a) { return a; });     // (key 0 exists for every query: finite)
+    float sum[HS];
+    Frag fp[HS][NCH];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      if constexpr (TPC == 2) {
-        const f32x4 p0 = S[2 * c], p1 = 2 * c + 1 < KTC ? S[2 * c + 1 < KTC ? 2 * c + 1 : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
-        fp[c] = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
-      } else {
-        fp[c] = S[c];
+    for (int hl = 0; hl < HS; ++hl) {
+#pragma unroll
+      for (int kt = 0; kt < KTC; ++kt) {
+        f32x4 mult;
+        if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * kt + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
+          if constexpr (DUP) e *= mult[i];
+          S[hl][kt][i] = e;
+          if constexpr (!kSumByMma) sum[hl] = kt + i == 0 ? e : sum[hl] + e;
+        }
       }
-    }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-      f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
-        Frag fv;
         if constexpr (TPC == 2) {
-          const bf16x4 lo = *reinterpret_cast<const bf16x4*>(smem + v_at[dt][2 * c] + hl * D * PV);
-          bf16x4 hi = {0, 0, 0, 0};
-          if (2 * c + 1 < KTC) hi = *reinterpret_cast<const bf16x4*>(smem + v_at[dt][2 * c + 1] + hl * D * PV);
-          fv = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          const f32x4 p0 = S[hl][2 * c], p1 = 2 * c + 1 < KTC ? S[hl][2 * c + 1 < KTC ? 2 * c + 1 : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
+          fp[hl][c] = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
         } else {
-          fv = *reinterpret_cast<const Frag*>(smem + v_at[dt][c] + hl * D * PV);
+          fp[hl][c] = S[hl][c];
         }
-        O = M::mma(fv, fp[c], O);
       }
-      *reinterpret_cast<Vec4*>(smem + o_at[dt] + hl * D * ES) = pack4<T>(O * inv);
     }
+    // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q]
+    f32x4 O[HS][DT];
+#pragma unroll
+    for (int hl = 0; hl < HS; ++hl) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          Frag fv;
+          if constexpr (TPC == 2) {
+            const bf16x4 lo = lds_read<bf16x4>(v_at[dt][2 * c] + (hb + hl) * D * PV);
+            bf16x4 hi = {0, 0, 0, 0};
+            if (2 * c + 1 < KTC) hi = lds_read<bf16x4>(v_at[dt][2 * c + 1] + (hb + hl) * D * PV);
+            fv = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          } else {
+            fv = lds_read<Frag>(v_at[dt][c] + (hb + hl) * D * PV);
+          }
+          O[hl][dt] = M::mma(fv, fp[hl][c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : O[hl][dt]);
+        }
+      }
+      if constexpr (kSumByMma) {
+        const bf16_t one = (bf16_t)1.f;
+        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) t = M::mma(Frag{one, one, one, one, one, one, one, one}, fp[hl][c], t);
+        sum[hl] = __builtin_amdgcn_rcpf(t[0]);
+      }
+    }
+    if constexpr (!kSumByMma) col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
+#pragma unroll
+    for (int hl = 0; hl < HS; ++hl)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) lds_write<Vec4>(o_at[dt] + (hb + hl) * D * ES, pack4<T>(O[hl][dt] * sum[hl]));
   }
 }
 
@@ -426,7 +456,7 @@ k_layer(LayerCall<T> call) {
       if ((tid & 1) == 0) {
         row_vox(t)[r] = (word >= 0 && word < n_voxels) ? word : -1;
       } else {
-        row_code(t)[r] = (word & 0xFFFFFF) * (HEADS * 4);
+        row_code(t)[r] = (word & 0xFFFFFF) * kRelRow;
         if constexpr (DUP) row_mult(t)[r] = (float)((unsigned)word >> 24);
       }
     }
@@ -552,7 +582,7 @@ k_layer(LayerCall<T> call) {
       const int4 c = call.coords[v];
       row_vox(tab)[r] = v;
       row_mult(tab)[r] = (float)run;
-      row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)(HEADS * 4));
+      row_code(tab)[r] = (int)((unsigned)((c.y * p.rel_my + c.z) * p.rel_mz + c.w) * (unsigned)kRelRow);
     }
   }
   lds_barrier();
@@ -796,14 +826,14 @@ k_layer(LayerCall<T> call) {
 
 // ------------------------------------------------------------------------------------------
 // Packed buffer of a layer: the four matrices in fragment order, each on a 256-byte boundary.
-struct PackedLayout { size_t off[6], total; int out[4], k[4]; int rel_size; };   // off[4]: position table [index][heads], off[5]: GELU table
+struct PackedLayout { size_t off[6], total; int out[4], k[4]; int rel_size; };   // off[4]: position table, off[5]: GELU table
 PackedLayout packed_layout(const dsvt_layer_w& w) {
   PackedLayout pl;
   const size_t es = w.dtype == DSVT_BF16 ? 2 : 4;
   const int out[4] = {3 * w.C, w.C, w.hidden, w.C}, k[4] = {w.C, w.C, w.C, w.hidden};
   size_t o = 0;
   for (int i = 0; i < 4; ++i) { pl.off[i] = o; pl.out[i] = out[i]; pl.k[i] = k[i]; o = dsvt_align_up(o + (size_t)out[i] * k[i] * es, 256); }
-  // position table [index][heads] plus one last row of -inf (the row of a key that does not exist); without a
+  // position table [heads / 4][index][4] plus one last row of -inf each (the row of a key that does not exist); without a
   // positional term the table is one row of zeros and that last row
   pl.rel_size = w.rel_bias != nullptr ? (2 * w.win[0] - 1) * (2 * w.win[1] - 1) * (2 * w.win[2] - 1) : 1;
   pl.off[4] = o;
@@ -814,12 +844,13 @@ PackedLayout packed_layout(const dsvt_layer_w& w) {
   return pl;
 }
 
-// [heads][size] -> [size + 1][heads], in units of log2(e) (the softmax works with exp2); row `size` holds -inf.
+// [heads][size] -> [heads / 4][size + 1][4], in units of log2(e) (the softmax works with exp2); row `size` holds -inf.
 // src == nullptr (no positional term): zeros.
 __global__ void k_pack_table(const float* __restrict__ src, float* __restrict__ dst, int heads, int size) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < heads * size) dst[(i % size) * heads + i / size] = src != nullptr ? src[i] * 1.4426950408889634f : 0.f;
-  else if (i < heads * (size + 1)) dst[i] = -INFINITY;
+  if (i >= heads * (size + 1)) return;
+  const int h = i / (size + 1), k = i - h * (size + 1);
+  dst[((size_t)(h / 4) * (size + 1) + k) * 4 + h % 4] = k == size ? -INFINITY : (src != nullptr ? src[(size_t)h * size + k] * 1.4426950408889634f : 0.f);
 }
 
 LayerDev to_dev(const dsvt_layer_w& w) {
@@ -834,7 +865,7 @@ LayerDev to_dev(const dsvt_layer_w& w) {
   d.ln_eps = w.ln_eps;
   const int my = 2 * w.win[1] - 1, mz = 2 * w.win[2] - 1;
   d.rel_my = my; d.rel_mz = mz;
-  const unsigned row = (unsigned)w.heads * 4u;
+  constexpr unsigned row = kRelRow;
   d.rel_last = (unsigned)(pl.rel_size - 1) * row;
   d.rel_none = (unsigned)pl.rel_size * row;
   d.rel_const = w.rel_bias != nullptr ? (unsigned)(((w.win[0] - 1) * my + (w.win[1] - 1)) * mz + (w.win[2] - 1)) * row : 0u;
