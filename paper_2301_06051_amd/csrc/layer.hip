@@ -29,13 +29,13 @@ __host__ __device__ constexpr int fixed_sets(int tau) { return tau <= kRowsMax /
 // The sets a kernel is instantiated for: of up to three key tiles (48 voxels), or of up to six (96), these last also in
 // a form of fewer registers.
 enum SetSize { kSets48, kSets96, kSets96Slim };
-// A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each; a larger one (its logits and
-// positional terms take more registers) into items of two heads: the table rows of a (query, key) pair and their
-// indices are fetched and computed once for both.  Per layer of the 20,000-voxel frame of 30 x 30 windows (C = 128, sets
-// of up to 90): one head per item 46 us, two 38 us, four 40 us (spills).  C = 192 with repeats counted as keys
-// keeps one head per item (two spill there), and so does kSets96Slim.  At most one set of a tile is that large, so a
-// tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
-__host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : 2; }
+// A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each.  A larger one's logits and positional terms
+// take more registers, and what bounds its items is the fetching of the terms, a load of the compute unit's memory pipe per key and
+// query tile whatever its width: C = 128 takes four heads an item, 32 keys at a time (attn_item()), the other shapes two heads and all keys (C = 192
+// spills 28 registers with four; C = 64 has four heads), C = 192 with repeats counted as keys one (two spill there), and so does kSets96Slim.  30 x 30 windows,
+// sets of up to 90, C = 128, 20,000 voxels: attention of a tile of 70 rows 16.3 -> 12.3 k clocks, pass 262 -> 246 us with four heads instead of
+// two.  At most one set of a tile is that large, so a tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
+__host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : C == 128 ? 4 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
 // A tile whose items leave half of the wavefronts without one -- a set or two: sparse frames -- gets items of a quarter of
 // the heads (sets of up to three key tiles; a larger one makes 16 items and more of eight heads, 8 to 12 at C = 64): an item's
@@ -214,11 +214,14 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   constexpr int D = L::D, KC = M::KC, KL = M::KL, ES = (int)sizeof(T);
   constexpr int PX = L::LDX * ES, PV = L::LDV * ES;                // row pitches in bytes
   constexpr int TPC = KC / 16;                    // key tiles per PV fragment: 2 (bf16) or 1 (fp32)
-  constexpr int NCH = (KTC + TPC - 1) / TPC;
   static_assert(HG == 1 || HG == 2 || HG == 4, "heads per item");
   static_assert(D <= KC, "one fragment per query");
   constexpr bool kSumByMma = sizeof(T) == 2;
+  // Four heads of four key tiles and more take the keys 32 at a time, with a running maximum: all logits at once do not fit the registers
+  // (and two heads at a time fetch the terms twice as often, 8 bytes a lane; a load is 17 clocks of the compute unit's memory pipe either way).
+  constexpr int CT = HG == 4 && KTC > 3 ? 2 : KTC;                // key tiles at a time
   constexpr int HS = C == 192 && KTC > 4 ? 1 : HG;                // heads side by side (two heads of six key tiles spill eight registers at C = 192)
+  static_assert(CT == KTC || HS == HG, "a running maximum per head");
   const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
   const int qi = 16 * qt + m;
   const int qrow = r0 + (qi < nu ? qi : nu - 1);
@@ -226,42 +229,42 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
 
   // The keys' positional terms, one table row per (query, key) for all heads of the item
   typedef float Terms __attribute__((ext_vector_type(HG)));          // (indexed by head)
-  Terms bias[KTC][4];
-  {
-    const unsigned qc = (unsigned)row_code[qrow] + p.rel_const;
-    const int left = nu - (16 * (KTC - 1) + 4 * g);                // keys of the last tile from this lane's first on
-    const char* tab = reinterpret_cast<const char*>(p.rel_bias) + (size_t)(hh * HG / 4) * ((size_t)p.rel_none + kRelRow) + hh * HG % 4 * 4;
+  const unsigned qc = (unsigned)row_code[qrow] + p.rel_const;
+  const int left = nu - (16 * (KTC - 1) + 4 * g);                  // keys of the last tile from this lane's first on
+  const char* tab = reinterpret_cast<const char*>(p.rel_bias) + (size_t)(hh * HG / 4) * ((size_t)p.rel_none + kRelRow) + hh * HG % 4 * 4;
+  Terms bias[CT][4];
+  const auto fetch_terms = [&](int k0) {
 #pragma unroll
-    for (int kt = 0; kt < KTC; ++kt) {
+    for (int kt = k0; kt < k0 + CT && kt < KTC; ++kt) {
       const int4 kl = *reinterpret_cast<const int4*>(row_code + r0 + 16 * kt + 4 * g);
       const int kls[4] = {kl.x, kl.y, kl.z, kl.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         unsigned at = min(qc - (unsigned)kls[i], p.rel_last);      // (modulo 2^32: right for every index of the table)
         if (kt == KTC - 1) at = i < left ? at : p.rel_none;        // only the last key tile is ragged
-        bias[kt][i] = *reinterpret_cast<const Terms*>(tab + at);
+        bias[kt - k0][i] = *reinterpret_cast<const Terms*>(tab + at);
       }
     }
-  }
+  };
+  fetch_terms(0);
   const int lds0 = (int)(uintptr_t)(lds_byte)smem;
   const bool live = g * KL < D;                   // lanes past the head width
   const int q_at = lds0 + (live ? q_off + qrow * PX + h0 + g * KL * ES : (int)L::off_zero);
   const int q_step = live ? D * ES : 0;
-  int k_at[KTC];
-#pragma unroll
-  for (int kt = 0; kt < KTC; ++kt)                // (dead k lanes: finite K times the zero Q)
-    k_at[kt] = lds0 + (int)L::off_k + (r0 + min(16 * kt + m, nu - 1)) * PX + h0 + (live ? g * KL * ES : 0);
+  // (dead k lanes: finite K times the zero Q)
+  const int k_first = lds0 + (int)L::off_k + (r0 + m) * PX + h0 + (live ? g * KL * ES : 0), k_last = k_first + (min(16 * (KTC - 1) + m, nu - 1) - m) * PX;
+  const auto k_at = [&](int kt) { return kt < KTC - 1 ? k_first + 16 * kt * PX : k_last; };
   // Key columns past the tile's rows hold no V: their P is an exact zero, so any finite column will do, and the set's first
   // one is read instead.  (Rows past the head width: the tile's row of a lane below it; results thrown away.)
   constexpr int DT = (D + 15) / 16;
-  int v_at[DT][NCH * TPC];
+  int v_first[DT], v_last[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int c = 0; c < NCH * TPC; ++c) {
-      const int col = r0 + 16 * c + 4 * g, dv = 16 * dt + m;
-      v_at[dt][c] = lds0 + (int)L::off_v + hh * HG * D * PV + (dv < D ? dv : m) * PV + (col < rows_ready ? col : r0) * ES;
-    }
+  for (int dt = 0; dt < DT; ++dt) {
+    const int dv = 16 * dt + m, row = lds0 + (int)L::off_v + hh * HG * D * PV + (dv < D ? dv : m) * PV + r0 * ES;
+    v_first[dt] = row + 4 * g * ES;
+    v_last[dt] = row + (r0 + 16 * (KTC - 1) + 4 * g < rows_ready ? 16 * (KTC - 1) + 4 * g : 0) * ES;
+  }
+  const auto v_at = [&](int dt, int kt) { return kt < KTC - 1 ? v_first[dt] + 16 * kt * ES : v_last[dt]; };
   int o_at[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -269,80 +272,107 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
 
 #pragma unroll
   for (int hb = 0; hb < HG; hb += HS) {
-    f32x4 S[HS][KTC];                               // S[hl][kt][i]: key 16*kt + 4*g + i, query 16*qt + m
+    constexpr f32x4 kZero = {0.f, 0.f, 0.f, 0.f};
+    float mx[HS], sum[HS];                          // of the keys so far
+    f32x4 O[HS][DT];                                // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q]
 #pragma unroll
-    for (int hl = 0; hl < HS; ++hl) {
-      const Frag fq = lds_read<Frag>(q_at + (hb + hl) * q_step);
+    for (int k0 = 0; k0 < KTC; k0 += CT) {
+      constexpr int NCH = (CT + TPC - 1) / TPC;     // PV fragments
+      const int kn = KTC - k0 < CT ? KTC - k0 : CT;
+      f32x4 S[HS][CT];                              // S[hl][kt][i]: key 16*(k0 + kt) + 4*g + i, query 16*qt + m
 #pragma unroll
-      for (int kt = 0; kt < KTC; ++kt) S[hl][kt] = M::mma(lds_read<Frag>(k_at[kt] + (hb + hl) * D * ES), fq, f32x4{0.f, 0.f, 0.f, 0.f});
-    }
-    // S + terms: the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
-    float mx[HS];
+      for (int hl = 0; hl < HS; ++hl) {
+        const Frag fq = lds_read<Frag>(q_at + (hb + hl) * q_step);
 #pragma unroll
-    for (int hl = 0; hl < HS; ++hl) {
-#pragma unroll
-      for (int k = 0; k < 4 * KTC; ++k) {
-        float& x = reinterpret_cast<float(&)[4]>(S[hl][k >> 2])[k & 3];
-        x += bias[k >> 2][k & 3][hb + hl];
-        mx[hl] = k == 0 ? x : fmaxf(mx[hl], x);
+        for (int kt = 0; kt < kn; ++kt) S[hl][kt] = M::mma(lds_read<Frag>(k_at(k0 + kt) + (hb + hl) * D * ES), fq, kZero);
       }
-    }
-    col_reduce(mx, [](float a, float b) { return raw_max(a, b); }, [](float a) { return a; });     // (key 0 exists for every query: finite)
-    float sum[HS];
-    Frag fp[HS][NCH];
+      // S + terms: the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
+      float cm[HS];
 #pragma unroll
-    for (int hl = 0; hl < HS; ++hl) {
+      for (int hl = 0; hl < HS; ++hl) {
 #pragma unroll
-      for (int kt = 0; kt < KTC; ++kt) {
-        f32x4 mult;
-        if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * kt + 4 * g);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
-          if constexpr (DUP) e *= mult[i];
-          S[hl][kt][i] = e;
-          if constexpr (!kSumByMma) sum[hl] = kt + i == 0 ? e : sum[hl] + e;
+        for (int k = 0; k < 4 * kn; ++k) {
+          const float x = S[hl][k >> 2][k & 3] + bias[k >> 2][k & 3][hb + hl];
+          S[hl][k >> 2][k & 3] = x;
+          cm[hl] = k == 0 ? x : fmaxf(cm[hl], x);
         }
       }
+      col_reduce(cm, [](float a, float b) { return raw_max(a, b); }, [](float a) { return a; });     // (key 0 exists for every query: finite)
+      float scale[HS];                              // of the keys before these
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        if constexpr (TPC == 2) {
-          const f32x4 p0 = S[hl][2 * c], p1 = 2 * c + 1 < KTC ? S[hl][2 * c + 1 < KTC ? 2 * c + 1 : 0] : f32x4{0.f, 0.f, 0.f, 0.f};
-          fp[hl][c] = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
-        } else {
-          fp[hl][c] = S[hl][c];
+      for (int hl = 0; hl < HS; ++hl) {
+        if (k0 > 0) {
+          cm[hl] = raw_max(cm[hl], mx[hl]);
+          scale[hl] = __builtin_amdgcn_exp2f(mx[hl] - cm[hl]);
         }
+        mx[hl] = cm[hl];
       }
-    }
-    // O^T[dv][q] = sum_key V^T[dv][key] P^T[key][q]
-    f32x4 O[HS][DT];
+      float part[HS];
+      Frag fp[HS][NCH];
 #pragma unroll
-    for (int hl = 0; hl < HS; ++hl) {
+      for (int hl = 0; hl < HS; ++hl) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
+        for (int kt = 0; kt < kn; ++kt) {
+          f32x4 mult;
+          if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * (k0 + kt) + 4 * g);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
+            if constexpr (DUP) e *= mult[i];
+            S[hl][kt][i] = e;
+            if constexpr (!kSumByMma) part[hl] = kt + i == 0 ? e : part[hl] + e;
+          }
+        }
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-          Frag fv;
           if constexpr (TPC == 2) {
-            const bf16x4 lo = lds_read<bf16x4>(v_at[dt][2 * c] + (hb + hl) * D * PV);
-            bf16x4 hi = {0, 0, 0, 0};
-            if (2 * c + 1 < KTC) hi = lds_read<bf16x4>(v_at[dt][2 * c + 1] + (hb + hl) * D * PV);
-            fv = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            const f32x4 p0 = S[hl][2 * c < kn ? 2 * c : 0], p1 = 2 * c + 1 < kn ? S[hl][2 * c + 1 < kn ? 2 * c + 1 : 0] : kZero;
+            fp[hl][c] = Frag{(bf16_t)p0[0], (bf16_t)p0[1], (bf16_t)p0[2], (bf16_t)p0[3], (bf16_t)p1[0], (bf16_t)p1[1], (bf16_t)p1[2], (bf16_t)p1[3]};
           } else {
-            fv = lds_read<Frag>(v_at[dt][c] + (hb + hl) * D * PV);
+            fp[hl][c] = S[hl][c];
           }
-          O[hl][dt] = M::mma(fv, fp[hl][c], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : O[hl][dt]);
         }
       }
-      if constexpr (kSumByMma) {
-        const bf16_t one = (bf16_t)1.f;
-        f32x4 t = {0.f, 0.f, 0.f, 0.f};
+      if (k0 + CT < KTC) fetch_terms(k0 + CT);
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) t = M::mma(Frag{one, one, one, one, one, one, one, one}, fp[hl][c], t);
-        sum[hl] = __builtin_amdgcn_rcpf(t[0]);
+      for (int hl = 0; hl < HS; ++hl) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          f32x4 o = k0 > 0 ? O[hl][dt] * scale[hl] : kZero;
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) {
+            if (c * TPC >= kn) continue;
+            Frag fv;
+            if constexpr (TPC == 2) {
+              const bf16x4 lo = lds_read<bf16x4>(v_at(dt, k0 + 2 * c) + (hb + hl) * D * PV);
+              bf16x4 hi = {0, 0, 0, 0};
+              if (2 * c + 1 < kn) hi = lds_read<bf16x4>(v_at(dt, k0 + 2 * c + 1) + (hb + hl) * D * PV);
+              fv = Frag{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            } else {
+              fv = lds_read<Frag>(v_at(dt, k0 + c) + (hb + hl) * D * PV);
+            }
+            o = M::mma(fv, fp[hl][c], o);
+          }
+          O[hl][dt] = o;
+        }
+        if constexpr (kSumByMma) {
+          const bf16_t one = (bf16_t)1.f;
+          f32x4 t = kZero;
+#pragma unroll
+          for (int c = 0; c < NCH; ++c)
+            if (c * TPC < kn) t = M::mma(Frag{one, one, one, one, one, one, one, one}, fp[hl][c], t);
+          part[hl] = t[0];
+        }
+        sum[hl] = k0 > 0 ? fmaf(sum[hl], scale[hl], part[hl]) : part[hl];
       }
+      if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (without it four to eight registers spill: 250 us instead of 246)
     }
-    if constexpr (!kSumByMma) col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
+    if constexpr (kSumByMma) {
+#pragma unroll
+      for (int hl = 0; hl < HS; ++hl) sum[hl] = __builtin_amdgcn_rcpf(sum[hl]);
+    } else {
+      col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
+    }
 #pragma unroll
     for (int hl = 0; hl < HS; ++hl)
 #pragma unroll
@@ -615,12 +645,18 @@ k_layer(LayerCall<T> call) {
     // of its output tiles instead, so that each of their weight fragments is loaded only once.  The last part may have fewer
     // row tiles than the others, or none: its wavefronts request no weights (C = 192, a tile of a single row tile: 220 KB of the
     // 800 KB such a tile takes through the compute unit's memory pipeline otherwise).
-    const int og_own = wave % SG, own_max = (RT + RS - 1) / RS, rt_own = wave / SG * own_max;
-    const int HC = RT - rt_own < 0 ? 0 : (RT - rt_own < own_max ? RT - rt_own : own_max);       // HC = 0: a wavefront without an item
+    // HC = 0: a wavefront without an item
+    const auto own_rows = [&](int w, int& rt_own) {
+      const int own_max = (RT + RS - 1) / RS;
+      rt_own = w / SG * own_max;
+      return RT - rt_own < 0 ? 0 : (RT - rt_own < own_max ? RT - rt_own : own_max);
+    };
     GemmPhase<T, NT_O, C, C, NW, RS> oproj(reinterpret_cast<const T*>(args->layer.w_o), wave);
     oproj.forget();
-    if (HC > 0) oproj.prefetch();                // in flight during the attention phase
-    const int o_own = og_own * 16 * NT_O;
+    {
+      int rt_own;
+      if (own_rows(wave, rt_own) > 0) oproj.prefetch();            // in flight during the attention phase
+    }
     // The set table, by the first wavefront: it is through with its part of the projection first (the compute unit issues its
     // oldest wavefronts first) and would wait for the others.  (In front of the rows' request every wavefront waits for it: 0.6 k
     // clocks a tile, 4 k with sets of 90 rows and a list of the items instead of this table.)
@@ -671,6 +707,11 @@ k_layer(LayerCall<T> call) {
     // (Neither the thread number nor a first value of `late` may live through the attention: four zeros kept for it were four
     // registers too many for sets of 49 to 72 voxels of C = 64 with repeats as keys, which spilled eight.)
     DSVT_REFRESH_LANE();
+    // (What follows from the wavefront's number is computed anew: kept through the attention, it spills five scalar registers where sets of more than 48
+    // voxels are taken, C = 128.)
+    int own_wave = wave, rt_own;
+    asm volatile("" : "+s"(own_wave));
+    const int og_own = own_wave % SG, HC = own_rows(own_wave, rt_own), o_own = og_own * 16 * NT_O;
     f32x4 late;
     opaque_def(late);
     if (full_layer && tid < kVecThreads) {

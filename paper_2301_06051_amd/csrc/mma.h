@@ -365,9 +365,9 @@ struct GemmPhase {
     static_assert(IPW == 1 && HC <= RH, "one item per wavefront");
     typedef typename Mma<T>::Frag Frag;
     constexpr int ALL = NKF_ALL * HC, RING = ALL < kKeepRing ? ALL : kKeepRing;       // activation fragments, k by k and row tile by row tile
-    const int lane = opaque_tid() & 63;
+    const unsigned lane = opaque_tid() & 63;
     const T* xp = Xs + (16 * rt0 + (lane & 15)) * ldx + (lane >> 4) * Mma<T>::KL;
-    const Frag* wp = reinterpret_cast<const Frag*>(Wp) + (size_t)((wave % N_OG) * NT) * NKF_ALL * 64 + lane;
+    const Frag* wp = reinterpret_cast<const Frag*>(Wp) + (size_t)((wave % N_OG) * NT) * NKF_ALL * 64;
     const auto read = [&](int f) { return *reinterpret_cast<const Frag*>(xp + 16 * (f % HC) * ldx + f / HC * KC); };
     Frag b[RING];
 #pragma unroll
@@ -380,7 +380,7 @@ struct GemmPhase {
       if (f + RING < ALL) b[f % RING] = read(f + RING);
       if (r == HC - 1 && kf + NKF < NKF_ALL) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) a[0].f[kf % NKF][nt] = wp[(nt * NKF_ALL + kf + NKF) * 64];
+        for (int nt = 0; nt < NT; ++nt) a[0].f[kf % NKF][nt] = (wp + (nt * NKF_ALL + kf + NKF) * 64)[lane];
       }
       __builtin_amdgcn_sched_barrier(0);
     }

@@ -14,7 +14,7 @@ from gpu_util import TOL, dev_coords, dev_feats, gpu_maps, rel_err  # noqa: E402
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
 @pytest.mark.parametrize("dup_mode", [0, 1])
 def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
-    """Sets of four to six key tiles (full windows of 64, 65, 80, 81 and 96 voxels): items of one or two heads."""
+    """Sets of four to six key tiles (full windows of 64, 65, 80, 81 and 96 voxels): items of one, two or four heads."""
     grid, win, tau = (60, 12, 1), (12, 12, 1), 96
     rng = np.random.Generator(np.random.Philox(11))
     rows = []
@@ -30,6 +30,30 @@ def test_large_sets_heads_per_item(C, heads, hidden, dtype, dup_mode):
     y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0), cd, dev_feats(x, dtype))
     torch.cuda.synchronize()
     assert rel_err(y, orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype]
+
+
+@pytest.mark.parametrize("slope", [0.3, 9.0, 400.0])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_logits_that_rise_and_fall_over_a_large_set(slope, dup_mode):
+    """C = 128 takes the keys of a large set 32 at a time with a running maximum: positional terms that rise along the set in half of the
+    heads and fall in the others, by little, by about what exp2 takes from one 32 keys to the next, and by far more."""
+    C, heads, grid, win, tau = 128, 8, (60, 12, 1), (12, 12, 1), 96
+    rng = np.random.Generator(np.random.Philox(71))
+    rows = []
+    for k, cnt in enumerate((49, 64, 65, 81, 96)):
+        cell = rng.permutation(144)[:cnt]
+        rows.append(np.stack([0 * cell, 12 * k + cell // 12, cell % 12, 0 * cell], 1))
+    coords = np.concatenate(rows).astype(np.int32)
+    x = synth.make_features(72, len(coords), C, "bf16")
+    w = synth.make_layer_weights(73, C, heads, 256, win, "bf16")
+    dx = np.arange(23 * 23) // 23 - 11                       # query - key
+    w["rel_bias"] = (slope * dx[None, :] * np.where(np.arange(heads) % 2 == 0, 1, -1)[:, None]).astype(np.float32)
+    print(f"[case] rising and falling logits slope={slope} dup={dup_mode}", flush=True)
+    om = orc.partition(coords, grid, win, (0, 0, 0), tau, 0)
+    cd = dev_coords(coords)
+    y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0), cd, dev_feats(x, "bf16"))
+    torch.cuda.synchronize()
+    assert rel_err(y, orc.set_attention(w, om, coords, x, dup_mode)) < TOL["bf16"]
 
 
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
