@@ -249,11 +249,22 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   fetch_terms(0);
   const int lds0 = (int)(uintptr_t)(lds_byte)smem;
   const bool live = g * KL < D;                   // lanes past the head width
-  const int q_at = lds0 + (live ? q_off + qrow * PX + h0 + g * KL * ES : (int)L::off_zero);
-  const int q_step = live ? D * ES : 0;
-  // (dead k lanes: finite K times the zero Q)
-  const int k_first = lds0 + (int)L::off_k + (r0 + m) * PX + h0 + (live ? g * KL * ES : 0), k_last = k_first + (min(16 * (KTC - 1) + m, nu - 1) - m) * PX;
-  const auto k_at = [&](int kt) { return kt < KTC - 1 ? k_first + 16 * kt * PX : k_last; };
+  // Addresses in swizzled rows, of the item's first head and (a head is an odd number of 16-byte pieces) of its second one: every other head on is
+  // a constant away.
+  constexpr int HB = D * ES, PAR = HB % 32 != 0 ? 2 : 1;
+  static_assert(L::off_k % 32 == 0 && PX % 32 == 0, "addresses are swizzled like places in a row");
+  const auto swizzled = [](int at, int row) { return at ^ (row & 4) << 2; };
+  int q_at[PAR], k_first[PAR], k_last[PAR];
+  const int k_row = r0 + min(16 * (KTC - 1) + m, nu - 1);
+#pragma unroll
+  for (int par = 0; par < PAR; ++par) {
+    const int piece = lds0 + h0 + par * HB + (live ? g * KL * ES : 0);       // (dead k lanes: finite K times the zero Q)
+    q_at[par] = live ? swizzled(q_off + qrow * PX + piece, qrow) : lds0 + (int)L::off_zero;
+    k_first[par] = swizzled((int)L::off_k + (r0 + m) * PX + piece, r0 + m);
+    k_last[par] = swizzled((int)L::off_k + k_row * PX + piece, k_row);
+  }
+  const int q_step = live ? PAR * HB : 0;
+  const auto k_at = [&](int h, int kt) { return (kt < KTC - 1 ? k_first[h % PAR] + 16 * kt * PX : k_last[h % PAR]) + h / PAR * PAR * HB; };
   // Key columns past the tile's rows hold no V: their P is an exact zero, so any finite column will do, and the set's first
   // one is read instead.  (Rows past the head width: the tile's row of a lane below it; results thrown away.)
   constexpr int DT = (D + 15) / 16;
@@ -265,10 +276,12 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
     v_last[dt] = row + (r0 + 16 * (KTC - 1) + 4 * g < rows_ready ? 16 * (KTC - 1) + 4 * g : 0) * ES;
   }
   const auto v_at = [&](int dt, int kt) { return kt < KTC - 1 ? v_first[dt] + 16 * kt * ES : v_last[dt]; };
-  int o_at[DT];
+  int o_at[DT][PAR];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
-    o_at[dt] = lds0 + (qi < nu && 16 * dt + 4 * g < D ? q_off + qrow * PX + h0 + (16 * dt + 4 * g) * ES : (int)L::off_spare);
+#pragma unroll
+    for (int par = 0; par < PAR; ++par)
+      o_at[dt][par] = qi < nu && 16 * dt + 4 * g < D ? swizzled(lds0 + q_off + qrow * PX + h0 + par * HB + (16 * dt + 4 * g) * ES, qrow) : lds0 + (int)L::off_spare + par * HB;
 
 #pragma unroll
   for (int hb = 0; hb < HG; hb += HS) {
@@ -282,9 +295,9 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
       f32x4 S[HS][CT];                              // S[hl][kt][i]: key 16*(k0 + kt) + 4*g + i, query 16*qt + m
 #pragma unroll
       for (int hl = 0; hl < HS; ++hl) {
-        const Frag fq = lds_read<Frag>(q_at + (hb + hl) * q_step);
+        const Frag fq = lds_read<Frag>(q_at[(hb + hl) % PAR] + (hb + hl) / PAR * q_step);
 #pragma unroll
-        for (int kt = 0; kt < kn; ++kt) S[hl][kt] = M::mma(lds_read<Frag>(k_at(k0 + kt) + (hb + hl) * D * ES), fq, kZero);
+        for (int kt = 0; kt < kn; ++kt) S[hl][kt] = M::mma(lds_read<Frag>(k_at(hb + hl, k0 + kt)), fq, kZero);
       }
       // S + terms: the logits in units of log2(e), -inf for the keys that do not exist: exp is a bare exp2
       float cm[HS];
@@ -376,7 +389,7 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
 #pragma unroll
     for (int hl = 0; hl < HS; ++hl)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) lds_write<Vec4>(o_at[dt] + (hb + hl) * D * ES, pack4<T>(O[hl][dt] * sum[hl]));
+      for (int dt = 0; dt < DT; ++dt) lds_write<Vec4>(o_at[dt][(hb + hl) % PAR] + (hb + hl) / PAR * PAR * HB, pack4<T>(O[hl][dt] * sum[hl]));
   }
 }
 
@@ -442,7 +455,7 @@ k_layer(LayerCall<T> call) {
   int tid = threadIdx.x, lane = tid & 63, m = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #define DSVT_REFRESH_LANE() do { tid = opaque_tid(); lane = tid & 63; m = lane & 15; g = lane >> 4; } while (0)
-  typedef GemmPhase<T, NT_QKV, C, 3 * C, NW> QkvPhase;
+  typedef GemmPhase<T, NT_QKV, C, 3 * C, NW, 1, 1, true> QkvPhase;
   // The first two output tiles of every wavefront's Q/K/V weights (C = 192: of three, C = 128: both, C = 64: the only one)
   // of a workgroup's first tile are requested behind the descriptor, and arrive during the two dependent trips to memory (descriptor, then the rows it
   // names) in which the compute unit's memory pipeline would have nothing else to do: it takes a 1 KB fragment every ~19
@@ -512,7 +525,8 @@ k_layer(LayerCall<T> call) {
     }
   };
   const auto store_rows = [&](const uint4 (&gv)[G], unsigned live, int off, int RT) {
-    const int r0 = tid / CH, c = tid - r0 * CH;
+    static_assert(GR % 8 == 0, "a thread's rows are swizzled alike");
+    const int r0 = tid / CH, c = (tid - r0 * CH) ^ (r0 >> 2 & 1);
 #pragma unroll
     for (int k = 0; k < G; ++k)
       if (r0 + k * GR < RT * 16)
@@ -559,7 +573,7 @@ k_layer(LayerCall<T> call) {
     const float q_scale = rsqrtf((float)L::D) * 1.4426950408889634f;
     const int o0 = wave * 16 * NT_QKV;
     // (part k of a row tile's epilogue takes output tile k - 1)
-    const auto store = [&](T* dst, int r, int nt, const f32x4& v) { *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + 4 * g) = pack4<T>(v); };
+    const auto store = [&](T* dst, int r, int nt, const f32x4& v) { *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + (4 * g ^ swizzle<T>(m))) = pack4<T>(v); };
     if (o0 >= 2 * C) {
       qkv.template run_rows<true>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
         if (k >= 1 && k <= NT_QKV) *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * (k - 1) + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[k - 1]);
@@ -651,7 +665,7 @@ k_layer(LayerCall<T> call) {
       rt_own = w / SG * own_max;
       return RT - rt_own < 0 ? 0 : (RT - rt_own < own_max ? RT - rt_own : own_max);
     };
-    GemmPhase<T, NT_O, C, C, NW, RS> oproj(reinterpret_cast<const T*>(args->layer.w_o), wave);
+    GemmPhase<T, NT_O, C, C, NW, RS, 1, true> oproj(reinterpret_cast<const T*>(args->layer.w_o), wave);
     oproj.forget();
     {
       int rt_own;
@@ -738,7 +752,7 @@ k_layer(LayerCall<T> call) {
     // (before the projection, after it, after the residual): a CU takes a 16-byte load per
     // wavefront every ~16 cycles, a wavefront waits until its requests are taken, and twelve
     // wavefronts asking at once would all stand still for 3 k cycles.
-    GemmPhase<T, NT_1, C, HID, NW> ffn1(reinterpret_cast<const T*>(args->layer.w_1), wave);
+    GemmPhase<T, NT_1, C, HID, NW, 1, 1, true> ffn1(reinterpret_cast<const T*>(args->layer.w_1), wave);
     const int pf_turn = full_layer ? wave / (NW / 3) : -1;
     ffn1.forget();
     if (pf_turn == 0) ffn1.prefetch();
@@ -771,7 +785,7 @@ k_layer(LayerCall<T> call) {
       b = *reinterpret_cast<const f32x4*>(affine_lds + C + o_own + 16 * nt + 4 * g);
     }, args->layer.ln_eps, [&](int, int row, const f32x4 (&y)[NT_O]) {
 #pragma unroll
-      for (int nt = 0; nt < NT_O; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + 4 * g) = pack4<T>(y[nt]);
+      for (int nt = 0; nt < NT_O; ++nt) *reinterpret_cast<Vec4*>(Xs + row * LDX + o_own + 16 * nt + (4 * g ^ swizzle<T>(m))) = pack4<T>(y[nt]);
     });
     if (more) store_desc(next_word, (int)L::kRowTab - tab, args->maps.n_voxels);
     lds_barrier();
@@ -786,7 +800,7 @@ k_layer(LayerCall<T> call) {
     // 120,000-voxel frame 707 / 699.  Slower than this at C = 192, each in one session with it: the matrix in three slices, two of
     // them requested here, 0.2-0.8 %; the same with the MLP's biases from LDS beside the LayerNorms' vectors 0.6-1.4 %; the second
     // bias requested in front of the weights 0.1-0.7 %.
-    GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1)> ffn2(reinterpret_cast<const T*>(args->layer.w_2), wave);
+    GemmPhase<T, NT_2, HID, C, NW, RS, (HID / Mma<T>::KC > 8 ? 2 : 1), true> ffn2(reinterpret_cast<const T*>(args->layer.w_2), wave);
     const float gelu0 = gelu_start(smem + L::off_gelu);
     // Parts of a row tile's epilogue: the table entries of output tile 0, 1, .. requested, then the values of output tile 0, 1, ..
     f32x2 chord[NT_1][4];
@@ -800,7 +814,7 @@ k_layer(LayerCall<T> call) {
         f32x4 v = acc[nt];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = kGeluTable ? fmaf(chord[nt][i].x, v[i], chord[nt][i].y) : gelu_erf_fast(v[i]);
-        *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o0 + 16 * nt + 4 * g) = pack4<T>(v);
+        *reinterpret_cast<Vec4*>(Hs + (16 * r + m) * LDH + o0 + 16 * nt + (4 * g ^ swizzle<T>(m))) = pack4<T>(v);
       }
     }, [&]() {
       ffn2.forget();

@@ -85,6 +85,14 @@ template <int A, int B> __device__ __forceinline__ void undefined(f32x4 (&v)[A][
 // on gfx950: 225 B/clk per CU against 125-150 B/clk for pitches of 16, 48 or 0 mod 64 bytes.
 template <typename T> constexpr int lds_pad() { return 32 / (int)sizeof(T); }
 
+// Swizzled rows: in every other group of four rows the two 16-byte pieces of each 32 bytes change places.  At that pitch the 8-byte stores of
+// accumulators (16 rows, one place in each) hit a bank four times, since a store sees 32 banks: 16.1 clocks an instruction; swizzled they
+// hit it twice, 8.2, and the fragment loads stay at their 4.0 (for stores alone an odd multiple of 8 bytes would be best, 6.4, but loads of 16 bytes take
+// 8.0 there).  Without -> with: a 64-row tile of C = 192 35.8 -> 35.3 k clocks (first MLP matrix 7.03 -> 6.56 k), an 82-row tile 42.9 -> 42.0 k; passes of
+// 30,000 pillars 321.3 -> 319.3 us, windows of 12 and 24 cells 454.3 -> 449.1, 30 x 30 windows 243.8 -> 242.5, 120,000 voxels 609.0 -> 606.9, 3,001
+// pillars and an fp32 block no difference.  Element of T in its row: e ^ swizzle<T>(row).  The pitch and all row starts are multiples of 32 bytes, so an address is swizzled like that too.
+template <typename T> __device__ __forceinline__ constexpr int swizzle(int row) { return (row >> 2 & 1) * (16 / (int)sizeof(T)); }
+
 // Packed weights.  A matrix W [OUT, K] is stored fragment by fragment in the order the MFMA "A"
 // operand wants it: fragment (tile, kf) -- output rows 16*tile .. +15, k in [kf*KC, (kf+1)*KC) --
 // is 1 KB, lane l's 16 bytes at offset 16*l, fragments ordered [tile][kf].  A wavefront's load of
@@ -164,8 +172,10 @@ constexpr int kStatGroupsMax = 6;                // LayerNorm phases: the C feat
 // registers for the whole item, run() requests the next item's before the current one is consumed, and the activations of
 // row tile r + 1 are read from LDS while row tile r is in the matrix cores.  Every activation
 // fragment read from LDS feeds NT MFMAs; a weight fragment is loaded by RSPLIT wavefronts.
-template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, int KSPLIT = 1>
+// SWZ: the rows of the activations are swizzled (not in run()).
+template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, int KSPLIT = 1, bool SWZ = false>
 struct GemmPhase {
+  static __device__ __forceinline__ int lane_piece(int lane) { return ((lane >> 4) * Mma<T>::KL) ^ (SWZ ? swizzle<T>(lane & 15) : 0); }
   static constexpr int KC = Mma<T>::KC;
   static constexpr int NKF_ALL = K / KC;
   static constexpr int NKF = NKF_ALL / KSPLIT;          // fragments held at a time (KSPLIT > 1: run_keep only)
@@ -308,7 +318,7 @@ struct GemmPhase {
   template <bool SWAPPED, typename Epi, typename Before>
   __device__ __forceinline__ void row_steps(const T* Xs, int ldx, int RT, const f32x4 (&start)[NT], Epi epi, Before before_last) const {
     const int lane = opaque_tid() & 63;
-    const T* next = Xs + (lane & 15) * ldx + (lane >> 4) * Mma<T>::KL;
+    const T* next = Xs + (lane & 15) * ldx + lane_piece(lane);
     f32x4 acc0[NT], acc1[NT];
     BRow<T, NKF> b;
 #pragma unroll
@@ -366,7 +376,7 @@ struct GemmPhase {
     typedef typename Mma<T>::Frag Frag;
     constexpr int ALL = NKF_ALL * HC, RING = ALL < kKeepRing ? ALL : kKeepRing;       // activation fragments, k by k and row tile by row tile
     const unsigned lane = opaque_tid() & 63;
-    const T* xp = Xs + (16 * rt0 + (lane & 15)) * ldx + (lane >> 4) * Mma<T>::KL;
+    const T* xp = Xs + (16 * rt0 + (lane & 15)) * ldx + lane_piece(lane);
     const Frag* wp = reinterpret_cast<const Frag*>(Wp) + (size_t)((wave % N_OG) * NT) * NKF_ALL * 64;
     const auto read = [&](int f) { return *reinterpret_cast<const Frag*>(xp + 16 * (f % HC) * ldx + f / HC * KC); };
     Frag b[RING];
@@ -484,7 +494,7 @@ __device__ __forceinline__ float gelu_erf_fast(float x) {
   q = q * q; q = q * q; q = q * q; q = q * q;
   return fmaf(-a, __builtin_amdgcn_rcpf(q), fmaxf(x, 0.f));
 }
-// v += rows of Xs (LDS, pitch ldx), for values in accumulator layout: features o0 .. o0 + 16*NT - 1 of rows 16*(rt0 + r) + m, r < cnt.
+// v += swizzled rows of Xs (LDS, pitch ldx), for values in accumulator layout: features o0 .. o0 + 16*NT - 1 of rows 16*(rt0 + r) + m, r < cnt.
 template <typename T, int NT, int RH>
 __device__ __forceinline__ void add_rows(f32x4 (&v)[NT][RH], const T* Xs, int ldx, int rt0, int cnt, int o0) {
   typedef typename Mma<T>::Vec4 Vec4;
@@ -494,7 +504,7 @@ __device__ __forceinline__ void add_rows(f32x4 (&v)[NT][RH], const T* Xs, int ld
 #pragma unroll
     for (int r = 0; r < RH; ++r)
       if (r < cnt) {
-        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * (rt0 + r) + m) * ldx + o0 + 16 * nt + 4 * g);
+        const Vec4 xr = *reinterpret_cast<const Vec4*>(Xs + (16 * (rt0 + r) + m) * ldx + o0 + 16 * nt + (4 * g ^ swizzle<T>(m)));
         v[nt][r] += f32x4{to_f32<T>(xr[0]), to_f32<T>(xr[1]), to_f32<T>(xr[2]), to_f32<T>(xr[3])};
       }
 }
