@@ -90,6 +90,59 @@ __device__ __forceinline__ f32x2 gelu_entry(float start, float x) {          // 
   return *(lds_pair)(uintptr_t)(__float_as_uint(t) & 0x3FFF8u);
 }
 
+// The tiles of a workgroup of a full grid (kComputeUnits or twice as many workgroups; tiles are listed most rows first).  Its first tile is the one of its
+// number.  Of the others n_tiles % grid workgroups, those with the smallest first tiles, take one more than the rest, and theirs are
+// n_more consecutive ones from `first` on (counted behind the first tiles); the rest take what lies before and behind.  Both go back and forth, every
+// second of their rounds in reverse, and `first` is chosen so that the two kinds of workgroups end together (first_of_more()).  Whatever
+// `first` is, every tile is taken once.
+struct Shares {
+  int rounds, more, n_more;                  // whole rounds, workgroups with a tile more, how many tiles those take behind their first ones
+  int grid;
+  __device__ __forceinline__ Shares(int n_tiles, int grid_) : rounds(n_tiles / grid_), more(n_tiles % grid_), n_more(rounds * more), grid(grid_) {}
+  __device__ __forceinline__ int others() const { return (rounds - 1) * (grid - more); }           // tiles behind the first ones that the rest take
+  // tile number `round` >= 1 of workgroup b, -1: there is none
+  __device__ __forceinline__ int tile(int b, int round, int first) const {
+    const bool has_more = b >= grid - more;
+    const int width = has_more ? more : grid - more, at = has_more ? b - (grid - more) : b, t = round - 1;
+    if (t >= (has_more ? rounds : rounds - 1)) return -1;
+    const int j = t * width + ((t & 1) != 0 ? at : width - 1 - at);
+    return grid + (has_more ? first + j : (j < first ? j : j + n_more));
+  }
+};
+// A wavefront chooses `first` from the rows of 64 tiles spread evenly over the list (rows: of tile (2 lane + 1) n_tiles / 128): the cost of a run of
+// tiles from their prefix sums, a tile costing its rows and what 31 rows do (11.5 k clocks beside 372 a row at C = 192), for 64 places of the run.
+// The rounds' sums differ by the last, partial round otherwise: of 6.26 rounds of the 120,000-voxel frame the slowest workgroup took 290 k clocks,
+// the mean 263 k.  Back and forth through the list -> this: passes of 120,000 voxels 641.6 -> 622.3 us, four frames 1,044 -> 1,008, skewed batch 7,005 -> 6,939.
+__device__ __forceinline__ int first_of_more(const Shares& sh, int n_tiles, int rows) {
+  const int lane = threadIdx.x & 63;
+  const float cost = (float)(rows < 0 ? 0 : (rows > kRowsMax ? kRowsMax : rows)) + 31.f, per = (float)n_tiles * (1.f / 64.f);
+  float before = cost;                             // inclusive sums over the lanes
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {
+    const float t = __shfl_up(before, d, 64);
+    if (lane >= d) before += t;
+  }
+  before -= cost;
+  const auto prefix = [&](int k) {                 // cost of the first k tiles
+    const float y = (float)k / per;
+    int i = (int)y;
+    i = i > 63 ? 63 : i;
+    return (__shfl(before, i, 64) + (y - (float)i) * __shfl(cost, i, 64)) * per;
+  };
+  const int first = lane * sh.others() / 63;
+  const float more = (prefix(sh.grid) - prefix(sh.grid - sh.more) + prefix(sh.grid + first + sh.n_more) - prefix(sh.grid + first));
+  const float rest = prefix(n_tiles) - more;
+  float worst = fmaxf(more / (float)sh.more, rest / (float)(sh.grid - sh.more));
+  int best = first;
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) {                // the smallest, of equal ones the first
+    const float w = __shfl_xor(worst, d, 64);
+    const int f = __shfl_xor(best, d, 64);
+    if (w < worst || (w == worst && f < best)) { worst = w; best = f; }
+  }
+  return best;
+}
+
 // Inclusive sum over the first 32 lanes of a wavefront (data-parallel-primitive shifts inside rows of 16 lanes, then lane 15's into
 // the second row).
 __device__ __forceinline__ int half_wave_scan(int v) {
@@ -153,7 +206,7 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t kRowTab = (size_t)(3 * kRowsPad + kHdrWords) * 4;       // rows' voxels, position codes, counts; header
   // of this tile and of the next one; 16 zero bytes, a place for results nobody needs (see attn_item), set table
   static constexpr size_t off_zero = off_misc + 2 * kRowTab, off_spare = off_zero + 16, kSpare = (size_t)C / 2 * sizeof(T) + 16 * sizeof(T);
-  static constexpr size_t off_sets = off_spare + kSpare, kMisc = off_sets + (size_t)(kSetWords + 2) * 4 - off_misc;
+  static constexpr size_t off_sets = off_spare + kSpare, kMisc = off_sets + (size_t)(kSetWords + 4) * 4 - off_misc;
   // after attention the V^T region holds the GELU table, the two LayerNorms' scales and shifts, and the LayerNorm statistics
   static constexpr size_t off_gelu = off_v, off_aff = off_v + 4096, off_stat = off_aff + (size_t)4 * C * 4, kStat = (size_t)2 * kStatGroupsMax * kRowsMax * 4;
   static_assert(off_stat + kStat <= off_misc, "GELU table and LayerNorm statistics must fit in the V^T region");
@@ -421,7 +474,7 @@ template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(Set
 // SETS: the instantiations for sets of four to six key tiles; the common one does not carry that code.
 //
 // The grid is as many workgroups as fit the GPU at once; each takes every gridDim.x-th tile, back and forth (tiles are listed
-// most rows first).  What bounds it is not one unit but the chain of a tile's phases; a tile's beginning -- descriptor, then the
+// most rows first), LONG: the tiles Shares says.  What bounds it is not one unit but the chain of a tile's phases; a tile's beginning -- descriptor, then the
 // rows it names, then weights -- takes 8 k of the 42 k clocks of a workgroup's only 64-row tile, and between two tiles of a workgroup all of it is
 // under way during the tile before: the descriptor is requested behind the attention, the rows behind the first MLP matrix
 // (stored over Q once the second one is through with it; X and Q change places), the Q/K/V weights around the last LayerNorm.
@@ -429,9 +482,9 @@ template <typename T, int C, int HEADS, int HID> constexpr int groups_per_cu(Set
 // -> this loop, pass of the 30,000-pillar frame (two tiles a workgroup) 360.0 -> 359.1 us, four frames 1,109 -> 1,078, 30 x 30
 // windows 316.9 -> 290.0, 120,000 voxels 679 -> 653, skewed batch 7,686 -> 7,383; 3,001 pillars (one tile a workgroup)
 // 158.5 -> 160.1, of which the kernel's own time is 16.0 -> 15.9 a layer.
-template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
-__global__ void __launch_bounds__(kLayerWaves * 64, (3 * groups_per_cu<T, C, HEADS, HID>(SETS)))
-k_layer(LayerCall<T> call) {
+// LONG: the frame has two full rounds of tiles and more (is_long()).
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP, bool LONG>
+__device__ __forceinline__ void layer_tiles(const LayerCall<T>& call) {
   const LayerDev& p = call.layer;
   const MapsDev& mp = call.maps;
   typedef LayerLds<T, C, HEADS, HID> L;
@@ -448,7 +501,7 @@ k_layer(LayerCall<T> call) {
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
   float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // over V^T once attention is done
-  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_sets);   // [kSetWords + 2]: set_word() of every set, number of items, whether they are split
+  unsigned* set_tab = reinterpret_cast<unsigned*>(smem + L::off_sets);   // [kSetWords + 4]: set_word() of every set, number of items, whether they are split; LONG: the next tile, Shares' `first`
 
   // wave-uniform values are read back through readfirstlane so that the compiler keeps them in
   // scalar registers: branches on them are scalar branches, not exec-mask divergence
@@ -482,7 +535,8 @@ k_layer(LayerCall<T> call) {
     n_sets = n_sets < mp.max_sets ? n_sets : mp.max_sets;
     n_tiles = (n_sets + per_wg - 1) / per_wg;
   }
-  int stride = 2 * (int)(gridDim.x - blockIdx.x) - 1;
+  constexpr int kGrid = kComputeUnits * groups_per_cu<T, C, HEADS, HID>(SETS);       // workgroups, if there are more tiles than that
+  int stride = LONG ? 1 : 2 * (int)(gridDim.x - blockIdx.x) - 1;      // to the next tile; LONG: the workgroup's tile number
   int xo = 0, tab = 0;                           // byte offsets of X (Q: the other side of K) and of this tile's row tables
   DSVT_PHASE(tile, 0);
 
@@ -643,7 +697,20 @@ k_layer(LayerCall<T> call) {
   DSVT_REFRESH_LANE();
   DSVT_PHASE(tile, 2);                                 // rows in LDS
   first.template prefetch_rest<kEarly>(p.b_qkv, 2 * C / (16 * NT_QKV));
-  project(first, RT);
+  if constexpr (LONG) {                            // (the second wavefront, which is early, finds out about the tiles)
+    int sample;
+    opaque_def(sample);
+    const bool choose = wave == 1 && n_tiles > kGrid && n_tiles % kGrid != 0;
+    if (choose) sample = mp.tile_desc[(size_t)((2 * lane + 1) * (int64_t)n_tiles / 128) * 256];
+    project(first, RT);
+    if (wave == 1) {
+      int from = 0;
+      if (choose) from = first_of_more(Shares(n_tiles, kGrid), n_tiles, sample);
+      if (lane == 0) set_tab[kSetWords + 3] = (unsigned)from;      // (its own)
+    }
+  } else {
+    project(first, RT);
+  }
 
   for (;;) {
     DSVT_REFRESH_LANE();
@@ -652,8 +719,8 @@ k_layer(LayerCall<T> call) {
     T* Xs = reinterpret_cast<T*>(smem + xo);
     T* Qs = reinterpret_cast<T*>(smem + (2 * L::kTile - xo));
     T* Hs = reinterpret_cast<T*>(smem + (L::kTile - xo / 2));
-    const int next = tile + stride;
-    const bool more = next < n_tiles;
+    int next = LONG ? 0 : tile + stride;
+    bool more = LONG || next < n_tiles;
     // LayerNorm phases (small weight matrices): every wavefront owns C / SG features of one part of
     // the row tiles; the Q/K/V and first MLP projections (bandwidth-heavy) give a wavefront all rows
     // of its output tiles instead, so that each of their weight fragments is loaded only once.  The last part may have fewer
@@ -689,10 +756,18 @@ k_layer(LayerCall<T> call) {
       if (lane < kSetWords)
         set_tab[lane] = lane < ns ? set_word(r0 < 0 ? 0 : (r0 > kRowsMax - 4 ? kRowsMax - 4 : r0), nu, (incl - cnt) << split) : kNoItem;
       if (lane == kSetWords - 1) { set_tab[kSetWords] = (unsigned)(incl << split); set_tab[kSetWords + 1] = (unsigned)split; }
+    } else if (LONG && wave == 1) {
+      int then = -1;
+      if (n_tiles > kGrid) then = Shares(n_tiles, kGrid).tile(blockIdx.x, stride, __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords + 3]));
+      if (lane == 0) set_tab[kSetWords + 2] = (unsigned)then;
     }
     lds_barrier();
     DSVT_REFRESH_LANE();
 
+    if constexpr (LONG) {
+      next = __builtin_amdgcn_readfirstlane((int)set_tab[kSetWords + 2]);
+      more = next >= 0;
+    }
     DSVT_PHASE(tile, 3);                               // Q, K, V^T in LDS
     // ---- 4. attention inside every set; O overwrites Q
     {
@@ -867,7 +942,7 @@ k_layer(LayerCall<T> call) {
     DSVT_PHASE(next, 1);
     qkv.template prefetch_rest<kEarly>(args->layer.b_qkv, 2 * C / (16 * NT_QKV));
     tile = next;
-    stride = 2 * (int)gridDim.x - stride;
+    stride = LONG ? stride + 1 : 2 * (int)gridDim.x - stride;
     xo = 2 * (int)L::kTile - xo;
     tab = (int)L::kRowTab - tab;
     R = tile_rows(tab);
@@ -878,6 +953,14 @@ k_layer(LayerCall<T> call) {
     project(qkv, RT);
   }
 }
+
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
+__global__ void __launch_bounds__(kLayerWaves * 64, (3 * groups_per_cu<T, C, HEADS, HID>(SETS)))
+k_layer(LayerCall<T> call) { layer_tiles<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP, false>(call); }
+// The same for frames of several rounds of tiles.
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
+__global__ void __launch_bounds__(kLayerWaves * 64, (3 * groups_per_cu<T, C, HEADS, HID>(SETS)))
+k_long_layer(LayerCall<T> call) { layer_tiles<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP, true>(call); }
 
 // ------------------------------------------------------------------------------------------
 // Packed buffer of a layer: the four matrices in fragment order, each on a 256-byte boundary.
@@ -956,10 +1039,14 @@ int check_maps(const dsvt_maps& mp) {
   return DSVT_OK;
 }
 
-template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP>
+template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2, SetSize SETS, bool DUP, bool LONG = false>
 int launch_layer_v(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,
                    hipStream_t st) {
-  auto kern = k_layer<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP>;
+  const auto kernel = []() {
+    if constexpr (LONG) return k_long_layer<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP>;
+    else return k_layer<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, SETS, DUP>;
+  };
+  auto kern = kernel();
   constexpr size_t lds = LayerLds<T, C, HEADS, HID>::total;
   static std::atomic<uint64_t> lds_allowed{0};
   if (int rc = dsvt_allow_lds(reinterpret_cast<const void*>(kern), lds, lds_allowed)) return rc;
@@ -990,6 +1077,14 @@ bool slim_sets(const dsvt_maps& mp) {
   return mp.tau <= 72 && mp.n_voxels > 256 * per_tile;
 }
 
+// Whole layers with a work list of at least two full rounds of tiles (a tile has at most 96 rows), sets of up to 48 voxels.  Where the number
+// of tiles does not follow from that of the voxels -- 41,000 pillars have 656 to 722 -- going back and forth through the list is within 1.5 % of it,
+// and finding the tiles costs a layer of a single round up to 1 %.
+template <typename T, int C, int HEADS, int HID>
+bool is_long(const dsvt_maps& mp, int full) {
+  return full && mp.tiles.tile_desc && mp.n_voxels > kRowsMax * 2 * kComputeUnits * groups_per_cu<T, C, HEADS, HID>(kSets48);
+}
+
 template <typename T, int C, int HEADS, int HID, int NT_QKV, int NT_O, int NT_1, int NT_2>
 int launch_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coords, const void* x, void* out, int full,
                  hipStream_t st) {
@@ -998,6 +1093,10 @@ int launch_layer(const dsvt_layer_w& w, const dsvt_maps& mp, const int32_t* coor
   constexpr bool kSlim = two_groups_fit<T, C, HEADS, HID>();
   const bool dup = w.dup_mode != 0;
   if (mp.tau <= 48) {
+    if (is_long<T, C, HEADS, HID>(mp, full)) {
+      if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, true, true>(w, mp, coords, x, out, full, st);
+      return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, false, true>(w, mp, coords, x, out, full, st);
+    }
     if (dup) return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, true>(w, mp, coords, x, out, full, st);
     return launch_layer_v<T, C, HEADS, HID, NT_QKV, NT_O, NT_1, NT_2, kSets48, false>(w, mp, coords, x, out, full, st);
   }

@@ -213,6 +213,49 @@ def test_workgroups_that_take_several_tiles(C, heads, hidden, dtype, tau, dup_mo
         assert torch.equal(again, y)
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype,n_win", [(192, 8, 384, "bf16", 2600), (192, 8, 384, "bf16", 3413), (128, 8, 256, "bf16", 2901),
+                                                        (64, 4, 128, "bf16", 5003), (64, 4, 128, "f32", 2701)])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_frames_of_several_rounds_and_a_part(C, heads, hidden, dtype, n_win, dup_mode):
+    """Frames of more than two rounds of tiles, the last of them partial, of windows of 1 to 36 voxels in random order: which workgroups take
+    a tile more, and which ones, depends on the tiles' rows; every tile is to be done once.  Five windows' oracle gives every row.  A work
+    list that ends early (128 tiles fewer, then fewer than there are workgroups) leaves the rows of the tiles past its end alone."""
+    win, tau, sizes = (12, 12, 1), 36, (36, 31, 22, 17, 1)
+    rng = np.random.Generator(np.random.Philox(81))
+    cells = [rng.permutation(144)[:s] for s in sizes]
+    which = rng.choice(5, n_win, p=(0.35, 0.2, 0.2, 0.2, 0.05))
+    place = lambda w, cell: np.stack([0 * cell, 12 * (w // 72) + cell // 12, 12 * (w % 72) + cell % 12, 0 * cell], 1).astype(np.int32)
+    grid = (864, 864, 1)
+    ws = [synth.make_layer_weights(82 + a, C, heads, hidden, win, dtype) for a in (0, 1)]
+    layers = [dsvt.LayerWeights(w, dup_mode) for w in ws]
+    one = np.concatenate([place(k, c) for k, c in enumerate(cells)])
+    x1 = synth.make_features(84, len(one), C, dtype)
+    ref1 = orc.block(ws, [orc.partition(one, grid, win, (0, 0, 0), tau, a) for a in (0, 1)], one, x1, dup_mode)
+    first = np.cumsum((0,) + sizes)
+    coords = np.concatenate([place(w, cells[k]) for w, k in enumerate(which)])
+    rows = np.concatenate([np.arange(first[k], first[k + 1]) for k in which])
+    cd, xd = dev_coords(coords), dev_feats(x1[rows], dtype)
+    maps = [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
+    n_tiles, groups = int(maps[0].n_tiles.item()), 512 if (C, dtype) == (64, "bf16") else 256
+    print(f"[case] {n_win} windows, {len(coords)} voxels, {n_tiles} tiles, C={C} {dtype} dup={dup_mode}", flush=True)
+    assert len(coords) > 96 * 2 * groups and n_tiles > 2 * groups and n_tiles % groups != 0
+    y = dsvt.dsvt_block(layers, maps, cd, xd)
+    torch.cuda.synchronize()
+    assert rel_err(y, ref1[rows]) < TOL[dtype]
+    for keep in (n_tiles - 128, groups - 1):
+        out = torch.full_like(xd, 7.0)
+        for m in maps:
+            m.n_tiles.fill_(keep)
+        dsvt.dsvt_block(layers, maps, cd, xd, x_out=out)
+        torch.cuda.synchronize()
+        done = np.zeros(len(coords), bool)
+        desc = maps[0].tile_desc[:keep].cpu().numpy()
+        listed = desc[:, 64::2][:, :96]
+        done[listed[(np.arange(96)[None, :] < desc[:, :1]) & (listed >= 0)]] = True
+        assert 0 < done.sum() < len(coords) and bool((out[torch.as_tensor(~done).cuda()] == 7.0).all())
+        assert torch.equal(out[torch.as_tensor(done).cuda()], y[torch.as_tensor(done).cuda()])
+
+
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
 @pytest.mark.parametrize("dup_mode", [0, 1])
 def test_attention_items_split_and_whole(C, heads, hidden, dtype, dup_mode):

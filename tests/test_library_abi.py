@@ -139,6 +139,14 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2 and "single-GPU" in r.stderr and r.stdout.strip() == ""
 
 
+def test_layer_kernels_of_long_frames_spill_nothing():
+    """The layer's kernels for frames of several rounds of tiles: sets of up to 48 voxels, repeats masked or as keys, four shapes."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    kernels = [k for k in _kernel_metadata(LIB) if "k_long_layer" in k[0]]
+    assert len(kernels) == 8 and [k for k in kernels if k[1] or k[2] or k[3]] == []
+
+
 def test_bench_reports_layer_traffic_only_for_the_sources_it_was_measured_with(tmp_path, monkeypatch):
     """bench.py takes the layer kernel's HBM bytes per launch from profiles/k_layer_hbm_traffic.txt, by workload, and
     only when the file's hash of layer.hip + mma.h is that of the sources in the tree."""
