@@ -268,8 +268,10 @@ __device__ __forceinline__ void fill_tile_starts(const int32_t* P, uint16_t* jum
 // fill_tile_starts leaves them).  A tile filled up to `cap` rows holds about cap - (mean set rows) / 2.  Filling pays
 // when it saves a whole round over the compute units, or when the frame takes more than two rounds anyway.  A frame
 // of a few rounds gets the capacity that puts its tile count just under a whole number of rounds (a last round of a
-// few full-size tiles costs as much as a full round); should the count still come out above it, the next number of
-// rounds is tried.  Frames of more than four rounds get the whole 96 rows: fewer, fuller tiles beat a full last round.
+// few full-size tiles costs as much as a full round); should the count still come out above it, the whole 96 rows are tried and
+// then the next number of rounds.  (Sets that fill a tile badly miss the count by a little.  Without -> with the 96 rows
+// in between: sets of up to 60 in 30 x 30 windows, C = 128, 15,000 voxels 311 -> 234 tiles, a pass of four layers 123.9 -> 109.2 us, two frames
+// of 15,000 613 -> 464 and 189.5 -> 163.0; sets of up to 48, 38,000 pillars in windows of 24 cells 939 -> 475, 261.2 -> 226.3.)  Frames of more than four rounds get the whole 96 rows: fewer, fuller tiles beat a full last round.
 // Two layers, C = 192, cut -> filled: 15,000 pillars (two rounds become one) 71.1 -> 49.4 us, 20,000 74.8 -> 57.0, 35,000 (three
 // become two) 116.7 -> 92.6, 40,000 117.3 -> 99.0, 45,000 119.1 -> 118.5, 52,000 149.5 -> 132.2, 64,000 180 -> 164; 22,000 to 30,000 keep
 // the cut.  Five rounds and more, tuned capacity -> 96 rows: 80,000 pillars 197 -> 189, 120,000 voxels 295.4 -> 293.8, 200,000 483 -> 465.
@@ -291,10 +293,11 @@ __device__ __forceinline__ bool fill_tiles(const int32_t* P, uint16_t* jump, uin
   const int32_t rounds_cut = (total_rows + kComputeUnits * rpc_max - 1) / (kComputeUnits * rpc_max);
   int32_t rounds = (int32_t)ceilf((float)total_rows / (256.f * best_fill));
   if (rounds_cut <= 1) return false;                         // (tile_cut spreads frames of less than a round)
-  for (int32_t attempt = 0; attempt < 2; ++attempt, ++rounds) {
+  bool whole = false;                                        // the whole 96 rows for these rounds
+  for (int32_t attempt = 0; attempt < 2; attempt += whole ? 0 : 1, rounds += whole ? 0 : 1) {
     if (!(rounds < rounds_cut || rounds_cut > 2)) return false;
     int32_t cap = kTileRows;
-    if (rounds <= kTunedRounds) {
+    if (rounds <= kTunedRounds && !whole) {
       const float fill = (float)total_rows / (0.97f * 256.f * (float)rounds);
       const int32_t c = ((int32_t)ceilf(fill + half_set) + 3) & ~3;
       cap = c > kTileRows ? kTileRows : c;
@@ -309,6 +312,7 @@ __device__ __forceinline__ bool fill_tiles(const int32_t* P, uint16_t* jump, uin
     const int32_t tiles = n_starts;
     lds_barrier();
     if (tiles <= rounds * kComputeUnits) return true;
+    whole = !whole && cap < kTileRows && (float)tiles * ((float)cap - half_set) <= (float)(rounds * kComputeUnits) * best_fill;      // (if it looks as if they would do)
   }
   return false;
 }

@@ -162,6 +162,25 @@ def test_large_frames_get_filled_tiles(cid, n):
         assert rows / nt > 66 and 0.88 < (nt / 256) / np.ceil(nt / 256) <= 1.0
 
 
+@pytest.mark.parametrize("seed,tuned,whole", [(90, 273, 195), (93, 286, 196), (95, 259, 216), (92, 242, 208)])
+def test_tiles_of_frames_that_a_tuned_capacity_misses(seed, tuned, whole):
+    """144 windows of 60 to 149 voxels, sets of up to 60: cut, their tiles need two rounds over 256 units; filled up to the capacity tuned
+    for one round (84 or 88 rows) they are `tuned`, which may be more than 256, filled up to 96 rows `whole`."""
+    grid, win, tau = (360, 360, 1), (30, 30, 1), 60
+    rng = np.random.Generator(np.random.Philox(seed))
+    cnt = rng.integers(60, 150, 144)
+    rows = []
+    for w, k in enumerate(cnt):
+        cell = rng.permutation(900)[:k]
+        rows.append(np.stack([0 * cell, 30 * (w // 12) + cell // 30, 30 * (w % 12) + cell % 30, 0 * cell], 1))
+    coords = np.concatenate(rows).astype(np.int32)
+    print(f"[case] {len(coords)} voxels, tuned capacity gives {tuned} tiles, 96 rows {whole}", flush=True)
+    pair = dsvt.dsvt_partition_xy(dsvt.part_cfg(grid, win, (0, 0, 0), tau, 1, 0), dev_coords(coords))
+    for axis, gm in enumerate(pair):
+        assert_maps_equal(gm, orc.partition(coords, grid, win, (0, 0, 0), tau, axis))
+        assert int(gm.n_tiles.item()) == (tuned if tuned <= 256 else whole)
+
+
 def test_partition_buffers_reused_across_frame_sizes():
     """A stream of frames with different voxel counts through one set of buffers (sized for the largest): the
     scratch buffer's bitmap is left clean by every call whatever the frame's size."""
