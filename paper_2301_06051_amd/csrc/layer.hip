@@ -13,6 +13,7 @@
 #include "common.h"
 #include "mma.h"
 #include "phase_clock.h"
+#include <cfloat>
 
 namespace {
 
@@ -364,7 +365,9 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           cm[hl] = k == 0 ? x : fmaxf(cm[hl], x);
         }
       }
-      col_reduce(cm, [](float a, float b) { return raw_max(a, b); }, [](float a) { return a; });     // (key 0 exists for every query: finite)
+      // (Key 0 exists for every query, but the table may hold -inf for it and for all keys of a step.  The running maximum starts at the lowest float
+      // then, which no finite logit lies below: -inf less it stays -inf, where -inf less -inf is NaN, and nothing of such a step counts in the next one.)
+      col_reduce(cm, [](float a, float b) { return raw_max(a, b); }, [&](float a) { return CT < KTC && k0 == 0 ? raw_max(a, -FLT_MAX) : a; });
       float scale[HS];                              // of the keys before these
 #pragma unroll
       for (int hl = 0; hl < HS; ++hl) {

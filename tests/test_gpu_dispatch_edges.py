@@ -57,6 +57,32 @@ def test_logits_that_rise_and_fall_over_a_large_set(slope, dup_mode):
 
 
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("lowest", [-np.inf, np.finfo(np.float32).min])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_position_tables_that_mask_keys(C, heads, hidden, dtype, lowest, dup_mode):
+    """Rows of 96, 81 and 50 voxels, one set each, and tables of -inf or the lowest float for pairs further apart than 32 cells on either side
+    or on both (the first 32 keys of the queries behind them, the last ones of those in front), for 32 to 63 cells (keys 32 to 63 of the last of 96
+    queries) and for all pairs but a voxel with itself.  Every query keeps its own key."""
+    grid, win, tau = (96, 3, 1), (96, 1, 1), 96
+    rng = np.random.Generator(np.random.Philox(91))
+    coords = np.array([(0, i, y, 0) for y, n in enumerate((96, 81, 50)) for i in rng.permutation(n)], np.int32)
+    x = synth.make_features(92, len(coords), C, dtype)
+    w = synth.make_layer_weights(93, C, heads, hidden, win, dtype)
+    own = w["rel_bias"]
+    d = np.arange(191) - 95                                  # query - key
+    om = orc.partition(coords, grid, win, (0, 0, 0), tau, 0)
+    assert om["n_sets"] == 3
+    cd = dev_coords(coords)
+    maps = gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0)
+    for name, masked in (("first", d > 32), ("last", d < -32), ("near", np.abs(d) > 32), ("middle", (d >= 32) & (d < 64)), ("others", d != 0)):
+        w["rel_bias"] = np.where(masked[None, :], np.float32(lowest), own).astype(np.float32)
+        print(f"[case] table masks {name} keys with {lowest}, C={C} {dtype} dup={dup_mode}", flush=True)
+        y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), maps, cd, dev_feats(x, dtype))
+        torch.cuda.synchronize()
+        assert rel_err(y, orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype], name
+
+
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
 @pytest.mark.parametrize("tau,dup_mode", [(96, 0), (96, 1), (48, 0), (48, 1)])
 def test_tiles_of_one_to_six_row_tiles(C, heads, hidden, dtype, tau, dup_mode):
     """A block over one window of 1 to 96 voxels, in one set or two: the projections' last trip has one or two row tiles, and with a
