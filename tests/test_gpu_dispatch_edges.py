@@ -308,6 +308,30 @@ def test_attention_items_split_and_whole(C, heads, hidden, dtype, dup_mode):
     assert rel_err(out[1], orc.set_attention(w, om, coords, x, dup_mode)) < TOL[dtype]
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype", [(192, 8, 384, "bf16"), (128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_a_set_alone_in_its_tile_and_beside_another(C, heads, hidden, dtype, dup_mode):
+    """A set of one or two key tiles that has its tile to itself is split into items of a quarter of the heads, beside another of two key tiles
+    it is not: the same bits.  Without a work list a tile is two sets."""
+    grid, win, tau = (12, 24, 1), (12, 12, 1), 48
+    rng = np.random.Generator(np.random.Philox(101))
+    w = synth.make_layer_weights(102, C, heads, hidden, win, dtype)
+    layer = dsvt.LayerWeights(w, dup_mode)
+    for cnt in (7, 16, 17, 25, 32):
+        cells = [rng.permutation(144)[:n] for n in (cnt, 32)]
+        coords = np.concatenate([np.stack([0 * c, c // 12, 12 * k + c % 12, 0 * c], 1) for k, c in enumerate(cells)]).astype(np.int32)
+        x = synth.make_features(103 + cnt, len(coords), C, dtype)
+        print(f"[case] {cnt} voxels alone and beside 32, C={C} {dtype} dup={dup_mode}", flush=True)
+        out = []
+        for n in (cnt, len(coords)):
+            cd = dev_coords(coords[:n])
+            maps = gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0, tiles=False)
+            assert int(maps.n_sets.item()) == (1 if n == cnt else 2)
+            out.append(dsvt.dsvt_set_attention(layer, maps, cd, dev_feats(x[:n], dtype)))
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], out[1][:cnt]), cnt
+
+
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
 @pytest.mark.parametrize("n_multi,n_single", [(0, 24576), (0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
 def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
