@@ -248,9 +248,8 @@ template <typename V> __device__ __forceinline__ void lds_write(int at, V v) { *
 // What bounds it is the issue of vector instructions (an item of two key tiles and four heads: 36 exp and rcp at a quarter of the rate and
 // 250 others, 3 wavefronts a SIMD) and, within a head, one dependent step after the other.  So the heads go through the steps side by side -- all
 // products with the keys, all maxima, .. --, the heads' maxima share the lane swaps (col_reduce()), the terms are added behind the
-// products (as the MFMAs' start values they had to be moved into place, an instruction each too, and to be there first).  In large bf16 sets, and in those with doubled
-// voxels (where 32-bit sums left items of one and of two heads with different last bits), the sums of the probabilities come from the matrix cores, from a fragment of ones: every lane gets them, from the very bf16 probabilities the
-// numerators have, added in 32 bits.  (Nearer to 64 bits than sums taken before the rounding, 0.997 to 0.9998 of the distance over whole stacks.  With
+// products (as the MFMAs' start values they had to be moved into place, an instruction each too, and to be there first).  In large bf16 sets the sums of the probabilities come from the matrix cores, from a fragment of ones: every lane gets them, from the
+// very bf16 probabilities the numerators have, added in 32 bits.  (Nearer to 64 bits than sums taken before the rounding, 0.997 to 0.9998 of the distance over whole stacks.  With
 // those four heads of a large set spill 37 to 73 registers, 244 -> 326 us; sets of up to 48 voxels keep them: 0 to 1 % of
 // a pass, and no other result than before but for the terms' own rounding.)  Head after head, 336 + 36 instructions and 46 waits -> this,
 // attention of a 64-row tile 7.6 -> 6.3 k clocks, of an 82-row tile 10.5 -> 9.0 k; passes of 3,001 pillars 141.9 -> 138.7 us, 30,000 337.6 -> 330.5,
@@ -271,7 +270,7 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   constexpr int TPC = KC / 16;                    // key tiles per PV fragment: 2 (bf16) or 1 (fp32)
   static_assert(HG == 1 || HG == 2 || HG == 4, "heads per item");
   static_assert(D <= KC, "one fragment per query");
-  constexpr bool kSumByMma = sizeof(T) == 2 && (KTC > 3 || DUP);
+  constexpr bool kSumByMma = sizeof(T) == 2 && KTC > 3;
   // Four heads of four key tiles and more take the keys 32 at a time, with a running maximum: all logits at once do not fit the registers
   // (and two heads at a time fetch the terms twice as often, 8 bytes a lane; a load is 17 clocks of the compute unit's memory pipe either way).
   constexpr int CT = HG == 4 && KTC > 3 ? 2 : KTC;                // key tiles at a time
@@ -387,10 +386,10 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           if constexpr (DUP) mult = *reinterpret_cast<const f32x4*>(row_mult + r0 + 16 * (k0 + kt) + 4 * g);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
-            if constexpr (DUP) e *= mult[i];
-            S[hl][kt][i] = e;
-            if constexpr (!kSumByMma) part[hl] = kt + i == 0 ? e : part[hl] + e;
+            const float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
+            S[hl][kt][i] = DUP ? e * mult[i] : e;
+            // (the fma written out: left to itself the compiler makes one of either product of the first two, and not the same one in every kernel)
+            if constexpr (!kSumByMma) part[hl] = kt + i == 0 ? S[hl][kt][i] : (DUP ? __builtin_fmaf(e, mult[i], part[hl]) : part[hl] + e);
           }
         }
 #pragma unroll

@@ -332,6 +332,33 @@ def test_a_set_alone_in_its_tile_and_beside_another(C, heads, hidden, dtype, dup
         assert torch.equal(out[0], out[1][:cnt]), cnt
 
 
+@pytest.mark.parametrize("C,heads,hidden", [(192, 8, 384), (128, 8, 256), (64, 4, 128)])
+@pytest.mark.parametrize("tau,cnt", [(48, 48), (48, 32)])
+@pytest.mark.parametrize("dup_mode", [0, 1])
+def test_sums_of_probabilities_are_of_32_bit_terms(C, heads, hidden, tau, cnt, dup_mode):
+    """bf16, sets without and with doubled voxels. All keys but the query's own have one probability, in the
+    middle between two bf16 numbers but for 2^-12 of it, and only the first voxel has values: its output is the value over the sum.  The value's
+    and the output's rounding are at most 2^-9 each way and even out over all mantissas and both directions of the probability
+    (mean of C: below 2^-11, five times its deviation for 64); probabilities rounded in front of the sum move it by up to 2^-8."""
+    grid, win = (96, 1, 1), (96, 1, 1)
+    coords = np.array([(0, i, 0, 0) for i in range(cnt)], np.int32)
+    x = np.zeros((cnt, C), np.float32)
+    x[0] = 1.0 + np.arange(C) % 128 / 128.0
+    w = synth.make_layer_weights(111, C, heads, hidden, win, "bf16")
+    w["w_qkv"] = np.concatenate([np.zeros((2 * C, C)), np.eye(C)]).astype(np.float32)
+    w["w_o"], w["b_qkv"], w["b_o"] = np.eye(C, dtype=np.float32), np.zeros(3 * C, np.float32), np.zeros(C, np.float32)
+    om = orc.partition(coords, grid, win, (0, 0, 0), tau, 0)
+    cd = dev_coords(coords)
+    maps = gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, 0)
+    for p in (1 + 2.0 ** -8 - 2.0 ** -12, 1 + 2.0 ** -8 + 2.0 ** -12):
+        w["rel_bias"] = np.where(np.arange(191)[None, :] == 95, 0.0, np.log(p / 2)).repeat(heads, 0).astype(np.float32)
+        print(f"[case] probabilities of {p} / 2, C={C} tau={tau} {cnt} voxels dup={dup_mode}", flush=True)
+        y = dsvt.dsvt_set_attention(dsvt.LayerWeights(w, dup_mode), maps, cd, dev_feats(x, "bf16"))
+        torch.cuda.synchronize()
+        ref = orc.set_attention(w, om, coords, x, dup_mode)[0]
+        assert abs(np.mean(y[0].double().cpu().numpy() / ref) - 1) < 2.0 ** -11, p
+
+
 @pytest.mark.parametrize("C,heads,dtype", [(192, 8, "bf16"), (128, 8, "bf16"), (64, 4, "bf16"), (64, 4, "f32")])
 @pytest.mark.parametrize("n_multi,n_single", [(0, 24576), (0, 24577), (1, 24623), (8193, 9000), (12289, 0), (20, 24576 + 47)])
 def test_pool_regions_of_one_voxel_apart(C, heads, dtype, n_multi, n_single):
