@@ -248,10 +248,9 @@ template <typename V> __device__ __forceinline__ void lds_write(int at, V v) { *
 // What bounds it is the issue of vector instructions (an item of two key tiles and four heads: 36 exp and rcp at a quarter of the rate and
 // 250 others, 3 wavefronts a SIMD) and, within a head, one dependent step after the other.  So the heads go through the steps side by side -- all
 // products with the keys, all maxima, .. --, the heads' maxima share the lane swaps (col_reduce()), the terms are added behind the
-// products (as the MFMAs' start values they had to be moved into place, an instruction each too, and to be there first).  In large bf16 sets the sums of the probabilities come from the matrix cores, from a fragment of ones: every lane gets them, from the
-// very bf16 probabilities the numerators have, added in 32 bits.  (Nearer to 64 bits than sums taken before the rounding, 0.997 to 0.9998 of the distance over whole stacks.  With
-// those four heads of a large set spill 37 to 73 registers, 244 -> 326 us; sets of up to 48 voxels keep them: 0 to 1 % of
-// a pass, and no other result than before but for the terms' own rounding.)  Head after head, 336 + 36 instructions and 46 waits -> this,
+// products (as the MFMAs' start values they had to be moved into place, an instruction each too, and to be there first).  The sums are of the 32-bit
+// probabilities, in one order of keys and lanes whatever the heads an item has (from the matrix cores, of those rounded to bf16: the same time in large sets, a value off by
+// up to 2^-8).  Head after head, 336 + 36 instructions and 46 waits -> this,
 // attention of a 64-row tile 7.6 -> 6.3 k clocks, of an 82-row tile 10.5 -> 9.0 k; passes of 3,001 pillars 141.9 -> 138.7 us, 30,000 337.6 -> 330.5,
 // windows of 12 and 24 cells 472.8 -> 458.1, 30 x 30 windows 267.7 -> 265.0, 120,000 voxels 619.7 -> 604.1.  Position
 // table rows of all heads -> of four: 30 x 30 windows 264.8 -> 261.2 (a table of 111 KB: the rows that a load touches lie in half as many
@@ -270,7 +269,6 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   constexpr int TPC = KC / 16;                    // key tiles per PV fragment: 2 (bf16) or 1 (fp32)
   static_assert(HG == 1 || HG == 2 || HG == 4, "heads per item");
   static_assert(D <= KC, "one fragment per query");
-  constexpr bool kSumByMma = sizeof(T) == 2 && KTC > 3;
   // Four heads of four key tiles and more take the keys 32 at a time, with a running maximum: all logits at once do not fit the registers
   // (and two heads at a time fetch the terms twice as often, 8 bytes a lane; a load is 17 clocks of the compute unit's memory pipe either way).
   constexpr int CT = HG == 4 && KTC > 3 ? 2 : KTC;                // key tiles at a time
@@ -373,10 +371,10 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
         if (k0 > 0) {
           cm[hl] = raw_max(cm[hl], mx[hl]);
           scale[hl] = __builtin_amdgcn_exp2f(mx[hl] - cm[hl]);
+          sum[hl] *= scale[hl];
         }
         mx[hl] = cm[hl];
       }
-      float part[HS];
       Frag fp[HS][NCH];
 #pragma unroll
       for (int hl = 0; hl < HS; ++hl) {
@@ -389,8 +387,11 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
             const float e = __builtin_amdgcn_exp2f(S[hl][kt][i] - mx[hl]);       // exp2(-inf) = 0
             S[hl][kt][i] = DUP ? e * mult[i] : e;
             // (the fma written out: left to itself the compiler makes one of either product of the first two, and not the same one in every kernel)
-            if constexpr (!kSumByMma) part[hl] = kt + i == 0 ? S[hl][kt][i] : (DUP ? __builtin_fmaf(e, mult[i], part[hl]) : part[hl] + e);
+            sum[hl] = k0 + kt + i == 0 ? S[hl][kt][i] : (DUP ? __builtin_fmaf(e, mult[i], sum[hl]) : sum[hl] + e);
           }
+          // (The sum up to here stands before the next key tile's: the compiler otherwise adds behind all conversions and keeps the 32-bit probabilities until
+          // then, and C = 128 spills 37 registers, 73 with repeats as keys, C = 64 in kSets96Slim four.)
+          if (KTC > 3) asm volatile("" : "+v"(sum[hl]));
         }
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
@@ -424,24 +425,10 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           }
           O[hl][dt] = o;
         }
-        if constexpr (kSumByMma) {
-          const bf16_t one = (bf16_t)1.f;
-          f32x4 t = kZero;
-#pragma unroll
-          for (int c = 0; c < NCH; ++c)
-            if (c * TPC < kn) t = M::mma(Frag{one, one, one, one, one, one, one, one}, fp[hl][c], t);
-          part[hl] = t[0];
-        }
-        sum[hl] = k0 > 0 ? fmaf(sum[hl], scale[hl], part[hl]) : part[hl];
       }
       if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (without it four to eight registers spill: 250 us instead of 246)
     }
-    if constexpr (kSumByMma) {
-#pragma unroll
-      for (int hl = 0; hl < HS; ++hl) sum[hl] = __builtin_amdgcn_rcpf(sum[hl]);
-    } else {
-      col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
-    }
+    col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
 #pragma unroll
     for (int hl = 0; hl < HS; ++hl)
 #pragma unroll

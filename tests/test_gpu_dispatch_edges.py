@@ -333,10 +333,10 @@ def test_a_set_alone_in_its_tile_and_beside_another(C, heads, hidden, dtype, dup
 
 
 @pytest.mark.parametrize("C,heads,hidden", [(192, 8, 384), (128, 8, 256), (64, 4, 128)])
-@pytest.mark.parametrize("tau,cnt", [(48, 48), (48, 32)])
+@pytest.mark.parametrize("tau,cnt", [(48, 48), (48, 32), (96, 96), (96, 70)])
 @pytest.mark.parametrize("dup_mode", [0, 1])
 def test_sums_of_probabilities_are_of_32_bit_terms(C, heads, hidden, tau, cnt, dup_mode):
-    """bf16, sets without and with doubled voxels. All keys but the query's own have one probability, in the
+    """bf16, small and large sets, without and with doubled voxels. All keys but the query's own have one probability, in the
     middle between two bf16 numbers but for 2^-12 of it, and only the first voxel has values: its output is the value over the sum.  The value's
     and the output's rounding are at most 2^-9 each way and even out over all mantissas and both directions of the probability
     (mean of C: below 2^-11, five times its deviation for 64); probabilities rounded in front of the sum move it by up to 2^-8."""
