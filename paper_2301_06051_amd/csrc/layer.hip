@@ -487,7 +487,7 @@ __device__ __forceinline__ void layer_tiles(const LayerCall<T>& call) {
   // fragment then loaded three times: 395.0, 154.0 and 286.1: it keeps all rows per wavefront.)
   constexpr int SG = C / (16 * NT_O), RS = NW / SG, kOwnTiles = kRowTiles / RS;
   static_assert(NT_O == NT_2 && SG * 16 * NT_O == C && RS * SG == NW && RS * kOwnTiles == kRowTiles && SG <= kStatGroupsMax, "LayerNorm phases: one item per wavefront");
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(32) unsigned char smem[];             // (addresses are swizzled like places in a row)
   T* Ks = reinterpret_cast<T*>(smem + L::off_k);
   T* Vt = reinterpret_cast<T*>(smem + L::off_v);
   float* stat = reinterpret_cast<float*>(smem + L::off_stat);           // over V^T once attention is done
@@ -619,15 +619,15 @@ __device__ __forceinline__ void layer_tiles(const LayerCall<T>& call) {
     // (part k of a row tile's epilogue takes output tile k - 1)
     const auto store = [&](T* dst, int r, int nt, const f32x4& v) { *reinterpret_cast<Vec4*>(dst + (16 * r + m) * LDX + 16 * nt + (4 * g ^ swizzle<T>(m))) = pack4<T>(v); };
     if (o0 >= 2 * C) {
-      qkv.template run_rows<true>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+      qkv.template run_rows<true, NT_QKV + 1>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
         if (k >= 1 && k <= NT_QKV) *reinterpret_cast<Vec4*>(Vt + (o0 - 2 * C + 16 * (k - 1) + m) * LDV + 16 * r + 4 * g) = pack4<T>(acc[k - 1]);
       });
     } else if (o0 >= C) {
-      qkv.template run_rows<false>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+      qkv.template run_rows<false, NT_QKV + 1>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
         if (k >= 1 && k <= NT_QKV) store(Ks + (o0 - C), r, k - 1, acc[k - 1]);
       });
     } else {
-      qkv.template run_rows<false>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
+      qkv.template run_rows<false, NT_QKV + 1>(Xs, LDX, RT, [&](int k, int r, f32x4 (&acc)[NT_QKV]) {
         if (k >= 1 && k <= NT_QKV) store(Qs + o0, r, k - 1, acc[k - 1] * q_scale);      // logits in units of log2(e)
       });
     }
@@ -869,7 +869,7 @@ __device__ __forceinline__ void layer_tiles(const LayerCall<T>& call) {
     const float gelu0 = gelu_start(smem + L::off_gelu);
     // Parts of a row tile's epilogue: the table entries of output tile 0, 1, .. requested, then the values of output tile 0, 1, ..
     f32x2 chord[NT_1][4];
-    ffn1.run_before(Xs, LDX, RT, args->layer.b_1, [&](int k, int o0, int r, f32x4 (&acc)[NT_1]) {
+    ffn1.template run_before<2 * NT_1>(Xs, LDX, RT, args->layer.b_1, [&](int k, int o0, int r, f32x4 (&acc)[NT_1]) {
       if (kGeluTable && k < NT_1) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) chord[k][i] = gelu_entry(gelu0, acc[k][i]);

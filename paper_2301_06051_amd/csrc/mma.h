@@ -172,7 +172,7 @@ constexpr int kStatGroupsMax = 6;                // LayerNorm phases: the C feat
 // registers for the whole item, run() requests the next item's before the current one is consumed, and the activations of
 // row tile r + 1 are read from LDS while row tile r is in the matrix cores.  Every activation
 // fragment read from LDS feeds NT MFMAs; a weight fragment is loaded by RSPLIT wavefronts.
-// SWZ: the rows of the activations are swizzled (not in run()).
+// SWZ: the rows of the activations are swizzled (run() reads them as they are and refuses it).
 template <typename T, int NT, int K, int NOUT, int NW, int RSPLIT = 1, int KSPLIT = 1, bool SWZ = false>
 struct GemmPhase {
   static __device__ __forceinline__ int lane_piece(int lane) { return ((lane >> 4) * Mma<T>::KL) ^ (SWZ ? swizzle<T>(lane & 15) : 0); }
@@ -248,6 +248,7 @@ struct GemmPhase {
   template <typename Epi>
   __device__ __forceinline__ void run(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi) {
     static_assert(KSPLIT == 1 && (RSPLIT == 1 || RSPLIT == 2), "run() holds the whole K, and an item takes all row tiles or halves");
+    static_assert(!SWZ, "run() reads rows that are not swizzled");
     const int h0 = RSPLIT == 1 ? RT : (RT + 1) >> 1;
 #pragma unroll
     for (int it = 0; it < IPW; ++it) {
@@ -313,10 +314,11 @@ struct GemmPhase {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // All row tiles (RT > 0) of one item.  The epilogue of a row tile runs in NKF parts -- epi(part, r, acc) -- beside the next one's
+  // All row tiles (RT > 0) of one item.  The epilogue of a row tile has PARTS parts; epi(part, r, acc) is called for parts 0 .. NKF - 1, beside the next one's
   // MFMAs; before_last() is called in front of the last one's, where the weights' registers are free.
-  template <bool SWAPPED, typename Epi, typename Before>
+  template <bool SWAPPED, int PARTS, typename Epi, typename Before>
   __device__ __forceinline__ void row_steps(const T* Xs, int ldx, int RT, const f32x4 (&start)[NT], Epi epi, Before before_last) const {
+    static_assert(PARTS <= NKF, "parts of an epilogue past the last k-fragment would never run");
     const int lane = opaque_tid() & 63;
     const T* next = Xs + (lane & 15) * ldx + lane_piece(lane);
     f32x4 acc0[NT], acc1[NT];
@@ -344,23 +346,23 @@ struct GemmPhase {
     for (int k = 0; k < NKF; ++k) epi(k, r - 1, acc0);
   }
   // run() of a phase of one item per wavefront, over all row tiles.  prefetch_rest() has fetched the bias.
-  template <bool SWAPPED, typename Epi>
+  template <bool SWAPPED, int PARTS, typename Epi>
   __device__ __forceinline__ void run_rows(const T* Xs, int ldx, int RT, Epi epi) const {
     static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1 && N_ITEMS == NW, "one item per wavefront");
     f32x4 b4[NT];
     start_bias(b4, bias0, SWAPPED);
-    row_steps<SWAPPED>(Xs, ldx, RT, b4, epi, []() {});
+    row_steps<SWAPPED, PARTS>(Xs, ldx, RT, b4, epi, []() {});
   }
 
   // The same with the bias fetched here and before_last_epi() called between the last MFMAs and the last epilogue: what it requests
   // travels while the epilogue computes.
-  template <typename Epi, typename Before>
+  template <int PARTS, typename Epi, typename Before>
   __device__ __forceinline__ void run_before(const T* Xs, int ldx, int RT, const float* __restrict__ bias, Epi epi, Before before_last_epi) const {
     static_assert(KSPLIT == 1 && RSPLIT == 1 && IPW == 1, "one item per wavefront");
     if (N_ITEMS >= NW || wave < N_ITEMS) {
       Bias bl;
       load_bias(bl, bias, wave, false);
-      row_steps<false>(Xs, ldx, RT, bl.v, [&](int k, int r, f32x4 (&acc)[NT]) { epi(k, wave * 16 * NT, r, acc); }, before_last_epi);
+      row_steps<false, PARTS>(Xs, ldx, RT, bl.v, [&](int k, int r, f32x4 (&acc)[NT]) { epi(k, wave * 16 * NT, r, acc); }, before_last_epi);
     } else {
       before_last_epi();
     }

@@ -113,6 +113,30 @@ def test_projection_over_parts_of_the_row_tiles_that_it_cannot_cover_does_not_co
     assert compiles or "all row tiles or halves" in r.stderr
 
 
+@pytest.mark.parametrize("phase,call,refusal", [
+    ("GemmPhase<float, 1, 64, 64, 8>", "run(x, 72, 6, b, [&](int o0, int r, f32x4 (&acc)[1]) { x[o0 + r] = acc[0][0]; })", None),
+    ("GemmPhase<float, 1, 64, 64, 8, 1, 1, true>", "run(x, 72, 6, b, [&](int o0, int r, f32x4 (&acc)[1]) { x[o0 + r] = acc[0][0]; })", "not swizzled"),
+    ("GemmPhase<float, 1, 64, 64, 4>", "template run_before<4>(x, 72, 6, b, [&](int k, int o0, int r, f32x4 (&acc)[1]) { x[o0 + r + k] = acc[0][0]; }, []() {})", None),
+    ("GemmPhase<float, 1, 64, 64, 4>", "template run_before<5>(x, 72, 6, b, [&](int k, int o0, int r, f32x4 (&acc)[1]) { x[o0 + r + k] = acc[0][0]; }, []() {})", "would never run"),
+    ("GemmPhase<float, 1, 64, 64, 4>", "template run_rows<false, 4>(x, 72, 6, [&](int k, int r, f32x4 (&acc)[1]) { x[r + k] = acc[0][0]; })", None),
+    ("GemmPhase<float, 1, 64, 64, 4>", "template run_rows<false, 5>(x, 72, 6, [&](int k, int r, f32x4 (&acc)[1]) { x[r + k] = acc[0][0]; })", "would never run")])
+def test_phases_that_would_drop_or_misread_rows_do_not_compile(tmp_path, phase, call, refusal):
+    """An epilogue has at most as many parts as the phase has k-fragments (four here), and run() does not read swizzled rows."""
+    import subprocess
+    from paper_2301_06051_amd import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no compiler")
+    src = tmp_path / "phase.hip"
+    src.write_text('#include "mma.h"\n'
+                   "__global__ void k(const float* w, const float* b, float* x) {\n"
+                   f"  {phase} phase(w, threadIdx.x >> 6);\n"
+                   f"  phase.{call};\n"
+                   "}\n")
+    r = subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-device-only", "-fsyntax-only", str(src)], capture_output=True, text=True)
+    assert (r.returncode == 0) == (refusal is None), r.stderr
+    assert refusal is None or refusal in r.stderr
+
+
 def test_host_only_calls_work_without_a_gpu():
     """dsvt_partition_bound is pure host arithmetic: the set bound and a positive scratch size."""
     if not os.path.exists(LIB):
