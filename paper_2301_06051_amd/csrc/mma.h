@@ -148,17 +148,6 @@ __device__ __forceinline__ void mma_row(f32x4 (&acc)[NT], const AFull<T, NT, NKF
     for (int nt = 0; nt < NT; ++nt) acc[nt] = Mma<T>::mma(a.f[kf][nt], b.f[kf], acc[nt]);
 }
 
-// Operands exchanged: the activations are the MFMA "A" operand and the weights "B" (their fragment
-// layouts are identical), so acc[nt][i] = Out[row 4*g + i][feature 16*nt + m]: a lane holds four
-// consecutive ROWS of one feature -- what a transposed store of the result wants.
-template <typename T, int NT, int NKF>
-__device__ __forceinline__ void mma_row_swapped(f32x4 (&acc)[NT], const AFull<T, NT, NKF>& a, const BRow<T, NKF>& b) {
-#pragma unroll
-  for (int kf = 0; kf < NKF; ++kf)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[nt] = Mma<T>::mma(b.f[kf], a.f[kf][nt], acc[nt]);
-}
-
 constexpr int kRowTiles = 6;                     // row tiles of a workgroup tile
 constexpr int kRowsMax = 16 * kRowTiles;         // 96 rows
 constexpr int kWaves = 8;                        // wavefronts of a pooling workgroup, two per SIMD
@@ -293,6 +282,8 @@ struct GemmPhase {
     }
   }
 
+  // (SWAPPED: operands exchanged.  The activations are the MFMA "A" operand and the weights "B" -- their fragment layouts are identical --, so
+  // acc[nt][i] = Out[row 4*g + i][feature 16*nt + m]: a lane holds four consecutive rows of one feature, what a transposed store of the result wants.)
   // One row tile, k-fragment by k-fragment: its MFMAs, the same fragment of the row tile at `next` (this lane's piece of it)
   // into the registers just read, then part kf of what the caller has to do meanwhile.  The order is fixed: left to
   // itself the compiler reads a fragment right in front of its MFMAs to save registers, and every one of them waits for LDS.
@@ -403,17 +394,7 @@ struct GemmPhase {
   }
 };
 
-// Reductions over the four lanes m, m + 16, m + 32, m + 48 (one accumulator column) with the
-// gfx950 lane-swap instructions: permlane16_swap(x, x) returns x's 16-lane rows (0,0,2,2) and
-// (1,1,3,3), permlane32_swap(x, x) its halves (lo,lo) and (hi,hi); no LDS round trip.
-__device__ __forceinline__ float col_sum(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float s = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const unsigned w = __float_as_uint(s);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
+// Reductions over the four lanes m, m + 16, m + 32, m + 48 (one accumulator column) with the gfx950 lane-swap instructions, no LDS round trip:
 // permlane32_swap(a, b) returns a's halves and b's as (a.lo, b.lo) and (a.hi, b.hi): a's sums over lanes l, l + 32 in the lower half,
 // b's in the upper one; permlane16_swap(a, b) the even and the odd 16-lane rows: (a0, b0, a2, b2) and (a1, b1, a3, b3).
 __device__ __forceinline__ float merge32(float a, float b) {
@@ -430,14 +411,6 @@ __device__ __forceinline__ float raw_max(float a, float b) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
-}
-__device__ __forceinline__ float col_max(float v) {
-  const unsigned u = __float_as_uint(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float s = raw_max(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const unsigned w = __float_as_uint(s);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return raw_max(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // Reduction of N = 1, 2 or 4 values over the four lanes of a column (m, m + 16, m + 32, m + 48), `fin` applied, in every lane.  Several
