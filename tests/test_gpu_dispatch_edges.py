@@ -282,6 +282,37 @@ def test_frames_of_several_rounds_and_a_part(C, heads, hidden, dtype, n_win, dup
         assert torch.equal(out[torch.as_tensor(done).cuda()], y[torch.as_tensor(done).cuda()])
 
 
+@pytest.mark.parametrize("C,heads,hidden,dtype,n_win", [(192, 8, 384, "bf16", 2600), (128, 8, 256, "bf16", 2600), (64, 4, 128, "bf16", 5003), (64, 4, 128, "f32", 2600)])
+def test_work_lists_of_whole_rounds_and_a_tile_more_or_less(C, heads, hidden, dtype, n_win):
+    """The kernel for frames of several rounds with lists of exactly one and two rounds (every workgroup has the same number of tiles), of a tile
+    more than one (nobody has a second one but its taker) and of a tile less than two: each listed tile is done, with the bits that the whole list gives it, and
+    no other row is written."""
+    win, tau, grid = (12, 12, 1), 36, (864, 864, 1)
+    rng = np.random.Generator(np.random.Philox(121))
+    sizes = rng.choice((36, 31, 22, 17), n_win)
+    cells = [rng.permutation(144)[:k] for k in sizes]
+    coords = np.concatenate([np.stack([0 * c, 12 * (w // 72) + c // 12, 12 * (w % 72) + c % 12, 0 * c], 1) for w, c in enumerate(cells)]).astype(np.int32)
+    layers = [dsvt.LayerWeights(synth.make_layer_weights(122 + a, C, heads, hidden, win, dtype)) for a in (0, 1)]
+    cd, xd = dev_coords(coords), dev_feats(synth.make_features(124, len(coords), C, dtype), dtype)
+    maps = [gpu_maps(cd, grid, win, (0, 0, 0), tau, 1, a) for a in (0, 1)]
+    n_tiles, groups = int(maps[0].n_tiles.item()), 512 if (C, dtype) == (64, "bf16") else 256
+    assert len(coords) > 96 * 2 * groups and n_tiles > 2 * groups
+    y = dsvt.dsvt_block(layers, maps, cd, xd)
+    desc = maps[0].tile_desc.cpu().numpy().reshape(-1, 256)
+    for keep in (groups, groups + 1, 2 * groups - 1, 2 * groups):
+        print(f"[case] {keep} of {n_tiles} tiles, C={C} {dtype}", flush=True)
+        out = torch.full_like(xd, 7.0)
+        for m in maps:
+            m.n_tiles.fill_(keep)
+        dsvt.dsvt_block(layers, maps, cd, xd, x_out=out)
+        torch.cuda.synchronize()
+        done = np.zeros(len(coords), bool)
+        listed = desc[:keep, 64::2][:, :96]
+        done[listed[(np.arange(96)[None, :] < desc[:keep, :1]) & (listed >= 0)]] = True
+        done = torch.as_tensor(done).cuda()
+        assert 0 < int(done.sum()) < len(coords) and bool((out[~done] == 7.0).all()) and torch.equal(out[done], y[done]), keep
+
+
 @pytest.mark.parametrize("C,heads,hidden,dtype", [(128, 8, 256, "bf16"), (64, 4, 128, "bf16"), (64, 4, 128, "f32")])
 @pytest.mark.parametrize("dup_mode", [0, 1])
 def test_attention_items_split_and_whole(C, heads, hidden, dtype, dup_mode):
