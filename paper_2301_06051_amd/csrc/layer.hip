@@ -33,17 +33,18 @@ enum SetSize { kSets48, kSets96, kSets96Slim };
 // A set of up to 3 key tiles (48 voxels) is split into items of half of the heads each.  A larger one's logits and positional terms
 // take more registers, and what bounds its items is the fetching of the terms, a load of the compute unit's memory pipe per key and
 // query tile whatever its width: C = 128 takes four heads an item, 32 keys at a time (attn_item()), the other shapes two heads and all keys (C = 192
-// spills 28 registers with four; C = 64 has four heads), C = 192 with repeats counted as keys one (two spill there), and so does kSets96Slim.  30 x 30 windows,
-// sets of up to 90, C = 128, 20,000 voxels: attention of a tile of 70 rows 16.3 -> 12.3 k clocks, pass 262 -> 246 us with four heads instead of
-// two.  At most one set of a tile is that large, so a tile has at most 8 * 6 + 2 * (3 + 11) = 76 items.
+// spills 40 registers and more with four; C = 64 has four heads), kSets96Slim one, and so does C = 192 with repeats counted as keys.  (There two spilled
+// when the line was drawn.  With the sums as they are now they do not, and a block of 20,000 voxels, 30 x 30 windows, sets of up to 90, takes 81.3 us where one
+// head takes 98.4, of 30,000 in 24 x 24 windows, sets of up to 60, 84.4 where it takes 89.7: not drawn anew yet.)  C = 128, two heads -> four: the same two blocks
+// 63.3 -> 58.5 us and 56.4 -> 54.5; attention of a tile of 70 rows 16.3 -> 12.0 k clocks.  At most one set of a tile is that large, so a tile has
+// at most 8 * 6 + 2 * (3 + 11) = 76 items.
 __host__ __device__ constexpr int big_heads(int C, bool dup, SetSize sz) { return sz == kSets96Slim || (C == 192 && dup) ? 1 : C == 128 ? 4 : 2; }
 __host__ __device__ constexpr int item_groups(int kts, int heads, int big) { return kts <= 3 ? 2 : heads / big; }
 // A tile whose items leave half of the wavefronts without one -- a set or two: sparse frames -- gets items of a quarter of
-// the heads (sets of up to three key tiles; a larger one makes 16 items and more of eight heads, 8 to 12 at C = 64): an item's
-// heads are one dependent chain after the other, 4.4 k of the 35 k clocks of a 24-row tile.  Pass of
-// 3,001 pillars 159.5 -> 157.9 us, one block of 2,000 voxels in fp32 52.1 -> 51.7; the code costs frames of full tiles up to
-// 0.2 %.  (Where more wavefronts have an item, halving them
-// costs the second fetch of the positional terms: 2-3 % of a layer.)
+// the heads (sets of up to three key tiles; a larger one makes 8 to 12 items at C = 128 and 64, 16 and more at C = 192).  An item's heads go through its
+// steps together, so half as many of them take little less than all.  Never split -> so: pass of 3,001 pillars 135.3 -> 134.4 us (attention
+// of its tiles of 24 rows 4.8 k of 26.6 k clocks), one block of 2,000 voxels in fp32 47.4 -> 47.1; frames of full tiles no difference.  (Where more
+// wavefronts have an item, halving them costs the second fetch of the positional terms: 2-3 % of a layer, read when heads followed one another.)
 __device__ __forceinline__ bool split_items(int items, bool large_set, int waves) { return !large_set && 2 * items <= waves; }
 // The attention phase's items -- (set, query tile, group of heads) -- are numbered set by set.  A set's table word: first row
 // (bits 0-7), distinct voxels (8-15) and the number of its first item (from 16 on); words past the last set hold
@@ -214,7 +215,7 @@ template <typename T, int C, int HEADS, int HID> struct LayerLds {
   static constexpr size_t total = off_misc + kMisc;
   static_assert((size_t)kRowsMax * LDH * sizeof(T) <= 2 * kTile, "hidden tile must fit in Q + K");
   static_assert(C % 64 == 0 && D % Mma<T>::KL == 0 && D % 4 == 0, "shape");
-  static_assert(total <= 160 * 1024, "LDS of one CU");            // C = 192: 163,320 bytes, 520 below it
+  static_assert(total <= 160 * 1024, "LDS of one CU");            // C = 192: 163,328 bytes, 512 below it
 };
 
 // Whether a tile leaves room in the LDS for a second workgroup on the compute unit: C = 64 in bf16.
@@ -222,10 +223,10 @@ template <typename T, int C, int HEADS, int HID> constexpr bool two_groups_fit()
 
 // Key tiles of the largest set in a tile whose items may be split (split_items).  At C = 64 in bf16 an item of a quarter of the heads is a
 // single head, and it is a workgroup beside it on the compute unit, not idle wavefronts, that fills its waits: sets of three key tiles
-// stay whole there, and so does every set once there are two workgroups to a compute unit (n_tiles > 256).  Two layers, 30 x 30
-// windows, sets of up to 48, all split -> so: 3,000 voxels 18.5 -> 16.9 us, 27,000 40.1 -> 36.2, 45,000 49.9 -> 42.7; 12 x 12 windows,
-// 60,000 49.5 -> 47.2; never split: 300 voxels 13.3 -> 13.6.  The other shapes, never split -> as here: fp32 500 voxels 21.1 -> 20.8,
-// 3,000 29.7 -> 29.1, C = 128 18.8 -> 18.2 and 23.6 -> 23.3, C = 192 25.0 -> 24.4 and 33.2 -> 32.3.
+// stay whole there, and so does every set once there are two workgroups to a compute unit (n_tiles > 256).  All split -> so, replayed blocks of
+// two layers: 3,000 voxels in 30 x 30 windows, sets of up to 48, 15.8 -> 15.3 us; 27,000 and 45,000 of them, and 60,000 in 12 x 12 windows, no difference any more (40.1 -> 36.2,
+// 49.9 -> 42.7 and 49.5 -> 47.2 when heads followed one another); never split: 300 voxels 11.75 -> 11.7.  The other shapes, never split -> as here, 500 and 3,000 voxels spread evenly over 12 x 12
+// windows: C = 192 20.4 -> 20.45 and 25.7 -> 25.6, C = 128 and fp32 within 0.1 (25.0 -> 24.4, 33.2 -> 32.3 and the like before).
 template <typename T, int C, int HEADS, int HID> constexpr int split_key_tiles() { return two_groups_fit<T, C, HEADS, HID>() ? 2 : 3; }
 
 // LDS by its 32-bit address: constants added to it become the instruction's offset.
@@ -272,7 +273,7 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
   // Four heads of four key tiles and more take the keys 32 at a time, with a running maximum: all logits at once do not fit the registers
   // (and two heads at a time fetch the terms twice as often, 8 bytes a lane; a load is 17 clocks of the compute unit's memory pipe either way).
   constexpr int CT = HG == 4 && KTC > 3 ? 2 : KTC;                // key tiles at a time
-  constexpr int HS = C == 192 && KTC > 4 ? 1 : HG;                // heads side by side (two heads of six key tiles spill eight registers at C = 192)
+  constexpr int HS = C == 192 && KTC > 4 ? 1 : HG;                // heads side by side (two of five or six key tiles, C = 192: no difference, 84.6 us a block either way)
   static_assert(CT == KTC || HS == HG, "a running maximum per head");
   const int lane = opaque_tid() & 63, m = lane & 15, g = lane >> 4;
   const int qi = 16 * qt + m;
@@ -426,7 +427,7 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           O[hl][dt] = o;
         }
       }
-      if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (without it four to eight registers spill: 250 us instead of 246)
+      if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (152 registers, 159 with repeats as keys; without it 162 and 161, a block 58.5 us either way)
     }
     col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
 #pragma unroll
