@@ -416,24 +416,24 @@ __device__ __forceinline__ float raw_max(float a, float b) {
 
 // Reduction of N = 1, 2 or 4 values over the four lanes of a column (m, m + 16, m + 32, m + 48), `fin` applied, in every lane.  Several
 // values share the lane swaps (merge32(), merge16() above): three swaps for two or for four values, where one at a time takes two each.
-// Lanes are added as (0 + 1) + (2 + 3) whatever N is, so that a head's result does not depend on the heads that it shares an item with.
+// Lanes are added as (0 + 2) + (1 + 3) whatever N is, so that a head's result does not depend on the heads that it shares an item with.
 template <int N, typename Op, typename Fin>
 __device__ __forceinline__ void col_reduce(float (&v)[N], Op op, Fin fin) {
   const auto swap32 = [](float a, float b) { return __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false); };
   const auto swap16 = [](float a, float b) { return __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false); };
   const auto fold = [&](auto p) { return op(__uint_as_float(p[0]), __uint_as_float(p[1])); };
   static_assert(N == 1 || N == 2 || N == 4, "");
-  // 16-lane rows of a: values 0, 1, 0, 1 (N = 1: 0 throughout), their lanes 0 + 1 in the lower half, 2 + 3 in the upper one; of b: values 2, 3, 2, 3
-  const float a = fold(swap16(v[0], v[N > 1 ? 1 : 0])), b = N == 4 ? fold(swap16(v[N / 2], v[N - 1])) : a;
-  const float r = fin(fold(swap32(a, b)));                         // values 0, 1, 2, 3 (N = 2: 0, 1, 0, 1)
+  // halves of a: values 0, 1 (N = 1: 0 in both), their lanes 0 + 2 in the even 16-lane rows, 1 + 3 in the odd ones; of b: values 2, 3
+  const float a = fold(swap32(v[0], v[N > 1 ? 1 : 0])), b = N == 4 ? fold(swap32(v[N / 2], v[N - 1])) : a;
+  const float r = fin(fold(swap16(a, b)));                         // 16-lane rows: values 0, 2, 1, 3 (N = 2: 0, 0, 1, 1)
   if constexpr (N == 1) {
     v[0] = r;
   } else if constexpr (N == 2) {
-    const auto p = swap16(r, r);
+    const auto p = swap32(r, r);
     v[0] = __uint_as_float(p[0]); v[1] = __uint_as_float(p[1]);
   } else {
-    const auto p = swap32(r, r);                                   // 0, 1, 0, 1 and 2, 3, 2, 3
-    const auto c = swap16(__uint_as_float(p[0]), __uint_as_float(p[0])), d = swap16(__uint_as_float(p[1]), __uint_as_float(p[1]));
+    const auto p = swap16(r, r);
+    const auto c = swap32(__uint_as_float(p[0]), __uint_as_float(p[0])), d = swap32(__uint_as_float(p[1]), __uint_as_float(p[1]));
     v[0] = __uint_as_float(c[0]); v[1] = __uint_as_float(c[1]);
     v[2] = __uint_as_float(d[0]); v[N - 1] = __uint_as_float(d[1]);
   }
