@@ -363,9 +363,9 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           cm[hl] = k == 0 ? x : fmaxf(cm[hl], x);
         }
       }
-      // (Key 0 exists for every query, but the table may hold -inf for it and for all keys of a step.  The running maximum starts at the lowest float
-      // then, which no finite logit lies below: -inf less it stays -inf, where -inf less -inf is NaN, and nothing of such a step counts in the next one.)
-      col_reduce(cm, [](float a, float b) { return raw_max(a, b); }, [&](float a) { return CT < KTC && k0 == 0 ? raw_max(a, -FLT_MAX) : a; });
+      // (Key 0 exists for every query, but the table may hold -inf for it and for all keys of a step.  The running maximum is kept at the lowest float or
+      // above, which no finite logit lies below: -inf less it stays -inf, where -inf less -inf is NaN, and nothing of such a step counts in the next one.)
+      col_reduce(cm, [](float a, float b) { return raw_max(a, b); }, [](float a) { return CT < KTC ? raw_max(a, -FLT_MAX) : a; });
       float scale[HS];                              // of the keys before these
 #pragma unroll
       for (int hl = 0; hl < HS; ++hl) {
@@ -427,7 +427,7 @@ __device__ __forceinline__ void attn_item(const PositionTable& p, unsigned char*
           O[hl][dt] = o;
         }
       }
-      if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (152 registers, 159 with repeats as keys; without it 162 and 161, a block 58.5 us either way)
+      if (CT < KTC) __builtin_amdgcn_sched_barrier(0);             // (156 registers, 160 with repeats as keys; without it a few more, a block 58.5 us either way)
     }
     col_reduce(sum, [](float a, float b) { return a + b; }, [](float a) { return __builtin_amdgcn_rcpf(a); });
 #pragma unroll
