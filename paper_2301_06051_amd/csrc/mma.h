@@ -290,8 +290,7 @@ struct GemmPhase {
   // Two row tiles a trip, fragments and table entries where the compiler puts them -> this and run_keep() as it is now: clocks of a 64-row
   // tile of C = 192 38.6 k -> 37.2 k (Q/K/V 6.8 -> 6.3 k, second MLP matrix 5.6 -> 5.1 k, first one 7.25 -> 7.0 k), of an 82-row tile 46.2 -> 44.4 k;
   // passes of 3,001 pillars 146.0 -> 141.8 us, 30,000 339.5 -> 331.4, four frames 1,067 -> 1,030, 30 x 30 windows 273.7 -> 265.6,
-  // 120,000 voxels 647.7 -> 631.3, skewed batch 7,217 -> 7,158 (in runs of seconds its clock falls as the units
-  // get busier, 2.32 -> 2.28 GHz from before this to the present kernel; the pillar frame's stays at 2.42).
+  // 120,000 voxels 647.7 -> 631.3, skewed batch 7,217 -> 7,158.
   template <bool SWAPPED, typename Part>
   __device__ __forceinline__ void row_step(f32x4 (&acc)[NT], const f32x4 (&start)[NT], BRow<T, NKF>& b, const T* next, Part part) const {
 #pragma unroll
